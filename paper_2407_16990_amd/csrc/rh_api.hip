@@ -101,8 +101,10 @@ extern "C" rh_status rh_create(const rh_config* cfg, const float* weights, size_
     if (e == hipSuccess && (ctx->device < 0 || ctx->device >= RH_MAX_DEVICES)) { delete ctx; return RH_E_DEVICE; }
     A(hipDeviceGetAttribute(&ctx->n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device));
     if (e == hipSuccess && ctx->n_cu < 1) ctx->n_cu = 1;
-    A(dalloc(&ctx->w_f32, n_floats));
-    A(hipMemcpy(ctx->w_f32, weights, n_floats * sizeof(float), hipMemcpyHostToDevice));
+    std::vector<float> blob(weights, weights + n_floats);
+    if (cfg->precision == RH_FP32) rh_pack_weights_f32(ctx, weights, blob);
+    A(dalloc(&ctx->w_f32, blob.size()));
+    A(hipMemcpy(ctx->w_f32, blob.data(), blob.size() * sizeof(float), hipMemcpyHostToDevice));
     A(dalloc(&ctx->frame_seg, cfg->max_frames)); A(dalloc(&ctx->seg_par, 4 * (size_t)cfg->max_frames));
     A(dalloc(&ctx->seg_T, cfg->max_frames)); A(dalloc(&ctx->seg_budget, cfg->max_frames));
     A(dalloc(&ctx->frame_nsel, cfg->max_frames)); A(dalloc(&ctx->frame_ties, cfg->max_frames));

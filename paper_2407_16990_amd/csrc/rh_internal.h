@@ -21,7 +21,7 @@ struct rh_layer {
     int cin, cout;          // true channel counts
     size_t w_off, b_off;    // offsets (floats) into the fp32 blob
     // bf16 path: weights repacked into MFMA fragment order (see conv_mfma.hip)
-    size_t wp_off;          // offset (bytes) into wpack
+    size_t wp_off;          // offset (bytes) into wpack (fp32 path: floats, into w_f32)
     size_t bp_off;          // offset (floats) into bpack (bias, permuted/padded like the weights)
     int cout_pad;           // cout rounded up to the kernel's M tile
     int ps;                 // pixel-shuffle factor folded into the output-channel order (1 = none)
@@ -57,7 +57,7 @@ struct rh_ctx {
     char err[256];
 
     std::vector<rh_layer> layers;
-    float* w_f32;           // dev: the fp32 blob as given
+    float* w_f32;           // dev: the fp32 blob as given (RH_FP32: and its layers in groups of 4 outputs, conv_fp32.hip)
     void* wpack;            // dev: bf16 weights in fragment order (RH_BF16 only)
     float* bpack;           // dev: biases matching wpack's channel order
     // EDSR-shaped nets, bf16: the upsampler and the last conv composed into one 5 x 5 conv (conv_fold.hip)
@@ -154,6 +154,7 @@ rh_status rh_launch_temporal_select(rh_ctx*, const uint64_t* phi, const int32_t*
                                     uint32_t* n_selected);
 rh_status rh_launch_temporal_spread(rh_ctx*, float* imp, int F, const uint8_t* selected, const uint32_t* reuse_from);
 rh_status rh_pack_weights_bf16(rh_ctx*, const float* host_blob);
+void rh_pack_weights_f32(rh_ctx*, const float* host_blob, std::vector<float>& all);
 rh_status rh_fold_weights(rh_ctx*, const float* host_blob);
 rh_status rh_plan_init(rh_ctx*);
 rh_status rh_mask_init(rh_ctx*);
