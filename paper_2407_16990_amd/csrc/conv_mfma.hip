@@ -524,14 +524,21 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     uint32_t n_conv = 0;
     rh_prof_begin(ctx, RH_PROF_CONV);
 #define CONV(...) do { st = conv(ctx, __VA_ARGS__); if (st != RH_OK) return st; ++n_conv; } while (0)
+#define BLOCK32(...) do { RH_HIP(ctx, rh_launch_block32(ctx, __VA_ARGS__)); n_conv += 2; } while (0)
 #define LAST_CONV(...) do { rh_prof_end(ctx, n_conv); rh_prof_scope ps_(ctx, RH_PROF_CONV_LAST); st = conv(ctx, __VA_ARGS__); if (st != RH_OK) return st; } while (0)
+    // 32 channels: two convs per launch (they are bound by memory, and the tensor between them stays on
+    // the chip); exact-border mode clears part of that tensor and runs them one by one
+    const bool pairs = C == 32 && !ctx->bz_boxes;
     if (d.topology == RH_NET_PLAIN) {
         const __bf16* x = h;
-        for (int l = 0; l < d.n_blocks - 2; ++l) { __bf16* o = (x == a) ? t : a; CONV(L[li++], x, o, nullptr, N, H, W, 1, false, 1, n_valid); ZERO(o, 1); x = o; }
+        int l = 0;
+        for (; pairs && l + 1 < d.n_blocks - 2; l += 2, li += 2) { __bf16* o = (x == a) ? t : a; BLOCK32(L[li], L[li + 1], x, o, N, H, W, false, n_valid); x = o; }
+        for (; l < d.n_blocks - 2; ++l) { __bf16* o = (x == a) ? t : a; CONV(L[li++], x, o, nullptr, N, H, W, 1, false, 1, n_valid); ZERO(o, 1); x = o; }
         LAST_CONV(L[li++], x, out, nullptr, N, H, W, 0, true, s, n_valid);
     } else {
         const __bf16* x = h;
         for (int b = 0; b < d.n_blocks; ++b) {
+            if (pairs) { __bf16* o = (x == a) ? t : a; BLOCK32(L[li], L[li + 1], x, o, N, H, W, true, n_valid); li += 2; x = o; continue; }
             CONV(L[li++], x, t, nullptr, N, H, W, 1, false, 1, n_valid); ZERO(t, 1);
             CONV(L[li++], t, a, x, N, H, W, 0, false, 1, n_valid); ZERO(a, 1);      // x + conv(t)
             x = a;
@@ -539,6 +546,7 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
         if (d.topology == RH_NET_RES) {
             LAST_CONV(L[li++], x, out, nullptr, N, H, W, 0, true, s, n_valid);
         } else {
+            if (x == t) { t = a; a = (__bf16*)x; }
             CONV(L[li++], x, t, h, N, H, W, 0, false, 1, n_valid); ZERO(t, 1);       // body end + long skip
             if (fold) {
                 rh_prof_end(ctx, n_conv);
@@ -557,6 +565,7 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
         }
     }
 #undef CONV
+#undef BLOCK32
 #undef LAST_CONV
 #undef ZERO
     RH_HIP(ctx, hipGetLastError());

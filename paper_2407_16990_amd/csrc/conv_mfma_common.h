@@ -60,6 +60,9 @@ __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u 
 
 // two-team kernel for the 64-channel bf16-output convs (conv_mfma_duo.hip)
 hipError_t rh_launch_conv_duo(hipStream_t stream, int device, const conv_args& a, int grid, bool skip, bool relu);
+// two 3x3 convs of a 32-channel net in one launch (conv_block32.hip); res: a residual block, else two ReLU layers.  in != out
+hipError_t rh_launch_block32(rh_ctx* ctx, const rh_layer& L1, const rh_layer& L2, const __bf16* in, __bf16* out, int N, int H, int W,
+                             bool res, const uint32_t* n_valid);
 // last conv with 3 output channels and no pixel shuffle (conv_tail.hip)
 hipError_t rh_launch_conv_tail3(hipStream_t stream, int device, const conv_args& a, int cin);
 // first conv 3 -> C on the matrix cores (conv_head.hip)
