@@ -1,14 +1,14 @@
 // Region-aware bin packing (Alg. 1) on macroblock indexes, entirely on the GPU:
-//   k_plan_label : RegionProps + Bound + Partition, one workgroup per frame (labels in LDS)
+//   k_plan_regions / k_plan_label : RegionProps + Bound + Partition, one wave per frame (rows as 64-bit masks), or for
+//                  larger frames one workgroup (labels in LDS)
 //   k_plan_rank  : Sort by importance density (rank by counting; the order is total)
 //   k_plan_place : the serial first-fit over the ordered free-rectangle list, one wave,
-//                  lanes test free rectangles in parallel, the list lives in LDS
+//                  lanes test free rectangles in parallel, the list lives in registers
 //   k_plan_emit  : placement rows for boxes and macroblocks
+//   k_plan_fused : all of these in one launch, for batches of few frames
 #include "rh_internal.h"
 
 #define NONE 0xFFFFFFFFu
-
-__global__ void k_plan_zero(uint32_t* pcount) { if (threadIdx.x < 8) pcount[threadIdx.x] = 0; }
 
 // One workgroup per frame.  LDS: lab[per], cminx[per], cmaxx[per], cmaxy[per] and, when it fits
 // (imp_in_lds), the frame's importance values: a box leader adds up to T*T of them one after the
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256) void k_plan_label(const uint8_t* __restrict__ 
         }
         owner_id[base + i] = (uint32_t)(base + leader);
         if (leader == i) {
-            uint32_t slot = atomicAdd(&pcount[0], 1u);
+            uint32_t slot = atomicAdd(&pcount[3], 1u);
             rh_rawbox b;
             b.frame = f; b.mbx0 = x0; b.mby0 = y0; b.wmb = x1 - x0 + 1; b.hmb = y1 - y0 + 1;
             b.id = (uint32_t)(base + i); b.sum = sum;
@@ -135,44 +135,69 @@ __device__ __forceinline__ bool box_before(double ka, uint32_t ia, double kb, ui
     return ia < ib;
 }
 
-// Sort by counting: the rank of a box is the number of boxes before it.
+// Sort by counting: the rank of a box is the number of boxes before it.  A wave ranks RANK_PER boxes at a
+// time, its lanes compare them with 64 others each step; keys pass through LDS in tiles.  (A thread per
+// box took 87 us for 752 boxes, three workgroups going through all boxes one by one.)
+#define RANK_PER 4
+#define RANK_TILE 1024
+
 __global__ __launch_bounds__(256) void k_plan_rank(const rh_rawbox* __restrict__ raw,
                                                    const uint32_t* __restrict__ pcount,
                                                    rh_rawbox* __restrict__ sorted,
                                                    uint32_t* __restrict__ rank_of_id)
 {
-    __shared__ double s_key[256];
-    __shared__ uint32_t s_id[256];
-    const uint32_t n = pcount[0];
-    if (blockIdx.x * 256u >= n) return;
-    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-    rh_rawbox me;
-    if (i < n) me = raw[i]; else { me.key = 0; me.id = 0; }
-    uint32_t rank = 0;
-    for (uint32_t t0 = 0; t0 < n; t0 += 256) {
-        __syncthreads();
-        if (t0 + threadIdx.x < n) { s_key[threadIdx.x] = raw[t0 + threadIdx.x].key; s_id[threadIdx.x] = raw[t0 + threadIdx.x].id; }
-        __syncthreads();
-        const uint32_t m = min(256u, n - t0);
-        if (i < n)
-            for (uint32_t j = 0; j < m; ++j) rank += box_before(s_key[j], s_id[j], me.key, me.id) ? 1u : 0u;
+    __shared__ unsigned long long s_key[RANK_TILE];
+    __shared__ uint32_t s_id[RANK_TILE];
+    const uint32_t n = pcount[3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (uint32_t b0 = blockIdx.x * (4 * RANK_PER); b0 < n; b0 += gridDim.x * (4 * RANK_PER)) {       // uniform over the workgroup
+        const uint32_t i0 = b0 + wave * RANK_PER;
+        unsigned long long mk[RANK_PER]; uint32_t mid[RANK_PER], rank[RANK_PER];
+#pragma unroll
+        for (int u = 0; u < RANK_PER; ++u) {
+            const uint32_t i = min(i0 + u, n - 1u);
+            mk[u] = ord_key(raw[i].key); mid[u] = raw[i].id; rank[u] = 0;
+        }
+        for (uint32_t t0 = 0; t0 < n; t0 += RANK_TILE) {
+            const uint32_t m = min((uint32_t)RANK_TILE, n - t0);
+            __syncthreads();
+            for (uint32_t j = tid; j < m; j += 256) { s_key[j] = ord_key(raw[t0 + j].key); s_id[j] = raw[t0 + j].id; }
+            __syncthreads();
+            for (uint32_t j = lane; j < m; j += 64) {
+                const unsigned long long k = s_key[j]; const uint32_t id = s_id[j];
+#pragma unroll
+                for (int u = 0; u < RANK_PER; ++u) rank[u] += (k > mk[u] || (k == mk[u] && id < mid[u])) ? 1u : 0u;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < RANK_PER; ++u) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) rank[u] += __shfl_xor(rank[u], o);
+            if (lane == u && i0 + u < n) { sorted[rank[u]] = raw[i0 + u]; rank_of_id[mid[u]] = rank[u]; }
+        }
     }
-    if (i < n) { sorted[rank] = me; rank_of_id[me.id] = rank; }
 }
 
 // First fit (Alg. 1 main loop) with the reading of InnerFree given in the header.
 // Free rectangle j: fxy[j] = x | y<<16, fwh[j] = w | h<<16, fbin[j].
-// box_pos[i] = {bin | turned<<16, bx | by<<16}; pcount[1] = n_bins, pcount[2] = overflow.
+// box_pos[i] = {bin | turned<<16, bx | by<<16}.
 // rotate: a rectangle that cannot take the box upright may take it turned (RotatePacking).
-// The loop over the boxes is serial by definition, so its cost is the latency of one step.  It
-// runs in ONE wave.  While the free list has at most 62 entries it lives in registers, entry j in
-// lane j: a ballot gives the first fit, the winner's fields are lane reads, and the entries behind
-// it move up or down by one lane with a whole-wave DPP shift - no memory in the loop at all.  The
-// first time the list could outgrow the wave it is written to LDS and stays there: the 64 lanes
-// then test 64 rectangles at a time; the hardware executes the LDS traffic of a single wave in
-// program order, and wave_sync() after every step in which lanes write what other lanes read next
-// keeps the compiler from moving LDS accesses across it.  Every lane tracks the list length and
-// bin count in registers.
+// The loop over the boxes is serial by definition, and it runs in ONE wave, which issues an instruction
+// every 4-5 cycles: its cost is the number of instructions of one step.  So
+//   - the free list lives in registers, entry j in lane j % 64 of chunk j / 64, up to FREE_CHUNKS * 64 - 2 entries
+//     (181 at most for 128 frames of 480 x 272); only the chunks in use are looked at;
+//   - a rectangle's sides carry a guard bit each, so that one subtraction tests both (and is the remainder);
+//   - what a step does not need is branched over, all branches are uniform: a box in a new bin touches no
+//     entry behind it, and one that leaves no usable strip (three boxes in four there) ends at once;
+//   - the entries behind a change are shifted by one lane with a whole-wave DPP shift.
+// Measured: 83 boxes of 16 frames of 480 x 272: 30 us instead of 40 in the launch's first fit; 752 boxes of 128 frames: 253 us
+// instead of about 370; 552 boxes of isolated macroblocks: 230-270 us instead of about 300.
+// A list that outgrows the registers is written to LDS and stays there: the 64 lanes then test 64
+// rectangles at a time; the hardware executes the LDS traffic of a single wave in program order, and
+// wave_sync() after every step in which lanes write what other lanes read next keeps the compiler
+// from moving LDS accesses across it.
+#define FREE_CHUNKS 4
+#define FREE_GUARD 0x80008000u           // bin sides are at most 4096
 // One wave.  sizes: box i's (wmb | hmb << 16) comes from size_of(i).  Returns through n_bins / overflow.
 __device__ __forceinline__ uint32_t lane_from_below(uint32_t v)      // lane l gets lane l-1's value, lane 0 keeps its own
 {
@@ -183,17 +208,21 @@ __device__ __forceinline__ uint32_t lane_from_above(uint32_t v)      // lane l g
     return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
 }
 
-template <typename SizeOf>
+template <bool ROTATE, typename SizeOf>
 __device__ __forceinline__ void place_boxes(uint32_t n, SizeOf size_of, uint32_t* fxy, uint32_t* fwh, uint32_t* fbin,
-                                            int halo, int S, int max_bins, int free_cap, int rotate,
+                                            int halo, int S, int max_bins, int free_cap,
                                             uint32_t* __restrict__ box_pos, int& n_bins_out, bool& overflow_out)
 {
     const int lane = threadIdx.x & 63;
     const int minside = RH_MB + 2 * halo;
-    constexpr int REG_MAX = 62;                              // a step adds at most 2 entries
+    constexpr int rotate = ROTATE;
+    constexpr int REG_MAX = FREE_CHUNKS * 64 - 2;            // a step adds at most 2 entries
     int nfree = 0, nbins = 0;
-    uint32_t i = 0, szv = 0, pos0 = 0, pos1 = 0;             // lane l keeps the position of box (i & ~63) + l
-    uint32_t rxy = 0, rwh = 0, rbn = 0;                      // register mode: free rectangle `lane`
+    uint32_t i = 0, pos0 = 0, pos1 = 0;                      // lane l keeps the position of box (i & ~63) + l
+    // rwh: with the guard bits; lanes past the list: no area.  Chunks by name, and no lambda that refers to them:
+    // the compiler puts arrays and captured variables into scratch memory here (0.5-0.7 us per box)
+    uint32_t rxy0 = 0, rxy1 = 0, rxy2 = 0, rxy3 = 0, rbn0 = 0, rbn1 = 0, rbn2 = 0, rbn3 = 0;
+    uint32_t rwh0 = FREE_GUARD, rwh1 = FREE_GUARD, rwh2 = FREE_GUARD, rwh3 = FREE_GUARD;
     bool overflow = false;
     // Results leave in groups of 64: a global store per box would be waited for by the next box's
     // loads (stores and loads share the wave's memory counter), half a microsecond each.
@@ -201,61 +230,166 @@ __device__ __forceinline__ void place_boxes(uint32_t n, SizeOf size_of, uint32_t
         const uint32_t g0 = (upto - 1u) & ~63u;
         if (upto && g0 + lane < upto) { box_pos[2 * (g0 + lane)] = pos0; box_pos[2 * (g0 + lane) + 1] = pos1; }
     };
-    // ---- register mode: the whole step is lane arithmetic and a few scalar selects ----
-    for (; i < n && !overflow && nfree <= REG_MAX; ++i) {
-        if ((i & 63u) == 0) {
-            flush(i);
-            szv = (i + lane < n) ? size_of(i + lane) : 0u;   // the next 64 box sizes, one per lane
+    // the next 64 box sizes, one per lane, requested 64 boxes ahead
+    uint32_t szv = 0, szn = (uint32_t)lane < n ? size_of(lane) : 0u;
+    uint32_t ndv = 0;                                        // bw | bh << 16 of these boxes, FREE_GUARD's lower bit: fills a bin of its own
+    auto next_sizes = [&]() __attribute__((always_inline)) {
+        flush(i);
+        szv = szn;
+        szn = i + 64 + lane < n ? size_of(i + 64 + lane) : 0u;
+        ndv = szv * RH_MB + 2u * halo * 0x10001u;
+        const int w = S - (int)(ndv & 0xFFFF), h = S - (int)(ndv >> 16);
+        ndv |= max(w, h) < minside ? 0x8000u : 0u;
+    };
+    auto lane_of = [](uint32_t v, int l) __attribute__((always_inline)) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+    auto with_lane = [&](uint32_t v, int l, uint32_t x) __attribute__((always_inline)) { return lane == l ? x : v; };
+#define PUT1(c, j, xy, wh) if (((j) >> 6) == c) { const bool me = lane == ((j) & 63); rxy##c = me ? (xy) : rxy##c; rwh##c = me ? (wh) : rwh##c; rbn##c = me ? (uint32_t)fb : rbn##c; }
+#define PUT(j, xy, wh) do { PUT1(0, j, xy, wh) PUT1(1, j, xy, wh) PUT1(2, j, xy, wh) PUT1(3, j, xy, wh) } while (0)
+    // ---- one chunk: straight-line code, every lane works out what would be left of its own rectangle ----
+    // The entry behind the list's last is the next bin's whole area (while there is one), so a new bin is an
+    // ordinary first fit; it is written anew after every step.
+    if (max_bins > 0) rwh0 = lane == 0 ? FREE_GUARD | (uint32_t)S | (uint32_t)S << 16 : rwh0;
+    for (; i < n && nfree < 61; ++i) {
+        if ((i & 63u) == 0) next_sizes();
+        const uint32_t nd = lane_of(ndv, (int)(i & 63u)), need = nd & ~0x8000u;
+        uint32_t left = rwh0 - need, bw = need & 0xFFFF, bh = need >> 16, turned = 0;
+        bool fit = (left & FREE_GUARD) == FREE_GUARD;
+        if constexpr (ROTATE) {                              // upright whenever that fits
+            const uint32_t leftt = rwh0 - (need >> 16 | need << 16), bw0 = bw;
+            left = fit ? left : leftt; bw = fit ? bw : bh; bh = fit ? bh : bw0; turned = fit ? 0u : 0x10000u;
+            fit = fit | ((leftt & FREE_GUARD) == FREE_GUARD);
         }
-        const uint32_t sz = (uint32_t)__builtin_amdgcn_readlane((int)szv, (int)(i & 63u));
-        const int bw0 = RH_MB * (int)(sz & 0xFFFF) + 2 * halo, bh0 = RH_MB * (int)(sz >> 16) + 2 * halo;
-        const int w = (int)(rwh & 0xFFFF), h = (int)(rwh >> 16);
-        const bool fit = lane < nfree && ((w >= bw0 && h >= bh0) || (rotate && w >= bh0 && h >= bw0));
-        const unsigned long long m = __ballot(fit);
-        const bool found = m != 0;
-        if (found ? nfree + 1 > free_cap : (nbins >= max_bins || nfree + 2 > free_cap)) { overflow = true; break; }
-        const int at = found ? __ffsll((long long)m) - 1 : nfree;              // a new bin's area goes to the end of the list
-        const uint32_t lxy = (uint32_t)__builtin_amdgcn_readlane((int)rxy, at), lwh = (uint32_t)__builtin_amdgcn_readlane((int)rwh, at);
-        const uint32_t lbn = (uint32_t)__builtin_amdgcn_readlane((int)rbn, at);
-        const uint32_t exy = found ? lxy : 0u, ewh = found ? lwh : ((uint32_t)S | ((uint32_t)S << 16));
-        const int fb = found ? (int)lbn : nbins;
-        const int cur_n = found ? nfree : nfree + 1;
-        nbins += found ? 0 : 1;
-        const int fx = exy & 0xFFFF, fy = exy >> 16, fw = ewh & 0xFFFF, fh = ewh >> 16;
-        const bool turned = !(fw >= bw0 && fh >= bh0);       // upright whenever that fits
-        const int bw = turned ? bh0 : bw0, bh = turned ? bw0 : bh0;            // occupied size
-        if (lane == (int)(i & 63u)) { pos0 = (uint32_t)fb | (turned ? 0x10000u : 0u); pos1 = (uint32_t)fx | ((uint32_t)fy << 16); }
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(fit);
+        const int at = __builtin_ctzll(m | 1ull << 63);      // lane 63 is never in use here
+        const int old = min(nfree - at, 1);                  // 0: a new bin  (integers: the compiler keeps uniform truth values in vector registers)
+        if (m == 0 || nfree + 2 - old > free_cap) { overflow = true; break; }
+        if (((uint32_t)old | (~nd & 0x8000u)) == 0) {        // most boxes of large batches: a bin of its own, nothing left
+            pos0 = with_lane(pos0, (int)(i & 63u), (uint32_t)nbins); pos1 = with_lane(pos1, (int)(i & 63u), 0u);
+            ++nbins;
+            rbn0 = with_lane(rbn0, at, (uint32_t)nbins);
+            if (nbins >= max_bins) rwh0 = with_lane(rwh0, at, FREE_GUARD);
+            continue;
+        }
+        const uint32_t rw = left & 0x7FFF, bhei = left >> 16 & 0x7FFF, fw = rwh0 & 0x7FFF, fh = rwh0 >> 16 & 0x7FFF;
+        const bool right_full = __umul24(rw, fh) >= __umul24(fw, bhei);
+        const uint32_t rh = right_full ? fh : bh, bwid = right_full ? bw : fw;
+        const bool keep_r = min(rw, rh) >= (uint32_t)minside, keep_b = min(bwid, bhei) >= (uint32_t)minside;
+        const uint32_t Rxy = rxy0 + bw, Rwh = (rh << 16 | rw) | FREE_GUARD, Bxy = (bh << 16) + rxy0, Bwh = (bhei << 16 | bwid) | FREE_GUARD;
+        const bool smaller = __umul24(bwid, bhei) < __umul24(rw, rh);
+        const bool b_first = keep_b & (!keep_r | smaller);   // both kept: the smaller one first
+        const uint32_t e0xy = b_first ? Bxy : Rxy, e0wh = b_first ? Bwh : Rwh, e1xy = b_first ? Rxy : Bxy, e1wh = b_first ? Rwh : Bwh;
+        // survivors of the chosen rectangle
+        const int ni = (int)(__builtin_amdgcn_ballot_w64(keep_r) >> at & 1ull) + (int)(__builtin_amdgcn_ballot_w64(keep_b) >> at & 1ull);
+        const bool me = lane == at;
+        // position: the chosen lane's corner and bin (the orientation is packed above the bin)
+        const uint32_t px = lane_of(rxy0, at), pb = lane_of(ROTATE ? rbn0 | turned : rbn0, at);
+        pos0 = with_lane(pos0, (int)(i & 63u), pb); pos1 = with_lane(pos1, (int)(i & 63u), px);
+        // a second survivor enters the shift at the chosen lane
+        const uint32_t vxy = me ? e1xy : rxy0, vwh = me ? e1wh : rwh0;
+        const uint32_t dxy = lane_from_below(vxy), dwh = lane_from_below(vwh), dbn = lane_from_below(rbn0);
+        const uint32_t uxy = lane_from_above(rxy0), uwh = lane_from_above(rwh0), ubn = lane_from_above(rbn0);
+        // as lane numbers, so that no truth value of the wave is involved: lanes from `lo2` on take the lane below, from `lo0` on the lane above
+        const int lo2 = ni == 2 ? at : 64, lo0 = ni == 0 ? at - 1 : 64, at1 = ni == 0 ? 64 : at;
+        const bool down = lane > lo2, up = lane > lo0, one = lane == at1;
+        rxy0 = down ? dxy : up ? uxy : one ? e0xy : rxy0;
+        rwh0 = down ? dwh : up ? uwh : one ? e0wh : rwh0;
+        rbn0 = down ? dbn : up ? ubn : rbn0;
+        nbins += 1 - old;
+        nfree += ni - old;
+        const bool tail = lane == nfree;
+        const uint32_t next_bin = nbins < max_bins ? FREE_GUARD | (uint32_t)S | (uint32_t)S << 16 : FREE_GUARD;
+        rxy0 = tail ? 0u : rxy0; rbn0 = tail ? (uint32_t)nbins : rbn0; rwh0 = tail ? next_bin : rwh0;
+    }
+    if (lane >= nfree) rwh0 = FREE_GUARD;                    // without the new bin's entry
+    // ---- several chunks ----
+    for (; i < n && !overflow && nfree <= REG_MAX; ++i) {
+        if ((i & 63u) == 0) next_sizes();
+        const uint32_t nd = lane_of(ndv, (int)(i & 63u));
+        uint32_t need = nd & ~0x8000u;
+        const uint32_t needt = need >> 16 | need << 16;
+        int at = -1;
+        uint32_t exy = 0, ewh = FREE_GUARD | (uint32_t)S | (uint32_t)S << 16;
+        int fb = nbins;
+#define FIRST(c)                                                                                    \
+        if (at < 0 && 64 * c < nfree) {                                                             \
+            bool fit = ((rwh##c - need) & FREE_GUARD) == FREE_GUARD;                                \
+            if (rotate) fit = fit || ((rwh##c - needt) & FREE_GUARD) == FREE_GUARD;                 \
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(fit);                          \
+            if (m) {                                                                                \
+                const int l = __builtin_ctzll(m);                                                   \
+                at = 64 * c + l;                                                                    \
+                exy = lane_of(rxy##c, l); ewh = lane_of(rwh##c, l); fb = (int)lane_of(rbn##c, l);   \
+            }                                                                                       \
+        }
+        FIRST(0) FIRST(1) FIRST(2) FIRST(3)
+#undef FIRST
+        const bool fresh = at < 0;
+        if (fresh ? (nbins >= max_bins || nfree + 2 > free_cap) : nfree + 1 > free_cap) { overflow = true; break; }
+        if (fresh && (nd & 0x8000u)) {                       // a bin of its own, nothing left
+            pos0 = with_lane(pos0, (int)(i & 63u), (uint32_t)nbins); pos1 = with_lane(pos1, (int)(i & 63u), 0u);
+            ++nbins;
+            continue;
+        }
+        uint32_t turned = 0;
+        if (rotate && ((ewh - need) & FREE_GUARD) != FREE_GUARD) { need = needt; turned = 0x10000u; }      // upright whenever that fits
+        if (fresh) { at = nfree; ++nbins; }                  // a new bin's area goes to the end of the list
+        pos0 = with_lane(pos0, (int)(i & 63u), (uint32_t)fb | turned);
+        pos1 = with_lane(pos1, (int)(i & 63u), exy);
         // remainder: the larger of (right strip, full height) and (bottom strip, full width),
         // plus what is left of the other
-        const int rw = fw - bw, bhei = fh - bh;
-        const bool right_full = rw * fh >= fw * bhei;
-        const int rh = right_full ? fh : bh, bwid = right_full ? bw : fw;
-        const bool keep_r = min(rw, rh) >= minside, keep_b = min(bwid, bhei) >= minside;
-        const uint32_t Rxy = (uint32_t)(fx + bw) | ((uint32_t)fy << 16), Rwh = (uint32_t)rw | ((uint32_t)rh << 16);
-        const uint32_t Bxy = (uint32_t)fx | ((uint32_t)(fy + bh) << 16), Bwh = (uint32_t)bwid | ((uint32_t)bhei << 16);
-        const bool b_first = keep_b && (!keep_r || bwid * bhei < rw * rh);     // both kept: the smaller one first
-        const uint32_t e0xy = b_first ? Bxy : Rxy, e0wh = b_first ? Bwh : Rwh, e1xy = b_first ? Rxy : Bxy, e1wh = b_first ? Rwh : Bwh;
-        const int ni = (keep_r ? 1 : 0) + (keep_b ? 1 : 0);
-        // the survivors replace entry `at`: the entries behind it move by ni - 1 lanes
-        const uint32_t dxy = lane_from_below(rxy), dwh = lane_from_below(rwh), dbn = lane_from_below(rbn);
-        const uint32_t uxy = lane_from_above(rxy), uwh = lane_from_above(rwh), ubn = lane_from_above(rbn);
-        const bool down = ni == 2 && lane > at + 1, up = ni == 0 && lane >= at;
-        rxy = down ? dxy : up ? uxy : rxy; rwh = down ? dwh : up ? uwh : rwh; rbn = down ? dbn : up ? ubn : rbn;
-        const bool s0 = ni > 0 && lane == at, s1 = ni > 1 && lane == at + 1;
-        rxy = s0 ? e0xy : s1 ? e1xy : rxy; rwh = s0 ? e0wh : s1 ? e1wh : rwh; rbn = (s0 || s1) ? (uint32_t)fb : rbn;
-        nfree = cur_n + ni - 1;
+        const uint32_t rem = (ewh - need) & ~FREE_GUARD;
+        const int rw = (int)(rem & 0xFFFF), bhei = (int)(rem >> 16);
+        int ni = 0;
+        if (max(rw, bhei) >= minside) {
+            const int fw = (int)(ewh & 0x7FFF), fh = (int)(ewh >> 16 & 0x7FFF), bw = (int)(need & 0xFFFF), bh = (int)(need >> 16);
+            const bool right_full = rw * fh >= fw * bhei;
+            const int rh = right_full ? fh : bh, bwid = right_full ? bw : fw;
+            const bool keep_r = min(rw, rh) >= minside, keep_b = min(bwid, bhei) >= minside;
+            const uint32_t Rxy = exy + (uint32_t)bw, Rwh = (uint32_t)rw | (uint32_t)rh << 16 | FREE_GUARD;
+            const uint32_t Bxy = exy + ((uint32_t)bh << 16), Bwh = (uint32_t)bwid | (uint32_t)bhei << 16 | FREE_GUARD;
+            const bool b_first = keep_b && (!keep_r || bwid * bhei < rw * rh);     // both kept: the smaller one first
+            ni = (keep_r ? 1 : 0) + (keep_b ? 1 : 0);
+            if (ni == 2) {
+#define UP(c, below)                                                                                \
+                if (64 * c <= nfree && c >= (at >> 6)) {                                            \
+                    uint32_t xy = lane_from_below(rxy##c), wh = lane_from_below(rwh##c), bn = lane_from_below(rbn##c);     \
+                    if (c > (at >> 6)) {                                                            \
+                        xy = with_lane(xy, 0, lane_of(rxy##below, 63)); wh = with_lane(wh, 0, lane_of(rwh##below, 63));    \
+                        bn = with_lane(bn, 0, lane_of(rbn##below, 63));                             \
+                    }                                                                               \
+                    const bool mv = lane + 64 * c > at;                                             \
+                    rxy##c = mv ? xy : rxy##c; rwh##c = mv ? wh : rwh##c; rbn##c = mv ? bn : rbn##c;                       \
+                }
+                if (!fresh) { UP(3, 2) UP(2, 1) UP(1, 0) UP(0, 0) }      // the entries behind `at` move up by one
+#undef UP
+                PUT(at + 1, b_first ? Rxy : Bxy, b_first ? Rwh : Bwh);
+            }
+            if (ni) PUT(at, b_first ? Bxy : Rxy, b_first ? Bwh : Rwh);
+        }
+#define DOWN(c, above)                                                                              \
+        if (64 * c < nfree && c >= (at >> 6)) {                                                     \
+            uint32_t xy = lane_from_above(rxy##c), wh = lane_from_above(rwh##c), bn = lane_from_above(rbn##c);             \
+            wh = with_lane(wh, 63, above > c ? lane_of(rwh##above, 0) : FREE_GUARD);                \
+            if (64 * c + 64 < nfree) { xy = with_lane(xy, 63, lane_of(rxy##above, 0)); bn = with_lane(bn, 63, lane_of(rbn##above, 0)); }    \
+            const bool mv = lane + 64 * c >= at;                                                    \
+            rxy##c = mv ? xy : rxy##c; rwh##c = mv ? wh : rwh##c; rbn##c = mv ? bn : rbn##c;        \
+        }
+        if (ni == 0 && !fresh) { DOWN(0, 1) DOWN(1, 2) DOWN(2, 3) DOWN(3, 3) }   // the entries behind `at` move down by one
+#undef DOWN
+        nfree += ni - (fresh ? 0 : 1);
     }
-    // ---- the list has outgrown the wave: it moves to LDS for the rest of the boxes ----
+#undef PUT
+#undef PUT1
+    // ---- the list has outgrown the registers: it moves to LDS for the rest of the boxes ----
     if (i < n && !overflow) {
-        if (lane < nfree) { fxy[lane] = rxy; fwh[lane] = rwh; fbin[lane] = rbn; }
+#define SPILL(c) if (64 * c + lane < nfree) { fxy[64 * c + lane] = rxy##c; fwh[64 * c + lane] = rwh##c & ~FREE_GUARD; fbin[64 * c + lane] = rbn##c; }
+        SPILL(0) SPILL(1) SPILL(2) SPILL(3)
+#undef SPILL
         wave_sync();
     }
     for (; i < n && !overflow; ++i) {
-        if ((i & 63u) == 0) {
-            flush(i);
-            szv = (i + lane < n) ? size_of(i + lane) : 0u;
-        }
-        const uint32_t sz = (uint32_t)__builtin_amdgcn_readlane((int)szv, (int)(i & 63u));
+        if ((i & 63u) == 0) next_sizes();
+        const uint32_t sz = lane_of(szv, (int)(i & 63u));
         int bw = RH_MB * (int)(sz & 0xFFFF) + 2 * halo, bh = RH_MB * (int)(sz >> 16) + 2 * halo;
         // first rectangle, in list order, that fits: every lane reads one entry whole, the winner's
         // fields are then taken from its lane
@@ -330,15 +464,18 @@ __device__ __forceinline__ void place_boxes(uint32_t n, SizeOf size_of, uint32_t
     n_bins_out = nbins; overflow_out = overflow;
 }
 
+// pcount: 0 boxes, 1 bins, 2 overflow, 3 boxes appended by the labelling kernel (0 between plans)
 __global__ __launch_bounds__(64) void k_plan_place(const rh_rawbox* __restrict__ sorted, uint32_t* pcount,
                                                    int halo, int S, int max_bins, int free_cap, int rotate,
                                                    uint32_t* __restrict__ box_pos)
 {
     extern __shared__ uint32_t sm[];
     int nbins; bool overflow;
-    place_boxes(pcount[0], [&](uint32_t i) { return (uint32_t)sorted[i].wmb | ((uint32_t)sorted[i].hmb << 16); },
-                sm, sm + free_cap, sm + 2 * free_cap, halo, S, max_bins, free_cap, rotate, box_pos, nbins, overflow);
-    if (threadIdx.x == 0) { pcount[1] = nbins; pcount[2] = overflow ? 1u : 0u; }
+    const uint32_t n = pcount[3];
+    auto size_of = [&](uint32_t i) { return (uint32_t)sorted[i].wmb | ((uint32_t)sorted[i].hmb << 16); };
+    if (rotate) place_boxes<true>(n, size_of, sm, sm + free_cap, sm + 2 * free_cap, halo, S, max_bins, free_cap, box_pos, nbins, overflow);
+    else place_boxes<false>(n, size_of, sm, sm + free_cap, sm + 2 * free_cap, halo, S, max_bins, free_cap, box_pos, nbins, overflow);
+    if (threadIdx.x == 0) { pcount[0] = n; pcount[1] = nbins; pcount[2] = overflow ? 1u : 0u; pcount[3] = 0; }
 }
 
 // Placement rows of box i and of selected macroblock i (Alg. 1's output).
@@ -403,11 +540,12 @@ __global__ __launch_bounds__(256) void k_plan_emit(const rh_rawbox* __restrict__
 //      importance values in ascending index (fp32, from an LDS copy of the frame's map) and
 //      writes the box and its macroblocks' owner.
 //   B  rank by counting over all threads (keys in LDS for up to PF_KEYS boxes)
-//   C  first fit by wave 0 (place_boxes), the free list in LDS
+//   C  first fit by wave 0 (place_boxes)
 //   D  placement rows by all threads
 #define PF_THREADS 1024
 #define PF_WAVES (PF_THREADS / 64)
 #define PF_KEYS 2048
+#define PF_FRAMES 16                      // more frames: phases in launches of their own (one round of waves here: 20 us; 128 frames: 160 us)
 #define PF_MAX_PER 2304                   // 16 waves x per x 4 B of importance <= 144 KB
 
 typedef unsigned long long u64;
@@ -420,6 +558,29 @@ __device__ __forceinline__ u64 fill_runs(u64 n, u64 m)     // extend the bits of
     return n | up | dn;
 }
 
+// 64-bit values of the lanes beside this one (0 past the ends), of one lane, and the union over all lanes: by DPP
+// and lane reads, a few cycles each, where a shuffle goes through LDS (about 100) - a region takes one
+// exchange for every row that it spans
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ u64 dpp64(u64 v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xF, false);
+    return (u64)hi << 32 | lo;
+}
+__device__ __forceinline__ u64 row_above(u64 v) { return dpp64<0x138 /* wave_shr:1 */>(v); }
+__device__ __forceinline__ u64 row_below(u64 v) { return dpp64<0x130 /* wave_shl:1 */>(v); }
+__device__ __forceinline__ u64 row_of(u64 v, int l)
+{
+    return (u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+}
+__device__ __forceinline__ u64 rows_or(u64 v)
+{
+    v |= dpp64<0x111 /* row_shr:1 */>(v); v |= dpp64<0x112>(v); v |= dpp64<0x114>(v); v |= dpp64<0x118>(v);
+    v |= dpp64<0x142 /* row_bcast:15 */, 0xA>(v); v |= dpp64<0x143 /* row_bcast:31 */, 0xC>(v);
+    return row_of(v, 63);
+}
+
 struct plan_args {
     const uint8_t* mask; const float* imp; const uint32_t* list; const uint32_t* n_sel;
     int F, mbw, mbh, conn, T, sort_policy, halo, S, max_bins, free_cap, rotate;
@@ -427,102 +588,139 @@ struct plan_args {
     rh_box* boxes; rh_mbplace* places; uint32_t* counts;
 };
 
+// Phase A for frame f, one wave: its regions, bounds and boxes.  append(k): first of k new slots of a.raw.
+template <typename Append>
+__device__ __forceinline__ void frame_boxes(const plan_args& a, int f, float* simp, Append append)
+{
+    const int lane = threadIdx.x & 63, mbw = a.mbw, mbh = a.mbh, per = mbw * mbh, T = a.T;
+    const size_t base = (size_t)f * per;
+    for (int i = lane; i < per; i += 64) simp[i] = a.imp[base + i];
+    u64 m = 0;
+    for (int y = 0; y < mbh; y += 8) {                   // eight rows' loads in flight at a time
+        uint8_t v8[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v8[u] = (lane < mbw && y + u < mbh) ? a.mask[base + (size_t)(y + u) * mbw + lane] : (uint8_t)0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const u64 row = __ballot(v8[u] != 0);
+            if (lane == y + u) m = row;
+        }
+    }
+    wave_sync();                                         // simp is read by other lanes below
+    // Macroblocks without a neighbour are regions and boxes of one macroblock: every row writes its own at
+    // the same time.  (One region after the other took 2 us each, half of them with scattered importance.)
+    u64 iso;
+    {
+        const u64 up = row_above(m), dn = row_below(m);
+        const u64 col = a.conn == 8 ? m | up | dn : m;
+        iso = m & ~((col << 1) | (col >> 1) | up | dn);
+    }
+    u64 rem = m & ~iso;
+    for (;;) {
+        const bool has = iso != 0;
+        const u64 hm = __ballot(has);
+        if (!hm) break;
+        uint32_t slot0 = 0;
+        if (lane == 0) slot0 = append((uint32_t)__popcll(hm));
+        slot0 = __shfl(slot0, 0);
+        if (has) {
+            const int x = __ffsll((long long)iso) - 1, g = lane * mbw + x;
+            iso &= iso - 1;
+            rh_rawbox b;
+            b.frame = f; b.mbx0 = x; b.mby0 = lane; b.wmb = 1; b.hmb = 1;
+            b.id = (uint32_t)(base + g); b.sum = __fadd_rn(0.0f, simp[g]);
+            b.key = a.sort_policy == RH_SORT_AREA ? 1.0 : (double)b.sum;
+            a.raw[slot0 + (uint32_t)__popcll(hm & ((1ull << lane) - 1ull))] = b;
+            a.owner_id[base + g] = b.id;
+        }
+    }
+    for (;;) {
+        const u64 rows_left = __ballot(rem != 0);
+        if (!rows_left) break;
+        const int ys = __ffsll((long long)rows_left) - 1;
+        const u64 seed_row = row_of(rem, ys);
+        u64 comp = lane == ys ? (seed_row & (~seed_row + 1)) : 0;           // lowest set bit: the region's label
+        for (;;) {                                       // RegionProps: grow until stable
+            const u64 up = row_above(comp), dn = row_below(comp);
+            u64 n;
+            if (a.conn == 8) { n = comp | up | dn; n |= (n << 1) | (n >> 1); }
+            else n = comp | up | dn | (comp << 1) | (comp >> 1);
+            n = fill_runs((n & m) | comp, m);
+            const bool changed = n != comp;
+            comp = n;
+            if (!__any(changed)) break;
+        }
+        rem &= ~comp;
+        // Bound
+        const u64 rows_in = __ballot(comp != 0);
+        const int y0 = __ffsll((long long)rows_in) - 1, y1 = 63 - __clzll((long long)rows_in);
+        const u64 cols = rows_or(comp);
+        const int x0 = __ffsll((long long)cols) - 1, x1 = 63 - __clzll((long long)cols);
+        // Partition: cells of the T x T grid anchored at (x0, y0), one lane per cell
+        const int ncx = (x1 - x0) / T + 1, ncy = (y1 - y0) / T + 1, cells = ncx * ncy;
+        for (int c0 = 0; c0 < cells; c0 += 64) {         // uniform over the wave
+            const int c = c0 + lane;
+            const bool active = c < cells;
+            const int cy = active ? c / ncx : 0, cx = active ? c - cy * ncx : 0;
+            const int ra = y0 + cy * T, rb = min(ra + T - 1, y1), ca = x0 + cx * T, cb = min(ca + T - 1, x1);
+            const u64 cmask = ((cb - ca + 1) >= 64 ? ~0ull : ((1ull << (cb - ca + 1)) - 1ull)) << ca;
+            int leader = -1, bx0 = 64, bx1 = -1, by0 = 64, by1 = -1;
+            float sum = 0.0f;
+            const int span = min(T, y1 - y0 + 1);       // rows a cell can have: uniform
+            for (int rr = 0; rr < span; ++rr) {
+                const int r = ra + rr;
+                const u64 rowbits = __shfl(comp, (active && r <= rb) ? r : 0);     // every lane takes part
+                u64 bits = (active && r <= rb) ? (rowbits & cmask) : 0;
+                if (bits) {
+                    if (leader < 0) { leader = r * mbw + (__ffsll((long long)bits) - 1); by0 = r; }
+                    by1 = r;
+                    bx0 = min(bx0, __ffsll((long long)bits) - 1); bx1 = max(bx1, 63 - __clzll((long long)bits));
+                    while (bits) {                       // ascending column = ascending flat index
+                        const int x = __ffsll((long long)bits) - 1;
+                        bits &= bits - 1;
+                        sum = __fadd_rn(sum, simp[r * mbw + x]);
+                        a.owner_id[base + r * mbw + x] = (uint32_t)(base + leader);
+                    }
+                }
+            }
+            const bool has = leader >= 0;
+            const u64 hm = __ballot(has);
+            uint32_t slot0 = 0;
+            if (lane == 0 && hm) slot0 = append((uint32_t)__popcll(hm));
+            slot0 = __shfl(slot0, 0);
+            if (has) {
+                rh_rawbox b;
+                b.frame = f; b.mbx0 = bx0; b.mby0 = by0; b.wmb = bx1 - bx0 + 1; b.hmb = by1 - by0 + 1;
+                b.id = (uint32_t)(base + leader); b.sum = sum;
+                const int area = (bx1 - bx0 + 1) * (by1 - by0 + 1);
+                b.key = a.sort_policy == RH_SORT_AREA ? (double)area : (double)sum / (double)area;
+                a.raw[slot0 + (uint32_t)__popcll(hm & ((1ull << lane) - 1ull))] = b;
+            }
+        }
+    }
+}
+
+// Phase A in a launch of its own, one frame per workgroup of one wave
+__global__ __launch_bounds__(64) void k_plan_regions(plan_args a, uint32_t* pcount)
+{
+    extern __shared__ float simp[];
+    frame_boxes(a, blockIdx.x, simp, [&](uint32_t k) { return atomicAdd(&pcount[3], k); });
+}
+
 __global__ __launch_bounds__(PF_THREADS) void k_plan_fused(plan_args a)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
     __shared__ uint32_t s_nraw, s_nbins, s_overflow;
     __shared__ uint32_t s_sz[PF_KEYS];                       // sizes of the sorted boxes, for the first fit
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int mbw = a.mbw, mbh = a.mbh, per = mbw * mbh, T = a.T;
+    const int mbw = a.mbw, per = mbw * a.mbh;
     if (tid == 0) s_nraw = 0;
     __syncthreads();
 
     // ---------------- A: regions and boxes, one wave per frame ----------------
     float* simp = (float*)dyn + (size_t)wave * per;
     for (int f = wave; f < a.F; f += PF_WAVES) {
-        const size_t base = (size_t)f * per;
-        for (int i = lane; i < per; i += 64) simp[i] = a.imp[base + i];
-        u64 m = 0;
-        for (int y = 0; y < mbh; y += 8) {                   // eight rows' loads in flight at a time
-            uint8_t v8[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v8[u] = (lane < mbw && y + u < mbh) ? a.mask[base + (size_t)(y + u) * mbw + lane] : (uint8_t)0;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const u64 row = __ballot(v8[u] != 0);
-                if (lane == y + u) m = row;
-            }
-        }
-        wave_sync();                                         // simp is read by other lanes below
-        u64 rem = m;
-        for (;;) {
-            const u64 rows_left = __ballot(rem != 0);
-            if (!rows_left) break;
-            const int ys = __ffsll((long long)rows_left) - 1;
-            const u64 seed_row = __shfl(rem, ys);
-            u64 comp = lane == ys ? (seed_row & (~seed_row + 1)) : 0;           // lowest set bit: the region's label
-            for (;;) {                                       // RegionProps: grow until stable
-                u64 up = __shfl_up(comp, 1), dn = __shfl_down(comp, 1);
-                if (lane == 0) up = 0;
-                if (lane == 63) dn = 0;
-                u64 n;
-                if (a.conn == 8) { n = comp | up | dn; n |= (n << 1) | (n >> 1); }
-                else n = comp | up | dn | (comp << 1) | (comp >> 1);
-                n = fill_runs((n & m) | comp, m);
-                const bool changed = n != comp;
-                comp = n;
-                if (!__any(changed)) break;
-            }
-            rem &= ~comp;
-            // Bound
-            const u64 rows_in = __ballot(comp != 0);
-            const int y0 = __ffsll((long long)rows_in) - 1, y1 = 63 - __clzll((long long)rows_in);
-            u64 cols = comp;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) cols |= __shfl_xor(cols, o);
-            const int x0 = __ffsll((long long)cols) - 1, x1 = 63 - __clzll((long long)cols);
-            // Partition: cells of the T x T grid anchored at (x0, y0), one lane per cell
-            const int ncx = (x1 - x0) / T + 1, ncy = (y1 - y0) / T + 1, cells = ncx * ncy;
-            for (int c0 = 0; c0 < cells; c0 += 64) {         // uniform over the wave
-                const int c = c0 + lane;
-                const bool active = c < cells;
-                const int cy = active ? c / ncx : 0, cx = active ? c - cy * ncx : 0;
-                const int ra = y0 + cy * T, rb = min(ra + T - 1, y1), ca = x0 + cx * T, cb = min(ca + T - 1, x1);
-                const u64 cmask = ((cb - ca + 1) >= 64 ? ~0ull : ((1ull << (cb - ca + 1)) - 1ull)) << ca;
-                int leader = -1, bx0 = 64, bx1 = -1, by0 = 64, by1 = -1;
-                float sum = 0.0f;
-                const int span = min(T, y1 - y0 + 1);       // rows a cell can have: uniform
-                for (int rr = 0; rr < span; ++rr) {
-                    const int r = ra + rr;
-                    const u64 rowbits = __shfl(comp, (active && r <= rb) ? r : 0);     // every lane takes part
-                    u64 bits = (active && r <= rb) ? (rowbits & cmask) : 0;
-                    if (bits) {
-                        if (leader < 0) { leader = r * mbw + (__ffsll((long long)bits) - 1); by0 = r; }
-                        by1 = r;
-                        bx0 = min(bx0, __ffsll((long long)bits) - 1); bx1 = max(bx1, 63 - __clzll((long long)bits));
-                        while (bits) {                       // ascending column = ascending flat index
-                            const int x = __ffsll((long long)bits) - 1;
-                            bits &= bits - 1;
-                            sum = __fadd_rn(sum, simp[r * mbw + x]);
-                            a.owner_id[base + r * mbw + x] = (uint32_t)(base + leader);
-                        }
-                    }
-                }
-                const bool has = leader >= 0;
-                const u64 hm = __ballot(has);
-                uint32_t slot0 = 0;
-                if (lane == 0 && hm) slot0 = atomicAdd(&s_nraw, (uint32_t)__popcll(hm));
-                slot0 = __shfl(slot0, 0);
-                if (has) {
-                    rh_rawbox b;
-                    b.frame = f; b.mbx0 = bx0; b.mby0 = by0; b.wmb = bx1 - bx0 + 1; b.hmb = by1 - by0 + 1;
-                    b.id = (uint32_t)(base + leader); b.sum = sum;
-                    const int area = (bx1 - bx0 + 1) * (by1 - by0 + 1);
-                    b.key = a.sort_policy == RH_SORT_AREA ? (double)area : (double)sum / (double)area;
-                    a.raw[slot0 + (uint32_t)__popcll(hm & ((1ull << lane) - 1ull))] = b;
-                }
-            }
-        }
+        frame_boxes(a, f, simp, [&](uint32_t k) { return atomicAdd(&s_nraw, k); });
         wave_sync();                                         // before the next frame overwrites simp
     }
     __threadfence_block();
@@ -560,9 +758,10 @@ __global__ __launch_bounds__(PF_THREADS) void k_plan_fused(plan_args a)
     // ---------------- C: first fit, wave 0 ----------------
     if (wave == 0) {
         int nbins; bool overflow;
-        place_boxes(n, [&](uint32_t i) { return i < PF_KEYS ? s_sz[i] : ((uint32_t)a.sorted[i].wmb | ((uint32_t)a.sorted[i].hmb << 16)); },
-                    dyn, dyn + a.free_cap, dyn + 2 * a.free_cap, a.halo, a.S, a.max_bins, a.free_cap, a.rotate, a.box_pos,
-                    nbins, overflow);
+        auto size_of = [&](uint32_t i) { return i < PF_KEYS ? s_sz[i] : ((uint32_t)a.sorted[i].wmb | ((uint32_t)a.sorted[i].hmb << 16)); };
+        uint32_t* fl = dyn;
+        if (a.rotate) place_boxes<true>(n, size_of, fl, fl + a.free_cap, fl + 2 * a.free_cap, a.halo, a.S, a.max_bins, a.free_cap, a.box_pos, nbins, overflow);
+        else place_boxes<false>(n, size_of, fl, fl + a.free_cap, fl + 2 * a.free_cap, a.halo, a.S, a.max_bins, a.free_cap, a.box_pos, nbins, overflow);
         if (lane == 0) { s_nbins = (uint32_t)nbins; s_overflow = overflow ? 1u : 0u; }
     }
     __threadfence_block();
@@ -592,31 +791,35 @@ rh_status rh_launch_plan(rh_ctx* ctx, int F, const float* imp, const uint8_t* ma
 {
     const int per = ctx->per, total = per * F;
     uint32_t* box_pos = ctx->pcount + 8;
-    if (ctx->mbw <= 64 && ctx->mbh <= 64 && per <= PF_MAX_PER) {
-        // the usual case: everything in one launch
+    plan_args a;
+    a.mask = mask; a.imp = imp; a.list = list; a.n_sel = n_sel;
+    a.F = F; a.mbw = ctx->mbw; a.mbh = ctx->mbh; a.conn = ctx->cfg.connectivity; a.T = ctx->T;
+    a.sort_policy = ctx->cfg.sort_policy; a.halo = ctx->cfg.halo; a.S = ctx->cfg.bin_size; a.max_bins = ctx->cfg.max_bins;
+    a.free_cap = ctx->free_cap; a.rotate = ctx->cfg.rotate;
+    a.owner_id = ctx->owner_id; a.rank_of_id = ctx->rank_of_id; a.raw = ctx->raw; a.sorted = ctx->sorted; a.box_pos = box_pos;
+    a.boxes = boxes; a.places = places; a.counts = counts;
+    const bool rows64 = ctx->mbw <= 64 && ctx->mbh <= 64 && per <= PF_MAX_PER;
+    if (rows64 && F <= PF_FRAMES) {
+        // the usual batch: everything in one launch
         size_t lds = (size_t)PF_WAVES * per * 4;
         if (lds < (size_t)PF_KEYS * 12) lds = (size_t)PF_KEYS * 12;
         if (lds < (size_t)ctx->free_cap * 12) lds = (size_t)ctx->free_cap * 12;
-        plan_args a;
-        a.mask = mask; a.imp = imp; a.list = list; a.n_sel = n_sel;
-        a.F = F; a.mbw = ctx->mbw; a.mbh = ctx->mbh; a.conn = ctx->cfg.connectivity; a.T = ctx->T;
-        a.sort_policy = ctx->cfg.sort_policy; a.halo = ctx->cfg.halo; a.S = ctx->cfg.bin_size; a.max_bins = ctx->cfg.max_bins;
-        a.free_cap = ctx->free_cap; a.rotate = ctx->cfg.rotate;
-        a.owner_id = ctx->owner_id; a.rank_of_id = ctx->rank_of_id; a.raw = ctx->raw; a.sorted = ctx->sorted; a.box_pos = box_pos;
-        a.boxes = boxes; a.places = places; a.counts = counts;
         rh_prof_scope ps(ctx, RH_PROF_PLAN, 1);
         hipLaunchKernelGGL(k_plan_fused, dim3(1), dim3(PF_THREADS), lds, ctx->stream, a);
         RH_HIP(ctx, hipGetLastError());
         return RH_OK;
     }
-    rh_prof_scope ps(ctx, RH_PROF_PLAN, 5);
-    hipLaunchKernelGGL(k_plan_zero, dim3(1), dim3(64), 0, ctx->stream, ctx->pcount);
-    const int imp_in_lds = (size_t)per * 20 <= 150 * 1024;
-    hipLaunchKernelGGL(k_plan_label, dim3(F), dim3(256), (size_t)per * (imp_in_lds ? 20 : 16), ctx->stream, mask, imp, ctx->mbw,
-                       ctx->mbh, ctx->cfg.connectivity, ctx->T, ctx->cfg.sort_policy, imp_in_lds, ctx->owner_id, ctx->raw,
-                       ctx->pcount);
+    rh_prof_scope ps(ctx, RH_PROF_PLAN, 4);
+    if (rows64) {
+        hipLaunchKernelGGL(k_plan_regions, dim3(F), dim3(64), (size_t)per * 4, ctx->stream, a, ctx->pcount);
+    } else {
+        const int imp_in_lds = (size_t)per * 20 <= 150 * 1024;
+        hipLaunchKernelGGL(k_plan_label, dim3(F), dim3(256), (size_t)per * (imp_in_lds ? 20 : 16), ctx->stream, mask, imp, ctx->mbw,
+                           ctx->mbh, ctx->cfg.connectivity, ctx->T, ctx->cfg.sort_policy, imp_in_lds, ctx->owner_id, ctx->raw,
+                           ctx->pcount);
+    }
     const int nblk = (total + 255) / 256;
-    hipLaunchKernelGGL(k_plan_rank, dim3(nblk), dim3(256), 0, ctx->stream, ctx->raw, ctx->pcount, ctx->sorted,
+    hipLaunchKernelGGL(k_plan_rank, dim3(min(512, (total + 15) / 16)), dim3(256), 0, ctx->stream, ctx->raw, ctx->pcount, ctx->sorted,
                        ctx->rank_of_id);
     hipLaunchKernelGGL(k_plan_place, dim3(1), dim3(64), (size_t)ctx->free_cap * 12, ctx->stream, ctx->sorted,
                        ctx->pcount, ctx->cfg.halo, ctx->cfg.bin_size, ctx->cfg.max_bins, ctx->free_cap, ctx->cfg.rotate,

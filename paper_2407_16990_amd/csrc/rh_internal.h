@@ -78,7 +78,7 @@ struct rh_ctx {
     uint32_t* rank_of_id;   // [total MBs] sorted position of the box with that id
     rh_rawbox* raw;         // [total MBs]
     rh_rawbox* sorted;      // [total MBs]
-    uint32_t* pcount;       // [8] plan counters: 0 n_raw boxes
+    uint32_t* pcount;       // [8] plan counters (k_plan_place)
     // temporal reuse scratch (dev)
     int32_t* tr_off;        // [max_frames + 1] first frame of each stream
     uint64_t* tr_A;         // [max_frames] cumulative change before each frame

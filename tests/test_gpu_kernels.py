@@ -7,7 +7,7 @@ import torch
 import oracle
 import workloads as wl
 from paper_2407_16990_amd import RH
-from gpu_common import check_net, dev
+from gpu_common import check_net, check_select_and_plan, dev, make_rh
 
 pytestmark = pytest.mark.gpu
 
@@ -63,4 +63,27 @@ def test_block32_tiles_do_not_depend_on_the_batch():
         rh.enhance(x[i:i + 1].contiguous(), out=one)
         assert torch.equal(one[0], out[i]), i
     assert bool((out[60] == -1.0).all())
+    rh.close()
+
+
+# Plans whose list of free rectangles stays in one, grows to several, or outgrows the registers' chunks of 64
+# (most entries: 32, 181, 206, 425, 263), of up to 16 frames (one launch) and more; isolated macroblocks with
+# either neighbourhood; turned boxes; bins that run out in either loop
+@pytest.mark.parametrize("F,w,h,halo,S,frac,kind,T,conn,rotate,max_bins", [
+    (17, 480, 272, 10, 128, 0.5, "clustered", 0, 8, False, 400), (128, 480, 272, 10, 128, 0.2, "clustered", 0, 8, False, 800),
+    (60, 480, 272, 10, 128, 0.12, "uniform", 0, 8, False, 600), (16, 640, 368, 10, 192, 0.4, "clustered", 3, 8, False, 300),
+    (12, 1008, 560, 10, 128, 0.5, "clustered", 0, 8, False, 900), (16, 480, 272, 10, 128, 0.12, "uniform", 0, 4, True, 200),
+    (60, 480, 272, 10, 128, 0.12, "uniform", 0, 4, True, 600), (16, 640, 368, 10, 192, 0.4, "clustered", 3, 8, True, 300),
+    (16, 480, 272, 10, 128, 0.12, "uniform", 0, 8, False, 37), (60, 480, 272, 10, 128, 0.12, "uniform", 0, 8, False, 350),
+    (20, 64, 1024, 0, 16, 0.3, "uniform", 0, 8, False, 2000), (1, 1024, 32, 3, 64, 1.0, "uniform", 2, 8, True, 60),
+])
+def test_plan_list_lengths(F, w, h, halo, S, frac, kind, T, conn, rotate, max_bins):
+    cfg = wl.replace(wl.config(3), n_frames=F, width=w, height=h, importance=kind, frac=frac, halo=halo, bin_size=S)
+    frames = np.random.default_rng(F).integers(0, 256, (F, h, w, 3), dtype=np.uint8)
+    net = wl.Net("plain", 1, 2, 1)
+    rh = make_rh(wl.replace(cfg, net=net), wl.make_weights(net, 0, "fp32"), max_bins=max_bins, precision="fp32", connectivity=conn,
+                 max_box_mbs=T, rotate=rotate)
+    plan, _, _ = check_select_and_plan(rh, cfg, frames, wl.make_importance(cfg), wl.make_segments(cfg), conn=conn, T=T or None,
+                                       max_bins=max_bins, rotate=rotate)
+    assert plan.overflow == (max_bins in (37, 350))
     rh.close()
