@@ -21,46 +21,49 @@ __device__ __forceinline__ uint32_t imp_key(float v)
 // then the number of selected macroblocks and admitted ties of each of its frames.
 // seg_par[seg] = {g_begin, g_end, k, thr bits}.
 // A queue of up to KREG * 1024 keys (a 30-frame chunk of 480x272 streams is 15k) is read from
-// global memory once and kept in registers over the four radix passes.
+// global memory once and kept in registers over the three radix passes; a longer one is read anew for each
+// pass, eight loads in flight per thread.  (64 keys per thread cost 128 registers and spills: slower at every size.)
 #define KREG 16
+#define BINS 2048            // digits of 11, 11 and 10 bits
+// Segment tables travel as kernel arguments (copied at launch), so the caller's array may be
+// freed as soon as rh_select_regions returns and no host synchronisation is needed.
+struct seg_chunk { uint32_t n, first; uint32_t fb[64], fe[64], k[64], thr[64]; };
+
 #define FCHUNK 1024          // frames whose counts are held in LDS at a time
 
-__device__ __forceinline__ void hist_add(uint32_t* hist, bool todo, uint32_t bin, bool aggregate)
+// Inclusive prefix sum over the wave, by DPP
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t v)
 {
-    if (!aggregate) { if (todo) atomicAdd(&hist[bin], 1u); return; }
-    // the top byte (sign and exponent) can put most keys of a wave into a few bins, which would
-    // serialise their atomics: the lanes that share the bin of the first pending lane are counted
-    // with one ballot and added by one lane, twice; what is left after that is spread out
-    unsigned long long act = __ballot(todo);
-#pragma unroll
-    for (int round = 0; round < 2; ++round) {
-        if (!act) break;
-        const int first = __ffsll((long long)act) - 1;
-        const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)bin, first);
-        const unsigned long long same = __ballot(todo && bin == b);
-        if ((int)(threadIdx.x & 63) == first) atomicAdd(&hist[b], (uint32_t)__popcll(same));
-        act &= ~same;
-        todo = todo && bin != b;
-    }
-    if (todo) atomicAdd(&hist[bin], 1u);
+#define STEP(ctrl, rows) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xF, false)
+    STEP(0x111 /* row_shr:1 */, 0xF); STEP(0x112, 0xF); STEP(0x114, 0xF); STEP(0x118, 0xF);
+    STEP(0x142 /* row_bcast:15 */, 0xA); STEP(0x143 /* row_bcast:31 */, 0xC);
+#undef STEP
+    return v;
 }
 
-__global__ __launch_bounds__(1024) void k_select_kth(const float* __restrict__ imp,
+// INLINE: the call's segments are all in c (seg_par is not read), and the frames without a segment get their
+// counts (0) here; otherwise k_upload_segments has written seg_par and frame_seg.
+template <bool INLINE>
+__global__ __launch_bounds__(1024) void k_select_kth(seg_chunk c, int F, const float* __restrict__ imp,
                                                      const uint32_t* __restrict__ seg_par, int mode,
                                                      int per, uint32_t* __restrict__ seg_T,
                                                      uint32_t* __restrict__ frame_nsel,
                                                      uint32_t* __restrict__ frame_ties)
 {
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t s_wtot[4];
+    __shared__ uint32_t hist[BINS];
+    __shared__ uint32_t s_wtot[16];
     __shared__ uint32_t s_prefix, s_remaining;
     __shared__ uint32_t s_gt[FCHUNK], s_eq[FCHUNK], s_scan[2][FCHUNK];
     const int tid = threadIdx.x, seg = blockIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    const uint32_t g0 = seg_par[4 * seg], g1 = seg_par[4 * seg + 1];
+    const uint32_t g0 = INLINE ? c.fb[seg] * (uint32_t)per : seg_par[4 * seg], g1 = INLINE ? c.fe[seg] * (uint32_t)per : seg_par[4 * seg + 1];
+    if (INLINE) {
+        for (uint32_t f = (seg ? c.fe[seg - 1] : 0u) + tid; f < c.fb[seg]; f += 1024) frame_nsel[f] = 0;
+        if (seg + 1 == (int)c.n) for (uint32_t f = c.fe[seg] + tid; f < (uint32_t)F; f += 1024) frame_nsel[f] = 0;
+    }
     const uint32_t n = g1 - g0;
     const uint32_t f0 = g0 / per, f1 = g1 / per;
-    uint32_t k = seg_par[4 * seg + 2];
+    uint32_t k = INLINE ? c.k[seg] : seg_par[4 * seg + 2];
     // a queue that fits is read once and stays in registers for the radix passes and the counts
     const bool in_regs = n <= KREG * 1024u && f1 - f0 <= FCHUNK;
     uint32_t keys[KREG];
@@ -73,7 +76,7 @@ __global__ __launch_bounds__(1024) void k_select_kth(const float* __restrict__ i
     }
     uint32_t T, budget;
     if (mode == RH_THRESHOLD) {
-        float thr = __uint_as_float(seg_par[4 * seg + 3]);
+        float thr = __uint_as_float(INLINE ? c.thr[seg] : seg_par[4 * seg + 3]);
         if (thr != thr) { T = 0xFFFFFFFFu; budget = 0u; }       // NaN threshold selects nothing
         else { T = imp_key(thr); budget = 0xFFFFFFFFu; }         // every key == T is taken
     } else {
@@ -81,41 +84,40 @@ __global__ __launch_bounds__(1024) void k_select_kth(const float* __restrict__ i
         if (k == 0) { T = 0xFFFFFFFFu; budget = 0u; }            // no key reaches 0xFFFFFFFF
         else {
             uint32_t prefix = 0, remaining = k;
-            for (int pass = 3; pass >= 0; --pass) {
-                const int shift = pass * 8;
-                const uint32_t hi_mask = (pass == 3) ? 0u : (0xFFFFFFFFu << (shift + 8));
-                if (tid < 256) hist[tid] = 0;
+            for (int pass = 0; pass < 3; ++pass) {
+                const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+                const uint32_t digit = pass == 2 ? 1023u : 2047u, hi_mask = pass == 0 ? 0u : (0xFFFFFFFFu << (pass == 1 ? 21 : 10));
+                hist[tid] = 0; hist[tid + 1024] = 0;
                 __syncthreads();
                 if (in_regs) {
 #pragma unroll
                     for (int j = 0; j < KREG; ++j) {
                         const uint32_t i = (uint32_t)j * 1024u + tid;
-                        if ((uint32_t)j * 1024u < n)                 // uniform over the workgroup
-                            hist_add(hist, i < n && (keys[j] & hi_mask) == prefix, (keys[j] >> shift) & 255u, pass == 3);
+                        if (i < n && (keys[j] & hi_mask) == prefix) atomicAdd(&hist[keys[j] >> shift & digit], 1u);
                     }
                 } else {
-                    for (uint32_t i0 = 0; i0 < n; i0 += 1024) {
-                        const uint32_t i = i0 + tid;
-                        const uint32_t key = i < n ? imp_key(imp[g0 + i]) : 0u;
-                        hist_add(hist, i < n && (key & hi_mask) == prefix, (key >> shift) & 255u, pass == 3);
+                    for (uint32_t i0 = 0; i0 < n; i0 += 8 * 1024) {
+                        float v[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) { const uint32_t i = i0 + u * 1024 + tid; v[u] = imp[g0 + min(i, n - 1u)]; }
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            const uint32_t i = i0 + u * 1024 + tid, key = imp_key(v[u]);
+                            if (i < n && (key & hi_mask) == prefix) atomicAdd(&hist[key >> shift & digit], 1u);
+                        }
                     }
                 }
                 __syncthreads();
                 // bin t holds the k-th key iff  above(t) < remaining <= above(t) + hist[t],  above(t) = sum of
-                // the bins over t: a suffix scan by shuffles inside each of the 4 waves that hold the bins
-                uint32_t h = 0, suf = 0;
-                if (tid < 256) {
-                    h = hist[tid]; suf = h;
-#pragma unroll
-                    for (int o = 1; o < 64; o <<= 1) { const uint32_t t = __shfl_down(suf, o); if (lane + o < 64) suf += t; }
-                    if (lane == 0) s_wtot[wave] = suf;
-                }
+                // the bins over t.  Thread t holds the bins 2047 - 2t and 2046 - 2t, so that is a prefix sum.
+                const uint32_t b1 = BINS - 1 - 2 * tid, h1 = hist[b1], h0 = hist[b1 - 1], incl = wave_prefix(h1 + h0);
+                if (lane == 63) s_wtot[wave] = incl;
                 __syncthreads();
-                if (tid < 256) {
-                    uint32_t above = suf - h;
-                    for (int w = wave + 1; w < 4; ++w) above += s_wtot[w];
-                    if (above < remaining && remaining <= above + h) { s_prefix = prefix | ((uint32_t)tid << shift); s_remaining = remaining - above; }
-                }
+                const uint32_t tot = wave_prefix(s_wtot[lane & 15]);           // lanes 0..15: inclusive sums of the waves' totals
+                const uint32_t above1 = incl - h1 - h0 + (wave ? (uint32_t)__builtin_amdgcn_readlane((int)tot, __builtin_amdgcn_readfirstlane(wave ? wave - 1 : 0)) : 0u);
+                const uint32_t above0 = above1 + h1;
+                if (above1 < remaining && remaining <= above1 + h1) { s_prefix = prefix | (b1 << shift); s_remaining = remaining - above1; }
+                if (above0 < remaining && remaining <= above0 + h0) { s_prefix = prefix | ((b1 - 1) << shift); s_remaining = remaining - above0; }
                 __syncthreads();
                 prefix = s_prefix; remaining = s_remaining;
             }
@@ -133,7 +135,7 @@ __global__ __launch_bounds__(1024) void k_select_kth(const float* __restrict__ i
             __syncthreads();
 #pragma unroll
             for (int j = 0; j < KREG; ++j) {
-                if ((uint32_t)j * 1024u >= n) continue;            // uniform over the workgroup
+                if ((uint32_t)j * 1024u >= n) break;               // uniform over the workgroup
                 const uint32_t i = (uint32_t)j * 1024u + tid;
                 const bool gt = i < n && keys[j] > T, eq = i < n && keys[j] == T;
                 const uint32_t fr = i / (uint32_t)per;             // frame within the segment
@@ -200,7 +202,8 @@ __device__ __forceinline__ uint32_t block_prefix256(bool pred, uint32_t* s_w /*[
 }
 
 // Kernel 2: one workgroup per frame writes the frame's mask and its slice of the list.
-__global__ __launch_bounds__(256) void k_select_write(const float* __restrict__ imp,
+template <bool INLINE>
+__global__ __launch_bounds__(256) void k_select_write(seg_chunk c, const float* __restrict__ imp,
                                                       const int32_t* __restrict__ frame_seg,
                                                       const uint32_t* __restrict__ seg_T,
                                                       const uint32_t* __restrict__ frame_nsel,
@@ -215,11 +218,17 @@ __global__ __launch_bounds__(256) void k_select_write(const float* __restrict__ 
     if (tid == 0) s_base = 0;
     __syncthreads();
     uint32_t local = 0;
-    for (int i = tid; i < f; i += 256) if (frame_seg[i] >= 0) local += frame_nsel[i];
+    if (!INLINE || c.n)                    // no segment at all: no counts
+        for (int i = tid; i < f; i += 256) if (INLINE || frame_seg[i] >= 0) local += frame_nsel[i];
     if (local) atomicAdd(&s_base, local);
     __syncthreads();
     const uint32_t base = s_base;
-    const int seg = frame_seg[f];
+    int seg = -1;
+    if constexpr (INLINE) {
+        const int s = tid & 63;            // lane s looks at segment s
+        const unsigned long long m = __ballot(s < (int)c.n && c.fb[s] <= (uint32_t)f && (uint32_t)f < c.fe[s]);
+        if (m) seg = __ffsll((long long)m) - 1;
+    } else seg = frame_seg[f];
     const size_t fb = (size_t)f * per;
     if (seg < 0) {
         for (int i = tid; i < per; i += 256) mask[fb + i] = 0;
@@ -228,8 +237,8 @@ __global__ __launch_bounds__(256) void k_select_write(const float* __restrict__ 
     }
     const uint32_t T = seg_T[seg], ties_allowed = frame_ties[f];
     uint32_t run_sel = 0, run_eq = 0;
-    for (int c = 0; c < per; c += 256) {
-        const int i = c + tid;
+    for (int p0 = 0; p0 < per; p0 += 256) {
+        const int i = p0 + tid;
         const bool valid = i < per;
         const uint32_t key = valid ? imp_key(imp[fb + i]) : 0u;
         const bool gt = valid && key > T, eq = valid && key == T;
@@ -245,10 +254,6 @@ __global__ __launch_bounds__(256) void k_select_write(const float* __restrict__ 
     }
     if (f == F - 1 && tid == 0) *n_sel = base + run_sel;
 }
-
-// Segment tables travel as kernel arguments (copied at launch), so the caller's array may be
-// freed as soon as rh_select_regions returns and no host synchronisation is needed.
-struct seg_chunk { uint32_t n, first; uint32_t fb[64], fe[64], k[64], thr[64]; };
 
 // One workgroup.  The first chunk of a call (c.first == 0) also marks every frame as belonging to
 // no segment before the segments' frames are labelled.
@@ -271,19 +276,30 @@ __global__ __launch_bounds__(256) void k_upload_segments(seg_chunk c, int per, i
 hipError_t rh_enqueue_select(hipStream_t stream, const rh_select_scratch& sc, const float* imp, int F, int per,
                                  const rh_segment* segs, int nseg, int mode, uint8_t* mask, uint32_t* list, uint32_t* n_sel)
 {
-    for (int s0 = 0; s0 < nseg || s0 == 0; s0 += 64) {       // at least one launch: it clears frame_seg
-        seg_chunk c;
+    seg_chunk c;
+    auto fill = [&](int s0) {
         c.n = (uint32_t)((nseg - s0) < 64 ? (nseg - s0) : 64); c.first = (uint32_t)s0;
         for (uint32_t i = 0; i < c.n; ++i) {
             const rh_segment& g = segs[s0 + i];
             c.fb[i] = g.frame_begin; c.fe[i] = g.frame_end; c.k[i] = g.k; memcpy(&c.thr[i], &g.thr, 4);
         }
+    };
+    if (nseg <= 64) {                                        // one launch less: 5 us with its gap
+        fill(0);
+        if (nseg > 0)
+            hipLaunchKernelGGL(k_select_kth<true>, dim3(nseg), dim3(1024), 0, stream, c, F, imp, sc.seg_par, mode, per, sc.seg_T,
+                               sc.frame_nsel, sc.frame_ties);
+        hipLaunchKernelGGL(k_select_write<true>, dim3(F), dim3(256), 0, stream, c, imp, sc.frame_seg, sc.seg_T, sc.frame_nsel,
+                           sc.frame_ties, per, F, mask, list, n_sel);
+        return hipGetLastError();
+    }
+    for (int s0 = 0; s0 < nseg; s0 += 64) {
+        fill(s0);
         hipLaunchKernelGGL(k_upload_segments, dim3(1), dim3(256), 0, stream, c, per, F, sc.seg_par, sc.frame_seg);
     }
-    if (nseg > 0)
-        hipLaunchKernelGGL(k_select_kth, dim3(nseg), dim3(1024), 0, stream, imp, sc.seg_par, mode, per, sc.seg_T,
-                           sc.frame_nsel, sc.frame_ties);
-    hipLaunchKernelGGL(k_select_write, dim3(F), dim3(256), 0, stream, imp, sc.frame_seg, sc.seg_T, sc.frame_nsel,
+    hipLaunchKernelGGL(k_select_kth<false>, dim3(nseg), dim3(1024), 0, stream, c, F, imp, sc.seg_par, mode, per, sc.seg_T,
+                       sc.frame_nsel, sc.frame_ties);
+    hipLaunchKernelGGL(k_select_write<false>, dim3(F), dim3(256), 0, stream, c, imp, sc.frame_seg, sc.seg_T, sc.frame_nsel,
                        sc.frame_ties, per, F, mask, list, n_sel);
     return hipGetLastError();
 }
@@ -313,7 +329,7 @@ rh_status rh_launch_select(rh_ctx* ctx, const float* imp, int F, const rh_segmen
     rh_status st;
     if (const char* msg = rh_check_select_args(imp, F, segs, nseg, mode, mask, list, n_sel, &st))
         RH_FAIL(ctx, st, "rh_select_regions: %s", msg);
-    const int n_up = nseg > 0 ? (nseg + 63) / 64 : 1;
+    const int n_up = nseg > 64 ? (nseg + 63) / 64 : 0;
     rh_prof_scope ps(ctx, RH_PROF_SELECT, n_up + (nseg > 0 ? 2 : 1));
     const rh_select_scratch sc = {ctx->frame_seg, ctx->seg_par, ctx->seg_T, ctx->frame_nsel, ctx->frame_ties};
     RH_HIP(ctx, rh_enqueue_select(ctx->stream, sc, imp, F, ctx->per, segs, nseg, mode, mask, list, n_sel));

@@ -7,7 +7,7 @@ import torch
 import oracle
 import workloads as wl
 from paper_2407_16990_amd import RH
-from gpu_common import check_net, check_select_and_plan, dev, make_rh
+from gpu_common import check_net, check_select_and_plan, dev, gpu_select, make_rh
 
 pytestmark = pytest.mark.gpu
 
@@ -86,4 +86,29 @@ def test_plan_list_lengths(F, w, h, halo, S, frac, kind, T, conn, rotate, max_bi
     plan, _, _ = check_select_and_plan(rh, cfg, frames, wl.make_importance(cfg), wl.make_segments(cfg), conn=conn, T=T or None,
                                        max_bins=max_bins, rotate=rotate)
     assert plan.overflow == (max_bins in (37, 350))
+    rh.close()
+
+
+# Selection: queues that are kept in registers (up to 16 384 keys) and longer ones, frames that belong to no segment
+# before, between and after the segments, empty segments, more segments than one launch's arguments hold (64)
+@pytest.mark.parametrize("F,w,h,segs,levels", [
+    (32, 480, 272, [(0, 32, 3000)], 0), (33, 480, 272, [(0, 33, 16829)], 0), (128, 480, 272, [(1, 127, 13056)], 7),
+    (40, 480, 272, [(2, 3, 1), (5, 5, 4), (9, 38, 14000)], 3), (64, 64, 16, [(i, i + 1, i % 6) for i in range(64)], 2),
+    (70, 64, 16, [(i, i + 1, i % 6) for i in range(1, 66)], 2), (5, 64, 16, [], 0), (3, 16, 16, [(0, 3, 2)], 1),
+])
+@pytest.mark.parametrize("mode", ["topk", "threshold"])
+def test_select_sizes(F, w, h, segs, levels, mode):
+    cfg = wl.replace(wl.config(3), n_frames=F, width=w, height=h)
+    r = np.random.default_rng(F)
+    imp = r.standard_normal((F, h // 16, w // 16)).astype(np.float32)
+    if levels:
+        imp = np.round(imp * levels) / levels
+    imp.reshape(-1)[::97] = np.nan
+    net = wl.Net("plain", 1, 2, 1)
+    rh = make_rh(wl.replace(cfg, net=net), wl.make_weights(net, 0, "fp32"), max_bins=4, precision="fp32")
+    thr = [0.3 + 0.1 * (i % 5) for i in range(len(segs))] if mode == "threshold" else None
+    o_mask, o_list = oracle.select(imp, np.array(segs, dtype=np.uint32).reshape(-1, 3), mode, thr)
+    for _ in range(2):                                       # the second call finds the first one's tables
+        g_mask, g_list, _ = gpu_select(rh, imp, [s + ((thr[i],) if thr else ()) for i, s in enumerate(segs)], mode)
+        assert np.array_equal(g_mask, o_mask) and np.array_equal(g_list, o_list)
     rh.close()
