@@ -24,6 +24,10 @@ struct conv_args {
     // (both dev); null: all tiles
     const uint32_t* tile_list;
     const uint32_t* n_list;
+    // exact-border mode (k_conv_mfma_duo): one bit per pixel, [N][H >> keep_sh][words of 32 pixels of W >> keep_sh], or null;
+    // keep_sh: log2 of the output pixel grid's resolution over the mask's (before the pixel shuffle)
+    const uint32_t* keep;
+    int keep_sh;
 };
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)

@@ -47,7 +47,9 @@ __device__ __forceinline__ void idle_phase() { phase_barrier(); phase_barrier();
 // all images.  The entry of the next tile is requested with a vector load at the start of the
 // compute phase and read at the start of the drain phase, a whole phase later: a scalar load would
 // share its counter with the LDS fragment reads and turn their partial waits into full ones.
-template <bool SKIP, bool RELU, int MID, bool LIST>
+// KEEP (exact-border mode): an output pixel is written as zero where a.keep has no bit for it.  A wave's row of 32
+// pixels is one word of the mask (half a word at twice its resolution), requested like the list entry.
+template <bool SKIP, bool RELU, int MID, bool LIST, bool KEEP>
 __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
 {
     constexpr int CIN = 64, MT = 2, KS = 4, NCH = 8, PIXB = 128, TH = 8, PH = TH + 2, RW = 2, NR = RW + 2;
@@ -214,6 +216,14 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
             __amdgpu_buffer_rsrc_t rsk = __builtin_amdgcn_make_buffer_rsrc(
                 (void*)((uint8_t*)a.skip + (size_t)n * out_img_bytes), 0, SKIP ? out_img_bytes : 0u, RSRC_FLAGS);
             uint4 sk[SKIP ? NOUT : 1];
+            uint32_t kw[RW];
+            if constexpr (KEEP) {
+                const int rows = a.H >> a.keep_sh, wpr = ((a.W >> a.keep_sh) + 31) >> 5;
+                __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)(a.keep + (size_t)n * rows * wpr), 0, (uint32_t)(rows * wpr) * 4u, RSRC_FLAGS);
+#pragma unroll
+                for (int r = 0; r < RW; ++r)
+                    kw[r] = __builtin_amdgcn_raw_buffer_load_b32(rk, (uint32_t)((((y0 + wave * RW + r) >> a.keep_sh) * wpr + (x0 >> (5 + a.keep_sh))) * 4), 0, 0);
+            }
             // ---------------- compute phase ----------------
             if constexpr (SEED_IN_COMPUTE) seed_acc();
             const uint8_t* wlane = lds_w + (lane << 4);
@@ -347,6 +357,11 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
                     o.z = pack_bf16x2(bf16_lo(o.z) + bf16_lo(sk[j].z), bf16_hi(o.z) + bf16_hi(sk[j].z));
                     o.w = pack_bf16x2(bf16_lo(o.w) + bf16_lo(sk[j].w), bf16_hi(o.w) + bf16_hi(sk[j].w));
                 }
+                if constexpr (KEEP) {
+                    const uint32_t at = ((uint32_t)x0 >> a.keep_sh & 31u) + ((uint32_t)((j % JPR) * PPJ + lcol) >> a.keep_sh);
+                    const uint32_t m = 0u - (kw[j / JPR] >> at & 1u);
+                    o.x &= m; o.y &= m; o.z &= m; o.w &= m;
+                }
                 const i32x4 v = {(int)o.x, (int)o.y, (int)o.z, (int)o.w};
                 __builtin_amdgcn_raw_buffer_store_b128(v, rout, out_off(j, y0, x0, si, sj), 0, 0);
                 if constexpr (SKIP) __builtin_amdgcn_sched_barrier(0);
@@ -360,17 +375,17 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
     }
 }
 
-template <bool SKIP, bool RELU, int MID, bool LIST>
+template <bool SKIP, bool RELU, int MID, bool LIST, bool KEEP = false>
 static hipError_t launch_duo(hipStream_t stream, int device, const conv_args& a, int grid)
 {
     constexpr int lds = 9 * 4 * 2 * 1024 + 2 * 10 * PW * 128 + 256;
     static bool attr_done[RH_MAX_DEVICES] = {};            // the attribute is per device
     if (!attr_done[device]) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_duo<SKIP, RELU, MID, LIST>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_duo<SKIP, RELU, MID, LIST, KEEP>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         attr_done[device] = true;
     }
-    hipLaunchKernelGGL((k_conv_mfma_duo<SKIP, RELU, MID, LIST>), dim3(grid), dim3(512), lds, stream, a);
+    hipLaunchKernelGGL((k_conv_mfma_duo<SKIP, RELU, MID, LIST, KEEP>), dim3(grid), dim3(512), lds, stream, a);
     return hipGetLastError();
 }
 
@@ -383,6 +398,11 @@ hipError_t rh_launch_conv_duo(hipStream_t stream, int device, const conv_args& a
         if (skip) return launch_duo<true, false, MID, true>(stream, device, a, grid);
         if (relu) return launch_duo<false, true, MID, true>(stream, device, a, grid);
         return launch_duo<false, false, MID, true>(stream, device, a, grid);
+    }
+    if (a.keep) {
+        if (skip) return launch_duo<true, false, MID, false, true>(stream, device, a, grid);
+        if (relu) return launch_duo<false, true, MID, false, true>(stream, device, a, grid);
+        return launch_duo<false, false, MID, false, true>(stream, device, a, grid);
     }
     if (skip) return launch_duo<true, false, MID, false>(stream, device, a, grid);
     if (relu) return launch_duo<false, true, MID, false>(stream, device, a, grid);

@@ -174,6 +174,53 @@ rh_status rh_zero_outside(rh_ctx* ctx, void* act, int px_bytes, int res, int N, 
     return RH_OK;
 }
 
+__global__ __launch_bounds__(256) void k_fill_ones(uint32_t* __restrict__ p, size_t n)
+{
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = 0xFFFFFFFFu;
+}
+
+// The same pixels as a mask: one wave per box, one lane per stored row clears the bits of its two runs.
+__global__ __launch_bounds__(64) void k_clear_outside_bits(uint32_t* __restrict__ keep, const rh_box* __restrict__ boxes,
+                                                           const uint32_t* __restrict__ counts, int n_img,
+                                                           const uint32_t* __restrict__ n_valid, int H, int W, int halo, int S)
+{
+    const int nv = n_valid ? min((int)*n_valid, n_img) : n_img, wpr = (S + 31) / 32;
+    for (uint32_t u = blockIdx.x; u < counts[0]; u += gridDim.x) {
+        const rh_box b = boxes[u];
+        if (b.bin == RH_NO_BIN || (int)b.bin >= nv) continue;
+        const int bw = RH_MB * b.wmb + 2 * halo, bh = RH_MB * b.hmb + 2 * halo;
+        const int sx0 = RH_MB * b.mbx0 - halo, sy0 = RH_MB * b.mby0 - halo;
+        if (sx0 >= 0 && sy0 >= 0 && sx0 + bw <= W && sy0 + bh <= H) continue;      // box entirely inside the frame
+        const int n_rows = b.rot ? bw : bh, n_cols = b.rot ? bh : bw;
+        if (b.bx + n_cols > S || b.by + n_rows > S) continue;                      // not a box of this geometry: never write outside the bin
+        const int r0 = b.rot ? sx0 : sy0, rlim = b.rot ? W : H;
+        const int c0s = b.rot ? sy0 : sx0, clim = b.rot ? H : W;
+        for (int j = threadIdx.x; j < n_rows; j += 64) {
+            const bool row_out = r0 + j < 0 || r0 + j >= rlim;
+            const int e0 = row_out ? n_cols : min(n_cols, max(0, -c0s)), b1 = row_out ? n_cols : max(0, min(n_cols, clim - c0s));
+            uint32_t* row = keep + ((size_t)b.bin * S + b.by + j) * wpr;
+            const int runs[2][2] = {{(int)b.bx, (int)b.bx + e0}, {(int)b.bx + b1, (int)b.bx + n_cols}};
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                for (int x = runs[q][0]; x < runs[q][1];) {                        // word by word; boxes share words
+                    const int lo = x & 31, n = min(32 - lo, runs[q][1] - x);
+                    atomicAnd(&row[x >> 5], ~((n == 32 ? 0xFFFFFFFFu : (1u << n) - 1u) << lo));
+                    x += n;
+                }
+        }
+    }
+}
+
+rh_status rh_outside_mask(rh_ctx* ctx, uint32_t* keep, int N, const uint32_t* n_valid)
+{
+    const size_t words = (size_t)N * ctx->cfg.bin_size * ((ctx->cfg.bin_size + 31) / 32);
+    hipLaunchKernelGGL(k_fill_ones, dim3((unsigned)(words < 256 * 1024 ? (words + 255) / 256 : 1024)), dim3(256), 0, ctx->stream, keep, words);
+    hipLaunchKernelGGL(k_clear_outside_bits, dim3(1024), dim3(64), 0, ctx->stream, keep, ctx->bz_boxes, ctx->bz_counts, N, n_valid,
+                       ctx->cfg.frame_h, ctx->cfg.frame_w, ctx->cfg.halo, ctx->cfg.bin_size);
+    RH_HIP(ctx, hipGetLastError());
+    return RH_OK;
+}
+
 rh_status rh_launch_gather(rh_ctx* ctx, const uint8_t* frames, int F, const rh_box* boxes,
                            const uint32_t* counts, uint8_t* bins)
 {

@@ -167,6 +167,8 @@ extern "C" int32_t rh_needed_radii(const rh_net_desc* net, int32_t per_layer_tai
 // exact-border mode: zero the out-of-frame part of every box in an activation tensor
 // [N][S*res][S*res][px_bytes]; a no-op unless an rh_enhance_exact call is in progress
 rh_status rh_zero_outside(rh_ctx*, void* act, int px_bytes, int res, int N, const uint32_t* n_valid);
+// exact-border mode: a mask of one bit per pixel, [N][S][words of 32 pixels], clear where rh_zero_outside writes
+rh_status rh_outside_mask(rh_ctx*, uint32_t* keep, int N, const uint32_t* n_valid);
 void rh_fill_i32(rh_ctx*, int32_t* p, int32_t v, size_t n);
 rh_status rh_ensure_workspace(rh_ctx*, size_t bytes);
 

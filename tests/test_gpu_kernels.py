@@ -7,6 +7,7 @@ import torch
 import oracle
 import workloads as wl
 from paper_2407_16990_amd import RH
+from test_gpu_parity import exact_border_check
 from gpu_common import check_net, check_select_and_plan, dev, gpu_select, make_rh
 
 pytestmark = pytest.mark.gpu
@@ -112,3 +113,15 @@ def test_select_sizes(F, w, h, segs, levels, mode):
         g_mask, g_list, _ = gpu_select(rh, imp, [s + ((thr[i],) if thr else ()) for i, s in enumerate(segs)], mode)
         assert np.array_equal(g_mask, o_mask) and np.array_equal(g_list, o_list)
     rh.close()
+
+
+# Exact-border mode's pixel mask: sides that are not multiples of 32 (words and tiles cut), of 8, fewer than 32 pixels,
+# both resolutions (the second upsampling conv of x4 runs on twice the mask's grid), turned boxes, every topology
+@pytest.mark.parametrize("net,halo,S,rotate", [
+    (wl.Net("edsr", 64, 1, 4, 0.02), 5, 76, True), (wl.Net("edsr", 64, 1, 2, 0.02), 7, 44, False),
+    (wl.Net("edsr", 64, 1, 3, 0.02), 3, 100, True), (wl.Net("res", 64, 1, 2, 0.02), 6, 28, True),
+    (wl.Net("plain", 64, 4, 2, 0.1), 4, 64, False), (wl.Net("edsr", 64, 1, 4, 0.02), 6, 36, False),
+])
+def test_exact_border_mask(net, halo, S, rotate):
+    cfg = wl.replace(wl.config(3), n_frames=2, width=112, height=80, halo=halo, bin_size=S, net=net)
+    exact_border_check(cfg, "bf16", rotate=rotate)
