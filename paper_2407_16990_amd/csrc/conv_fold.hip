@@ -94,9 +94,8 @@ __global__ __launch_bounds__(256) void k_conv_fold(fold_args a)
     const int tid = threadIdx.x, lane = tid & 63, lx = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    const int n_img = a.n_valid ? min((int)*a.n_valid, a.N) : a.N;
-    const int tiles_x = (a.W + 31) / 32, tiles_y = (a.H + TH - 1) / TH, tiles_img = tiles_x * tiles_y;
-    const int n_tiles = LIST ? (int)*a.n_list : n_img * tiles_img;
+    const uint32_t* counter = LIST ? a.n_list : a.n_valid;
+    const uint32_t n_found = counter ? *counter : (uint32_t)a.N;
     // tile lanes and chunks: as in the 3 x 3 kernel, the chunks of a layer are dealt to the workgroups
     // of one XCD that share a tile lane (the input then comes from HBM once), XCD-contiguous tile runs
     const bool deal = a.n_chunks > 1 && gridDim.x % (8 * a.n_chunks) == 0;
@@ -104,6 +103,14 @@ __global__ __launch_bounds__(256) void k_conv_fold(fold_args a)
     const int xcd = blockIdx.x % 8, local = blockIdx.x / 8;
     const int wg = deal ? xcd * (G / 8) + local / a.n_chunks : ((G % 8 == 0) ? xcd * (G / 8) + local : (int)blockIdx.x);
     const int chunk_begin = deal ? local % a.n_chunks : 0, chunk_end = deal ? chunk_begin + 1 : a.n_chunks;
+    // the first chunk's weights are on their way before the image count is known
+    auto load_weights = [&](int chunk) __attribute__((always_inline)) {
+        lds_dma<256, WBYTES>(lds_w, a.wp + (size_t)chunk * (WBYTES / 16), wave, lane);
+    };
+    load_weights(chunk_begin);
+    const int n_img = min((int)n_found, a.N);
+    const int tiles_x = (a.W + 31) / 32, tiles_y = (a.H + TH - 1) / TH, tiles_img = tiles_x * tiles_y;
+    const int n_tiles = LIST ? (int)n_found : n_img * tiles_img;
     const uint32_t in_img_bytes = (uint32_t)a.H * a.W * PIXB;
 
     // patch pieces of this thread: piece j is 16-byte group p_c of patch pixel (p_row, p_col)
@@ -152,25 +159,26 @@ __global__ __launch_bounds__(256) void k_conv_fold(fold_args a)
                                                  tile < n_tiles ? in_img_bytes : 0u, RSRC_FLAGS);
     };
 
+    int cn = 0, cy0 = 0, cx0 = 0, e_next = 0;             // LIST: origin of the current tile, entry of the next one
+    auto first_patch = [&]() __attribute__((always_inline)) {
+        tile_origin(wg, cn, cy0, cx0);
+        if constexpr (LIST) e_next = list_load(wg + G);
+        __amdgpu_buffer_rsrc_t rin = in_rsrc(wg, wg < n_tiles ? cn : 0);
+#pragma unroll
+        for (int j = 0; j < NPRE; ++j) load_piece(j, rin, cy0, cx0);
+    };
+    first_patch();                                         // ahead of what the compiler computes once for all turns of the loops
     for (int chunk = chunk_begin; chunk < chunk_end; ++chunk) {
-        __syncthreads();                                   // previous chunk's LDS reads are done
-        {
-            const uint4* src = a.wp + (size_t)chunk * (WBYTES / 16);
-            for (int i = tid; i < WBYTES / 16; i += 256) ((uint4*)lds_w)[i] = src[i];
+        if (chunk != chunk_begin) {
+            __syncthreads();                               // previous chunk's LDS reads are done
+            load_weights(chunk);
+            first_patch();
         }
         f32x16 biasv;                                      // lane holds rows 8q + 4hi + e in [4q + e]
 #pragma unroll
         for (int e = 0; e < 16; ++e) biasv[e] = a.bias[chunk * 32 + (e >> 2) * 8 + hi * 4 + (e & 3)];
         int tile = wg;
-        int cn = 0, cy0 = 0, cx0 = 0, e_next = 0;         // LIST: origin of the current tile, entry of the next one
-        {
-            int n, y0, x0; tile_origin(tile, n, y0, x0);
-            cn = n; cy0 = y0; cx0 = x0;
-            if constexpr (LIST) e_next = list_load(tile + G);
-            __amdgpu_buffer_rsrc_t rin = in_rsrc(tile, tile < n_tiles ? n : 0);
-#pragma unroll
-            for (int j = 0; j < NPRE; ++j) load_piece(j, rin, y0, x0);
-        }
+        lds_dma_wait();                                    // weights, before the loop's first barriers
         for (; tile < n_tiles; tile += G) {                // trip count uniform over the workgroup
             int n, y0, x0;
             if constexpr (LIST) { n = cn; y0 = cy0; x0 = cx0; } else tile_origin(tile, n, y0, x0);

@@ -59,6 +59,24 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
 
+// `bytes` from `src` to LDS, 16 bytes per thread and turn, with no registers between: every piece of a layer's
+// weights is in flight at once.  `wave` (scalar) is the thread's wave of the THREADS / 64; the data is there
+// after lds_dma_wait() of all waves and a barrier.
+template <int THREADS, int BYTES>
+__device__ __forceinline__ void lds_dma(uint8_t* lds, const void* src, int wave, int lane)
+{
+    static_assert(BYTES % 1024 == 0, "whole waves only");
+#pragma unroll
+    for (int i = 0; i < (BYTES + THREADS * 16 - 1) / (THREADS * 16); ++i) {
+        const int off = (i * (THREADS / 64) + wave) * 1024;
+        if ((i + 1) * THREADS * 16 > BYTES && off >= BYTES) break;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((const uint8_t*)src + off + lane * 16),
+                                         (__attribute__((address_space(3))) void*)(lds + off), 16, 0, 0);
+    }
+}
+// The builtin (vmcnt 0, the other counters open), not inline asm: the compiler's own count of outstanding loads has to see it.
+__device__ __forceinline__ void lds_dma_wait() { __builtin_amdgcn_s_waitcnt(0x0F70); asm volatile("" ::: "memory"); }
+
 #define RSRC_FLAGS 0x00020000            // raw buffer, 32-bit data format (gfx9 family)
 #define OOB_OFF 0x80000000u              // beyond any descriptor used here (images are < 2 GiB)
 

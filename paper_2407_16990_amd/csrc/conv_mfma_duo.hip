@@ -75,11 +75,9 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
     uint8_t* lds_p = lds + WBYTES + team * PATCHB;
     float* lds_b = (float*)(lds + WBYTES + 2 * PATCHB);       // the chunk's 64 biases
 
-    const int n_img = a.n_valid ? min((int)*a.n_valid, a.N) : a.N;
-    const int tiles_x = (a.W + 31) / 32, tiles_y = (a.H + 15) / 16;
-    const int tiles_img = tiles_x * tiles_y;
-    // half tiles; with a list, its entries are half tiles packed as RH_CELL_ENTRY(image, row of 8, column of 32)
-    const int n_units = LIST ? (int)*a.n_list : 2 * n_img * tiles_img;
+    // requested first of all (behind the copy to LDS, which may write anything, it would be a vector load that waits for it)
+    const uint32_t* counter = LIST ? a.n_list : a.n_valid;
+    const uint32_t n_found = counter ? *counter : (uint32_t)a.N;
     // Tile order.  Workgroups go to the 8 XCDs round-robin; XCD x takes a contiguous run of tile
     // lanes so that neighbouring tiles (shared halo pixels) meet in one L2.
     // Layers with several output chunks (the upsampling convs): when the grid allows it the chunks
@@ -93,6 +91,18 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
     const int wg = deal ? xcd * (G / 8) + local / a.n_chunks
                         : ((G % 8 == 0) ? xcd * (G / 8) + local : (int)blockIdx.x);
     const int chunk_begin = deal ? local % a.n_chunks : 0, chunk_end = deal ? chunk_begin + 1 : a.n_chunks;
+    // The first chunk's weights depend on nothing that is read from memory: they are on their way to LDS before the
+    // image count is known and the first patch can be asked for.  (Behind it, through registers, three pieces at a
+    // time, they made four round trips in a row out of what are two.)
+    auto load_weights = [&](int chunk) __attribute__((always_inline)) {
+        lds_dma<512, WBYTES>(lds_w, a.wp + (size_t)chunk * (WBYTES / 16), team * 4 + wave, lane);
+    };
+    load_weights(chunk_begin);
+    const int n_img = min((int)n_found, a.N);
+    const int tiles_x = (a.W + 31) / 32, tiles_y = (a.H + 15) / 16;
+    const int tiles_img = tiles_x * tiles_y;
+    // half tiles; with a list, its entries are half tiles packed as RH_CELL_ENTRY(image, row of 8, column of 32)
+    const int n_units = LIST ? (int)n_found : 2 * n_img * tiles_img;
     auto units_from = [&](int first) { return n_units > first ? (n_units - first + 2 * G - 1) / (2 * G) : 0; };
     const int u_first = wg + team * G;                         // this team's units: u_first, u_first + 2G, ...
     const int iters0 = units_from(wg), iters1 = units_from(wg + G);           // team 1 has as many as team 0 or one fewer
@@ -166,30 +176,24 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
     };
 
     int cn = 0, cy0 = 0, cx0 = 0;                          // LIST: origin of the tile about to be computed
+    float bias = 0.0f;
+    auto first_patch = [&](int chunk) __attribute__((always_inline)) {         // requests it, of both teams
+        if (tid < CQ) bias = a.bias[chunk * CQ + tid];
+        unit_origin(u_first, cn, cy0, cx0);
+        __amdgpu_buffer_rsrc_t rin = in_rsrc(u_first, u_first < n_units ? cn : 0);
+#pragma unroll
+        for (int j = 0; j < NPRE; ++j) load_piece(j, rin, cy0, cx0);
+    };
+    first_patch(chunk_begin);                              // ahead of the loops: ahead of what the compiler computes for all of their turns
     for (int chunk = chunk_begin; chunk < chunk_end; ++chunk) {
-        __syncthreads();                                   // all 8 waves: previous chunk completely done
-        {   // the chunk's weights and the first patch of both teams: all loads are issued before
-            // the first LDS store waits for any of them
-            constexpr int NWL = WBYTES / 16 / 512;         // 16-byte weight pieces per thread
-            static_assert(NWL * 512 * 16 == WBYTES, "weights must split evenly over the workgroup");
-            const uint4* src = a.wp + (size_t)chunk * (WBYTES / 16);
-            int n, y0, x0; unit_origin(u_first, n, y0, x0);
-            cn = n; cy0 = y0; cx0 = x0;
-            __amdgpu_buffer_rsrc_t rin = in_rsrc(u_first, u_first < n_units ? n : 0);
-#pragma unroll
-            for (int j = 0; j < NPRE; ++j) load_piece(j, rin, y0, x0);
-            constexpr int WB = 3;                          // weight pieces in flight per thread (register budget)
-#pragma unroll
-            for (int i0 = 0; i0 < NWL; i0 += WB) {
-                uint4 wreg[WB];
-#pragma unroll
-                for (int i = 0; i < WB; ++i) if (i0 + i < NWL) wreg[i] = src[(i0 + i) * 512 + tid];
-#pragma unroll
-                for (int i = 0; i < WB; ++i) if (i0 + i < NWL) ((uint4*)lds_w)[(i0 + i) * 512 + tid] = wreg[i];
-            }
-            if (tid < CQ) lds_b[tid] = a.bias[chunk * CQ + tid];
-            store_patch();
+        if (chunk != chunk_begin) {
+            __syncthreads();                               // all 8 waves: previous chunk completely done
+            load_weights(chunk);
+            first_patch(chunk);
         }
+        if (tid < CQ) lds_b[tid] = bias;
+        store_patch();
+        lds_dma_wait();
         const int si = chunk / ps, sj = chunk - si * ps;
         __syncthreads();
 
