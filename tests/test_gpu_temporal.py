@@ -107,6 +107,16 @@ def run_select(rh, phi_q, off, n_total):
     return sel, reuse
 
 
+@pytest.mark.parametrize("ns", [1, 511, 512, 513])
+def test_select_stream_tables_around_one_chunk(ns):
+    """Tables of up to 512 offsets travel with the first kernel, longer ones in a launch of their own."""
+    rng = np.random.default_rng(ns)
+    off = np.concatenate([[0], np.cumsum(rng.integers(1, 4, ns))])
+    rh = make_ctx(32, 32, int(off[-1]))
+    run_select(rh, rng.integers(0, 1 << 36, int(off[-1])).astype(np.uint64), off, ns + ns // 3)
+    rh.close()
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_select_random_streams(seed):
     rng = np.random.default_rng(seed)
