@@ -464,7 +464,11 @@ __device__ __forceinline__ void place_boxes(uint32_t n, SizeOf size_of, uint32_t
     n_bins_out = nbins; overflow_out = overflow;
 }
 
-// pcount: 0 boxes, 1 bins, 2 overflow, 3 boxes appended by the labelling kernel (0 between plans)
+// pcount: 0 boxes, 1 bins, 2 overflow, 3 boxes appended by the labelling kernel.  Every plan of several launches
+// clears the append counter itself: were it left at 0 by the plan before, one lost launch would
+// make all later plans append behind stale boxes and past the end of raw.
+__global__ void k_plan_zero(uint32_t* pcount) { pcount[3] = 0; }
+
 __global__ __launch_bounds__(64) void k_plan_place(const rh_rawbox* __restrict__ sorted, uint32_t* pcount,
                                                    int halo, int S, int max_bins, int free_cap, int rotate,
                                                    uint32_t* __restrict__ box_pos)
@@ -475,7 +479,7 @@ __global__ __launch_bounds__(64) void k_plan_place(const rh_rawbox* __restrict__
     auto size_of = [&](uint32_t i) { return (uint32_t)sorted[i].wmb | ((uint32_t)sorted[i].hmb << 16); };
     if (rotate) place_boxes<true>(n, size_of, sm, sm + free_cap, sm + 2 * free_cap, halo, S, max_bins, free_cap, box_pos, nbins, overflow);
     else place_boxes<false>(n, size_of, sm, sm + free_cap, sm + 2 * free_cap, halo, S, max_bins, free_cap, box_pos, nbins, overflow);
-    if (threadIdx.x == 0) { pcount[0] = n; pcount[1] = nbins; pcount[2] = overflow ? 1u : 0u; pcount[3] = 0; }
+    if (threadIdx.x == 0) { pcount[0] = n; pcount[1] = nbins; pcount[2] = overflow ? 1u : 0u; }
 }
 
 // Placement rows of box i and of selected macroblock i (Alg. 1's output).
@@ -809,7 +813,11 @@ rh_status rh_launch_plan(rh_ctx* ctx, int F, const float* imp, const uint8_t* ma
         RH_HIP(ctx, hipGetLastError());
         return RH_OK;
     }
-    rh_prof_scope ps(ctx, RH_PROF_PLAN, 4);
+    // A launch that fails ends the call: the kernels behind it would read what it has not written.
+#define LAUNCHED() RH_HIP(ctx, hipGetLastError())
+    rh_prof_scope ps(ctx, RH_PROF_PLAN, 5);
+    hipLaunchKernelGGL(k_plan_zero, dim3(1), dim3(1), 0, ctx->stream, ctx->pcount);
+    LAUNCHED();
     if (rows64) {
         hipLaunchKernelGGL(k_plan_regions, dim3(F), dim3(64), (size_t)per * 4, ctx->stream, a, ctx->pcount);
     } else {
@@ -818,15 +826,19 @@ rh_status rh_launch_plan(rh_ctx* ctx, int F, const float* imp, const uint8_t* ma
                            ctx->mbh, ctx->cfg.connectivity, ctx->T, ctx->cfg.sort_policy, imp_in_lds, ctx->owner_id, ctx->raw,
                            ctx->pcount);
     }
+    LAUNCHED();
     const int nblk = (total + 255) / 256;
     hipLaunchKernelGGL(k_plan_rank, dim3(min(512, (total + 15) / 16)), dim3(256), 0, ctx->stream, ctx->raw, ctx->pcount, ctx->sorted,
                        ctx->rank_of_id);
+    LAUNCHED();
     hipLaunchKernelGGL(k_plan_place, dim3(1), dim3(64), (size_t)ctx->free_cap * 12, ctx->stream, ctx->sorted,
                        ctx->pcount, ctx->cfg.halo, ctx->cfg.bin_size, ctx->cfg.max_bins, ctx->free_cap, ctx->cfg.rotate,
                        box_pos);
+    LAUNCHED();
     hipLaunchKernelGGL(k_plan_emit, dim3(nblk), dim3(256), 0, ctx->stream, ctx->sorted, box_pos, ctx->pcount,
                        list, n_sel, ctx->owner_id, ctx->rank_of_id, ctx->mbw, per, ctx->cfg.halo, boxes, places,
                        counts);
-    RH_HIP(ctx, hipGetLastError());
+    LAUNCHED();
+#undef LAUNCHED
     return RH_OK;
 }

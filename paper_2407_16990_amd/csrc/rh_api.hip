@@ -111,8 +111,6 @@ extern "C" rh_status rh_create(const rh_config* cfg, const float* weights, size_
     A(dalloc(&ctx->owner_id, total)); A(dalloc(&ctx->rank_of_id, total));
     A(dalloc(&ctx->raw, total)); A(dalloc(&ctx->sorted, total));
     A(dalloc(&ctx->pcount, 8 + 2 * total));
-    const uint32_t zero8[8] = {};
-    A(hipMemcpy(ctx->pcount, zero8, sizeof(zero8), hipMemcpyHostToDevice));      // a plan leaves its append counter at zero
     A(dalloc(&ctx->tr_off, (size_t)cfg->max_frames + 1)); A(dalloc(&ctx->tr_A, cfg->max_frames)); A(dalloc(&ctx->tr_T, cfg->max_frames));
 #undef A
     if (e != hipSuccess) {

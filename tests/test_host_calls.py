@@ -1,0 +1,72 @@
+"""What the C entry points do on the host: which kernels they launch in which order, what they
+allocate, and how they end when a launch or an allocation fails.  A recording stand-in takes the
+place of the HIP runtime (recording_hip.cpp), so this needs no GPU and runs no kernel; each test is a
+child process, because the stand-in has to be loaded before librh.so."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PRELUDE = r'''
+import ctypes as C, sys
+rec = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+L = C.CDLL(sys.argv[2])
+rec.rec_log.restype = C.c_char_p; rec.rec_new_left.restype = C.c_long; rec.rec_fail_new.argtypes = [C.c_long]
+L.rh_last_error.restype = C.c_char_p
+P = lambda n=1: C.c_void_p(n << 24)                      # stands for a device buffer
+PLAIN, RES, EDSR = 0, 1, 2
+
+def weights(top, ch, nb, s):
+    io = [(3, ch)] + [(ch, ch)] * (nb - 2 if top == PLAIN else 2 * nb)
+    if top == EDSR:
+        io += [(ch, ch)] + ([(ch, ch * s * s)] if s < 4 else [(ch, 4 * ch)] * 2) + [(ch, 3)]
+    else:
+        io.append((ch, 3 * s * s))
+    return (C.c_float * sum(9 * i * o + o for i, o in io))()
+
+def create(top, ch, nb, s, bf16, w=480, h=272, F=32, halo=6, S=64, bins=8, tail=0):
+    cfg = (C.c_int32 * 16)(w, h, F, halo, S, bins, 8, 0, bf16, top, ch, nb, s, 0, 0, tail)
+    blob, ctx = weights(top, ch, nb, s), C.c_void_p()
+    return L.rh_create(cfg, blob, C.c_size_t(len(blob)), None, C.byref(ctx)), ctx
+
+def names(): return [n for n in rec.rec_log().decode().split("\n") if n]
+def pack(ctx, F): return L.rh_pack(ctx, P(1), F, P(2), P(3), P(4), P(5), P(6), P(7), P(8), P(9))
+'''
+
+
+@pytest.fixture(scope="module")
+def run_child(tmp_path_factory):
+    from paper_2407_16990_amd import binding
+    binding.load_library()                                   # built if it is missing or stale
+    lib = str(tmp_path_factory.mktemp("rec") / "librecording_hip.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-Wall", "-shared", "-fPIC", "-o", lib, os.path.join(HERE, "recording_hip.cpp")])
+
+    def run(body):
+        r = subprocess.run([sys.executable, "-c", PRELUDE + body + "\nprint('DONE')", lib, binding.lib_path()], capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0 and r.stdout.strip().endswith("DONE"), r.stdout[-2000:] + r.stderr[-3000:]
+    return run
+
+
+@pytest.mark.parametrize("w,h,F", [(480, 272, 17), (480, 272, 32), (1040, 64, 2)])
+def test_a_plan_does_not_depend_on_how_the_last_one_ended(run_child, w, h, F):
+    """The labelling kernel appends boxes at a counter: whichever launch of the plan before was lost, and
+    also where none was, the counter is cleared in the same call and ahead of everything that uses it."""
+    run_child(f'''
+st, ctx = create(PLAIN, 4, 2, 2, 0, w={w}, h={h}, F={F})
+assert st == 0
+def check():
+    rec.rec_reset()
+    assert pack(ctx, {F}) == 0
+    n = names()
+    assert "k_plan_zero" in n[0] and sum("k_plan_zero" in x for x in n) == 1, n
+    return len(n)
+launches = check()
+for k in range(launches):
+    rec.rec_reset(); rec.rec_fail_launch(k)
+    assert pack(ctx, {F}) == 4, k                            # RH_E_DEVICE
+    assert len(names()) == k                                 # and nothing behind the lost launch
+    assert check() == launches
+''')
