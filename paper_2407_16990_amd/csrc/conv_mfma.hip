@@ -505,7 +505,10 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // bf16-output convs do it themselves, by a mask of one bit per pixel: a launch of k_zero_outside behind every
     // layer took 5 us; with the mask a step of 15 bins of 160 x 160 takes 1302 us instead of 1424.
     const bool masked = ctx->bz_boxes && C == 64;
-    const size_t mask_words = masked ? (size_t)N * H * ((W + 31) / 32) : 0;
+    // Every 64-channel call with these layers makes room for the mask, so that an exact-border call never
+    // needs more than a plain one of as many pixels.  A word per 16 pixels holds it: bins are at least 16 wide,
+    // so their ceil(S / 32) words per row are at most S / 16.
+    const size_t mask_words = C == 64 && !fold ? ((size_t)N * H * W + 15) / 16 : 0;
     need = (need + 1) & ~(size_t)1;
     rh_status st = rh_ensure_workspace(ctx, need * 2 + mask_words * 4);
     if (st != RH_OK) return st;

@@ -70,3 +70,19 @@ for k in range(launches):
     assert len(names()) == k                                 # and nothing behind the lost launch
     assert check() == launches
 ''')
+
+
+@pytest.mark.parametrize("net", ["PLAIN, 64, 4, 2", "RES, 64, 1, 3", "EDSR, 64, 1, 4", "RES, 32, 1, 2"])
+def test_an_exact_border_call_fits_the_workspace_of_an_equally_large_call(run_child, net):
+    """rh_enhance on images of as many pixels, with the same layers, has sized the workspace: the exact-border call
+    that follows neither allocates nor synchronises (it may be under stream capture)."""
+    run_child(f'''
+for S, shapes in ((36, [(6, 36, 36), (1, 36, 216), (81, 4, 24)]), (64, [(6, 64, 64), (2, 48, 256)]), (16, [(6, 16, 16)])):
+    for n, h, w in shapes:
+        st, ctx = create({net}, 1, halo=0, S=S, tail=1)
+        assert st == 0 and n * h * w == 6 * S * S
+        assert L.rh_enhance(ctx, P(1), n, h, w, P(2), None) == 0
+        rec.rec_reset()
+        assert L.rh_enhance_exact(ctx, P(1), 6, P(3), P(4), P(2), None) == 0
+        assert (rec.rec_mallocs(), rec.rec_syncs()) == (0, 0), (S, n, h, w)
+''')
