@@ -27,6 +27,8 @@
 // and 6 activation fragments for 10 MFMAs.
 #include <string.h>
 
+#include <atomic>
+#include <new>
 #include <thread>
 #include <type_traits>
 
@@ -420,7 +422,7 @@ rh_status rh_fold_weights(rh_ctx* ctx, const float* blob)
     fold_bias(st, grid, bias_all);
     // Wc[class][i][j][co][tap][ci]; the class's pixel sits at row / column 0, 2 or 4 of the 5 x 5 image
     std::vector<double> Wc((size_t)9 * R * 25 * C, 0.0);
-    auto work = [&](int job0, int job1) {
+    auto compose = [&](int job0, int job1) {
         std::vector<double> g;
         for (int job = job0; job < job1; ++job) {
             const int cls = job / R, o = job - cls * R, py = 2 * (cls / 3), px = 2 * (cls % 3);
@@ -434,11 +436,18 @@ rh_status rh_fold_weights(rh_ctx* ctx, const float* blob)
             }
         }
     };
+    std::atomic<bool> out_of_memory{false};                // a thread that ended by an exception would end the process
+    auto work = [&](int job0, int job1) { try { compose(job0, job1); } catch (const std::bad_alloc&) { out_of_memory = true; } };
     {
         const int jobs = 9 * R, nt = 8;
         std::vector<std::thread> th;
-        for (int t = 0; t < nt; ++t) th.emplace_back(work, jobs * t / nt, jobs * (t + 1) / nt);
+        th.reserve(nt);
+        for (int t = 0; t < nt; ++t) {
+            try { th.emplace_back(work, jobs * t / nt, jobs * (t + 1) / nt); }
+            catch (const std::exception&) { work(jobs * t / nt, jobs * (t + 1) / nt); }      // no thread to be had
+        }
         for (auto& t : th) t.join();
+        if (out_of_memory) throw std::bad_alloc();
     }
     std::vector<uint16_t> wp((size_t)9 * n_chunks * 25 * KS * 64 * 8);
     std::vector<float> bp((size_t)9 * n_chunks * 32, 0.0f);

@@ -162,20 +162,20 @@ __global__ __launch_bounds__(256) void k_conv3x3_f32_lds(const void* __restrict_
     }
 }
 
-// Appends [co / 4][tap][ci][4] copies of the layers with at most LDS_CIN input channels to the blob
-void rh_pack_weights_f32(rh_ctx* ctx, const float* blob, std::vector<float>& all)
+// [co / 4][tap][ci][4] copies of the layers with at most LDS_CIN input channels; they lie behind the blob
+void rh_pack_weights_f32(rh_ctx* ctx, const float* blob, size_t n_floats, std::vector<float>& packed)
 {
     for (rh_layer& L : ctx->layers) {
         if (L.cin > LDS_CIN) continue;
-        all.resize((all.size() + 3) & ~(size_t)3);           // 16-byte pieces
-        L.wp_off = all.size();
+        packed.resize(packed.size() + (0 - n_floats - packed.size()) % 4);       // 16-byte pieces
+        L.wp_off = n_floats + packed.size();
         const int nb = (L.cout + CO_L - 1) / CO_L;
         for (int b = 0; b < nb; ++b)
             for (int tap = 0; tap < 9; ++tap)
                 for (int ci = 0; ci < L.cin; ++ci)
                     for (int j = 0; j < CO_L; ++j) {
                         const int co = b * CO_L + j;
-                        all.push_back(co < L.cout ? blob[L.w_off + ((size_t)co * 9 + tap) * L.cin + ci] : 0.0f);
+                        packed.push_back(co < L.cout ? blob[L.w_off + ((size_t)co * 9 + tap) * L.cin + ci] : 0.0f);
                     }
     }
 }

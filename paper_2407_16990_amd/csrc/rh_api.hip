@@ -2,7 +2,8 @@
 // which the kernels of each call are enqueued.  No arithmetic of the method lives here.
 #include <string.h>
 
-#include <new>
+#include <exception>
+#include <memory>
 
 #include "rh_internal.h"
 
@@ -63,8 +64,8 @@ extern "C" void rh_destroy(rh_ctx* ctx)
     delete ctx;
 }
 
-extern "C" rh_status rh_create(const rh_config* cfg, const float* weights, size_t n_floats, void* hip_stream,
-                               rh_ctx** out)
+// May throw std::bad_alloc (vectors): rh_create turns that into a status.
+static rh_status create(const rh_config* cfg, const float* weights, size_t n_floats, void* hip_stream, rh_ctx** out)
 {
     if (!cfg || !weights || !out) return RH_E_INVALID;
     *out = nullptr;
@@ -80,31 +81,34 @@ extern "C" rh_status rh_create(const rh_config* cfg, const float* weights, size_
     if (cfg->precision != RH_FP32 && cfg->precision != RH_BF16) return RH_E_INVALID;
     const int Tmax = (cfg->bin_size - 2 * cfg->halo) / RH_MB;
     if (cfg->max_box_mbs < 0 || cfg->max_box_mbs > Tmax || Tmax > 255) return RH_E_SHAPE;
-    rh_ctx* ctx = new (std::nothrow) rh_ctx();
-    if (!ctx) return RH_E_NOMEM;
+    // until something lies on the device there is nothing to synchronise with
+    const auto undo = [](rh_ctx* c) { if (c->w_f32) rh_destroy(c); else delete c; };
+    std::unique_ptr<rh_ctx, void (*)(rh_ctx*)> owner(new rh_ctx(), undo);
+    rh_ctx* ctx = owner.get();
     ctx->cfg = *cfg; ctx->stream = (hipStream_t)hip_stream; ctx->err[0] = 0;
     // a partial macroblock at the right / bottom edge counts as one
     ctx->mbw = (cfg->frame_w + RH_MB - 1) / RH_MB; ctx->mbh = (cfg->frame_h + RH_MB - 1) / RH_MB; ctx->per = ctx->mbw * ctx->mbh;
     ctx->T = cfg->max_box_mbs ? cfg->max_box_mbs : Tmax;
     size_t need = 0;
-    if (!build_layers(cfg->net, ctx->layers, need) || need != n_floats) { delete ctx; return RH_E_SHAPE; }
+    if (!build_layers(cfg->net, ctx->layers, need) || need != n_floats) return RH_E_SHAPE;
     // LDS limits of the planning kernels: 16 B per macroblock of a frame; 12 B per free rectangle
     const int side = RH_MB + 2 * cfg->halo, per_bin = (cfg->bin_size / side) * (cfg->bin_size / side);
     long fc = (long)cfg->max_bins * per_bin + 2;
     ctx->free_cap = (int)(fc < 12000 ? fc : 12000);
-    if ((size_t)ctx->per * 16 > 150 * 1024) { delete ctx; return RH_E_SHAPE; }
+    if ((size_t)ctx->per * 16 > 150 * 1024) return RH_E_SHAPE;
     const size_t total = (size_t)ctx->per * cfg->max_frames;
-    if (total > 0x7FFFFFFFu) { delete ctx; return RH_E_SHAPE; }
+    if (total > 0x7FFFFFFFu) return RH_E_SHAPE;
     rh_status st = RH_OK;
     hipError_t e = hipGetDevice(&ctx->device);
 #define A(call) if (e == hipSuccess) e = (call)
-    if (e == hipSuccess && (ctx->device < 0 || ctx->device >= RH_MAX_DEVICES)) { delete ctx; return RH_E_DEVICE; }
+    if (e == hipSuccess && (ctx->device < 0 || ctx->device >= RH_MAX_DEVICES)) return RH_E_DEVICE;
     A(hipDeviceGetAttribute(&ctx->n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device));
     if (e == hipSuccess && ctx->n_cu < 1) ctx->n_cu = 1;
-    std::vector<float> blob(weights, weights + n_floats);
-    if (cfg->precision == RH_FP32) rh_pack_weights_f32(ctx, weights, blob);
-    A(dalloc(&ctx->w_f32, blob.size()));
-    A(hipMemcpy(ctx->w_f32, blob.data(), blob.size() * sizeof(float), hipMemcpyHostToDevice));
+    std::vector<float> packed;                       // what the fp32 path adds to the blob
+    if (cfg->precision == RH_FP32) rh_pack_weights_f32(ctx, weights, n_floats, packed);
+    A(dalloc(&ctx->w_f32, n_floats + packed.size()));
+    A(hipMemcpy(ctx->w_f32, weights, n_floats * sizeof(float), hipMemcpyHostToDevice));
+    if (!packed.empty()) A(hipMemcpy(ctx->w_f32 + n_floats, packed.data(), packed.size() * sizeof(float), hipMemcpyHostToDevice));
     A(dalloc(&ctx->frame_seg, cfg->max_frames)); A(dalloc(&ctx->seg_par, 4 * (size_t)cfg->max_frames));
     A(dalloc(&ctx->seg_T, cfg->max_frames)); A(dalloc(&ctx->seg_budget, cfg->max_frames));
     A(dalloc(&ctx->frame_nsel, cfg->max_frames)); A(dalloc(&ctx->frame_ties, cfg->max_frames));
@@ -121,9 +125,15 @@ extern "C" rh_status rh_create(const rh_config* cfg, const float* weights, size_
     if (st == RH_OK && cfg->precision == RH_BF16 && cfg->net.channels == 64) st = rh_mask_init(ctx);
     if (st == RH_OK && cfg->precision == RH_BF16) st = rh_pack_weights_bf16(ctx, weights);
     if (st == RH_OK && cfg->precision == RH_BF16 && !cfg->per_layer_tail) st = rh_fold_weights(ctx, weights);
-    if (st != RH_OK) { rh_destroy(ctx); return st; }
-    *out = ctx;
-    return RH_OK;
+    if (st == RH_OK) *out = owner.release();
+    return st;
+}
+
+extern "C" rh_status rh_create(const rh_config* cfg, const float* weights, size_t n_floats, void* hip_stream,
+                               rh_ctx** out)
+{
+    try { return create(cfg, weights, n_floats, hip_stream, out); }
+    catch (const std::exception&) { return RH_E_NOMEM; }
 }
 
 static hipEvent_t prof_event(rh_ctx* ctx)

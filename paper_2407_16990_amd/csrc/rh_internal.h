@@ -154,7 +154,7 @@ rh_status rh_launch_temporal_select(rh_ctx*, const uint64_t* phi, const int32_t*
                                     uint32_t* n_selected);
 rh_status rh_launch_temporal_spread(rh_ctx*, float* imp, int F, const uint8_t* selected, const uint32_t* reuse_from);
 rh_status rh_pack_weights_bf16(rh_ctx*, const float* host_blob);
-void rh_pack_weights_f32(rh_ctx*, const float* host_blob, std::vector<float>& all);
+void rh_pack_weights_f32(rh_ctx*, const float* host_blob, size_t n_floats, std::vector<float>& packed);
 rh_status rh_fold_weights(rh_ctx*, const float* host_blob);
 rh_status rh_plan_init(rh_ctx*);
 rh_status rh_mask_init(rh_ctx*);

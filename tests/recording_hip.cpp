@@ -5,6 +5,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <atomic>
 #include <map>
 #include <new>
 #include <string>
@@ -18,12 +19,13 @@ static std::string g_log;
 static int g_launches, g_mallocs, g_syncs, g_fail_launch = -1;
 static err_t g_last;
 static uint64_t g_next = 1ull << 40;
-static long g_fail_new = -1;
+static int g_live;                                       // device allocations not yet freed
+static std::atomic<long> g_fail_new{-1};
 static struct { dim3 grid, block; size_t lds; void* stream; } g_cfg;
 
 void* operator new(size_t n)
 {
-    if (g_fail_new >= 0 && g_fail_new-- == 0) throw std::bad_alloc();
+    if (g_fail_new >= 0 && g_fail_new.fetch_sub(1) == 0) throw std::bad_alloc();
     if (void* p = malloc(n ? n : 1)) return p;
     throw std::bad_alloc();
 }
@@ -33,9 +35,10 @@ void operator delete(void* p, size_t) noexcept { free(p); }
 extern "C" {
 void rec_reset() { g_log.clear(); g_launches = g_mallocs = g_syncs = 0; g_fail_launch = -1; g_last = OK; }
 void rec_fail_launch(int k) { g_fail_launch = k; }       // the k-th launch from here on fails; -1: none
-void rec_fail_new(long k) { g_fail_new = k; }
+void rec_fail_new(long k) { g_fail_new = k; }             // likewise the k-th operator new of any thread
 long rec_new_left() { return g_fail_new; }
 int rec_mallocs() { return g_mallocs; }
+int rec_live() { return g_live; }
 int rec_syncs() { return g_syncs; }
 const char* rec_log() { return g_log.c_str(); }          // names of the launched kernels, one a line
 
@@ -57,8 +60,8 @@ err_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, void*)
     return OK;
 }
 err_t hipGetLastError() { const err_t e = g_last; g_last = OK; return e; }
-err_t hipMalloc(void** p, size_t n) { *p = (void*)g_next; g_next += (n + 4095) & ~(size_t)4095; ++g_mallocs; return OK; }
-err_t hipFree(void*) { return OK; }
+err_t hipMalloc(void** p, size_t n) { *p = (void*)g_next; g_next += (n + 4095) & ~(size_t)4095; ++g_mallocs; ++g_live; return OK; }
+err_t hipFree(void* p) { if (p) --g_live; return OK; }
 err_t hipMemcpy(void*, const void*, size_t, int) { return OK; }
 err_t hipMemcpyAsync(void*, const void*, size_t, int, void*) { return OK; }
 err_t hipMemset(void*, int, size_t) { return OK; }

@@ -86,3 +86,29 @@ for S, shapes in ((36, [(6, 36, 36), (1, 36, 216), (81, 4, 24)]), (64, [(6, 64, 
         assert L.rh_enhance_exact(ctx, P(1), 6, P(3), P(4), P(2), None) == 0
         assert (rec.rec_mallocs(), rec.rec_syncs()) == (0, 0), (S, n, h, w)
 ''')
+
+
+@pytest.mark.parametrize("net", ["PLAIN, 16, 3, 2, 0", "RES, 64, 1, 2, 1", "EDSR, 32, 1, 2, 1"])
+def test_create_reports_any_failed_host_allocation(run_child, net):
+    """Nothing throws across the C ABI: whichever host allocation fails, rh_create returns RH_E_NOMEM, with no context
+    and nothing left on the device."""
+    run_child(f'''
+FAR = 1 << 40
+rec.rec_fail_new(FAR)
+st, ctx = create({net})
+assert st == 0
+total = FAR - rec.rec_new_left()
+rec.rec_fail_new(-1)
+L.rh_destroy(ctx)
+assert rec.rec_live() == 0 and total > 8
+for k in sorted(set(list(range(min(total, 40))) + [total * i // 40 for i in range(40)] + [total - 1])):
+    rec.rec_fail_new(k)
+    st, ctx = create({net})
+    rec.rec_fail_new(-1)
+    if st == 0:                                              # only a helper thread was not to be had: its share is done without it
+        assert "{net}".startswith("EDSR")
+        L.rh_destroy(ctx)
+    else:
+        assert st == 5 and not ctx.value, (k, total, st)     # RH_E_NOMEM
+    assert rec.rec_live() == 0, k
+''')
