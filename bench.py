@@ -34,7 +34,7 @@ HBM_PEAK = 8.0e12          # B/s
 # the plain-copy calibration stated there); only reported for that workload and kernel set.
 PROFILED_TRAFFIC = {"cfg3_16x480x272_edsr64_x4_bf16": (404.2e6, "profiles/conv_mfma_cfg3_hbm_counters.md")}
 CONV_KERNEL = {64: "k_conv_mfma_duo<SKIP,RELU,10> (64-channel bf16-output convs of the network body: ReLU and skip-add instantiations)",
-               32: "k_conv_mfma<32,1,16,false,SKIP,RELU> (bf16-output 32-channel convs)"}
+               32: "k_block32<RES> (pairs of bf16-output 32-channel convs; one left over: k_conv_mfma<32,1,16,false,SKIP,RELU>)"}
 
 
 def live_cell_fraction(boxes, halo, S, n_bins, cell_h=8, cell_w=32):
@@ -69,13 +69,13 @@ def needed_cell_fractions(places, S, n_bins, radii, cell_h=8, cell_w=32):
 
 
 def net_flops(net, composed_tail):
-    """Per packed low-resolution pixel: flop and launches of the profiled conv class (bf16 path: the
+    """Per packed low-resolution pixel: flop of the profiled conv class (bf16 path: the
     C-input / bf16-output convs; 18*cin*cout per output pixel at the layer's resolution), the
     network's flop as defined layer by layer, and the flop the kernels execute (they differ when
     the linear tail of an EDSR-shaped net runs as one composed 5x5 conv on padded MFMA rows)."""
     C, s = net.channels, net.scale
     body = net.n_blocks - 2 if net.topology == "plain" else 2 * net.n_blocks + (1 if net.topology == "edsr" else 0)
-    cls_fl, cls_n = body * 18 * C * C, body
+    cls_fl = body * 18 * C * C
     head = 18 * 3 * C
     if net.topology == "edsr":
         ups = 18 * C * 4 * C + 4 * 18 * C * 4 * C if s == 4 else 18 * C * C * s * s
@@ -85,10 +85,9 @@ def net_flops(net, composed_tail):
         else:
             executed = network
             cls_fl += ups
-            cls_n += 2 if s == 4 else 1
     else:
         network = executed = head + cls_fl + 18 * C * 3 * s * s
-    return cls_fl, cls_n, network, executed
+    return cls_fl, network, executed
 
 
 class Runner:
@@ -208,13 +207,12 @@ class Runner:
         S = cfg.bin_size
         n_boxes, n_bins, _, k_sel = counts
         px_lr = n_bins * S * S
-        cls_fl, cls_n, network_fl, executed_fl = net_flops(cfg.net, self.composed)
+        cls_fl, network_fl, executed_fl = net_flops(cfg.net, self.composed)
         if cfg.precision != "bf16":
-            import workloads as wl
-            cls_fl, cls_n = network_fl, len(wl.net_layers(cfg.net))      # fp32 path: all layers are one class
+            cls_fl = network_fl      # fp32 path: all layers are one class
         conv_ms, conv_n = prof["conv"]
         launch_s = conv_ms / max(conv_n, 1) * 1e-3
-        flop_per_launch = cls_fl * px_lr * self.live_frac / max(cls_n, 1)      # box-masked mode: live cells only
+        flop_per_launch = cls_fl * px_lr * self.live_frac / max(conv_n, 1)      # box-masked mode: live cells only
         achieved = flop_per_launch / launch_s if launch_s > 0 else 0.0
         peak = MFMA_BF16_PEAK if cfg.precision == "bf16" else FP32_VALU_PEAK
         enh_s = sum(prof[k][0] for k in ("head", "conv", "conv_last")) * 1e-3
@@ -328,7 +326,7 @@ def main():
         "output_mpixel_per_s": F * cfg.height * s * cfg.width * s / (ms_step * 1e-3) / 1e6,
         "kernel_ms_per_step": sm["kernel_ms_per_step"],
         "roofline": {"bound": "mfma" if cfg.precision == "bf16" else "alu",
-                     "kernel": CONV_KERNEL.get(cfg.net.channels, "k_conv_mfma") if cfg.precision == "bf16" else "k_conv3x3_f32 (all layers)",
+                     "kernel": CONV_KERNEL.get(cfg.net.channels, "k_conv_mfma") if cfg.precision == "bf16" else "k_conv3x3_f32_lds (all layers with up to 64 input channels)",
                      "achieved": cc["achieved_tflops"], "peak": (MFMA_BF16_PEAK if cfg.precision == "bf16" else FP32_VALU_PEAK) / 1e12,
                      "unit": "TFLOP/s", "frac": cc["frac_of_peak"],
                      "traffic": traffic[0] if traffic else None, "traffic_source": traffic[1] if traffic else None,

@@ -322,7 +322,9 @@ rh_status rh_temporal_spread(rh_ctx* ctx, float* importance, int32_t F, const ui
  * rh_profile_read synchronises, adds up the elapsed times and launch counts since the last
  * read into ms[RH_PROF_N] / launches[RH_PROF_N] (host arrays) and resets them.
  * RH_PROF_CONV is the bf16 MFMA conv with C input and bf16 output channels (the body and the
- * upsampling convs), the kernel that dominates the path; with RH_FP32 it covers all layers.
+ * upsampling convs; of 32-channel networks two convs go in one launch), the kernel that dominates the path;
+ * with RH_FP32 it covers all layers.  What a mode of rh_enhance launches besides counts with RH_PROF_HEAD
+ * where it runs ahead of the body (cell lists, border mask), clearing between the layers with theirs.
  */
 enum { RH_PROF_SELECT = 0, RH_PROF_PLAN = 1, RH_PROF_GATHER = 2, RH_PROF_HEAD = 3, RH_PROF_CONV = 4,
        RH_PROF_CONV_LAST = 5, RH_PROF_UNPACK = 6, RH_PROF_TEMPORAL = 7, RH_PROF_N = 8 };

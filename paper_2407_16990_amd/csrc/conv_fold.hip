@@ -506,7 +506,7 @@ static hipError_t launch_fold(rh_ctx* ctx, const fold_args& a)
     return hipGetLastError();
 }
 
-// t: the body's output [N][H][W][C] bf16 -> raw network output fp32 [N][sH][sW][3]; two launches.
+// t: the body's output [N][H][W][C] bf16 -> raw network output fp32 [N][sH][sW][3]; two launches (one: see launch_fold).
 rh_status rh_launch_fold(rh_ctx* ctx, const __bf16* t, float* out, int N, int H, int W, const uint32_t* n_valid, int rev,
                          const uint32_t* tile_list, const uint32_t* n_list)
 {

@@ -513,7 +513,6 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     rh_status st = rh_ensure_workspace(ctx, need * 2 + mask_words * 4);
     if (st != RH_OK) return st;
     uint32_t* keep = masked ? (uint32_t*)((uint8_t*)ctx->act + need * 2) : nullptr;
-    if (masked) { st = rh_outside_mask(ctx, keep, N, n_valid); if (st != RH_OK) return st; }
     __bf16* a = (__bf16*)ctx->act; __bf16* t = a + lr; __bf16* h = t + lr; __bf16* u1 = h + lr; __bf16* u2 = u1 + up1;
     ctx->conv_parity = 0;                  // the head conv walks forward, the first conv after it backward
     const std::vector<rh_layer>& L = ctx->layers;
@@ -521,23 +520,24 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     const int head_relu = d.topology == RH_NET_PLAIN;
     {
         const rh_layer& l0 = L[li++];
-        rh_prof_scope ps(ctx, RH_PROF_HEAD);
+        // with what a mode launches ahead of the other convs
+        rh_prof_scope ps(ctx, RH_PROF_HEAD, 1u + (masked ? 2u : 0u) + (ctx->bz_boxes ? 1u : 0u) + (ctx->mk_boxes ? 3u : 0u) + (ctx->nd_places ? 2u : 0u));
+        if (masked) { st = rh_outside_mask(ctx, keep, N, n_valid); if (st != RH_OK) return st; }
         RH_HIP(ctx, rh_launch_head_mfma(ctx->stream, C, in, (const uint4*)((const uint8_t*)ctx->wpack + l0.wp_off),
                                         ctx->bpack + l0.bp_off, h, N, H, W, head_relu, n_valid));
         // box-masked mode: from here to the end of the body the three tensors are zero outside the live cells
         if (ctx->mk_boxes) { st = rh_launch_cell_lists(ctx, N, n_valid, h, a, t); if (st != RH_OK) return st; }
         if (ctx->nd_places) { ctx->nd_conv = 0; st = rh_launch_need_lists(ctx, N, n_valid); if (st != RH_OK) return st; }
+        // exact-border mode (a no-op otherwise): clear the out-of-frame part of the boxes in a layer's output
+        st = rh_zero_outside(ctx, h, C * 2, 1, N, n_valid); if (st != RH_OK) return st;
     }
-    // exact-border mode (a no-op otherwise): clear the out-of-frame part of the boxes in a layer's output
-#define ZERO1(buf, res) do { st = rh_zero_outside(ctx, (void*)(buf), C * 2, (res), N, n_valid); if (st != RH_OK) return st; } while (0)
-    ZERO1(h, 1);
-#define ZERO(buf, res) do { if (!masked) ZERO1(buf, res); } while (0)
+#define ZERO(buf, res) do { if (ctx->bz_boxes && !masked) { st = rh_zero_outside(ctx, (void*)(buf), C * 2, (res), N, n_valid); if (st != RH_OK) return st; ++n_conv; } } while (0)
     // one event pair around the run of bf16-output convs (they are launched back to back) and
     // one around the last conv: per-launch events would put a bubble between the launches
     uint32_t n_conv = 0;
     rh_prof_begin(ctx, RH_PROF_CONV);
 #define CONV(...) do { st = conv(ctx, __VA_ARGS__, n_valid, keep); if (st != RH_OK) return st; ++n_conv; } while (0)
-#define BLOCK32(...) do { RH_HIP(ctx, rh_launch_block32(ctx, __VA_ARGS__)); n_conv += 2; } while (0)
+#define BLOCK32(...) do { RH_HIP(ctx, rh_launch_block32(ctx, __VA_ARGS__)); ++n_conv; } while (0)
 #define LAST_CONV(...) do { rh_prof_end(ctx, n_conv); rh_prof_scope ps_(ctx, RH_PROF_CONV_LAST); st = conv(ctx, __VA_ARGS__); if (st != RH_OK) return st; } while (0)
     // 32 channels: two convs per launch (they are bound by memory, and the tensor between them stays on
     // the chip); exact-border mode clears part of that tensor and runs them one by one
@@ -563,7 +563,7 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
             CONV(L[li++], x, t, h, N, H, W, 0, false, 1); ZERO(t, 1);       // body end + long skip
             if (fold) {
                 rh_prof_end(ctx, n_conv);
-                rh_prof_scope ps_(ctx, RH_PROF_CONV_LAST, 2);
+                rh_prof_scope ps_(ctx, RH_PROF_CONV_LAST, ctx->nd_places && ctx->cfg.halo >= 1 ? 1 : 2);      // rh_launch_fold
                 // needed-region mode: the composed tail's output is needed on the pasted macroblocks only (radius 0)
                 st = rh_launch_fold(ctx, t, out, N, H, W, n_valid, ctx->conv_parity ^= 1,
                                     ctx->nd_places ? ctx->need_lists : nullptr, ctx->nd_places ? ctx->need_cnt : nullptr);
@@ -581,7 +581,6 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
 #undef BLOCK32
 #undef LAST_CONV
 #undef ZERO
-#undef ZERO1
     RH_HIP(ctx, hipGetLastError());
     return RH_OK;
 }

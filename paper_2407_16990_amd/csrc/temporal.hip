@@ -489,13 +489,13 @@ rh_status rh_launch_temporal_select(rh_ctx* ctx, const uint64_t* phi, const int3
 {
     // A table of one chunk goes with k_tr_prefix: one launch less (temporal reuse of 10 x 30 frames: 114.0 -> 111.4 us).
     const bool arg = n_streams < 512;
+    rh_prof_scope ps(ctx, RH_PROF_TEMPORAL, 2 + (arg ? 0 : (n_streams + 1 + 511) / 512));
     tr_off_chunk c;
     for (int s0 = 0; s0 <= n_streams; s0 += 512) {
         c.first = s0; c.n = (n_streams + 1 - s0) < 512 ? (n_streams + 1 - s0) : 512;
         for (int i = 0; i < c.n; ++i) c.v[i] = stream_off[s0 + i];
         if (!arg) hipLaunchKernelGGL(k_tr_upload, dim3(1), dim3(256), 0, ctx->stream, c, ctx->tr_off);
     }
-    rh_prof_scope ps(ctx, RH_PROF_TEMPORAL, 2);
     hipLaunchKernelGGL(arg ? k_tr_prefix<true> : k_tr_prefix<false>, dim3(n_streams), dim3(256), 0, ctx->stream, c, (const unsigned long long*)phi,
                        ctx->tr_off, (unsigned long long*)ctx->tr_A, (unsigned long long*)ctx->tr_T, n_selected);
     hipLaunchKernelGGL(k_tr_choose, dim3(n_streams), dim3(256), 0, ctx->stream, (const unsigned long long*)ctx->tr_A,

@@ -112,3 +112,58 @@ for k in sorted(set(list(range(min(total, 40))) + [total * i // 40 for i in rang
         assert st == 5 and not ctx.value, (k, total, st)     # RH_E_NOMEM
     assert rec.rec_live() == 0, k
 ''')
+
+
+@pytest.mark.parametrize("net,modes", [("PLAIN, 32, 5, 2, 1", "plain exact"), ("RES, 32, 3, 2, 1", "plain exact"), ("EDSR, 32, 2, 3, 1", "plain exact"),
+                                       ("RES, 64, 2, 2, 1", "plain exact masked needed"), ("EDSR, 64, 1, 4, 1", "plain exact masked needed"),
+                                       ("EDSR, 8, 1, 4, 0", "plain exact"), ("PLAIN, 68, 3, 2, 0", "plain exact")])
+@pytest.mark.parametrize("halo,tail", [(6, 0), (0, 1)])
+def test_profile_counts_every_launch_once(run_child, net, modes, halo, tail):
+    """rh_profile_read's counts add up to the kernels that went out, and those of the convs to the conv kernels."""
+    run_child(f'''
+st, ctx = create({net}, halo={halo}, tail={tail})
+assert st == 0 and L.rh_profile_enable(ctx, 1) == 0
+ms, n = (C.c_double * 8)(), (C.c_uint32 * 8)()
+def counted(call):
+    rec.rec_reset()
+    st = call()
+    if st == 7 and {tail}: return                            # the needed-region mode does not take a layer-by-layer tail
+    assert st == 0, (st, L.rh_last_error(ctx))
+    assert L.rh_profile_read(ctx, ms, n) == 0
+    k = names()
+    assert sum(n) == len(k), (list(n), k)
+    convs = [x for x in k if any(s in x for s in ("k_conv_mfma", "k_block32", "k_conv3x3_f32", "k_conv_tail3", "k_conv_fold"))]
+    cleared = [x for x in k if "k_zero_outside" in x]
+    if convs:                                                # conv + last conv (k_fold_ring goes with the composed tail)
+        assert len(convs) <= n[4] + n[5] <= len(convs) + len(cleared) + 1, (list(n), k)
+seg = (C.c_uint32 * 8)(0, 1, 3, 0, 1, 9, 5, 0)
+counted(lambda: L.rh_select_regions(ctx, P(1), 9, seg, 2, 0, P(2), P(3), P(4)))
+segs = (C.c_uint32 * (4 * 32))(*[v for i in range(32) for v in (i, i + 1, 1, 0)])
+counted(lambda: L.rh_select_regions(ctx, P(1), 32, segs, 32, 0, P(2), P(3), P(4)))
+for F in (1, 16, 17, 32): counted(lambda: pack(ctx, F))
+for mode in "{modes}".split():
+    for nv in (None, P(11)):
+        counted({{"plain": lambda: L.rh_enhance(ctx, P(1), 5, 64, 64, P(2), nv),
+                 "exact": lambda: L.rh_enhance_exact(ctx, P(1), 5, P(3), P(4), P(2), nv),
+                 "masked": lambda: L.rh_enhance_masked(ctx, P(1), 5, P(3), P(4), P(2), nv),
+                 "needed": lambda: L.rh_enhance_needed(ctx, P(1), 5, P(3), P(4), P(2), nv)}}[mode])
+counted(lambda: L.rh_unpack(ctx, P(1), 5, 64, 64, P(2), P(3), P(4), 8, P(5), None))
+''')
+
+
+def test_profile_counts_every_launch_of_the_temporal_reuse(run_child):
+    run_child('''
+st, ctx = create(PLAIN, 4, 2, 2, 0, w=32, h=32, F=1030)
+assert st == 0 and L.rh_profile_enable(ctx, 1) == 0
+ms, n = (C.c_double * 8)(), (C.c_uint32 * 8)()
+def counted(call):
+    rec.rec_reset()
+    assert call() == 0, L.rh_last_error(ctx)
+    assert L.rh_profile_read(ctx, ms, n) == 0
+    assert n[7] == sum(n) == len(names()), (list(n), names())
+counted(lambda: L.rh_temporal_phi(ctx, P(1), 30, 12, 1, P(2)))
+for ns in (1, 511, 512, 1024):
+    off = (C.c_int32 * (ns + 1))(*range(ns + 1))
+    counted(lambda: L.rh_temporal_select(ctx, P(1), off, ns, ns, P(2), P(3), P(4), P(5)))
+counted(lambda: L.rh_temporal_spread(ctx, P(1), 30, P(2), P(3)))
+''')
