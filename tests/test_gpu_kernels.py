@@ -69,7 +69,7 @@ def test_block32_tiles_do_not_depend_on_the_batch():
 
 # Plans whose list of free rectangles stays in one, grows to several, or outgrows the registers' chunks of 64
 # (most entries: 32, 181, 206, 425, 263), of up to 16 frames (one launch) and more; isolated macroblocks with
-# either neighbourhood; turned boxes; bins that run out in either loop
+# either neighbourhood; turned boxes; bins that run out
 @pytest.mark.parametrize("F,w,h,halo,S,frac,kind,T,conn,rotate,max_bins", [
     (17, 480, 272, 10, 128, 0.5, "clustered", 0, 8, False, 400), (128, 480, 272, 10, 128, 0.2, "clustered", 0, 8, False, 800),
     (60, 480, 272, 10, 128, 0.12, "uniform", 0, 8, False, 600), (16, 640, 368, 10, 192, 0.4, "clustered", 3, 8, False, 300),
@@ -125,3 +125,159 @@ def test_select_sizes(F, w, h, segs, levels, mode):
 def test_exact_border_mask(net, halo, S, rotate):
     cfg = wl.replace(wl.config(3), n_frames=2, width=112, height=80, halo=halo, bin_size=S, net=net)
     exact_border_check(cfg, "bf16", rotate=rotate)
+
+
+# Bins that run out in each of the first fit's three loops: by the first box that needs bin `max_bins`, the list holds
+# about 31 rectangles (10 bins: one chunk of registers), 160 (40: several chunks), 385 (110: LDS), 400 (the last bin of 145 or
+# 183); upright and turned; 16 frames are planned in one launch, 20 in several.  All boxes from that one on are
+# without a bin, the ones before it keep theirs.
+@pytest.mark.parametrize("F,max_bins", [(16, 10), (16, 40), (16, 110), (16, 144), (20, 10), (20, 40), (20, 110), (20, 182)])
+@pytest.mark.parametrize("rotate", [False, True])
+def test_plan_runs_out_of_bins_in_every_loop(F, max_bins, rotate):
+    cfg = wl.replace(wl.config(3), n_frames=F, width=640, height=368, frac=0.4, halo=10, bin_size=192)
+    frames = np.random.default_rng(F).integers(0, 256, (F, 368, 640, 3), dtype=np.uint8)
+    net = wl.Net("plain", 1, 2, 1)
+    rh = make_rh(wl.replace(cfg, net=net), wl.make_weights(net, 0, "fp32"), max_bins=max_bins, precision="fp32", max_box_mbs=3, rotate=rotate)
+    plan, _, _ = check_select_and_plan(rh, cfg, frames, wl.make_importance(cfg), wl.make_segments(cfg), T=3, max_bins=max_bins, rotate=rotate)
+    assert plan.overflow and plan.n_bins == max_bins
+    rh.close()
+
+
+# Networks of weights 0 and +-1 on images of 0 and 255: every product, sum and activation is a whole number of at most
+# 256, which bf16 holds, so no order of sums and no rounding point is left that could differ, and the output has to
+# be the oracle's in every bit - at every tile edge, padded border and cleared pixel.
+def whole_number_weights(net, seed, taps):
+    """`taps` weights of +-1 per output (the last conv: 40), biases 0 or 1."""
+    r = np.random.default_rng(seed)
+    parts, bound, layers = [], 1, wl.net_layers(net)
+    for i, (cin, cout, role) in enumerate(layers):
+        n = 40 if role == "last" else taps
+        w = np.zeros((cout, 9 * cin), dtype=np.float32)
+        at = np.argsort(r.random(w.shape), axis=1)[:, :min(n, 9 * cin)]
+        np.put_along_axis(w, at, r.choice(np.float32([-1, 1]), at.shape), axis=1)
+        parts += [w.ravel(), r.integers(0, 2, cout).astype(np.float32)]
+        skipped = block_in if role == "res2" else head if net.topology == "edsr" and i == 2 * net.n_blocks + 1 else 0
+        if role != "res2":
+            block_in = bound
+        bound = n * bound + 1 + skipped
+        if i == 0:
+            head = bound
+        assert role == "last" or bound <= 256, (i, bound)
+    return np.concatenate(parts)
+
+
+WHOLE_NETS = [(wl.Net("res", 32, 2, 2), "bf16", 2), (wl.Net("res", 32, 3, 1), "bf16", 1), (wl.Net("plain", 32, 6, 2), "bf16", 2),
+              (wl.Net("plain", 32, 7, 3), "bf16", 2), (wl.Net("edsr", 32, 1, 4), "bf16", 2), (wl.Net("edsr", 32, 2, 3), "bf16", 1),
+              (wl.Net("res", 64, 2, 2), "bf16", 2), (wl.Net("plain", 64, 5, 2), "bf16", 2), (wl.Net("edsr", 64, 1, 2), "bf16", 2),
+              (wl.Net("edsr", 64, 1, 3), "bf16", 2), (wl.Net("edsr", 64, 1, 4), "bf16", 2),
+              (wl.Net("plain", 16, 4, 2), "fp32", 2), (wl.Net("edsr", 20, 1, 4), "fp32", 2), (wl.Net("res", 64, 2, 2), "fp32", 2)]
+
+
+@pytest.mark.parametrize("net,precision,taps,tail", [c + (False,) for c in WHOLE_NETS] +
+                         [c + (True,) for c in WHOLE_NETS if c[0].topology == "edsr" and c[1] == "bf16"])      # and layer by layer
+@pytest.mark.parametrize("shape", [(2, 37, 70), (1, 16, 32), (3, 19, 33)])
+def test_whole_number_nets_are_exact(net, precision, taps, tail, shape):
+    N, H, W = shape
+    blob = whole_number_weights(net, 3, taps)
+    rh = RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=32, max_bins=4, net=net, weights=blob, precision=precision, per_layer_tail=tail)
+    x = np.random.default_rng(N * H * W).integers(0, 2, (N, H, W, 3), dtype=np.uint8) * np.uint8(255)
+    out = torch.full((N, H * net.scale, W * net.scale, 3), float("nan"), device="cuda")
+    rh.enhance(dev(x), out=out)
+    o = oracle.sr_forward(net, blob, x)
+    assert len(np.unique(o)) > 5 and np.array_equal(out.cpu().numpy().astype(np.float64), o)
+    rh.close()
+
+
+# Exact-border mode with boxes that leave the frame on all sides: the 64-channel convs' bit mask, k_zero_outside elsewhere
+@pytest.mark.parametrize("net,precision,taps", WHOLE_NETS)
+@pytest.mark.parametrize("halo,S,rotate", [(5, 76, True), (6, 44, False), (3, 100, True)])
+def test_whole_number_nets_are_exact_at_frame_borders(net, precision, taps, halo, S, rotate):
+    cfg = wl.replace(wl.config(3), n_frames=2, width=112, height=75, halo=halo, bin_size=S, net=net)
+    frames = np.random.default_rng(S).integers(0, 2, (2, 75, 112, 3), dtype=np.uint8) * np.uint8(255)
+    imp = wl.make_importance(cfg)
+    imp[:, 0, :] += 5.0; imp[:, :, 0] += 5.0; imp[:, -1, -3:] += 5.0
+    blob = whole_number_weights(net, 4, taps)
+    rh = make_rh(cfg, blob, precision=precision, rotate=rotate)
+    plan, po, (_, _, o_bins) = check_select_and_plan(rh, cfg, frames, imp, wl.make_segments(cfg), rotate=rotate)
+    keep = oracle.border_keep(cfg.height, cfg.width, plan.boxes, halo, S, plan.n_bins)
+    o = oracle.sr_forward(net, blob, o_bins, keep)
+    out = torch.full((plan.n_bins, S * net.scale, S * net.scale, 3), float("nan"), device="cuda")
+    rh.enhance_exact(po.bins, po.boxes, po.counts, n=plan.n_bins, n_valid=po.counts[1:2], out=out)
+    assert (keep == 0).any() and not np.array_equal(o, oracle.sr_forward(net, blob, o_bins))
+    assert np.array_equal(out.cpu().numpy().astype(np.float64), o)
+    rh.close()
+
+
+# Exact-border mode without boxes clears nothing and runs every layer in a launch of its own (32 channels), or with a mask
+# that keeps every pixel (64): the same bits as the plain call's pairs of convs and plain stores.
+@pytest.mark.parametrize("net", [wl.Net("res", 32, 3, 2, 0.03), wl.Net("plain", 32, 5, 2, 0.1), wl.Net("plain", 32, 6, 3, 0.1), wl.Net("edsr", 32, 2, 3, 0.03),
+                                 wl.Net("res", 64, 2, 2, 0.02), wl.Net("plain", 64, 5, 2, 0.1), wl.Net("edsr", 64, 1, 2, 0.02),
+                                 wl.Net("edsr", 64, 1, 3, 0.02), wl.Net("edsr", 64, 1, 4, 0.02)])
+@pytest.mark.parametrize("S,N", [(36, 5), (100, 3), (64, 70)])
+def test_exact_mode_without_boxes_is_the_plain_call_bit_for_bit(net, S, N):
+    rh = RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=S, max_bins=N, net=net, weights=wl.make_weights(net, 14, "bf16"),
+            precision="bf16", per_layer_tail=True)
+    x = torch.randint(0, 256, (N, S, S, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(S))
+    boxes, counts = torch.zeros((1, 24), dtype=torch.uint8, device="cuda"), torch.zeros(4, dtype=torch.int32, device="cuda")
+    assert torch.equal(rh.enhance(x), rh.enhance_exact(x, boxes, counts))
+    rh.close()
+
+
+# The patch kernel's sums go in the order of the kernel for more than 64 channels: a net in 68 channels whose added
+# ones carry zeros gives the same bits (a product with zero leaves a sum as it is).
+@pytest.mark.parametrize("net", [wl.Net("plain", 6, 4, 3, 0.1), wl.Net("res", 16, 2, 2, 0.05), wl.Net("edsr", 20, 1, 4, 0.05), wl.Net("edsr", 64, 1, 2, 0.05)])
+def test_fp32_patch_kernel_is_the_direct_kernel_bit_for_bit(net):
+    big = wl.replace(net, channels=68)
+    small_blob, parts, off = wl.make_weights(net, 15, "fp32"), [], 0
+    for (ci, co, _), (cI, cO, _) in zip(wl.net_layers(net), wl.net_layers(big)):
+        w, b = np.zeros((cO, 9, cI), dtype=np.float32), np.zeros(cO, dtype=np.float32)
+        w[:co, :, :ci] = small_blob[off:off + co * 9 * ci].reshape(co, 9, ci); off += co * 9 * ci
+        b[:co] = small_blob[off:off + co]; off += co
+        parts += [w.ravel(), b]
+    x = torch.randint(0, 256, (2, 35, 50, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(2))
+    outs = []
+    for n, blob in ((net, small_blob), (big, np.concatenate(parts))):
+        rh = RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=32, max_bins=4, net=n, weights=blob, precision="fp32")
+        outs.append(rh.enhance(x))
+        rh.close()
+    assert torch.equal(outs[0], outs[1])
+
+
+# A step recorded into a graph after one eager step of the same size: nothing allocates, and every replay
+# clears what it counts.  16 frames are planned in one launch, 20 in several.
+@pytest.mark.parametrize("F,net", [(16, wl.Net("res", 64, 1, 2, 0.02)), (20, wl.Net("res", 32, 1, 2, 0.03)), (20, wl.Net("plain", 64, 3, 2, 0.1))])
+def test_recorded_step_replays(F, net):
+    cfg = wl.replace(wl.config(3), n_frames=F, width=160, height=112, halo=4, bin_size=64, net=net)
+    blob, stream = wl.make_weights(net, 3, "bf16"), torch.cuda.Stream()
+    frames, segs = dev(wl.make_frames(cfg)), [tuple(r) for r in wl.make_segments(cfg).tolist()]
+    imps = [dev(np.roll(wl.make_importance(cfg), k, axis=0)) for k in range(4)]
+    rh = make_rh(cfg, blob, max_bins=80, stream=stream)
+    imp = imps[0].clone()
+    po = None
+
+    def step(po):
+        po = rh.pack(frames, imp, *rh.select_regions(imp, segs), out=po)
+        net_out = rh.enhance_exact(po.bins, po.boxes, po.counts, n=80, n_valid=po.counts[1:2])
+        return po, rh.unpack(net_out, po.places, po.counts[3:4], frames)[0]
+
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        po, _ = step(None)
+        want = []
+        for v in imps:
+            imp.copy_(v)
+            po, hr = step(po)
+            want.append((po.counts.clone(), hr.clone()))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        _, hr = step(po)
+    for k in (3, 0, 2, 1, 3):
+        with torch.cuda.stream(stream):
+            imp.copy_(imps[k])
+            hr.zero_(); po.counts.zero_()
+            graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(po.counts, want[k][0]) and torch.equal(hr, want[k][1]), k
+    assert int(want[0][0][0]) > 0 and not torch.equal(want[0][1], want[1][1])
+    rh.close()
