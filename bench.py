@@ -326,7 +326,7 @@ def main():
         "output_mpixel_per_s": F * cfg.height * s * cfg.width * s / (ms_step * 1e-3) / 1e6,
         "kernel_ms_per_step": sm["kernel_ms_per_step"],
         "roofline": {"bound": "mfma" if cfg.precision == "bf16" else "alu",
-                     "kernel": CONV_KERNEL.get(cfg.net.channels, "k_conv_mfma") if cfg.precision == "bf16" else "k_conv3x3_f32_lds (all layers with up to 64 input channels)",
+                     "kernel": CONV_KERNEL.get(cfg.net.channels, "k_conv_mfma") if cfg.precision == "bf16" else "k_conv3x3_f32_lds (all layers with up to 120 input channels)",
                      "achieved": cc["achieved_tflops"], "peak": (MFMA_BF16_PEAK if cfg.precision == "bf16" else FP32_VALU_PEAK) / 1e12,
                      "unit": "TFLOP/s", "frac": cc["frac_of_peak"],
                      "traffic": traffic[0] if traffic else None, "traffic_source": traffic[1] if traffic else None,

@@ -66,9 +66,12 @@ __global__ __launch_bounds__(256) void k_conv3x3_f32(const void* __restrict__ in
 // in the same order: results are bit for bit those of the kernel above.
 // Measured, whole networks: 8 bins of 64 x 64, 4 layers of 16 channels: 98.9 -> 34.5 us; residual net, 7
 // layers of 32 channels, 4 x 96 x 96: 1455 -> 234; EDSR with 64 channels, 64 x 96 x 96: 86.9 -> 25.3 ms.
-// More than 64 channels keep the kernel above: the patch would leave less than a workgroup per CU.
+// The line lies where the patch stops fitting a CU's LDS (120 channels: 157 of 160 KB), because a single workgroup
+// per CU still gains.  Kernel above -> patch, EDSR x4 of 2 blocks on 16 x 128 x 128: 68 channels 150 -> 52 ms,
+// 96: 268 -> 100, 120: 436 -> 156; 4 plain layers on one image of 64 x 64: 377 -> 116, 529 -> 155, 663 -> 186 us.
 #define CO_L 4
-#define LDS_CIN 64
+#define LDS_CIN 120
+static_assert(18 * 18 * (LDS_CIN + 4) * sizeof(float) <= 160 * 1024, "the patch fits the LDS of a CU");
 
 template <bool U8>
 __global__ __launch_bounds__(256) void k_conv3x3_f32_lds(const void* __restrict__ in_, const float* __restrict__ w4,

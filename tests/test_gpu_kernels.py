@@ -13,12 +13,13 @@ from gpu_common import check_net, check_select_and_plan, dev, gpu_select, make_r
 pytestmark = pytest.mark.gpu
 
 
-# 16 x 16 tiles, channels in groups of 4 (and 4 outputs), the patch kernel up to 64 input channels
+# 16 x 16 tiles, channels in groups of 4 (and 4 outputs), the patch kernel up to 120 input channels
 @pytest.mark.parametrize("net,shape", [
     (wl.Net("plain", 1, 3, 1, 0.1), (2, 3, 16)), (wl.Net("plain", 4, 3, 2, 0.1), (1, 16, 17)),
     (wl.Net("plain", 6, 3, 3, 0.1), (2, 15, 33)), (wl.Net("res", 16, 1, 2, 0.05), (3, 31, 32)),
     (wl.Net("edsr", 20, 1, 3, 0.05), (1, 17, 5)), (wl.Net("plain", 64, 3, 2, 0.1), (1, 18, 20)),
-    (wl.Net("plain", 65, 3, 2, 0.1), (1, 18, 20)),
+    (wl.Net("plain", 65, 3, 2, 0.1), (1, 18, 20)), (wl.Net("res", 119, 1, 2, 0.05), (1, 17, 19)),
+    (wl.Net("plain", 120, 3, 2, 0.1), (2, 18, 20)), (wl.Net("plain", 121, 3, 2, 0.1), (1, 18, 20)),
 ])
 def test_fp32_conv_shapes(net, shape):
     N, H, W = shape
@@ -27,7 +28,7 @@ def test_fp32_conv_shapes(net, shape):
     x = np.random.default_rng(N * H * W).integers(0, 256, (N, H, W, 3), dtype=np.uint8)
     out = torch.full((N, H * net.scale, W * net.scale, 3), float("nan"), device="cuda")
     rh.enhance(dev(x), out=out)
-    # the bar of the fp32 path (1e-5 of the norm, sums of at most 9 x 65 products)
+    # the bar of the fp32 path (1e-5 of the norm, sums of at most 9 x 121 products)
     check_net(out.cpu().numpy(), oracle.sr_forward(net, blob, x), "fp32", f"{net} {shape}")
     rh.close()
 
@@ -223,11 +224,12 @@ def test_exact_mode_without_boxes_is_the_plain_call_bit_for_bit(net, S, N):
     rh.close()
 
 
-# The patch kernel's sums go in the order of the kernel for more than 64 channels: a net in 68 channels whose added
+# The patch kernel's sums go in the order of the kernel for more than 120 channels: a net in 124 channels whose added
 # ones carry zeros gives the same bits (a product with zero leaves a sum as it is).
-@pytest.mark.parametrize("net", [wl.Net("plain", 6, 4, 3, 0.1), wl.Net("res", 16, 2, 2, 0.05), wl.Net("edsr", 20, 1, 4, 0.05), wl.Net("edsr", 64, 1, 2, 0.05)])
+@pytest.mark.parametrize("net", [wl.Net("plain", 6, 4, 3, 0.1), wl.Net("res", 16, 2, 2, 0.05), wl.Net("edsr", 20, 1, 4, 0.05), wl.Net("edsr", 64, 1, 2, 0.05),
+                                 wl.Net("plain", 65, 4, 2, 0.1), wl.Net("res", 119, 1, 2, 0.05), wl.Net("edsr", 120, 1, 2, 0.05)])
 def test_fp32_patch_kernel_is_the_direct_kernel_bit_for_bit(net):
-    big = wl.replace(net, channels=68)
+    big = wl.replace(net, channels=124)
     small_blob, parts, off = wl.make_weights(net, 15, "fp32"), [], 0
     for (ci, co, _), (cI, cO, _) in zip(wl.net_layers(net), wl.net_layers(big)):
         w, b = np.zeros((cO, 9, cI), dtype=np.float32), np.zeros(cO, dtype=np.float32)

@@ -116,7 +116,7 @@ for k in sorted(set(list(range(min(total, 40))) + [total * i // 40 for i in rang
 
 @pytest.mark.parametrize("net,modes", [("PLAIN, 32, 5, 2, 1", "plain exact"), ("RES, 32, 3, 2, 1", "plain exact"), ("EDSR, 32, 2, 3, 1", "plain exact"),
                                        ("RES, 64, 2, 2, 1", "plain exact masked needed"), ("EDSR, 64, 1, 4, 1", "plain exact masked needed"),
-                                       ("EDSR, 8, 1, 4, 0", "plain exact"), ("PLAIN, 68, 3, 2, 0", "plain exact")])
+                                       ("EDSR, 8, 1, 4, 0", "plain exact"), ("PLAIN, 68, 3, 2, 0", "plain exact"), ("RES, 124, 1, 2, 0", "plain exact")])
 @pytest.mark.parametrize("halo,tail", [(6, 0), (0, 1)])
 def test_profile_counts_every_launch_once(run_child, net, modes, halo, tail):
     """rh_profile_read's counts add up to the kernels that went out, and those of the convs to the conv kernels."""
@@ -148,6 +148,19 @@ for mode in "{modes}".split():
                  "masked": lambda: L.rh_enhance_masked(ctx, P(1), 5, P(3), P(4), P(2), nv),
                  "needed": lambda: L.rh_enhance_needed(ctx, P(1), 5, P(3), P(4), P(2), nv)}}[mode])
 counted(lambda: L.rh_unpack(ctx, P(1), 5, 64, 64, P(2), P(3), P(4), 8, P(5), None))
+''')
+
+
+@pytest.mark.parametrize("channels,patch", [(64, True), (65, True), (120, True), (121, False)])
+def test_fp32_convs_take_the_patch_kernel_as_long_as_the_patch_fits(run_child, channels, patch):
+    run_child(f'''
+st, ctx = create(RES, {channels}, 1, 2, 0)
+assert st == 0
+rec.rec_reset()
+assert L.rh_enhance(ctx, P(1), 2, 20, 20, P(2), None) == 0
+n = names()
+assert len(n) == 4 and "k_conv3x3_f32_lds" in n[0], n        # the first conv has 3 input channels
+assert all(("k_conv3x3_f32_lds" in x) == {patch} for x in n[1:]), n
 ''')
 
 
