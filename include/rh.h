@@ -188,7 +188,8 @@ rh_status rh_enhance(rh_ctx* ctx, const uint8_t* in, int32_t N, int32_t H, int32
  * pixels lie outside the frame (at that layer's resolution): with halo >= the network's
  * receptive-field radius the packed result then equals the frame-based one at every selected
  * macroblock, border ones included.  boxes / counts: dev, as written by rh_pack for these bins
- * (turned boxes are handled).  Costs one small extra launch per layer.
+ * (turned boxes are handled).  Costs one small extra launch per layer; with RH_BF16 and 64 channels three
+ * per call, since the convs then clear these pixels in their own stores.
  */
 rh_status rh_enhance_exact(rh_ctx* ctx, const uint8_t* in, int32_t N, const rh_box* boxes,
                            const uint32_t* counts, float* out, const uint32_t* n_valid);

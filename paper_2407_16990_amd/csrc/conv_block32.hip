@@ -5,7 +5,8 @@
 // intermediate tensor m exists in LDS only.
 //
 // Why: with 32 channels a conv is bound by memory (144 flop per byte, 96 with a skip), and a block of two
-// convs moved x, m, m, x, out.  Here it moves x (with a halo of 2, re-read from L2) and out.
+// convs moved x, m, m, x, out.  Here it moves x and out; the halo of 2 and the second reading of x come from L2 for the
+// most part (on 113 bins of 96 x 96 107 MiB are fetched for 64 MiB of x).
 //
 // Tile: 16 x 32 outputs = 18 x 34 values of m = 20 x 36 pixels of x, a workgroup of 4 waves, two
 // workgroups per CU (so that one's loads, barriers and stores run under the other's MFMAs).
@@ -20,8 +21,9 @@
 // that LDS has room for, and an activation fragment feeds the up to 3 rows it belongs to: 6 reads per
 // 12 MFMAs.  x's values for the residual add and the next tile's patch are requested before these MFMAs.
 // Measured, residual net of 8 blocks on 121 bins of 96 x 96: 52-55 us per block against 35.3 + 43.3 us for the two
-// launches (0.95 PFLOP/s executed, 12 % of it the halo of m; the clock falls to 1.5-1.8 GHz under this load,
-// which is why reading 22 % less LDS with a row-wise conv1 changed nothing); 64 tiles: 10.6 us.
+// launches (0.84-0.89 PFLOP/s executed, 11 % of it the halo of m); 64 tiles: 10.6 us.  Counters, 113 bins: clock 1.78 GHz, matrix
+// pipe busy 45 % and LDS 50 % of the CU's cycles, 3.4 TB/s; a row-wise conv1 that reads 22 % less LDS changed nothing.  None of
+// them is the limit by itself; what is left is the chain of short phases between barriers (not tested on its own).
 #include "conv_mfma_common.h"
 
 #define BTH 16

@@ -549,7 +549,12 @@ __global__ __launch_bounds__(256) void k_plan_emit(const rh_rawbox* __restrict__
 #define PF_THREADS 1024
 #define PF_WAVES (PF_THREADS / 64)
 #define PF_KEYS 2048
-#define PF_FRAMES 16                      // more frames: phases in launches of their own (one round of waves here: 20 us; 128 frames: 160 us)
+// More frames: phases in launches of their own.  Up to 16 the labelling is one round of waves here.  Plan + gather in us,
+// one launch / several: 480 x 272, 17 frames 58.1 / 56.4, 24: 79.5 / 69.3, 32: 104 / 84; scattered, 17: 267 / 242; 640 x 368,
+// 17: 86.8 / 78.9; 320 x 192, 17: 69.6 / 68.0.  Below the line several launches lose 5-8 us of 24-116 on up to 6 frames, are within
+// 2 us at 14-16 (16 frames of 480 x 272: 56.4 / 57.0), and gain from 12 on where there are many boxes, a number that the host
+// does not know: 16 frames of 640 x 368 79.9 / 75.1, scattered 245 / 228.
+#define PF_FRAMES 16
 #define PF_MAX_PER 2304                   // 16 waves x per x 4 B of importance <= 144 KB
 
 typedef unsigned long long u64;
