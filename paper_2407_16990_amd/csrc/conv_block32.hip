@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256, 2) void k_block32(block_args a)
                 o.w = pack_bf16x2(bf16_lo(o.w) + bf16_lo(sk[j].w), bf16_hi(o.w) + bf16_hi(sk[j].w));
             }
             const i32x4 v = {(int)o.x, (int)o.y, (int)o.z, (int)o.w};
-            __builtin_amdgcn_raw_buffer_store_b128(v, rout, out_off(j, l), 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(v, rout, out_off(j, l), 0, ST_THROUGH);
         }
         tile = next;
     }

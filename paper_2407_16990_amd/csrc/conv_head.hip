@@ -106,12 +106,14 @@ __global__ __launch_bounds__(256) void k_head_mfma(const uint8_t* __restrict__ i
     // the slice is private to the wave: no barrier, only the wave's own LDS writes must have landed
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     const int lcol = lane / NCHO, lc = lane % NCHO;
+    __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc((uint8_t*)out + (size_t)n * H * W * OPIXB, 0, (uint32_t)H * W * OPIXB, RSRC_FLAGS);
 #pragma unroll
     for (int j = 0; j < NOUT; ++j) {
         const int p = j * PPJ + lcol, r = p >> 5, px = p & 31;            // 64 pixels of the wave's two rows
         const int y = y0 + wave * 2 + r, x = x0 + px;
         const uint4 o = *(const uint4*)(stg + (r * 32 + px) * OPIXB + ((lc ^ (px & (NCHO - 1))) << 4));
-        if (y < H && x < W) *(uint4*)((uint8_t*)out + (((size_t)n * H + y) * W + x) * OPIXB + lc * 16) = o;
+        const i32x4 v = {(int)o.x, (int)o.y, (int)o.z, (int)o.w};
+        __builtin_amdgcn_raw_buffer_store_b128(v, rout, y < H && x < W ? (uint32_t)(y * W + x) * OPIXB + lc * 16 : OOB_OFF, 0, ST_THROUGH);
     }
 }
 

@@ -243,7 +243,7 @@ __global__ __launch_bounds__(256, MINB) void k_conv_mfma(conv_args a)
                         const int j = st * SPS + sl;
                         if (j < NOUT) {
                             const i32x4 v = {(int)outv[j].x, (int)outv[j].y, (int)outv[j].z, (int)outv[j].w};
-                            __builtin_amdgcn_raw_buffer_store_b128(v, rout, out_off(j, oty * TH, otx * TW, si, sj), 0, 0);
+                            __builtin_amdgcn_raw_buffer_store_b128(v, rout, out_off(j, oty * TH, otx * TW, si, sj), 0, ST_THROUGH);
                         }
                     } else if (sl < n_st + n_ld) {
                         const int j = st * LPS + (sl - n_st);
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(256, MINB) void k_conv_mfma(conv_args a)
 #pragma unroll
                 for (int j = 0; j < NOUT; ++j) {
                     const i32x4 v = {(int)outv[j].x, (int)outv[j].y, (int)outv[j].z, (int)outv[j].w};
-                    __builtin_amdgcn_raw_buffer_store_b128(v, rout, out_off(j, oty * TH, otx * TW, si, sj), 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(v, rout, out_off(j, oty * TH, otx * TW, si, sj), 0, ST_THROUGH);
                 }
             }
         }

@@ -367,7 +367,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
                     o.x &= m; o.y &= m; o.z &= m; o.w &= m;
                 }
                 const i32x4 v = {(int)o.x, (int)o.y, (int)o.z, (int)o.w};
-                __builtin_amdgcn_raw_buffer_store_b128(v, rout, out_off(j, y0, x0, si, sj), 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(v, rout, out_off(j, y0, x0, si, sj), 0, ST_THROUGH);
                 if constexpr (SKIP) __builtin_amdgcn_sched_barrier(0);
             }
             phase_barrier();                                  // 1: every wave of the team has read its slice back
