@@ -56,9 +56,6 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
     constexpr int WBYTES = 9 * KS * MT * 1024, PATCHB = PH * PW * PIXB, NSTEP = 3 * KS, CQ = 64;
     constexpr int NMAIN = PH, NHP = PH * 2 * NCH, NHALO = 1, NPRE = NMAIN + NHALO;      // 16-byte patch pieces per thread
     static_assert(NHP <= 256, "halo pieces must fit one per thread");
-    // The accumulators start from the bias.  The skip variant's drain phase is the longer of the two
-    // phases, so there the seeding belongs to the compute phase; otherwise it is done in the drain phase.
-    constexpr bool SEED_IN_COMPUTE = SKIP;
     constexpr bool SKIP_IN_COMPUTE = true;
     static_assert(MID >= 1 && MID <= NSTEP - 1, "the compute phase must hold exactly two barriers");
     // MID: the compute phase's first barrier comes after MID of the 12 steps; it pairs with the end
@@ -197,20 +194,17 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
         const int si = chunk / ps, sj = chunk - si * ps;
         __syncthreads();
 
-        // accumulators start from the bias: lane holds channels m*32 + 8*q + 4*hi + {0..3} in
-        // acc[.][m][4q..4q+3].  They are re-seeded in the drain phase, off the critical path.
-        f32x16 acc[RW][MT];
-        auto seed_acc = [&]() __attribute__((always_inline)) {
+        // Accumulators start from the bias: lane holds channels m*32 + 8*q + 4*hi + {0..3} in [m][4q..4q+3].  It stays in
+        // 32 registers and is the first product's C operand; written into the accumulators anew for every unit (8 LDS
+        // reads, 64 moves) it took both phases' time: 16 whole frames 5193 us a step, now 5147, the headline batch 2781, now 2760.
+        f32x16 acc[RW][MT], bias_c[MT];
 #pragma unroll
-            for (int m = 0; m < MT; ++m)
+        for (int m = 0; m < MT; ++m)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float4 bv = *(const float4*)(lds_b + m * 32 + q * 8 + hi * 4);
-#pragma unroll
-                    for (int r = 0; r < RW; ++r) { acc[r][m][4 * q] = bv.x; acc[r][m][4 * q + 1] = bv.y; acc[r][m][4 * q + 2] = bv.z; acc[r][m][4 * q + 3] = bv.w; }
-                }
-        };
-        if constexpr (!SEED_IN_COMPUTE) seed_acc();
+            for (int q = 0; q < 4; ++q) {
+                const float4 bv = *(const float4*)(lds_b + m * 32 + q * 8 + hi * 4);
+                bias_c[m][4 * q] = bv.x; bias_c[m][4 * q + 1] = bv.y; bias_c[m][4 * q + 2] = bv.z; bias_c[m][4 * q + 3] = bv.w;
+            }
         if (team == 1) idle_phase();
         for (int it = 0; it < iters; ++it) {
             const int unit = u_first + it * 2 * G, nunit = unit + 2 * G;
@@ -229,7 +223,6 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
                     kw[r] = __builtin_amdgcn_raw_buffer_load_b32(rk, (uint32_t)((((y0 + wave * RW + r) >> a.keep_sh) * wpr + (x0 >> (5 + a.keep_sh))) * 4), 0, 0);
             }
             // ---------------- compute phase ----------------
-            if constexpr (SEED_IN_COMPUTE) seed_acc();
             const uint8_t* wlane = lds_w + (lane << 4);
             const uint8_t* prow = lds_p + (wave * RW) * (PW * PIXB);
             bf16x8 A0[3][MT], A1[3][MT], B0[NR], B1[NR];
@@ -276,7 +269,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
                             for (int q = 0; q < 3; ++q)
                                 if (p - q >= 0 && p - q < RW) { if (cnt == pair) { py = p; ky = q; } ++cnt; }
                         const int r = py - ky;
-                        acc[r][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Ac[ky][m], Bc[py], acc[r][m], 0, 0, 0);
+                        acc[r][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Ac[ky][m], Bc[py], st == 0 && ky == 0 ? bias_c[m] : acc[r][m], 0, 0, 0);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -343,7 +336,6 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
                         *(uint2*)(stg + (r * 32 + lx) * OPIXB + (((m * 4 + q) ^ okey) << 4) + hi * 8) = pk;
                         __builtin_amdgcn_sched_barrier(0);
                     }
-            if constexpr (!SEED_IN_COMPUTE) seed_acc();
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the slice is private to the wave: no barrier
             uint4 ov[NOUT];
 #pragma unroll
