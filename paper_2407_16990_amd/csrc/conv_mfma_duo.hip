@@ -85,8 +85,6 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
     const bool deal = a.n_chunks > 1 && gridDim.x % (8 * a.n_chunks) == 0;
     const int G = deal ? gridDim.x / a.n_chunks : gridDim.x;                  // tile lanes
     const int xcd = blockIdx.x % 8, local = blockIdx.x / 8;
-    const int wg = deal ? xcd * (G / 8) + local / a.n_chunks
-                        : ((G % 8 == 0) ? xcd * (G / 8) + local : (int)blockIdx.x);
     const int chunk_begin = deal ? local % a.n_chunks : 0, chunk_end = deal ? chunk_begin + 1 : a.n_chunks;
     // The first chunk's weights depend on nothing that is read from memory: they are on their way to LDS before the
     // image count is known and the first patch can be asked for.  (Behind it, through registers, three pieces at a
@@ -100,6 +98,10 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
     const int tiles_img = tiles_x * tiles_y;
     // half tiles; with a list, its entries are half tiles packed as RH_CELL_ENTRY(image, row of 8, column of 32)
     const int n_units = LIST ? (int)n_found : 2 * n_img * tiles_img;
+    // Few units: one after the other to all XCDs.  In runs the XCDs work, in step, at addresses a power of two apart, on the
+    // same memory channels (EDSR x4 on 128 x 128 bins, us, runs / this: 3 bins 395 / 343, 6: 647 / 475, 8: 529 / 509; 16: 767 / 803).
+    const int wg = deal ? xcd * (G / 8) + local / a.n_chunks
+                        : ((G % 8 == 0 && n_units > 2 * G) ? xcd * (G / 8) + local : (int)blockIdx.x);
     auto units_from = [&](int first) { return n_units > first ? (n_units - first + 2 * G - 1) / (2 * G) : 0; };
     const int u_first = wg + team * G;                         // this team's units: u_first, u_first + 2G, ...
     const int iters0 = units_from(wg), iters1 = units_from(wg + G);           // team 1 has as many as team 0 or one fewer
