@@ -16,7 +16,8 @@
 template <int C>
 __global__ __launch_bounds__(256) void k_head_mfma(const uint8_t* __restrict__ in, const uint4* __restrict__ wp /*[3][MT][64]*/,
                                                    const float* __restrict__ bias, __bf16* __restrict__ out, int N, int H,
-                                                   int W, int relu, const uint32_t* __restrict__ n_valid)
+                                                   int W, int relu, const uint32_t* __restrict__ n_valid,
+                                                   uint32_t* __restrict__ clear, uint32_t n_clear)
 {
     constexpr int MT = C / 32, PH = HEAD_TH + 2, PWB = 34 * 3, OPIXB = C * 2, NCHO = OPIXB / 16;
     constexpr int PPJ = 64 / NCHO, NOUT = 2 * 32 / PPJ;                  // pixels per store instruction, stores per wave
@@ -27,6 +28,8 @@ __global__ __launch_bounds__(256) void k_head_mfma(const uint8_t* __restrict__ i
     const int tid = threadIdx.x, lane = tid & 63, lx = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);          // uniform over the wave: keeps row indices scalar
 
+    // words that the launch behind this one wants to find at zero (at most 256 per tile)
+    if (blockIdx.x * 256u + tid < n_clear) clear[blockIdx.x * 256u + tid] = 0;
     const int n_img = n_valid ? min((int)*n_valid, N) : N;
     const int tiles_x = (W + 31) / 32, tiles_y = (H + HEAD_TH - 1) / HEAD_TH, tiles_img = tiles_x * tiles_y;
     const int n_tiles = n_img * tiles_img;
@@ -119,20 +122,20 @@ __global__ __launch_bounds__(256) void k_head_mfma(const uint8_t* __restrict__ i
 
 template <int C>
 static hipError_t launch_head(hipStream_t stream, const uint8_t* in, const uint4* wp, const float* bias, __bf16* out, int N,
-                              int H, int W, int relu, const uint32_t* n_valid)
+                              int H, int W, int relu, const uint32_t* n_valid, uint32_t* clear, uint32_t n_clear)
 {
     const long long tiles = (long long)N * ((H + HEAD_TH - 1) / HEAD_TH) * ((W + 31) / 32);
     const long long grid = (tiles + 8 * HEAD_RUN - 1) / (8 * HEAD_RUN) * (8 * HEAD_RUN);
-    if (grid > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_head_mfma<C>, dim3((unsigned)grid), dim3(256), 0, stream, in, wp, bias, out, N, H, W, relu, n_valid);
+    if (grid > 0x7FFFFFFFLL || n_clear > 256 * tiles) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_head_mfma<C>, dim3((unsigned)grid), dim3(256), 0, stream, in, wp, bias, out, N, H, W, relu, n_valid, clear, n_clear);
     return hipGetLastError();
 }
 
 // wp: [ky 3][m C/32][64 lanes][8] bf16 with cout = m*32 + lane%32 and k = 8*(lane/32) + e = kx*3 + c (k >= 9: zero)
 hipError_t rh_launch_head_mfma(hipStream_t stream, int C, const uint8_t* in, const uint4* wp, const float* bias, __bf16* out,
-                               int N, int H, int W, int relu, const uint32_t* n_valid)
+                               int N, int H, int W, int relu, const uint32_t* n_valid, uint32_t* clear, uint32_t n_clear)
 {
-    if (C == 64) return launch_head<64>(stream, in, wp, bias, out, N, H, W, relu, n_valid);
-    if (C == 32) return launch_head<32>(stream, in, wp, bias, out, N, H, W, relu, n_valid);
+    if (C == 64) return launch_head<64>(stream, in, wp, bias, out, N, H, W, relu, n_valid, clear, n_clear);
+    if (C == 32) return launch_head<32>(stream, in, wp, bias, out, N, H, W, relu, n_valid, clear, n_clear);
     return hipErrorInvalidValue;
 }

@@ -14,6 +14,7 @@
 // Activations are bf16 channels-last [N][H][W][C]; the network's last conv writes fp32.
 // Pixel shuffle is folded into the output-channel order of the upsampling convs: chunk q of
 // the permuted weights produces all C channels of sub-pixel q, i.e. one whole output pixel.
+#include <algorithm>
 #include <stdlib.h>
 #include <string.h>
 
@@ -509,13 +510,23 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // needs more than a plain one of as many pixels.  A word per 16 pixels holds it: bins are at least 16 wide,
     // so their ceil(S / 32) words per row are at most S / 16.
     const size_t mask_words = C == 64 && !fold ? ((size_t)N * H * W + 15) / 16 : 0;
-    need = (need + 1) & ~(size_t)1;
-    rh_status st = rh_ensure_workspace(ctx, need * 2 + mask_words * 4);
+    // The body of a 64-channel net in one launch (conv_body.hip) where a launch per layer would be short: us for EDSR x4 on
+    // 128 x 128 bins, per layer / in one, 3 bins 343 / 310, 8: 509 / 420, 16: 750 / 684, 24: 995 / 937, 32: 1320 / 1287, 40: 1544 / 1515,
+    // 48: 1811 / 1825, 76: 3039 / 3172.  Large batches run at the chip's power limit and lose what is read past the L2.
+    // The line is at 48 bins' units, or 12 a workgroup; how many of the N images are valid the host does not know.
+    const std::vector<rh_layer>& L = ctx->layers;
+    const int body_layers = d.topology == RH_NET_PLAIN ? d.n_blocks - 2 : 2 * d.n_blocks + (d.topology == RH_NET_EDSR);
+    const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32);
+    const bool one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && !ctx->nd_places && cells <= 12 * (size_t)ctx->n_cu;
+    // its counters, in room that is sized like the mask's: bins have at most one half tile per 128 pixels
+    const size_t sync_words = C == 64 ? BODY_ROLL_WORDS + 4 * std::max(cells, ((size_t)N * H * W + 127) / 128) : 0;
+    need = (need + 63) & ~(size_t)63;
+    rh_status st = rh_ensure_workspace(ctx, need * 2 + (sync_words + mask_words) * 4);
     if (st != RH_OK) return st;
-    uint32_t* keep = masked ? (uint32_t*)((uint8_t*)ctx->act + need * 2) : nullptr;
+    uint32_t* sync = (uint32_t*)((uint8_t*)ctx->act + need * 2);
+    uint32_t* keep = masked ? sync + sync_words : nullptr;
     __bf16* a = (__bf16*)ctx->act; __bf16* t = a + lr; __bf16* h = t + lr; __bf16* u1 = h + lr; __bf16* u2 = u1 + up1;
     ctx->conv_parity = 0;                  // the head conv walks forward, the first conv after it backward
-    const std::vector<rh_layer>& L = ctx->layers;
     size_t li = 0;
     const int head_relu = d.topology == RH_NET_PLAIN;
     {
@@ -524,7 +535,7 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
         rh_prof_scope ps(ctx, RH_PROF_HEAD, 1u + (masked ? 2u : 0u) + (ctx->bz_boxes ? 1u : 0u) + (ctx->mk_boxes ? 3u : 0u) + (ctx->nd_places ? 2u : 0u));
         if (masked) { st = rh_outside_mask(ctx, keep, N, n_valid); if (st != RH_OK) return st; }
         RH_HIP(ctx, rh_launch_head_mfma(ctx->stream, C, in, (const uint4*)((const uint8_t*)ctx->wpack + l0.wp_off),
-                                        ctx->bpack + l0.bp_off, h, N, H, W, head_relu, n_valid));
+                                        ctx->bpack + l0.bp_off, h, N, H, W, head_relu, n_valid, sync, one_launch ? (uint32_t)(BODY_ROLL_WORDS + 4 * cells) : 0u));
         // box-masked mode: from here to the end of the body the three tensors are zero outside the live cells
         if (ctx->mk_boxes) { st = rh_launch_cell_lists(ctx, N, n_valid, h, a, t); if (st != RH_OK) return st; }
         if (ctx->nd_places) { ctx->nd_conv = 0; st = rh_launch_need_lists(ctx, N, n_valid); if (st != RH_OK) return st; }
@@ -542,15 +553,25 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // 32 channels: two convs per launch (they are bound by memory, and the tensor between them stays on
     // the chip); exact-border mode clears part of that tensor and runs them one by one
     const bool pairs = C == 32 && !ctx->bz_boxes;
+    const __bf16* body_out = nullptr;
+    if (one_launch) {
+        body_args b;
+        b.h = h; b.a = a; b.t = t; b.wp = (const uint4*)((const uint8_t*)ctx->wpack + L[li].wp_off); b.bias = ctx->bpack + L[li].bp_off;
+        b.n_valid = n_valid; b.keep = keep; b.N = N; b.H = H; b.W = W; b.layers = body_layers; b.topology = d.topology;
+        b.roll = sync; b.done = sync + BODY_ROLL_WORDS;
+        RH_HIP(ctx, rh_launch_conv_body(ctx->stream, ctx->device, ctx->n_cu, b));
+        ++n_conv; li += body_layers;
+        body_out = d.topology == RH_NET_EDSR ? t : d.topology == RH_NET_RES ? a : (body_layers & 1) ? a : t;
+    }
     if (d.topology == RH_NET_PLAIN) {
-        const __bf16* x = h;
-        int l = 0;
+        const __bf16* x = one_launch ? body_out : h;
+        int l = one_launch ? body_layers : 0;
         for (; pairs && l + 1 < d.n_blocks - 2; l += 2, li += 2) { __bf16* o = (x == a) ? t : a; BLOCK32(L[li], L[li + 1], x, o, N, H, W, false, n_valid); x = o; }
         for (; l < d.n_blocks - 2; ++l) { __bf16* o = (x == a) ? t : a; CONV(L[li++], x, o, nullptr, N, H, W, 1, false, 1); ZERO(o, 1); x = o; }
         LAST_CONV(L[li++], x, out, nullptr, N, H, W, 0, true, s, n_valid);
     } else {
-        const __bf16* x = h;
-        for (int b = 0; b < d.n_blocks; ++b) {
+        const __bf16* x = one_launch ? body_out : h;
+        for (int b = 0; b < d.n_blocks && !one_launch; ++b) {
             if (pairs) { __bf16* o = (x == a) ? t : a; BLOCK32(L[li], L[li + 1], x, o, N, H, W, true, n_valid); li += 2; x = o; continue; }
             CONV(L[li++], x, t, nullptr, N, H, W, 1, false, 1); ZERO(t, 1);
             CONV(L[li++], t, a, x, N, H, W, 0, false, 1); ZERO(a, 1);      // x + conv(t)
@@ -559,8 +580,10 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
         if (d.topology == RH_NET_RES) {
             LAST_CONV(L[li++], x, out, nullptr, N, H, W, 0, true, s, n_valid);
         } else {
-            if (x == t) { t = a; a = (__bf16*)x; }
-            CONV(L[li++], x, t, h, N, H, W, 0, false, 1); ZERO(t, 1);       // body end + long skip
+            if (!one_launch) {
+                if (x == t) { t = a; a = (__bf16*)x; }
+                CONV(L[li++], x, t, h, N, H, W, 0, false, 1); ZERO(t, 1);   // body end + long skip
+            }
             if (fold) {
                 rh_prof_end(ctx, n_conv);
                 rh_prof_scope ps_(ctx, RH_PROF_CONV_LAST, ctx->nd_places && ctx->cfg.halo >= 1 ? 1 : 2);      // rh_launch_fold

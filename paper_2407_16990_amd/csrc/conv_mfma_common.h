@@ -84,6 +84,21 @@ __device__ __forceinline__ void lds_dma_wait() { __builtin_amdgcn_s_waitcnt(0x0F
 // 33 body convs on 3 bins of 128 x 128 484 -> 461 us per step, on 76 bins 2923 -> 2870, on 15 of 160 x 160 1197 -> 1164.
 #define ST_THROUGH 16
 
+// all 64-channel convs between the first one and the tail in one launch (conv_body.hip)
+struct body_args {
+    __bf16 *h, *a, *t;       // [N][H][W][64]: the first conv's output, and what the blocks are computed in
+    const uint4* wp;         // the layers' packed weights, one behind the other
+    const float* bias;       // 64 a layer
+    const uint32_t* n_valid;
+    const uint32_t* keep;    // as in conv_args, or null
+    int N, H, W, layers, topology;
+    uint32_t* roll;          // workgroups that take part; zero at the launch, as
+    uint32_t* done;          // [half tiles of 8 x 32][4]: layers that each wave of its team has stored
+    uint32_t img_magic, row_magic;       // division by the half tiles of an image and of its rows (set by the launcher)
+};
+// words for `roll` and `done` together; `done` begins BODY_ROLL_WORDS behind `roll`
+#define BODY_ROLL_WORDS 32
+hipError_t rh_launch_conv_body(hipStream_t stream, int device, int n_cu, body_args a);
 // two-team kernel for the 64-channel bf16-output convs (conv_mfma_duo.hip)
 hipError_t rh_launch_conv_duo(hipStream_t stream, int device, const conv_args& a, int grid, bool skip, bool relu);
 // two 3x3 convs of a 32-channel net in one launch (conv_block32.hip); res: a residual block, else two ReLU layers.  in != out
@@ -93,7 +108,7 @@ hipError_t rh_launch_block32(rh_ctx* ctx, const rh_layer& L1, const rh_layer& L2
 hipError_t rh_launch_conv_tail3(hipStream_t stream, int device, const conv_args& a, int cin);
 // first conv 3 -> C on the matrix cores (conv_head.hip)
 hipError_t rh_launch_head_mfma(hipStream_t stream, int C, const uint8_t* in, const uint4* wp, const float* bias, __bf16* out,
-                               int N, int H, int W, int relu, const uint32_t* n_valid);
+                               int N, int H, int W, int relu, const uint32_t* n_valid, uint32_t* clear, uint32_t n_clear);
 // upsampler + last conv of an EDSR-shaped net as one composed 5 x 5 conv (conv_fold.hip): t -> raw network output
 // tile_list / n_list (dev, or null for all tiles): the 8 x 32 tiles to compute, as RH_CELL_ENTRY(n, ty, tx)
 rh_status rh_launch_fold(rh_ctx* ctx, const __bf16* t, float* out, int N, int H, int W, const uint32_t* n_valid, int rev,

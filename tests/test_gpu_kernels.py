@@ -283,3 +283,54 @@ def test_recorded_step_replays(F, net):
         assert torch.equal(po.counts, want[k][0]) and torch.equal(hr, want[k][1]), k
     assert int(want[0][0][0]) > 0 and not torch.equal(want[0][1], want[1][1])
     rh.close()
+
+
+# The body of a 64-channel net in one launch (up to 12 half tiles per compute unit) against the launch per layer that larger
+# batches take: the same images in a batch of that size with a device-side count.  One unit in all, fewer units than
+# workgroups, one and two and some rounds a layer, ragged rows and columns, an odd number of layers, a first layer alone.
+@pytest.mark.parametrize("net", [wl.Net("edsr", 64, 1, 2, 0.02), wl.Net("edsr", 64, 3, 4, 0.02), wl.Net("res", 64, 1, 2, 0.02), wl.Net("res", 64, 4, 3, 0.02),
+                                 wl.Net("plain", 64, 4, 2, 0.1), wl.Net("plain", 64, 7, 2, 0.1)])
+@pytest.mark.parametrize("n,H,W", [(1, 3, 5), (1, 8, 32), (2, 9, 33), (3, 50, 100), (7, 64, 128), (31, 57, 33), (40, 60, 140), (3, 200, 1000)])
+def test_one_launch_body_is_a_launch_per_layer_bit_for_bit(net, n, H, W):
+    rh = RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=32, max_bins=4, net=net, weights=wl.make_weights(net, 16, "bf16"),
+            precision="bf16")
+    lim = 12 * torch.cuda.get_device_properties(0).multi_processor_count
+    cells = -(-H // 8) * -(-W // 32)
+    assert n * cells <= lim
+    big = lim // cells + 1
+    x = torch.randint(0, 256, (n, H, W, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(n))
+    xb = torch.zeros((big, H, W, 3), dtype=torch.uint8, device="cuda")
+    xb[:n] = x
+    count = torch.tensor([n], dtype=torch.int32, device="cuda")
+    want = rh.enhance(xb, n_valid=count)[:n].clone()
+    for _ in range(3):                                       # again with the counters of the call before
+        assert torch.equal(rh.enhance(x), want)
+    few = max(1, n // 2)
+    got = rh.enhance(x, n_valid=torch.tensor([few], dtype=torch.int32, device="cuda"))
+    assert torch.equal(got[:few], want[:few])
+    assert torch.equal(rh.enhance(x, n_valid=torch.zeros(1, dtype=torch.int32, device="cuda"), out=got.fill_(3.0)), torch.full_like(got, 3.0))
+    rh.close()
+
+
+def test_one_launch_bodies_share_the_gpu():
+    # two contexts on two streams, each with units for every compute unit: whichever workgroups start, all units are done
+    net = wl.Net("edsr", 64, 4, 2, 0.02)
+    rhs, xs, wants, streams = [], [], [], [torch.cuda.Stream(), torch.cuda.Stream()]
+    for k in range(2):
+        rhs.append(RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=64, max_bins=64, net=net, weights=wl.make_weights(net, 17 + k, "bf16"),
+                      precision="bf16", stream=streams[k]))
+        xs.append(torch.randint(0, 256, (40 + 20 * k, 64, 64, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(k)))
+    outs = [[torch.zeros((len(x), 128, 128, 3), device="cuda") for _ in range(12)] for x in xs]
+    torch.cuda.synchronize()
+    for k in range(2):                                       # one alone
+        wants.append(torch.zeros_like(outs[k][0]))
+        torch.cuda.synchronize()
+        rhs[k].enhance(xs[k], out=wants[k])
+        torch.cuda.synchronize()
+    for i in range(12):
+        for k in range(2):
+            rhs[k].enhance(xs[k], out=outs[k][i])
+    torch.cuda.synchronize()
+    for k in range(2):
+        assert all(torch.equal(o, wants[k]) for o in outs[k])
+        rhs[k].close()
