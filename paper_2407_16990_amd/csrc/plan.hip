@@ -183,15 +183,18 @@ __global__ __launch_bounds__(256) void k_plan_rank(const rh_rawbox* __restrict__
 // box_pos[i] = {bin | turned<<16, bx | by<<16}.
 // rotate: a rectangle that cannot take the box upright may take it turned (RotatePacking).
 // The loop over the boxes is serial by definition, and it runs in ONE wave, which issues an instruction
-// every 4-5 cycles: its cost is the number of instructions of one step.  So
+// every 4-6 cycles: its cost is the number of instructions of one step.  So
 //   - the free list lives in registers, entry j in lane j % 64 of chunk j / 64, up to FREE_CHUNKS * 64 - 2 entries
-//     (181 at most for 128 frames of 480 x 272); only the chunks in use are looked at;
+//     (159 at most for 128 frames of 480 x 272); only the chunks in use are looked at;
 //   - a rectangle's sides carry a guard bit each, so that one subtraction tests both (and is the remainder);
-//   - what a step does not need is branched over, all branches are uniform: a box in a new bin touches no
-//     entry behind it, and one that leaves no usable strip (three boxes in four there) ends at once;
-//   - the entries behind a change are shifted by one lane with a whole-wave DPP shift.
-// Measured: 83 boxes of 16 frames of 480 x 272: 30 us instead of 40 in the launch's first fit; 752 boxes of 128 frames: 253 us
-// instead of about 370; 552 boxes of isolated macroblocks: 230-270 us instead of about 300.
+//   - the lanes only test their entries: the chosen one is read from its lane, what is left of it is worked out on
+//     the scalar unit, with a branch for each outcome, and written back to its lane (v_writelane);
+//   - an entry of which nothing is left stays as one without area, which nothing fits; the list is packed anew when it has
+//     reached the last lane.  Entries move (a whole-wave DPP shift) only where a used one leaves two in front of others;
+//   - a box that fills a bin (three in four of large batches) takes no step.
+// Measured, before (every box a step of 170 instructions on the vector unit, entries moved after most of them) / now: the launch of the first fit
+// of 745 boxes of 128 frames of 480 x 272 243 / 169 us, the one-launch plan of 139 boxes of 8 frames of 640 x 368 71 / 53 us, of 551
+// isolated macroblocks 249-415 / 229-415 us.
 // A list that outgrows the registers is written to LDS and stays there: the 64 lanes then test 64
 // rectangles at a time; the hardware executes the LDS traffic of a single wave in program order, and
 // wave_sync() after every step in which lanes write what other lanes read next keeps the compiler
@@ -207,6 +210,9 @@ __device__ __forceinline__ uint32_t lane_from_above(uint32_t v)      // lane l g
 {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
 }
+
+// v_writelane_b32, for which there is no builtin: `old` with lane l's value replaced
+__device__ int write_lane(int value, int l, int old) __asm("llvm.amdgcn.writelane.i32");
 
 template <bool ROTATE, typename SizeOf>
 __device__ __forceinline__ void place_boxes(uint32_t n, SizeOf size_of, uint32_t* fxy, uint32_t* fwh, uint32_t* fbin,
@@ -242,149 +248,185 @@ __device__ __forceinline__ void place_boxes(uint32_t n, SizeOf size_of, uint32_t
         ndv |= max(w, h) < minside ? 0x8000u : 0u;
     };
     auto lane_of = [](uint32_t v, int l) __attribute__((always_inline)) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
-    auto with_lane = [&](uint32_t v, int l, uint32_t x) __attribute__((always_inline)) { return lane == l ? x : v; };
-#define PUT1(c, j, xy, wh) if (((j) >> 6) == c) { const bool me = lane == ((j) & 63); rxy##c = me ? (xy) : rxy##c; rwh##c = me ? (wh) : rwh##c; rbn##c = me ? (uint32_t)fb : rbn##c; }
-#define PUT(j, xy, wh) do { PUT1(0, j, xy, wh) PUT1(1, j, xy, wh) PUT1(2, j, xy, wh) PUT1(3, j, xy, wh) } while (0)
-    // ---- one chunk: straight-line code, every lane works out what would be left of its own rectangle ----
-    // The entry behind the list's last is the next bin's whole area (while there is one), so a new bin is an
-    // ordinary first fit; it is written anew after every step.
-    if (max_bins > 0) rwh0 = lane == 0 ? FREE_GUARD | (uint32_t)S | (uint32_t)S << 16 : rwh0;
-    for (; i < n && nfree < 61; ++i) {
-        if ((i & 63u) == 0) next_sizes();
-        const uint32_t nd = lane_of(ndv, (int)(i & 63u)), need = nd & ~0x8000u;
-        uint32_t left = rwh0 - need, bw = need & 0xFFFF, bh = need >> 16, turned = 0;
-        bool fit = (left & FREE_GUARD) == FREE_GUARD;
-        if constexpr (ROTATE) {                              // upright whenever that fits
-            const uint32_t leftt = rwh0 - (need >> 16 | need << 16), bw0 = bw;
-            left = fit ? left : leftt; bw = fit ? bw : bh; bh = fit ? bh : bw0; turned = fit ? 0u : 0x10000u;
-            fit = fit | ((leftt & FREE_GUARD) == FREE_GUARD);
+    auto with_lane = [](uint32_t v, int l, uint32_t x) __attribute__((always_inline)) { return (uint32_t)write_lane((int)x, l, (int)v); };
+    // A box that fills a bin fits no rectangle that another box has left (one side of such a rectangle is at most
+    // S - minside), so it opens a bin and leaves nothing.  Such boxes take no step: only the other ones of a group of
+    // 64 do (`todo`), and where all of them are placed, the group's full bins are
+    // numbered at once.  Where bins or registers might run out within the group, every box takes its step.
+    unsigned long long todo = 0, alone = 0, opened = 0;      // alone: the group's boxes that take none; opened: those of the others that opened a bin
+    uint32_t g0 = 0;                                         // the group's first box
+    int nb0 = 0;                                             // bins before the group; nbins: those and what `opened` says
+    int dead = 0;                                            // entries without area among the nfree
+    bool grouped = false, more = true;
+    auto next_group = [&]() __attribute__((always_inline)) -> bool {
+        if (grouped) {
+            const unsigned long long bins = alone | opened;
+            const int b = nb0 + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bins >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bins, 0u));
+            const bool mine = alone >> lane & 1ull;
+            pos0 = mine ? (uint32_t)b : pos0; pos1 = mine ? 0u : pos1;
+            nbins += __builtin_popcountll(alone);
+            i = min(g0 + 64u, n);
         }
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(fit);
-        const int at = __builtin_ctzll(m | 1ull << 63);      // lane 63 is never in use here
-        const int old = min(nfree - at, 1);                  // 0: a new bin  (integers: the compiler keeps uniform truth values in vector registers)
-        if (m == 0 || nfree + 2 - old > free_cap) { overflow = true; break; }
-        if (((uint32_t)old | (~nd & 0x8000u)) == 0) {        // most boxes of large batches: a bin of its own, nothing left
-            pos0 = with_lane(pos0, (int)(i & 63u), (uint32_t)nbins); pos1 = with_lane(pos1, (int)(i & 63u), 0u);
-            ++nbins;
-            rbn0 = with_lane(rbn0, at, (uint32_t)nbins);
-            if (nbins >= max_bins) rwh0 = with_lane(rwh0, at, FREE_GUARD);
-            continue;
-        }
-        const uint32_t rw = left & 0x7FFF, bhei = left >> 16 & 0x7FFF, fw = rwh0 & 0x7FFF, fh = rwh0 >> 16 & 0x7FFF;
-        const bool right_full = __umul24(rw, fh) >= __umul24(fw, bhei);
+        if (i >= n) return false;
+        grouped = true;
+        g0 = i;
+        next_sizes();
+        const unsigned long long all = n - i >= 64u ? ~0ull : (1ull << (n - i)) - 1ull;
+        alone = __builtin_amdgcn_ballot_w64((ndv & 0x8000u) != 0) & all;
+        if (nbins + __builtin_popcountll(all) > max_bins || nfree + 2 * __builtin_popcountll(all & ~alone) > REG_MAX) alone = 0;
+        todo = all & ~alone; opened = 0; nb0 = nbins;
+        return true;
+    };
+    // What is left of a rectangle (ewh, with guard bits, at exy) below and beside a box (need) in its corner: the larger of (right
+    // strip, full height) and (bottom strip, full width), plus what is left of the other.  first, last: the survivors in
+    // the list's order (the smaller one first), as many as `ni` says.  Conditions are integers: the compiler keeps uniform
+    // truth values in vector registers and branches around them.
+    uint32_t first_xy, first_wh, last_xy, last_wh, ni;
+    auto less = [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return (a - b) >> 31; };       // both below 2^31
+    auto rest = [&](uint32_t exy, uint32_t ewh, uint32_t need) __attribute__((always_inline)) {
+        const uint32_t rem = ewh - need, rw = rem & 0x7FFF, bhei = rem >> 16 & 0x7FFF;
+        const uint32_t fw = ewh & 0x7FFF, fh = ewh >> 16 & 0x7FFF, bw = need & 0xFFFF, bh = need >> 16;
+        const bool right_full = rw * fh >= fw * bhei;
         const uint32_t rh = right_full ? fh : bh, bwid = right_full ? bw : fw;
-        const bool keep_r = min(rw, rh) >= (uint32_t)minside, keep_b = min(bwid, bhei) >= (uint32_t)minside;
-        const uint32_t Rxy = rxy0 + bw, Rwh = (rh << 16 | rw) | FREE_GUARD, Bxy = (bh << 16) + rxy0, Bwh = (bhei << 16 | bwid) | FREE_GUARD;
-        const bool smaller = __umul24(bwid, bhei) < __umul24(rw, rh);
-        const bool b_first = keep_b & (!keep_r | smaller);   // both kept: the smaller one first
-        const uint32_t e0xy = b_first ? Bxy : Rxy, e0wh = b_first ? Bwh : Rwh, e1xy = b_first ? Rxy : Bxy, e1wh = b_first ? Rwh : Bwh;
-        // survivors of the chosen rectangle
-        const int ni = (int)(__builtin_amdgcn_ballot_w64(keep_r) >> at & 1ull) + (int)(__builtin_amdgcn_ballot_w64(keep_b) >> at & 1ull);
-        const bool me = lane == at;
-        // position: the chosen lane's corner and bin (the orientation is packed above the bin)
-        const uint32_t px = lane_of(rxy0, at), pb = lane_of(ROTATE ? rbn0 | turned : rbn0, at);
-        pos0 = with_lane(pos0, (int)(i & 63u), pb); pos1 = with_lane(pos1, (int)(i & 63u), px);
-        // a second survivor enters the shift at the chosen lane
-        const uint32_t vxy = me ? e1xy : rxy0, vwh = me ? e1wh : rwh0;
-        const uint32_t dxy = lane_from_below(vxy), dwh = lane_from_below(vwh), dbn = lane_from_below(rbn0);
-        const uint32_t uxy = lane_from_above(rxy0), uwh = lane_from_above(rwh0), ubn = lane_from_above(rbn0);
-        // as lane numbers, so that no truth value of the wave is involved: lanes from `lo2` on take the lane below, from `lo0` on the lane above
-        const int lo2 = ni == 2 ? at : 64, lo0 = ni == 0 ? at - 1 : 64, at1 = ni == 0 ? 64 : at;
-        const bool down = lane > lo2, up = lane > lo0, one = lane == at1;
-        rxy0 = down ? dxy : up ? uxy : one ? e0xy : rxy0;
-        rwh0 = down ? dwh : up ? uwh : one ? e0wh : rwh0;
-        rbn0 = down ? dbn : up ? ubn : rbn0;
-        nbins += 1 - old;
-        nfree += ni - old;
-        const bool tail = lane == nfree;
-        const uint32_t next_bin = nbins < max_bins ? FREE_GUARD | (uint32_t)S | (uint32_t)S << 16 : FREE_GUARD;
-        rxy0 = tail ? 0u : rxy0; rbn0 = tail ? (uint32_t)nbins : rbn0; rwh0 = tail ? next_bin : rwh0;
+        const uint32_t no_r = less(min(rw, rh), (uint32_t)minside), no_b = less(min(bwid, bhei), (uint32_t)minside);
+        const uint32_t b_first = (1u - no_b) & (no_r | less(bwid * bhei, rw * rh));
+        const uint32_t Rxy = exy + bw, Rwh = (rw | rh << 16) | FREE_GUARD, Bxy = exy + (need & 0xFFFF0000u), Bwh = (bwid | bhei << 16) | FREE_GUARD;
+        first_xy = b_first ? Bxy : Rxy; first_wh = b_first ? Bwh : Rwh; last_xy = b_first ? Rxy : Bxy; last_wh = b_first ? Rwh : Bwh;
+        ni = 2u - no_r - no_b;
+    };
+    // Steps of a list of one chunk.  The entry behind the list's last is the next bin's whole area, so a new bin is an
+    // ordinary first fit; its bin number is not kept.  The list's capacity needs no look: its rectangles are
+    // disjoint with sides of at least minside, of which a bin holds at most the (S / minside)^2 that free_cap counts.
+    const uint32_t whole = FREE_GUARD | (uint32_t)S | (uint32_t)S << 16;
+    for (;;) {
+        if (todo == 0) {
+            more = next_group();
+            if (!more) break;
+        }
+        if (nfree >= 61 && dead >= 16) {                     // the last lanes are in use: without the entries without area
+            const unsigned long long live = __builtin_amdgcn_ballot_w64(lane < nfree && rwh0 != FREE_GUARD);
+            const int to = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u));
+            if (live >> lane & 1ull) { fxy[to] = rxy0; fwh[to] = rwh0; fbin[to] = rbn0; }
+            wave_sync();
+            nfree -= dead; dead = 0;
+            rwh0 = FREE_GUARD;
+            if (lane < nfree) { rxy0 = fxy[lane]; rwh0 = fwh[lane]; rbn0 = fbin[lane]; }
+            wave_sync();
+        }
+        // as many steps as lanes and bins are there for in any case
+        int steps = min(min(__builtin_popcountll(todo), (62 - nfree) / 2), max_bins - nbins - __builtin_popcountll(alone));
+        if (steps <= 0 && todo != 0) break;
+        rwh0 = with_lane(rwh0, nfree, whole); rxy0 = with_lane(rxy0, nfree, 0u);
+        for (; steps > 0; --steps) {
+            const int k = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            uint32_t need = lane_of(ndv, k) & ~0x8000u;
+            bool fit = ((rwh0 - need) & FREE_GUARD) == FREE_GUARD;
+            const uint32_t needt = need >> 16 | need << 16;
+            if constexpr (ROTATE) fit = fit | (((rwh0 - needt) & FREE_GUARD) == FREE_GUARD);
+            const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(fit));
+            const uint32_t exy = lane_of(rxy0, at), ewh = lane_of(rwh0, at);
+            const int bin_now = nbins + __builtin_popcountll(alone & ((1ull << k) - 1ull));
+            const uint32_t eb = at == nfree ? (uint32_t)bin_now : lane_of(rbn0, at);
+            uint32_t turned = 0;
+            if constexpr (ROTATE) {                          // upright whenever that fits
+                const bool up = ((ewh - need) & FREE_GUARD) == FREE_GUARD;
+                need = up ? need : needt; turned = up ? 0u : 0x10000u;
+            }
+            pos0 = with_lane(pos0, k, eb | turned); pos1 = with_lane(pos1, k, exy);
+            rest(exy, ewh, need);
+            const uint32_t old = min((uint32_t)(nfree - at), 1u), fresh = 1u - old;      // fresh: what is left of a new bin goes to the list's end
+            nbins += (int)fresh; opened |= (unsigned long long)fresh << k;
+            if (ni == 2u) {
+                if (old) {                                   // the entries behind `at` move up by one
+                    const uint32_t dxy = lane_from_below(rxy0), dwh = lane_from_below(rwh0), dbn = lane_from_below(rbn0);
+                    const bool up = lane > at;
+                    rxy0 = up ? dxy : rxy0; rwh0 = up ? dwh : rwh0; rbn0 = up ? dbn : rbn0;
+                }
+                rxy0 = with_lane(rxy0, at + 1, last_xy); rwh0 = with_lane(rwh0, at + 1, last_wh); rbn0 = with_lane(rbn0, at + 1, eb);
+            }
+            rxy0 = with_lane(rxy0, at, first_xy); rwh0 = with_lane(rwh0, at, ni ? first_wh : FREE_GUARD); rbn0 = with_lane(rbn0, at, eb);
+            dead += (int)(old & less(ni, 1u));
+            nfree += (int)(ni - min(ni, old));
+            rxy0 = with_lane(rxy0, nfree, 0u); rwh0 = with_lane(rwh0, nfree, whole);
+        }
     }
     if (lane >= nfree) rwh0 = FREE_GUARD;                    // without the new bin's entry
     // ---- several chunks ----
-    for (; i < n && !overflow && nfree <= REG_MAX; ++i) {
-        if ((i & 63u) == 0) next_sizes();
-        const uint32_t nd = lane_of(ndv, (int)(i & 63u));
-        uint32_t need = nd & ~0x8000u;
+    while (more && !overflow && nfree <= REG_MAX) {
+        if (todo == 0) { more = next_group(); continue; }
+        const int k = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        uint32_t need = lane_of(ndv, k) & ~0x8000u;
         const uint32_t needt = need >> 16 | need << 16;
+#define FITS(c)                                                                                     \
+        bool fit##c = ((rwh##c - need) & FREE_GUARD) == FREE_GUARD;                                 \
+        if constexpr (ROTATE) fit##c = fit##c | (((rwh##c - needt) & FREE_GUARD) == FREE_GUARD);
+        FITS(0) FITS(1) FITS(2) FITS(3)
+#undef FITS
+#define PUT1(c, j, xy, wh) if (((j) >> 6) == c) { rxy##c = with_lane(rxy##c, (j) & 63, xy); rwh##c = with_lane(rwh##c, (j) & 63, wh); rbn##c = with_lane(rbn##c, (j) & 63, eb); }
+#define PUT(j, xy, wh) do { PUT1(0, j, xy, wh) else PUT1(1, j, xy, wh) else PUT1(2, j, xy, wh) else PUT1(3, j, xy, wh) } while (0)
+        if (__builtin_amdgcn_ballot_w64(fit0 | fit1 | fit2 | fit3) == 0) {      // a new bin: what is left of it goes to the list's end
+            const uint32_t eb = (uint32_t)nbins + (uint32_t)__builtin_popcountll(alone & ((1ull << k) - 1ull));
+            if ((int)eb >= max_bins) { overflow = true; i = g0 + k; break; }
+            ++nbins; opened |= 1ull << k;
+            pos0 = with_lane(pos0, k, eb); pos1 = with_lane(pos1, k, 0u);
+            rest(0u, whole, need);
+            if (ni >= 1u) { PUT(nfree, first_xy, first_wh); ++nfree; }
+            if (ni == 2u) { PUT(nfree, last_xy, last_wh); ++nfree; }
+            continue;
+        }
         int at = -1;
-        uint32_t exy = 0, ewh = FREE_GUARD | (uint32_t)S | (uint32_t)S << 16;
-        int fb = nbins;
+        uint32_t exy = 0, ewh = 0, eb = 0;
 #define FIRST(c)                                                                                    \
-        if (at < 0 && 64 * c < nfree) {                                                             \
-            bool fit = ((rwh##c - need) & FREE_GUARD) == FREE_GUARD;                                \
-            if (rotate) fit = fit || ((rwh##c - needt) & FREE_GUARD) == FREE_GUARD;                 \
-            const unsigned long long m = __builtin_amdgcn_ballot_w64(fit);                          \
+        if (at < 0) {                                                                               \
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(fit##c);                       \
             if (m) {                                                                                \
                 const int l = __builtin_ctzll(m);                                                   \
                 at = 64 * c + l;                                                                    \
-                exy = lane_of(rxy##c, l); ewh = lane_of(rwh##c, l); fb = (int)lane_of(rbn##c, l);   \
+                exy = lane_of(rxy##c, l); ewh = lane_of(rwh##c, l); eb = lane_of(rbn##c, l);        \
             }                                                                                       \
         }
         FIRST(0) FIRST(1) FIRST(2) FIRST(3)
 #undef FIRST
-        const bool fresh = at < 0;
-        if (fresh ? (nbins >= max_bins || nfree + 2 > free_cap) : nfree + 1 > free_cap) { overflow = true; break; }
-        if (fresh && (nd & 0x8000u)) {                       // a bin of its own, nothing left
-            pos0 = with_lane(pos0, (int)(i & 63u), (uint32_t)nbins); pos1 = with_lane(pos1, (int)(i & 63u), 0u);
-            ++nbins;
-            continue;
-        }
         uint32_t turned = 0;
-        if (rotate && ((ewh - need) & FREE_GUARD) != FREE_GUARD) { need = needt; turned = 0x10000u; }      // upright whenever that fits
-        if (fresh) { at = nfree; ++nbins; }                  // a new bin's area goes to the end of the list
-        pos0 = with_lane(pos0, (int)(i & 63u), (uint32_t)fb | turned);
-        pos1 = with_lane(pos1, (int)(i & 63u), exy);
-        // remainder: the larger of (right strip, full height) and (bottom strip, full width),
-        // plus what is left of the other
-        const uint32_t rem = (ewh - need) & ~FREE_GUARD;
-        const int rw = (int)(rem & 0xFFFF), bhei = (int)(rem >> 16);
-        int ni = 0;
-        if (max(rw, bhei) >= minside) {
-            const int fw = (int)(ewh & 0x7FFF), fh = (int)(ewh >> 16 & 0x7FFF), bw = (int)(need & 0xFFFF), bh = (int)(need >> 16);
-            const bool right_full = rw * fh >= fw * bhei;
-            const int rh = right_full ? fh : bh, bwid = right_full ? bw : fw;
-            const bool keep_r = min(rw, rh) >= minside, keep_b = min(bwid, bhei) >= minside;
-            const uint32_t Rxy = exy + (uint32_t)bw, Rwh = (uint32_t)rw | (uint32_t)rh << 16 | FREE_GUARD;
-            const uint32_t Bxy = exy + ((uint32_t)bh << 16), Bwh = (uint32_t)bwid | (uint32_t)bhei << 16 | FREE_GUARD;
-            const bool b_first = keep_b && (!keep_r || bwid * bhei < rw * rh);     // both kept: the smaller one first
-            ni = (keep_r ? 1 : 0) + (keep_b ? 1 : 0);
-            if (ni == 2) {
+        if constexpr (ROTATE) if (((ewh - need) & FREE_GUARD) != FREE_GUARD) { need = needt; turned = 0x10000u; }      // upright whenever that fits
+        pos0 = with_lane(pos0, k, eb | turned); pos1 = with_lane(pos1, k, exy);
+        rest(exy, ewh, need);
+        if (ni == 0) { ++dead; first_wh = FREE_GUARD; }      // an entry without area
+        if (ni == 2) {
 #define UP(c, below)                                                                                \
-                if (64 * c <= nfree && c >= (at >> 6)) {                                            \
-                    uint32_t xy = lane_from_below(rxy##c), wh = lane_from_below(rwh##c), bn = lane_from_below(rbn##c);     \
-                    if (c > (at >> 6)) {                                                            \
-                        xy = with_lane(xy, 0, lane_of(rxy##below, 63)); wh = with_lane(wh, 0, lane_of(rwh##below, 63));    \
-                        bn = with_lane(bn, 0, lane_of(rbn##below, 63));                             \
-                    }                                                                               \
-                    const bool mv = lane + 64 * c > at;                                             \
-                    rxy##c = mv ? xy : rxy##c; rwh##c = mv ? wh : rwh##c; rbn##c = mv ? bn : rbn##c;                       \
-                }
-                if (!fresh) { UP(3, 2) UP(2, 1) UP(1, 0) UP(0, 0) }      // the entries behind `at` move up by one
-#undef UP
-                PUT(at + 1, b_first ? Rxy : Bxy, b_first ? Rwh : Bwh);
+            if (64 * c <= nfree && c >= (at >> 6)) {                                                \
+                uint32_t xy = lane_from_below(rxy##c), wh = lane_from_below(rwh##c), bn = lane_from_below(rbn##c);     \
+                if (c > (at >> 6)) {                                                                \
+                    xy = with_lane(xy, 0, lane_of(rxy##below, 63)); wh = with_lane(wh, 0, lane_of(rwh##below, 63));    \
+                    bn = with_lane(bn, 0, lane_of(rbn##below, 63));                                 \
+                }                                                                                   \
+                const bool mv = lane + 64 * c > at;                                                 \
+                rxy##c = mv ? xy : rxy##c; rwh##c = mv ? wh : rwh##c; rbn##c = mv ? bn : rbn##c;    \
             }
-            if (ni) PUT(at, b_first ? Bxy : Rxy, b_first ? Bwh : Rwh);
+            UP(3, 2) UP(2, 1) UP(1, 0) UP(0, 0)              // the entries behind `at` move up by one
+#undef UP
+            PUT(at + 1, last_xy, last_wh);
+            ++nfree;
         }
-#define DOWN(c, above)                                                                              \
-        if (64 * c < nfree && c >= (at >> 6)) {                                                     \
-            uint32_t xy = lane_from_above(rxy##c), wh = lane_from_above(rwh##c), bn = lane_from_above(rbn##c);             \
-            wh = with_lane(wh, 63, above > c ? lane_of(rwh##above, 0) : FREE_GUARD);                \
-            if (64 * c + 64 < nfree) { xy = with_lane(xy, 63, lane_of(rxy##above, 0)); bn = with_lane(bn, 63, lane_of(rbn##above, 0)); }    \
-            const bool mv = lane + 64 * c >= at;                                                    \
-            rxy##c = mv ? xy : rxy##c; rwh##c = mv ? wh : rwh##c; rbn##c = mv ? bn : rbn##c;        \
-        }
-        if (ni == 0 && !fresh) { DOWN(0, 1) DOWN(1, 2) DOWN(2, 3) DOWN(3, 3) }   // the entries behind `at` move down by one
-#undef DOWN
-        nfree += ni - (fresh ? 0 : 1);
-    }
+        PUT(at, first_xy, first_wh);
 #undef PUT
 #undef PUT1
+    }
     // ---- the list has outgrown the registers: it moves to LDS for the rest of the boxes ----
-    if (i < n && !overflow) {
-#define SPILL(c) if (64 * c + lane < nfree) { fxy[64 * c + lane] = rxy##c; fwh[64 * c + lane] = rwh##c & ~FREE_GUARD; fbin[64 * c + lane] = rbn##c; }
+    if (more && !overflow) {                                 // amid a group that leaves out no box
+        i = todo ? g0 + (uint32_t)__builtin_ctzll(todo) : min(g0 + 64u, n);
+        int to = 0;                                          // without the entries without area
+#define SPILL(c) {                                                                                  \
+        const bool has = 64 * c + lane < nfree && rwh##c != FREE_GUARD;                             \
+        const unsigned long long live = __builtin_amdgcn_ballot_w64(has);                           \
+        const int j = to + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u));    \
+        if (has) { fxy[j] = rxy##c; fwh[j] = rwh##c & ~FREE_GUARD; fbin[j] = rbn##c; }              \
+        to += __builtin_popcountll(live); }
         SPILL(0) SPILL(1) SPILL(2) SPILL(3)
 #undef SPILL
+        nfree = to;
         wave_sync();
     }
     for (; i < n && !overflow; ++i) {

@@ -116,6 +116,20 @@ def test_select_sizes(F, w, h, segs, levels, mode):
     rh.close()
 
 
+# Boxes that fill a bin among others: numbered by groups of 64 while bins are left for a whole group, one by one behind that
+# (bins that run out in a group's first, middle and last boxes, after one group and more); one and several chunks of the list
+@pytest.mark.parametrize("F,S,T,max_bins", [(16, 128, 0, 200), (16, 128, 0, 63), (16, 128, 0, 64), (16, 128, 0, 66), (40, 128, 0, 400), (40, 128, 0, 129),
+                                            (40, 128, 0, 190), (40, 96, 0, 600), (40, 96, 0, 260), (64, 128, 5, 700), (64, 192, 0, 300), (1, 128, 0, 80)])
+@pytest.mark.parametrize("rotate", [False, True])
+def test_plan_full_bins(F, S, T, max_bins, rotate):
+    cfg = wl.replace(wl.config(3), n_frames=F, width=480, height=272, frac=0.35, halo=10, bin_size=S)
+    frames = np.random.default_rng(F).integers(0, 256, (F, 272, 480, 3), dtype=np.uint8)
+    net = wl.Net("plain", 1, 2, 1)
+    rh = make_rh(wl.replace(cfg, net=net), wl.make_weights(net, 0, "fp32"), max_bins=max_bins, precision="fp32", max_box_mbs=T, rotate=rotate)
+    check_select_and_plan(rh, cfg, frames, wl.make_importance(cfg), wl.make_segments(cfg), T=T or None, max_bins=max_bins, rotate=rotate)
+    rh.close()
+
+
 # Exact-border mode's pixel mask: sides that are not multiples of 32 (words and tiles cut), of 8, fewer than 32 pixels,
 # both resolutions (the second upsampling conv of x4 runs on twice the mask's grid), turned boxes, every topology
 @pytest.mark.parametrize("net,halo,S,rotate", [
