@@ -79,7 +79,7 @@ __global__ __launch_bounds__(256) void k_gather(const uint8_t* __restrict__ fram
     const int nb = (S + RB - 1) / RB;                                      // bands per bin
     // A unit is a run of bpu bands of one bin; the box list is scanned once per unit.  Small batches
     // take one band per unit (enough units to occupy the chip), large ones a whole bin.
-    const int bpu = (uint64_t)n_bins * (uint64_t)nb <= 2048u ? 1 : nb;
+    const int bpu = (uint64_t)n_bins * (uint64_t)nb <= 2048u ? 1 : 2;
     const int upb = (nb + bpu - 1) / bpu;                                  // units per bin
     const int tid = threadIdx.x;
     for (uint32_t u = blockIdx.x; u < n_bins * (uint32_t)upb; u += gridDim.x) {

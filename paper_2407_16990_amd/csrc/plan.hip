@@ -258,15 +258,16 @@ __device__ __forceinline__ void place_boxes(uint32_t n, SizeOf size_of, uint32_t
     int nb0 = 0;                                             // bins before the group; nbins: those and what `opened` says
     int dead = 0;                                            // entries without area among the nfree
     bool grouped = false, more = true;
+    auto end_group = [&]() __attribute__((always_inline)) {
+        const unsigned long long bins = alone | opened;
+        const int b = nb0 + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bins >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bins, 0u));
+        const bool mine = alone >> lane & 1ull;
+        pos0 = mine ? (uint32_t)b : pos0; pos1 = mine ? 0u : pos1;
+        nbins += __builtin_popcountll(alone);
+        i = min(g0 + 64u, n);
+    };
     auto next_group = [&]() __attribute__((always_inline)) -> bool {
-        if (grouped) {
-            const unsigned long long bins = alone | opened;
-            const int b = nb0 + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bins >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bins, 0u));
-            const bool mine = alone >> lane & 1ull;
-            pos0 = mine ? (uint32_t)b : pos0; pos1 = mine ? 0u : pos1;
-            nbins += __builtin_popcountll(alone);
-            i = min(g0 + 64u, n);
-        }
+        if (grouped) end_group();
         if (i >= n) return false;
         grouped = true;
         g0 = i;
@@ -295,140 +296,151 @@ __device__ __forceinline__ void place_boxes(uint32_t n, SizeOf size_of, uint32_t
         ni = 2u - no_r - no_b;
     };
     // Steps of a list of one chunk.  The entry behind the list's last is the next bin's whole area, so a new bin is an
-    // ordinary first fit; its bin number is not kept.  The list's capacity needs no look: its rectangles are
+    // ordinary first fit.  The list's capacity needs no look: its rectangles are
     // disjoint with sides of at least minside, of which a bin holds at most the (S / minside)^2 that free_cap counts.
     const uint32_t whole = FREE_GUARD | (uint32_t)S | (uint32_t)S << 16;
-    for (;;) {
-        if (todo == 0) {
-            more = next_group();
-            if (!more) break;
+    // The list to LDS without the entries without area, in any case less than free_cap, and back
+#define PACK(c) {                                                                                   \
+        const bool has = 64 * c + lane < nfree && rwh##c != FREE_GUARD;                             \
+        const unsigned long long live = __builtin_amdgcn_ballot_w64(has);                           \
+        const int j = packed + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u));    \
+        if (has) { fxy[j] = rxy##c; fwh[j] = rwh##c & ~FREE_GUARD; fbin[j] = rbn##c; }              \
+        packed += __builtin_popcountll(live); }
+#define PACKED() { wave_sync(); nfree = packed; packed = 0; dead = 0; }
+#define TAKE(c) {                                                                                   \
+        const int j = 64 * c + lane;                                                                \
+        rwh##c = FREE_GUARD;                                                                        \
+        if (j < nfree) { rxy##c = fxy[j]; rwh##c = fwh[j] | FREE_GUARD; rbn##c = fbin[j]; } }
+    int packed = 0;
+    do {
+        for (;;) {
+            if (todo == 0) {
+                more = next_group();
+                if (!more) break;
+            }
+            if (nfree >= 61 && dead >= 16) { PACK(0) PACKED() TAKE(0) wave_sync(); }      // the last lanes are in use
+            // as many steps as lanes and bins are there for in any case
+            int steps = min(min(__builtin_popcountll(todo), (62 - nfree) / 2), max_bins - nbins - __builtin_popcountll(alone));
+            if (steps <= 0 && todo != 0) break;
+            // what a step needs of its box is at hand before the step: its number in the group, its sides, the bin it would open
+            int k = 0;
+            uint32_t need = 0;
+#define NEXT_BOX() {                                                                                \
+                k = __builtin_ctzll(todo | 1ull << 63);                                             \
+                need = lane_of(ndv, k) & ~0x8000u;                                                  \
+                const int bin = nbins + __builtin_popcountll(alone & ((1ull << k) - 1ull));         \
+                rxy0 = with_lane(rxy0, nfree, 0u); rwh0 = with_lane(rwh0, nfree, whole); rbn0 = with_lane(rbn0, nfree, (uint32_t)bin); }
+            NEXT_BOX()
+            for (; steps > 0; --steps) {
+                bool fit = ((rwh0 - need) & FREE_GUARD) == FREE_GUARD;
+                const uint32_t needt = need >> 16 | need << 16;
+                if constexpr (ROTATE) fit = fit | (((rwh0 - needt) & FREE_GUARD) == FREE_GUARD);
+                const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(fit));
+                const uint32_t exy = lane_of(rxy0, at), ewh = lane_of(rwh0, at), eb = lane_of(rbn0, at);
+                uint32_t turned = 0;
+                if constexpr (ROTATE) {                          // upright whenever that fits
+                    const bool up = ((ewh - need) & FREE_GUARD) == FREE_GUARD;
+                    need = up ? need : needt; turned = up ? 0u : 0x10000u;
+                }
+                pos0 = with_lane(pos0, k, eb | turned); pos1 = with_lane(pos1, k, exy);
+                rest(exy, ewh, need);
+                const uint32_t old = min((uint32_t)(nfree - at), 1u), fresh = 1u - old;      // fresh: what is left of a new bin goes to the list's end
+                nbins += (int)fresh; opened |= (unsigned long long)fresh << k;
+                if (ni == 2u) {
+                    if (old) {                                   // the entries behind `at` move up by one
+                        const uint32_t dxy = lane_from_below(rxy0), dwh = lane_from_below(rwh0), dbn = lane_from_below(rbn0);
+                        const bool up = lane > at;
+                        rxy0 = up ? dxy : rxy0; rwh0 = up ? dwh : rwh0; rbn0 = up ? dbn : rbn0;
+                    }
+                    rxy0 = with_lane(rxy0, at + 1, last_xy); rwh0 = with_lane(rwh0, at + 1, last_wh); rbn0 = with_lane(rbn0, at + 1, eb);
+                }
+                rxy0 = with_lane(rxy0, at, first_xy); rwh0 = with_lane(rwh0, at, ni ? first_wh : FREE_GUARD);
+                dead += (int)(old & less(ni, 1u));
+                nfree += (int)(ni - min(ni, old));
+                todo &= todo - 1;
+                NEXT_BOX()
+            }
+#undef NEXT_BOX
         }
-        if (nfree >= 61 && dead >= 16) {                     // the last lanes are in use: without the entries without area
-            const unsigned long long live = __builtin_amdgcn_ballot_w64(lane < nfree && rwh0 != FREE_GUARD);
-            const int to = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u));
-            if (live >> lane & 1ull) { fxy[to] = rxy0; fwh[to] = rwh0; fbin[to] = rbn0; }
-            wave_sync();
-            nfree -= dead; dead = 0;
-            rwh0 = FREE_GUARD;
-            if (lane < nfree) { rxy0 = fxy[lane]; rwh0 = fwh[lane]; rbn0 = fbin[lane]; }
-            wave_sync();
-        }
-        // as many steps as lanes and bins are there for in any case
-        int steps = min(min(__builtin_popcountll(todo), (62 - nfree) / 2), max_bins - nbins - __builtin_popcountll(alone));
-        if (steps <= 0 && todo != 0) break;
-        rwh0 = with_lane(rwh0, nfree, whole); rxy0 = with_lane(rxy0, nfree, 0u);
-        for (; steps > 0; --steps) {
+        if (lane >= nfree) rwh0 = FREE_GUARD;                    // without the new bin's entry
+        // ---- several chunks ----
+        while (more && !overflow) {
+            if (nfree > REG_MAX || (todo == 0 && dead >= 64)) {
+                PACK(0) PACK(1) PACK(2) PACK(3) PACKED()
+                TAKE(0) TAKE(1) TAKE(2) TAKE(3)
+                wave_sync();
+                if (nfree > REG_MAX - 8 || nfree < 40) break;
+            }
+            if (todo == 0) { more = next_group(); continue; }
             const int k = __builtin_ctzll(todo);
             todo &= todo - 1;
             uint32_t need = lane_of(ndv, k) & ~0x8000u;
-            bool fit = ((rwh0 - need) & FREE_GUARD) == FREE_GUARD;
             const uint32_t needt = need >> 16 | need << 16;
-            if constexpr (ROTATE) fit = fit | (((rwh0 - needt) & FREE_GUARD) == FREE_GUARD);
-            const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(fit));
-            const uint32_t exy = lane_of(rxy0, at), ewh = lane_of(rwh0, at);
-            const int bin_now = nbins + __builtin_popcountll(alone & ((1ull << k) - 1ull));
-            const uint32_t eb = at == nfree ? (uint32_t)bin_now : lane_of(rbn0, at);
-            uint32_t turned = 0;
-            if constexpr (ROTATE) {                          // upright whenever that fits
-                const bool up = ((ewh - need) & FREE_GUARD) == FREE_GUARD;
-                need = up ? need : needt; turned = up ? 0u : 0x10000u;
-            }
-            pos0 = with_lane(pos0, k, eb | turned); pos1 = with_lane(pos1, k, exy);
-            rest(exy, ewh, need);
-            const uint32_t old = min((uint32_t)(nfree - at), 1u), fresh = 1u - old;      // fresh: what is left of a new bin goes to the list's end
-            nbins += (int)fresh; opened |= (unsigned long long)fresh << k;
-            if (ni == 2u) {
-                if (old) {                                   // the entries behind `at` move up by one
-                    const uint32_t dxy = lane_from_below(rxy0), dwh = lane_from_below(rwh0), dbn = lane_from_below(rbn0);
-                    const bool up = lane > at;
-                    rxy0 = up ? dxy : rxy0; rwh0 = up ? dwh : rwh0; rbn0 = up ? dbn : rbn0;
-                }
-                rxy0 = with_lane(rxy0, at + 1, last_xy); rwh0 = with_lane(rwh0, at + 1, last_wh); rbn0 = with_lane(rbn0, at + 1, eb);
-            }
-            rxy0 = with_lane(rxy0, at, first_xy); rwh0 = with_lane(rwh0, at, ni ? first_wh : FREE_GUARD); rbn0 = with_lane(rbn0, at, eb);
-            dead += (int)(old & less(ni, 1u));
-            nfree += (int)(ni - min(ni, old));
-            rxy0 = with_lane(rxy0, nfree, 0u); rwh0 = with_lane(rwh0, nfree, whole);
-        }
-    }
-    if (lane >= nfree) rwh0 = FREE_GUARD;                    // without the new bin's entry
-    // ---- several chunks ----
-    while (more && !overflow && nfree <= REG_MAX) {
-        if (todo == 0) { more = next_group(); continue; }
-        const int k = __builtin_ctzll(todo);
-        todo &= todo - 1;
-        uint32_t need = lane_of(ndv, k) & ~0x8000u;
-        const uint32_t needt = need >> 16 | need << 16;
 #define FITS(c)                                                                                     \
-        bool fit##c = ((rwh##c - need) & FREE_GUARD) == FREE_GUARD;                                 \
-        if constexpr (ROTATE) fit##c = fit##c | (((rwh##c - needt) & FREE_GUARD) == FREE_GUARD);
-        FITS(0) FITS(1) FITS(2) FITS(3)
+            bool fit##c = ((rwh##c - need) & FREE_GUARD) == FREE_GUARD;                                 \
+            if constexpr (ROTATE) fit##c = fit##c | (((rwh##c - needt) & FREE_GUARD) == FREE_GUARD);
+            FITS(0) FITS(1) FITS(2) FITS(3)
 #undef FITS
 #define PUT1(c, j, xy, wh) if (((j) >> 6) == c) { rxy##c = with_lane(rxy##c, (j) & 63, xy); rwh##c = with_lane(rwh##c, (j) & 63, wh); rbn##c = with_lane(rbn##c, (j) & 63, eb); }
 #define PUT(j, xy, wh) do { PUT1(0, j, xy, wh) else PUT1(1, j, xy, wh) else PUT1(2, j, xy, wh) else PUT1(3, j, xy, wh) } while (0)
-        if (__builtin_amdgcn_ballot_w64(fit0 | fit1 | fit2 | fit3) == 0) {      // a new bin: what is left of it goes to the list's end
-            const uint32_t eb = (uint32_t)nbins + (uint32_t)__builtin_popcountll(alone & ((1ull << k) - 1ull));
-            if ((int)eb >= max_bins) { overflow = true; i = g0 + k; break; }
-            ++nbins; opened |= 1ull << k;
-            pos0 = with_lane(pos0, k, eb); pos1 = with_lane(pos1, k, 0u);
-            rest(0u, whole, need);
-            if (ni >= 1u) { PUT(nfree, first_xy, first_wh); ++nfree; }
-            if (ni == 2u) { PUT(nfree, last_xy, last_wh); ++nfree; }
-            continue;
-        }
-        int at = -1;
-        uint32_t exy = 0, ewh = 0, eb = 0;
-#define FIRST(c)                                                                                    \
-        if (at < 0) {                                                                               \
-            const unsigned long long m = __builtin_amdgcn_ballot_w64(fit##c);                       \
-            if (m) {                                                                                \
-                const int l = __builtin_ctzll(m);                                                   \
-                at = 64 * c + l;                                                                    \
-                exy = lane_of(rxy##c, l); ewh = lane_of(rwh##c, l); eb = lane_of(rbn##c, l);        \
-            }                                                                                       \
-        }
-        FIRST(0) FIRST(1) FIRST(2) FIRST(3)
-#undef FIRST
-        uint32_t turned = 0;
-        if constexpr (ROTATE) if (((ewh - need) & FREE_GUARD) != FREE_GUARD) { need = needt; turned = 0x10000u; }      // upright whenever that fits
-        pos0 = with_lane(pos0, k, eb | turned); pos1 = with_lane(pos1, k, exy);
-        rest(exy, ewh, need);
-        if (ni == 0) { ++dead; first_wh = FREE_GUARD; }      // an entry without area
-        if (ni == 2) {
-#define UP(c, below)                                                                                \
-            if (64 * c <= nfree && c >= (at >> 6)) {                                                \
-                uint32_t xy = lane_from_below(rxy##c), wh = lane_from_below(rwh##c), bn = lane_from_below(rbn##c);     \
-                if (c > (at >> 6)) {                                                                \
-                    xy = with_lane(xy, 0, lane_of(rxy##below, 63)); wh = with_lane(wh, 0, lane_of(rwh##below, 63));    \
-                    bn = with_lane(bn, 0, lane_of(rbn##below, 63));                                 \
-                }                                                                                   \
-                const bool mv = lane + 64 * c > at;                                                 \
-                rxy##c = mv ? xy : rxy##c; rwh##c = mv ? wh : rwh##c; rbn##c = mv ? bn : rbn##c;    \
+            if (__builtin_amdgcn_ballot_w64(fit0 | fit1 | fit2 | fit3) == 0) {      // a new bin: what is left of it goes to the list's end
+                const uint32_t eb = (uint32_t)nbins + (uint32_t)__builtin_popcountll(alone & ((1ull << k) - 1ull));
+                if ((int)eb >= max_bins) { overflow = true; i = g0 + k; break; }
+                ++nbins; opened |= 1ull << k;
+                pos0 = with_lane(pos0, k, eb); pos1 = with_lane(pos1, k, 0u);
+                rest(0u, whole, need);
+                if (ni >= 1u) { PUT(nfree, first_xy, first_wh); ++nfree; }
+                if (ni == 2u) { PUT(nfree, last_xy, last_wh); ++nfree; }
+                continue;
             }
-            UP(3, 2) UP(2, 1) UP(1, 0) UP(0, 0)              // the entries behind `at` move up by one
+            int at = -1;
+            uint32_t exy = 0, ewh = 0, eb = 0;
+#define FIRST(c)                                                                                    \
+            if (at < 0) {                                                                               \
+                const unsigned long long m = __builtin_amdgcn_ballot_w64(fit##c);                       \
+                if (m) {                                                                                \
+                    const int l = __builtin_ctzll(m);                                                   \
+                    at = 64 * c + l;                                                                    \
+                    exy = lane_of(rxy##c, l); ewh = lane_of(rwh##c, l); eb = lane_of(rbn##c, l);        \
+                }                                                                                       \
+            }
+            FIRST(0) FIRST(1) FIRST(2) FIRST(3)
+#undef FIRST
+            uint32_t turned = 0;
+            if constexpr (ROTATE) if (((ewh - need) & FREE_GUARD) != FREE_GUARD) { need = needt; turned = 0x10000u; }      // upright whenever that fits
+            pos0 = with_lane(pos0, k, eb | turned); pos1 = with_lane(pos1, k, exy);
+            rest(exy, ewh, need);
+            if (ni == 0) { ++dead; first_wh = FREE_GUARD; }      // an entry without area
+            if (ni == 2) {
+#define UP(c, below)                                                                                \
+                if (64 * c <= nfree && c >= (at >> 6)) {                                                \
+                    uint32_t xy = lane_from_below(rxy##c), wh = lane_from_below(rwh##c), bn = lane_from_below(rbn##c);     \
+                    if (c > (at >> 6)) {                                                                \
+                        xy = with_lane(xy, 0, lane_of(rxy##below, 63)); wh = with_lane(wh, 0, lane_of(rwh##below, 63));    \
+                        bn = with_lane(bn, 0, lane_of(rbn##below, 63));                                 \
+                    }                                                                                   \
+                    const bool mv = lane + 64 * c > at;                                                 \
+                    rxy##c = mv ? xy : rxy##c; rwh##c = mv ? wh : rwh##c; rbn##c = mv ? bn : rbn##c;    \
+                }
+                UP(3, 2) UP(2, 1) UP(1, 0) UP(0, 0)              // the entries behind `at` move up by one
 #undef UP
-            PUT(at + 1, last_xy, last_wh);
-            ++nfree;
-        }
-        PUT(at, first_xy, first_wh);
+                PUT(at + 1, last_xy, last_wh);
+                ++nfree;
+            }
+            PUT(at, first_xy, first_wh);
 #undef PUT
 #undef PUT1
-    }
+        }
+    } while (more && !overflow && nfree < 40);
     // ---- the list has outgrown the registers: it moves to LDS for the rest of the boxes ----
-    if (more && !overflow) {                                 // amid a group that leaves out no box
-        i = todo ? g0 + (uint32_t)__builtin_ctzll(todo) : min(g0 + 64u, n);
-        int to = 0;                                          // without the entries without area
-#define SPILL(c) {                                                                                  \
-        const bool has = 64 * c + lane < nfree && rwh##c != FREE_GUARD;                             \
-        const unsigned long long live = __builtin_amdgcn_ballot_w64(has);                           \
-        const int j = to + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u));    \
-        if (has) { fxy[j] = rxy##c; fwh[j] = rwh##c & ~FREE_GUARD; fbin[j] = rbn##c; }              \
-        to += __builtin_popcountll(live); }
-        SPILL(0) SPILL(1) SPILL(2) SPILL(3)
-#undef SPILL
-        nfree = to;
-        wave_sync();
+    if (more && !overflow) {                                 // not amid a group that leaves out boxes
+        if (todo == 0) end_group();
+        else i = g0 + (uint32_t)__builtin_ctzll(todo);
+        PACK(0) PACK(1) PACK(2) PACK(3) PACKED()
     }
+#undef PACK
+#undef PACKED
+#undef TAKE
     for (; i < n && !overflow; ++i) {
         if ((i & 63u) == 0) next_sizes();
         const uint32_t sz = lane_of(szv, (int)(i & 63u));
