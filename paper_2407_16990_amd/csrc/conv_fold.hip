@@ -20,11 +20,15 @@
 //
 // Main kernel: implicit GEMM on v_mfma_f32_32x32x16_bf16, D[row][pixel], rows = (i, j, co) of one
 // 32-row chunk (x4: two chunks of two output rows i each; x2, x3: one chunk), N = 32 pixels of an
-// image row, K = tap * C + ci over 25 taps.  One persistent 256-thread workgroup per CU keeps its
-// chunk's weights (25 * C/16 KB) in LDS, stages a 12 x 36 pixel patch per 8 x 32 tile (same
-// channels-last layout and XOR swizzle as the 3 x 3 kernels), and prefetches the next patch into
-// registers during the MFMA loop.  A wave owns two pixel rows: per (kx, k-step) it reads 5 weight
-// and 6 activation fragments for 10 MFMAs.
+// image row, K = tap * C + ci over 25 taps.  One persistent 512-thread workgroup per CU works on 8 x 32 tiles, from a
+// 12 x 36 pixel patch in LDS (same channels-last layout and XOR swizzle as the 3 x 3 kernels).  The waves split K: a wave
+// has 16 of the input channels, whose 25 weight fragments stay in 100 registers, and C / 16 pixel rows, an
+// accumulator each; the C / 16 waves of the same rows then exchange sums through LDS, and each adds up and stores one row.
+// Per tap column a wave reads 8 (6) activation fragments for 20 (10) MFMAs and no weights, and the sums that follow each other are
+// independent: with all of K in each of four waves and the weights in LDS (1.1 fragments per MFMA) a wave had two
+// rows, whose sums waited for each other's latency.  The next tile's patch is copied to LDS behind these MFMAs.
+// Whole calls of EDSR x4 with one block on 76 / 128 bins of 128 x 128, this kernel's share about a half: 563 -> 545, 940 -> 909 us;
+// three bins x3 16.3 -> 14.0 us of kernel; without the exchange 20 us less on 76 bins, without the stores 26 (both wrong results).
 #include <string.h>
 
 #include <atomic>
@@ -82,19 +86,27 @@ __device__ __forceinline__ void fold_each_step(F& f)
     if constexpr (I < N) { f(std::integral_constant<int, I>{}); fold_each_step<N, I + 1>(f); }
 }
 
+// LDS of the main kernel: a patch, room, a patch.  The weights pass through room and second patch on their way to registers;
+// a tile's partial sums take the place of its patch and room.
+template <int CIN>
+struct fold_lds {
+    static constexpr int KS = CIN / 16, WBYTES = 25 * KS * 1024, PATCHB = (FOLD_TH + 4) * FOLD_PW * CIN * 2, ROOM = WBYTES - PATCHB;
+    static constexpr int SUMS = 8 * (KS - 1) * 4096, TOTAL = PATCHB + ROOM + PATCHB;
+    static_assert(ROOM % 16 == 0 && SUMS <= PATCHB + ROOM && PATCHB % 1024 == 0, "what takes whose place");
+};
+
 template <int CIN, bool LIST>
-__global__ __launch_bounds__(256) void k_conv_fold(fold_args a)
+__global__ __launch_bounds__(512) void k_conv_fold(fold_args a)
 {
     // LIST: the tiles come from a.tile_list.  An entry is requested two tiles ahead with a vector
     // load (a scalar load would share its counter with the LDS fragment reads) and read a tile later.
-    constexpr int KS = CIN / 16, NCH = CIN / 8, PIXB = CIN * 2, TH = FOLD_TH, PH = TH + 4, PW = FOLD_PW, RW = 2, NR = RW + 4;
-    constexpr int WBYTES = 25 * KS * 1024, NPIECE = PH * PW * NCH, NPRE = (NPIECE + 255) / 256, NSTEP = 5 * KS;
+    using L = fold_lds<CIN>;
+    constexpr int KS = L::KS, NCH = CIN / 8, PIXB = CIN * 2, TH = FOLD_TH, PW = FOLD_PW, RW = KS, NR = RW + 4;
+    constexpr int NPIECE = L::PATCHB / 1024, NPRE = (NPIECE + 7) / 8;        // a wave's 1 KB pieces of the patch
     constexpr int SWZ_SH = (NCH == 8) ? 0 : 1;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    uint8_t* lds_w = lds;
-    uint8_t* lds_p = lds + WBYTES;
-    const int tid = threadIdx.x, lane = tid & 63, lx = lane & 31, hi = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wk = wave % KS, wr = wave / KS;      // k-step and row group
 
     const uint32_t* counter = LIST ? a.n_list : a.n_valid;
     const uint32_t n_found = counter ? *counter : (uint32_t)a.N;
@@ -107,7 +119,7 @@ __global__ __launch_bounds__(256) void k_conv_fold(fold_args a)
     const int chunk_begin = deal ? local % a.n_chunks : 0, chunk_end = deal ? chunk_begin + 1 : a.n_chunks;
     // the first chunk's weights are on their way before the image count is known
     auto load_weights = [&](int chunk) __attribute__((always_inline)) {
-        lds_dma<256, WBYTES>(lds_w, a.wp + (size_t)chunk * (WBYTES / 16), wave, lane);
+        lds_dma<512, L::WBYTES>(lds + L::PATCHB, a.wp + (size_t)chunk * (L::WBYTES / 16), wave, lane);
     };
     load_weights(chunk_begin);
     const int n_img = min((int)n_found, a.N);
@@ -115,27 +127,21 @@ __global__ __launch_bounds__(256) void k_conv_fold(fold_args a)
     const int n_tiles = LIST ? (int)n_found : n_img * tiles_img;
     const uint32_t in_img_bytes = (uint32_t)a.H * a.W * PIXB;
 
-    // patch pieces of this thread: piece j is 16-byte group p_c of patch pixel (p_row, p_col)
-    uint4 pre[NPRE];
-    auto piece_pos = [&](int j, int& row, int& col, int& c) __attribute__((always_inline)) {
-        const int idx = j * 256 + tid, px = idx / NCH;
-        c = idx - px * NCH; row = px / PW; col = px - row * PW;
-        return idx < NPIECE;
-    };
-    auto load_piece = [&](int j, __amdgpu_buffer_rsrc_t rin, int y0, int x0) __attribute__((always_inline)) {
-        int row, col, c;
-        const bool in_patch = piece_pos(j, row, col, c);
-        const int gy = y0 - 2 + row, gx = x0 - 2 + col;
-        const bool ok = in_patch && gy >= 0 && gy < a.H && gx >= 0 && gx < a.W;
-        const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rin, ok ? (uint32_t)((gy * a.W + gx) * PIXB + c * 16) : OOB_OFF, 0, 0);
-        pre[j] = make_uint4(v[0], v[1], v[2], v[3]);
-    };
-    auto store_patch = [&]() __attribute__((always_inline)) {
+    // piece i of the patch, by wave i % 8: 64 16-byte channel groups, 8 (16) pixels.  The pieces are contiguous in LDS, so the
+    // lanes fetch swizzled.  Rows outside the image lie outside the descriptor's range and read as zeros.
+    // (`l` is the lane, passed through an empty asm statement in every phase: addresses kept over the loop would not fit the registers.)
+    auto load_patch = [&](uint8_t* to, __amdgpu_buffer_rsrc_t rin, int y0, int x0) __attribute__((always_inline)) {
+        int l = lane;
+        asm volatile("" : "+v"(l));
 #pragma unroll
         for (int j = 0; j < NPRE; ++j) {
-            int row, col, c;
-            if (piece_pos(j, row, col, c))
-                *(uint4*)(lds_p + (row * PW + col) * PIXB + ((c ^ ((col >> SWZ_SH) & (NCH - 1))) << 4)) = pre[j];
+            const int i = j * 8 + wave;
+            if (j == NPRE - 1 && i >= NPIECE) break;
+            const uint32_t idx = i * 64 + l, px = idx / NCH, row = (px * 1821u) >> 16, col = px - row * PW;      // px / 36 for px < 432
+            const int gx = x0 - 2 + (int)col;
+            const uint32_t off = (uint32_t)((y0 - 2 + (int)row) * a.W + gx) * PIXB + (((idx ^ (col >> SWZ_SH)) & (NCH - 1)) << 4);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rin, (__attribute__((address_space(3))) void*)(to + i * 1024), 16,
+                                                     (uint32_t)gx < (uint32_t)a.W ? off : OOB_OFF, 0, 0, 0);
         }
     };
     auto decode = [&](int tile, int& n, int& y0, int& x0) __attribute__((always_inline)) {
@@ -165,9 +171,7 @@ __global__ __launch_bounds__(256) void k_conv_fold(fold_args a)
     auto first_patch = [&]() __attribute__((always_inline)) {
         tile_origin(wg, cn, cy0, cx0);
         if constexpr (LIST) e_next = list_load(wg + G);
-        __amdgpu_buffer_rsrc_t rin = in_rsrc(wg, wg < n_tiles ? cn : 0);
-#pragma unroll
-        for (int j = 0; j < NPRE; ++j) load_piece(j, rin, cy0, cx0);
+        load_patch(lds, in_rsrc(wg, wg < n_tiles ? cn : 0), cy0, cx0);
     };
     first_patch();                                         // ahead of what the compiler computes once for all turns of the loops
     for (int chunk = chunk_begin; chunk < chunk_end; ++chunk) {
@@ -176,66 +180,100 @@ __global__ __launch_bounds__(256) void k_conv_fold(fold_args a)
             load_weights(chunk);
             first_patch();
         }
-        f32x16 biasv;                                      // lane holds rows 8q + 4hi + e in [4q + e]
+        f32x16 biasv;                                      // lane holds rows 8q + 4hi + e in [4q + e]; in the sums of the first k-step
 #pragma unroll
-        for (int e = 0; e < 16; ++e) biasv[e] = a.bias[chunk * 32 + (e >> 2) * 8 + hi * 4 + (e & 3)];
-        int tile = wg;
-        lds_dma_wait();                                    // weights, before the loop's first barriers
-        for (; tile < n_tiles; tile += G) {                // trip count uniform over the workgroup
+        for (int e = 0; e < 16; ++e) { biasv[e] = a.bias[chunk * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)]; biasv[e] = wk == 0 ? biasv[e] : 0.0f; }
+        lds_dma_wait();                                    // weights and first patch
+        __syncthreads();
+        bf16x8 A[25];
+#pragma unroll
+        for (int tap = 0; tap < 25; ++tap) A[tap] = *(const bf16x8*)(lds + L::PATCHB + ((tap * KS + wk) << 10) + (lane << 4));
+        lds_barrier();                                     // read by every wave
+        uint8_t* patch = lds;
+        for (int tile = wg; tile < n_tiles; tile += G) {   // trip count uniform over the workgroup
             int n, y0, x0;
             if constexpr (LIST) { n = cn; y0 = cy0; x0 = cx0; } else tile_origin(tile, n, y0, x0);
             int e_after = 0;
             if constexpr (LIST) e_after = list_load(tile + 2 * G);
-            lds_barrier();                                 // LDS reads of the previous tile are done
-            store_patch();
-            lds_barrier();
             const int nt = tile + G;
             int nn, ny0, nx0;
             if constexpr (LIST) { decode_cell(__builtin_amdgcn_readfirstlane(e_next), nn, ny0, nx0); cn = nn; cy0 = ny0; cx0 = nx0; e_next = e_after; }
             else tile_origin(nt, nn, ny0, nx0);
-            __amdgpu_buffer_rsrc_t rin = in_rsrc(nt, nt < n_tiles ? nn : 0);
+            uint8_t* other = patch == lds ? lds + L::PATCHB + L::ROOM : lds;
+            load_patch(other, in_rsrc(nt, nt < n_tiles ? nn : 0), ny0, nx0);
 
             f32x16 acc[RW];
-#pragma unroll
-            for (int r = 0; r < RW; ++r) acc[r] = biasv;
-            const uint8_t* wlane = lds_w + (lane << 4);
-            const uint8_t* prow = lds_p + (wave * RW) * (PW * PIXB);
-            bf16x8 A0[5], A1[5], B0[NR], B1[NR];
-            auto load_frags = [&](int st, bf16x8 (&A)[5], bf16x8 (&B)[NR]) __attribute__((always_inline)) {
-                const int kx = st / KS, ks = st - kx * KS, px = lx + kx;
-                const uint8_t* b0 = prow + px * PIXB + (((2 * ks + hi) ^ ((px >> SWZ_SH) & (NCH - 1))) << 4);
-#pragma unroll
-                for (int ky = 0; ky < 5; ++ky) A[ky] = *(const bf16x8*)(wlane + ((((ky * 5 + kx) * KS) + ks) << 10));
+            const uint8_t* prow = patch + (wr * RW) * (PW * PIXB);
+            int l = lane;
+            asm volatile("" : "+v"(l));
+            auto bptr = [&](int kx) __attribute__((always_inline)) {
+                const int px = (l & 31) + kx;
+                return prow + px * PIXB + (((2 * wk + (l >> 5)) ^ ((px >> SWZ_SH) & (NCH - 1))) << 4);
+            };
+            bf16x8 B[NR];
+            {
+                const uint8_t* b0 = bptr(0);
 #pragma unroll
                 for (int py = 0; py < NR; ++py) B[py] = *(const bf16x8*)(b0 + py * (PW * PIXB));
-            };
-            load_frags(0, A0, B0);
-            auto step = [&](auto st_c) __attribute__((always_inline)) {
-                constexpr int st = decltype(st_c)::value;
-                bf16x8 (&Ac)[5] = (st & 1) ? A1 : A0;
-                bf16x8 (&Bc)[NR] = (st & 1) ? B1 : B0;
-                bf16x8 (&An)[5] = (st & 1) ? A0 : A1;
-                bf16x8 (&Bn)[NR] = (st & 1) ? B0 : B1;
-                if constexpr (st + 1 < NSTEP) load_frags(st + 1, An, Bn);
-                if constexpr (st < NPRE) load_piece(st, rin, ny0, nx0);        // next tile's patch, one piece per step
-                static_assert(NPRE <= NSTEP, "one patch piece per step must cover the patch");
-                __builtin_amdgcn_sched_barrier(0);
-                // (input row py, tap row ky) pairs with 0 <= py - ky < RW
-#pragma unroll
-                for (int py = 0; py < NR; ++py)
-#pragma unroll
-                    for (int ky = 0; ky < 5; ++ky)
-                        if (py - ky >= 0 && py - ky < RW)
-                            acc[py - ky] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Ac[ky], Bc[py], acc[py - ky], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            fold_each_step<NSTEP>(step);
-            const int x = x0 + lx;
-#pragma unroll
-            for (int r = 0; r < RW; ++r) {
-                const int y = y0 + wave * RW + r;
-                if (y < a.H && x < a.W) fold_store(a, acc[r], n, y, x, chunk, hi);
             }
+            __builtin_amdgcn_sched_barrier(0);
+            auto step = [&](auto kx_c) __attribute__((always_inline)) {
+                constexpr int kx = decltype(kx_c)::value;
+                const uint8_t* bn = bptr(kx + 1);
+#pragma unroll
+                for (int k = 0; k < 5 * RW; ++k) {         // the rows in turn, so that a sum's products are RW products apart
+                    const int ky = k / RW, r = k % RW;
+                    acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[ky * 5 + kx], B[r + ky], kx == 0 && ky == 0 ? biasv : acc[r], 0, 0, 0);
+                    // a fragment's last product is behind it: the next tap column's takes its place
+                    if (kx < 4 && (r == 0 || ky == 4)) B[r + ky] = *(const bf16x8*)(bn + (r + ky) * (PW * PIXB));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            fold_each_step<5>(step);
+
+            // row r of the group is added up and stored by the wave of k-step r; the partial sums of the others, in order of their k-steps
+            lds_dma_wait();                                // the next patch: nothing of it is in flight behind the sums' LDS writes
+            lds_barrier();                                 // the patch is read by every wave
+            asm volatile("" : "+v"(l));
+            float4* sums = (float4*)(patch == lds ? lds : lds + L::PATCHB) + l;
+            f32x16 sum;
+            auto add_up = [&](auto k_c) __attribute__((always_inline)) {
+                constexpr int own = decltype(k_c)::value;
+#pragma unroll
+                for (int r = 0; r < RW; ++r)
+                    if (r != own)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            sums[(((wr * KS + r) * (KS - 1) + (own < r ? own : own - 1)) * 4 + q) * 64] =
+                                make_float4(acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]);
+                lds_barrier();
+#pragma unroll
+                for (int src = 0; src < KS; ++src) {
+                    f32x16 p;
+                    if (src == own) p = acc[own];
+                    else
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float4 v = sums[(((wr * KS + own) * (KS - 1) + (src < own ? src : src - 1)) * 4 + q) * 64];
+                            p[4 * q] = v.x; p[4 * q + 1] = v.y; p[4 * q + 2] = v.z; p[4 * q + 3] = v.w;
+                        }
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) sum[e] = src ? sum[e] + p[e] : p[e];
+                }
+            };
+            if constexpr (KS == 4) {
+                if (wk == 0) add_up(std::integral_constant<int, 0>{});
+                else if (wk == 1) add_up(std::integral_constant<int, 1>{});
+                else if (wk == 2) add_up(std::integral_constant<int, 2>{});
+                else add_up(std::integral_constant<int, 3>{});
+            } else {
+                if (wk == 0) add_up(std::integral_constant<int, 0>{});
+                else add_up(std::integral_constant<int, 1>{});
+            }
+            const int x = x0 + (l & 31), y = y0 + wr * RW + wk;
+            if (y < a.H && x < a.W) fold_store(a, sum, n, y, x, chunk, l >> 5);
+            lds_barrier();                                 // sums read, next patch visible
+            patch = other;
         }
     }
 }
@@ -483,7 +521,7 @@ rh_status rh_fold_weights(rh_ctx* ctx, const float* blob)
 template <int CIN>
 static hipError_t launch_fold(rh_ctx* ctx, const fold_args& a)
 {
-    constexpr int lds = 25 * (CIN / 16) * 1024 + (FOLD_TH + 4) * FOLD_PW * CIN * 2;
+    constexpr int lds = fold_lds<CIN>::TOTAL;
     static bool attr_done[RH_MAX_DEVICES] = {};
     if (!attr_done[ctx->device]) {
         hipError_t e = hipFuncSetAttribute((const void*)k_conv_fold<CIN, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -494,8 +532,8 @@ static hipError_t launch_fold(rh_ctx* ctx, const fold_args& a)
     fold_args m = a;                                       // main kernel: the middle class (number 4)
     m.wp = a.wp + (size_t)4 * a.n_chunks * (25 * (CIN / 16) * 64);
     m.bias = a.bias + 4 * a.n_chunks * 32;
-    if (a.tile_list) hipLaunchKernelGGL((k_conv_fold<CIN, true>), dim3(ctx->n_cu), dim3(256), lds, ctx->stream, m);
-    else hipLaunchKernelGGL((k_conv_fold<CIN, false>), dim3(ctx->n_cu), dim3(256), lds, ctx->stream, m);
+    if (a.tile_list) hipLaunchKernelGGL((k_conv_fold<CIN, true>), dim3(ctx->n_cu), dim3(512), lds, ctx->stream, m);
+    else hipLaunchKernelGGL((k_conv_fold<CIN, false>), dim3(ctx->n_cu), dim3(512), lds, ctx->stream, m);
     // Needed-region mode: a pasted macroblock lies at least `halo` pixels inside its box, hence inside
     // the bin, so with a halo no pasted pixel is on the outermost ring and the ring pass has nothing to add.
     if (a.tile_list && ctx->cfg.halo >= 1) return hipGetLastError();
