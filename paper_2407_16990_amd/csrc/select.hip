@@ -41,6 +41,95 @@ __device__ __forceinline__ uint32_t wave_prefix(uint32_t v)
     return v;
 }
 
+// The bin of `hist` that holds the k-th key (k = remaining, counted from the top) goes to *s_prefix behind the digits that are
+// known, and what is left of k to *s_remaining.  All 1024 threads, which have counted; they find both after it.
+__device__ __forceinline__ void pick_bin(const uint32_t* hist, int shift, uint32_t prefix, uint32_t remaining, uint32_t* s_wtot,
+                                         uint32_t* s_prefix, uint32_t* s_remaining)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // bin t holds the k-th key iff  above(t) < remaining <= above(t) + hist[t],  above(t) = sum of
+    // the bins over t.  Thread t holds the bins 2047 - 2t and 2046 - 2t, so that is a prefix sum.
+    const uint32_t b1 = BINS - 1 - 2 * tid, h1 = hist[b1], h0 = hist[b1 - 1], incl = wave_prefix(h1 + h0);
+    if (lane == 63) s_wtot[wave] = incl;
+    __syncthreads();
+    const uint32_t tot = wave_prefix(s_wtot[lane & 15]);           // lanes 0..15: inclusive sums of the waves' totals
+    const uint32_t above1 = incl - h1 - h0 + (wave ? (uint32_t)__builtin_amdgcn_readlane((int)tot, __builtin_amdgcn_readfirstlane(wave ? wave - 1 : 0)) : 0u);
+    const uint32_t above0 = above1 + h1;
+    if (above1 < remaining && remaining <= above1 + h1) { *s_prefix = prefix | (b1 << shift); *s_remaining = remaining - above1; }
+    if (above0 < remaining && remaining <= above0 + h0) { *s_prefix = prefix | ((b1 - 1) << shift); *s_remaining = remaining - above0; }
+    __syncthreads();
+}
+
+// The whole top-k selection in one launch, where every segment's queue stays in one workgroup's registers.  A segment
+// selects min(k, n) keys, so where its part of the list begins is known without the other segments' keys; ties go
+// to the smallest indexes, so one prefix sum over the queue numbers them and what is selected, and frames need no counts.
+// Two launches / this one, us of kernels: one segment of 240 keys 11.6 / 6.8, of 8160 behind a step of convs 27.9 / 17.1.
+__global__ __launch_bounds__(1024) void k_select_once(seg_chunk c, int F, const float* __restrict__ imp, int per, uint8_t* __restrict__ mask,
+                                                      uint32_t* __restrict__ list, uint32_t* __restrict__ n_sel)
+{
+    __shared__ uint32_t hist[BINS];
+    __shared__ uint32_t s_wtot[16];
+    __shared__ uint32_t s_prefix, s_remaining;
+    __shared__ __attribute__((aligned(16))) uint32_t s_cnt[KREG * 16];     // keys above the threshold | ties << 16 of a wave's 64 keys
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), seg = blockIdx.x;
+    const uint32_t g0 = c.fb[seg] * (uint32_t)per, n = c.fe[seg] * (uint32_t)per - g0, k = min(c.k[seg], n);
+    uint32_t keys[KREG];
+#pragma unroll
+    for (int j = 0; j < KREG; ++j) {
+        const uint32_t i = (uint32_t)j * 1024u + tid;
+        keys[j] = i < n ? imp_key(imp[g0 + i]) : 0u;
+    }
+    // frames of no segment in front of this one, and behind the last
+    for (uint32_t i = (seg ? c.fe[seg - 1] * (uint32_t)per : 0u) + tid; i < g0; i += 1024) mask[i] = 0;
+    if (seg + 1 == (int)c.n) for (uint32_t i = g0 + n + tid; i < (uint32_t)F * (uint32_t)per; i += 1024) mask[i] = 0;
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)wave_prefix(lane < seg ? min(c.k[lane], (c.fe[lane] - c.fb[lane]) * (uint32_t)per) : 0u), 63);
+    if (seg + 1 == (int)c.n && tid == 0) *n_sel = first + k;
+    uint32_t T = 0xFFFFFFFFu, budget = 0;                      // no key reaches 0xFFFFFFFF
+    if (k) {
+        uint32_t prefix = 0, remaining = k;
+        for (int pass = 0; pass < 3; ++pass) {
+            const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+            const uint32_t digit = pass == 2 ? 1023u : 2047u, hi_mask = pass == 0 ? 0u : (0xFFFFFFFFu << (pass == 1 ? 21 : 10));
+            hist[tid] = 0; hist[tid + 1024] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < KREG; ++j) {
+                const uint32_t i = (uint32_t)j * 1024u + tid;
+                if (i < n && (keys[j] & hi_mask) == prefix) atomicAdd(&hist[keys[j] >> shift & digit], 1u);
+            }
+            __syncthreads();
+            pick_bin(hist, shift, prefix, remaining, s_wtot, &s_prefix, &s_remaining);
+            prefix = s_prefix; remaining = s_remaining;
+        }
+        T = prefix; budget = remaining;
+    }
+#pragma unroll
+    for (int j = 0; j < KREG; ++j) {
+        const bool in = (uint32_t)j * 1024u + tid < n;
+        const uint32_t gt = (uint32_t)__popcll(__ballot(in && keys[j] > T)), eq = (uint32_t)__popcll(__ballot(in && keys[j] == T));
+        if (lane == 0) s_cnt[j * 16 + wave] = gt | eq << 16;
+    }
+    __syncthreads();
+    // every wave sums up all 256 counts in order of the keys: lane l has four of them, from wave l % 4 * 4 of row l / 4 on
+    static_assert(KREG == 16, "four counts a lane");
+    const uint4 v = ((const uint4*)s_cnt)[lane];
+    const uint32_t x0 = wave_prefix(v.x + v.y + v.z + v.w) - (v.x + v.y + v.z + v.w), x1 = x0 + v.x, x2 = x1 + v.y, x3 = x2 + v.z;
+    const uint32_t before = (wave & 3) == 0 ? x0 : (wave & 3) == 1 ? x1 : (wave & 3) == 2 ? x2 : x3;
+    const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int j = 0; j < KREG; ++j) {
+        const uint32_t i = (uint32_t)j * 1024u + tid;
+        if ((uint32_t)j * 1024u >= n) break;                   // uniform over the workgroup
+        const bool gt = i < n && keys[j] > T, eq = i < n && keys[j] == T;
+        const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)before, j * 4 + (wave >> 2));
+        const uint32_t ties = (b >> 16) + (uint32_t)__popcll(__ballot(eq) & below);
+        const uint32_t at = first + (b & 0xFFFFu) + (uint32_t)__popcll(__ballot(gt) & below) + min(ties, budget);
+        const bool sel = gt || (eq && ties < budget);
+        if (i < n) mask[g0 + i] = sel ? 1 : 0;
+        if (sel) list[at] = g0 + i;
+    }
+}
+
 // INLINE: the call's segments are all in c (seg_par is not read), and the frames without a segment get their
 // counts (0) here; otherwise k_upload_segments has written seg_par and frame_seg.
 template <bool INLINE>
@@ -108,17 +197,7 @@ __global__ __launch_bounds__(1024) void k_select_kth(seg_chunk c, int F, const f
                     }
                 }
                 __syncthreads();
-                // bin t holds the k-th key iff  above(t) < remaining <= above(t) + hist[t],  above(t) = sum of
-                // the bins over t.  Thread t holds the bins 2047 - 2t and 2046 - 2t, so that is a prefix sum.
-                const uint32_t b1 = BINS - 1 - 2 * tid, h1 = hist[b1], h0 = hist[b1 - 1], incl = wave_prefix(h1 + h0);
-                if (lane == 63) s_wtot[wave] = incl;
-                __syncthreads();
-                const uint32_t tot = wave_prefix(s_wtot[lane & 15]);           // lanes 0..15: inclusive sums of the waves' totals
-                const uint32_t above1 = incl - h1 - h0 + (wave ? (uint32_t)__builtin_amdgcn_readlane((int)tot, __builtin_amdgcn_readfirstlane(wave ? wave - 1 : 0)) : 0u);
-                const uint32_t above0 = above1 + h1;
-                if (above1 < remaining && remaining <= above1 + h1) { s_prefix = prefix | (b1 << shift); s_remaining = remaining - above1; }
-                if (above0 < remaining && remaining <= above0 + h0) { s_prefix = prefix | ((b1 - 1) << shift); s_remaining = remaining - above0; }
-                __syncthreads();
+                pick_bin(hist, shift, prefix, remaining, s_wtot, &s_prefix, &s_remaining);
                 prefix = s_prefix; remaining = s_remaining;
             }
             T = prefix; budget = remaining;
@@ -273,6 +352,18 @@ __global__ __launch_bounds__(256) void k_upload_segments(seg_chunk c, int per, i
     }
 }
 
+// k_select_once: queues that stay in registers, and few enough macroblocks outside the segments for one workgroup to clear
+static bool in_one_launch(const rh_segment* segs, int nseg, int mode, int F, int per)
+{
+    if (mode != RH_TOPK || nseg < 1 || nseg > 64) return false;
+    uint32_t longest = 0, covered = 0;                       // frames
+    for (int i = 0; i < nseg; ++i) {
+        const uint32_t len = segs[i].frame_end - segs[i].frame_begin;
+        longest = longest > len ? longest : len; covered += len;
+    }
+    return (uint64_t)longest * (uint64_t)per <= KREG * 1024u && (uint64_t)((uint32_t)F - covered) * (uint64_t)per <= 65536u;
+}
+
 hipError_t rh_enqueue_select(hipStream_t stream, const rh_select_scratch& sc, const float* imp, int F, int per,
                                  const rh_segment* segs, int nseg, int mode, uint8_t* mask, uint32_t* list, uint32_t* n_sel)
 {
@@ -284,6 +375,11 @@ hipError_t rh_enqueue_select(hipStream_t stream, const rh_select_scratch& sc, co
             c.fb[i] = g.frame_begin; c.fe[i] = g.frame_end; c.k[i] = g.k; memcpy(&c.thr[i], &g.thr, 4);
         }
     };
+    if (in_one_launch(segs, nseg, mode, F, per)) {
+        fill(0);
+        hipLaunchKernelGGL(k_select_once, dim3(nseg), dim3(1024), 0, stream, c, F, imp, per, mask, list, n_sel);
+        return hipGetLastError();
+    }
     if (nseg <= 64) {                                        // one launch less: 5 us with its gap
         fill(0);
         if (nseg > 0)
@@ -329,8 +425,8 @@ rh_status rh_launch_select(rh_ctx* ctx, const float* imp, int F, const rh_segmen
     rh_status st;
     if (const char* msg = rh_check_select_args(imp, F, segs, nseg, mode, mask, list, n_sel, &st))
         RH_FAIL(ctx, st, "rh_select_regions: %s", msg);
-    const int n_up = nseg > 64 ? (nseg + 63) / 64 : 0;
-    rh_prof_scope ps(ctx, RH_PROF_SELECT, n_up + (nseg > 0 ? 2 : 1));
+    const int n_up = nseg > 64 ? (nseg + 63) / 64 : 0, once = in_one_launch(segs, nseg, mode, F, ctx->per);
+    rh_prof_scope ps(ctx, RH_PROF_SELECT, once ? 1 : n_up + (nseg > 0 ? 2 : 1));
     const rh_select_scratch sc = {ctx->frame_seg, ctx->seg_par, ctx->seg_T, ctx->frame_nsel, ctx->frame_ties};
     RH_HIP(ctx, rh_enqueue_select(ctx->stream, sc, imp, F, ctx->per, segs, nseg, mode, mask, list, n_sel));
     return RH_OK;
