@@ -644,6 +644,16 @@ __device__ __forceinline__ u64 rows_or(u64 v)
     return row_of(v, 63);
 }
 
+// The sum of all lanes' values
+__device__ __forceinline__ uint32_t lane_sum(uint32_t v)
+{
+#define STEP(ctrl, rows) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xF, false)
+    STEP(0x111 /* row_shr:1 */, 0xF); STEP(0x112, 0xF); STEP(0x114, 0xF); STEP(0x118, 0xF);
+    STEP(0x142 /* row_bcast:15 */, 0xA); STEP(0x143 /* row_bcast:31 */, 0xC);
+#undef STEP
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 struct plan_args {
     const uint8_t* mask; const float* imp; const uint32_t* list; const uint32_t* n_sel;
     int F, mbw, mbh, conn, T, sort_policy, halo, S, max_bins, free_cap, rotate;
@@ -797,23 +807,34 @@ __global__ __launch_bounds__(PF_THREADS) void k_plan_fused(plan_args a)
     if (keys_in_lds)
         for (uint32_t j = tid; j < n; j += PF_THREADS) { s_key[j] = ord_key(a.raw[j].key); s_id[j] = a.raw[j].id; }
     __syncthreads();
-    for (uint32_t i = tid; i < n; i += PF_THREADS) {
-        const rh_rawbox me = a.raw[i];
-        uint32_t rank = 0;
-        if (keys_in_lds) {
-            const u64 mk = ord_key(me.key);
-            uint32_t j = 0;
-            for (; j + 8 <= n; j += 8) {                     // eight independent LDS reads in flight
-                u64 k8[8]; uint32_t d8[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) { k8[u] = s_key[j + u]; d8[u] = s_id[j + u]; }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) rank += (k8[u] > mk || (k8[u] == mk && d8[u] < me.id)) ? 1u : 0u;
+    if (keys_in_lds) {
+        // a wave ranks two boxes at a time, its lanes compare them with 64 others each step (a thread per box, eight keys at a
+        // time: 27 us of 551 boxes, 7.5 of 139; their plans 314 -> 301 and 53 -> 49 us)
+        for (uint32_t i0 = wave * 2; i0 < n; i0 += PF_WAVES * 2) {
+            const uint32_t i1 = min(i0 + 1, n - 1u), d0 = s_id[i0], d1 = s_id[i1];
+            const u64 k0 = s_key[i0], k1 = s_key[i1];
+            uint32_t r0 = 0, r1 = 0;
+            for (uint32_t j = lane; j < n; j += 64) {
+                const u64 k = s_key[j]; const uint32_t id = s_id[j];
+                r0 += (k > k0 || (k == k0 && id < d0)) ? 1u : 0u;
+                r1 += (k > k1 || (k == k1 && id < d1)) ? 1u : 0u;
             }
-            for (; j < n; ++j) rank += (s_key[j] > mk || (s_key[j] == mk && s_id[j] < me.id)) ? 1u : 0u;
-        } else for (uint32_t j = 0; j < n; ++j) rank += box_before(a.raw[j].key, a.raw[j].id, me.key, me.id) ? 1u : 0u;
-        a.sorted[rank] = me; a.rank_of_id[me.id] = rank;
-        if (rank < PF_KEYS) s_sz[rank] = (uint32_t)me.wmb | ((uint32_t)me.hmb << 16);
+            r0 = lane_sum(r0 | r1 << 16);                    // at most PF_KEYS each
+            const uint32_t rank = lane ? r0 >> 16 : r0 & 0xFFFFu;
+            const rh_rawbox* me = a.raw + min(i0 + lane, n - 1u);
+            if (i0 + lane < n && lane < 2) {
+                a.sorted[rank] = *me; a.rank_of_id[me->id] = rank;
+                s_sz[rank] = (uint32_t)me->wmb | ((uint32_t)me->hmb << 16);
+            }
+        }
+    } else {
+        for (uint32_t i = tid; i < n; i += PF_THREADS) {
+            const rh_rawbox me = a.raw[i];
+            uint32_t rank = 0;
+            for (uint32_t j = 0; j < n; ++j) rank += box_before(a.raw[j].key, a.raw[j].id, me.key, me.id) ? 1u : 0u;
+            a.sorted[rank] = me; a.rank_of_id[me.id] = rank;
+            if (rank < PF_KEYS) s_sz[rank] = (uint32_t)me.wmb | ((uint32_t)me.hmb << 16);
+        }
     }
     __threadfence_block();
     __syncthreads();                                         // keys are dead: the free list takes their place
