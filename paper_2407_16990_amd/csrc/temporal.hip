@@ -75,17 +75,27 @@ __device__ __forceinline__ uint64_t tr_edge(int ly)
 // other end of one.
 __device__ __forceinline__ uint64_t tr_listed(int ly) { return ly == 0 ? ~0ull : 0x8000000000000001ull; }
 
+// Orders the LDS accesses of one wave: what lanes wrote before it is what any lane reads after it.
+__device__ __forceinline__ void tr_wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Bound by latencies, so by the waves in flight: eight workgroups a CU (20.5 KB of LDS, with the residuals in room of their own, were
+// 272 bytes too much for the eighth), and few enough scalar registers for eight waves a SIMD: 300 frames of 480 x 272 48.8 -> 45 us,
+// the three calls 98.7 -> 95.
 template <bool WIDE>
-__global__ __launch_bounds__(64 * TR_WAVES) void k_tr_init(const int16_t* __restrict__ res, tr_geom g, int tau,
+__global__ __launch_bounds__(64 * TR_WAVES, 8) void k_tr_init(const int16_t* __restrict__ res, tr_geom g, int tau,
                                                  uint32_t* __restrict__ label, uint32_t* __restrict__ area,
                                                  uint32_t* __restrict__ border, uint32_t* n_border,
                                                  uint32_t* __restrict__ roots, uint32_t* n_roots)
 {
     __shared__ uint32_t s_lab[TR_TILE_H * 64];
-    __shared__ uint32_t s_cnt[TR_TILE_H * 64];
+    __shared__ __attribute__((aligned(16))) uint32_t s_cnt[TR_TILE_H * 64];
     __shared__ unsigned long long s_mask[TR_TILE_H];
     __shared__ __attribute__((aligned(16))) uint32_t s_mine[4];
-    __shared__ __attribute__((aligned(16))) int16_t s_res[WIDE ? TR_TILE_H * 64 : 8];
     const int lane = threadIdx.x & 63, ly0 = (threadIdx.x >> 6) * TR_ROWS;
     const int tx0 = blockIdx.x * 64, ty0 = blockIdx.y * TR_TILE_H;
     const int f = blockIdx.z, x = tx0 + lane;
@@ -102,13 +112,16 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_init(const int16_t* __rest
         const int prow = ty0 + (int)(threadIdx.x >> 3), px = tx0 + (int)(threadIdx.x & 7) * 8;
         uint4 v = make_uint4(0, 0, 0, 0);
         if (prow < g.H && px < g.W) v = *(const uint4*)(res + base + (size_t)prow * g.W + px);
-        ((uint4*)s_res)[threadIdx.x] = v;
-        __syncthreads();
+        // A wave's threads fetch just the wave's rows, so these pass through its part of s_cnt without a barrier.
+        int16_t* rows = (int16_t*)(s_cnt + ly0 * 64);
+        ((uint4*)rows)[lane] = v;
+        tr_wave_sync();
 #pragma unroll
         for (int j = 0; j < TR_ROWS; ++j) {
-            const int r = s_res[(ly0 + j) * 64 + lane];
+            const int r = rows[j * 64 + lane];
             fg[j] = (r < 0 ? -r : r) > tau;                      // zero-filled outside the frame
         }
+        tr_wave_sync();                                          // before the counts are cleared
     } else {
 #pragma unroll
         for (int j = 0; j < TR_ROWS; ++j) fg[j] = tr_changed(res, base, ty0 + ly0 + j, x, g.H, g.W, tau);   // 0 outside the frame
