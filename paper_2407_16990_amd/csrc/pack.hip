@@ -77,8 +77,10 @@ __global__ __launch_bounds__(256) void k_gather(const uint8_t* __restrict__ fram
     __shared__ uint32_t s_cnt;
     const uint32_t n_boxes = counts[0], n_bins = counts[1];
     const int nb = (S + RB - 1) / RB;                                      // bands per bin
-    // A unit is a run of bpu bands of one bin; the box list is scanned once per unit.  Small batches
-    // take one band per unit (enough units to occupy the chip), large ones a whole bin.
+    // A unit is a run of bpu bands of one bin; the box list is scanned once per unit.  Small batches take one band per
+    // unit (enough units to occupy the chip), large ones two: half the scans, and still many workgroups a CU.  Whole call of
+    // select, plan and gather, us, one / two / four bands / whole bins: 538 bins of 128 x 128 266 / 268 / 272 / 289, 1077: 778 / 771 / 776 / 780,
+    // 440 of 192 x 192 278 / 274 / 278 / 345, 335 with 2 042 boxes 712 / 711 / 723 / 742; 134 bins: level.
     const int bpu = (uint64_t)n_bins * (uint64_t)nb <= 2048u ? 1 : 2;
     const int upb = (nb + bpu - 1) / bpu;                                  // units per bin
     const int tid = threadIdx.x;
