@@ -15,8 +15,8 @@
 // layers pad with zeros at their own tensor's border, so the intermediate tensors outside the
 // image are zero, not "what the previous conv would give there": Wc differs for the pixels of the
 // outermost low-resolution ring.  There are 9 position classes (top / middle / bottom row x left
-// / middle / right column); the main kernel computes every pixel with the middle class, a small
-// second kernel recomputes the ring with the class weights.
+// / middle / right column); the interior is computed with the middle class, the ring pixel by pixel with the
+// weights of its class.
 //
 // Main kernel: implicit GEMM on v_mfma_f32_32x32x16_bf16, D[row][pixel], rows = (i, j, co) of one
 // 32-row chunk (x4: two chunks of two output rows i each; x2, x3: one chunk), N = 32 pixels of an
@@ -43,13 +43,14 @@
 
 struct fold_args {
     const __bf16* in;        // t: [N][H][W][CIN]
-    const uint4* wp;         // main kernel: middle-class weights [chunk][tap][ks][lane]; ring kernel: all classes
+    const uint4* wp;         // [class][chunk][tap][ks][lane]
     const float* bias;       // [class][chunk][32]
     float* out;              // [N][s*H][s*W][3]
     const uint32_t* n_valid;
     int N, H, W;
     int s, n_chunks, rows, ipc;   // scale, chunks, valid rows per chunk, output rows i per chunk
     int rev;
+    int ring;                // 1: the outermost ring with its classes' weights; 0: it is not needed (no pixel of it is pasted)
     const uint32_t* tile_list;   // the tiles to compute (needed-region mode), or null: all tiles
     const uint32_t* n_list;
 };
@@ -86,6 +87,65 @@ __device__ __forceinline__ void fold_each_step(F& f)
     if constexpr (I < N) { f(std::integral_constant<int, I>{}); fold_each_step<N, I + 1>(f); }
 }
 
+// The outermost ring of every image, with the weights of its position class: wave `w` of `waves` takes every waves-th group of
+// 32 ring pixels and chunk, operands straight from global memory (the ring is 3 % of the pixels).
+// Classes are numbered 3 * (0 top / 1 middle / 2 bottom) + (0 left / 1 middle / 2 right).
+// Two rows of taps of an edge pixel lie outside the image (or two columns): 15 taps of 25 are left, 9 at a corner, three in flight.
+// A launch of its own behind the main kernel took 45 us on 76 bins of 128 x 128 and 9 on three; as the work that the main
+// kernel's waves do when they are out of tiles (idle workgroups at once): whole calls of EDSR x3 with one block on three bins 59.6 -> 51.6 us,
+// x4 on 76 566 -> 563, on 128 943 -> 938, on 16 of 64 x 64 60.0 -> 60.6.
+template <int CIN>
+__device__ __forceinline__ void fold_ring(const fold_args& a, int n_img, long w, long waves)
+{
+    constexpr int KS = CIN / 16;
+    const int lane = threadIdx.x & 63, lx = lane & 31, hi = lane >> 5;
+    const long row_g = ((long)n_img * (a.W - 2) + 31) / 32, col_g = ((long)n_img * (a.H - 2) + 31) / 32, corner_g = (n_img + 31) / 32;
+    const long groups = 2 * row_g + 2 * col_g + 4 * corner_g;
+    for (long u = w; u < groups * a.n_chunks; u += waves) {      // uniform over the wave
+        const int chunk = (int)(u / groups);
+        long g = u - chunk * groups;
+        int kind = 0;                                        // top, bottom, left, right edges, then the corners
+        for (long size; g >= (size = kind < 2 ? row_g : kind < 4 ? col_g : corner_g); ++kind) g -= size;
+        const int per = kind < 2 ? a.W - 2 : kind < 4 ? a.H - 2 : 1;      // ring pixels of this class per image
+        const bool top = kind == 0 || kind == 4 || kind == 5, bottom = kind == 1 || kind >= 6;
+        const bool left = kind == 2 || kind == 4 || kind == 6, right = kind == 3 || kind == 5 || kind == 7;
+        const int cls = (top ? 0 : bottom ? 6 : 3) + (left ? 0 : right ? 2 : 1);
+        const long q = g * 32 + lx;
+        const bool valid = q < (long)n_img * per;
+        const int n = valid ? (int)(q / per) : 0, k = valid ? (int)(q - (long)n * per) : 0;
+        const int y = top ? 0 : bottom ? a.H - 1 : 1 + k, x = left ? 0 : right ? a.W - 1 : 1 + k;
+        const uint4* wp = a.wp + (size_t)(cls * a.n_chunks + chunk) * (25 * KS * 64);
+        const float* bias = a.bias + (cls * a.n_chunks + chunk) * 32;
+        f32x16 acc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = bias[(e >> 2) * 8 + hi * 4 + (e & 3)];
+        const __bf16* img = a.in + (size_t)n * a.H * a.W * CIN;
+        const int ky0 = top ? 2 : 0, kx0 = left ? 2 : 0, nkx = kind < 2 ? 5 : 3, taps = kind < 4 ? 15 : 9;
+        uint4 A[3][KS], B[3][KS];
+        auto load_tap = [&](int t, uint4 (&At)[KS], uint4 (&Bt)[KS]) __attribute__((always_inline)) {
+            const int ky = ky0 + t / nkx, kx = kx0 + t % nkx, yy = y + ky - 2, xx = x + kx - 2;
+            const bool ok = valid && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                At[ks] = wp[((ky * 5 + kx) * KS + ks) * 64 + lane];
+                Bt[ks] = ok ? *(const uint4*)(img + ((size_t)yy * a.W + xx) * CIN + ks * 16 + hi * 8) : make_uint4(0, 0, 0, 0);
+            }
+        };
+#pragma unroll
+        for (int t = 0; t < 3; ++t) load_tap(t, A[t], B[t]);
+        for (int t0 = 0; t0 < taps; t0 += 3) {
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)&A[t][ks], *(const bf16x8*)&B[t][ks], acc, 0, 0, 0);
+                load_tap(min(t0 + t + 3, taps - 1), A[t], B[t]);
+            }
+        }
+        if (valid) fold_store(a, acc, n, y, x, chunk, hi);
+    }
+}
+
 // LDS of the main kernel: a patch, room, a patch.  The weights pass through room and second patch on their way to registers;
 // a tile's partial sums take the place of its patch and room.
 template <int CIN>
@@ -119,7 +179,7 @@ __global__ __launch_bounds__(512) void k_conv_fold(fold_args a)
     const int chunk_begin = deal ? local % a.n_chunks : 0, chunk_end = deal ? chunk_begin + 1 : a.n_chunks;
     // the first chunk's weights are on their way before the image count is known
     auto load_weights = [&](int chunk) __attribute__((always_inline)) {
-        lds_dma<512, L::WBYTES>(lds + L::PATCHB, a.wp + (size_t)chunk * (L::WBYTES / 16), wave, lane);
+        lds_dma<512, L::WBYTES>(lds + L::PATCHB, a.wp + (size_t)(4 * a.n_chunks + chunk) * (L::WBYTES / 16), wave, lane);      // the middle class
     };
     load_weights(chunk_begin);
     const int n_img = min((int)n_found, a.N);
@@ -182,7 +242,7 @@ __global__ __launch_bounds__(512) void k_conv_fold(fold_args a)
         }
         f32x16 biasv;                                      // lane holds rows 8q + 4hi + e in [4q + e]; in the sums of the first k-step
 #pragma unroll
-        for (int e = 0; e < 16; ++e) { biasv[e] = a.bias[chunk * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)]; biasv[e] = wk == 0 ? biasv[e] : 0.0f; }
+        for (int e = 0; e < 16; ++e) { biasv[e] = a.bias[(4 * a.n_chunks + chunk) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)]; biasv[e] = wk == 0 ? biasv[e] : 0.0f; }
         lds_dma_wait();                                    // weights and first patch
         __syncthreads();
         bf16x8 A[25];
@@ -271,76 +331,17 @@ __global__ __launch_bounds__(512) void k_conv_fold(fold_args a)
                 else add_up(std::integral_constant<int, 1>{});
             }
             const int x = x0 + (l & 31), y = y0 + wr * RW + wk;
-            if (y < a.H && x < a.W) fold_store(a, sum, n, y, x, chunk, l >> 5);
+            const int off = a.ring;                        // the ring's pixels are another wave's
+            if (y >= off && y < a.H - off && x >= off && x < a.W - off) fold_store(a, sum, n, y, x, chunk, l >> 5);
             lds_barrier();                                 // sums read, next patch visible
             patch = other;
         }
     }
-}
-
-// The outermost ring of every image again, with the weights of its position class.  One wave per
-// (class, 32 ring pixels, chunk): operands straight from global memory (the ring is 3 % of the pixels).
-// Classes are numbered 3 * (0 top / 1 middle / 2 bottom) + (0 left / 1 middle / 2 right).
-template <int CIN>
-__global__ __launch_bounds__(64) void k_fold_ring(fold_args a)
-{
-    constexpr int KS = CIN / 16;
-    const int lane = threadIdx.x, lx = lane & 31, hi = lane >> 5;
-    const int chunk = blockIdx.z;
-    const int cls_tab[8] = {1, 7, 3, 5, 0, 2, 6, 8};       // top, bottom, left, right edges, then the corners
-    const int kind = blockIdx.y, cls = cls_tab[kind];
-    const int n_img = a.n_valid ? min((int)*a.n_valid, a.N) : a.N;
-    const int per = kind < 2 ? a.W - 2 : (kind < 4 ? a.H - 2 : 1);      // ring pixels of this class per image
-    const long total = (long)n_img * per;
-    if ((long)blockIdx.x * 32 >= total) return;
-    const long q = (long)blockIdx.x * 32 + lx;
-    const bool valid = q < total;
-    const int n = valid ? (int)(q / per) : 0, k = valid ? (int)(q - (long)n * per) : 0;
-    int y, x;
-    switch (kind) {
-        case 0: y = 0; x = 1 + k; break;
-        case 1: y = a.H - 1; x = 1 + k; break;
-        case 2: y = 1 + k; x = 0; break;
-        case 3: y = 1 + k; x = a.W - 1; break;
-        case 4: y = 0; x = 0; break;
-        case 5: y = 0; x = a.W - 1; break;
-        case 6: y = a.H - 1; x = 0; break;
-        default: y = a.H - 1; x = a.W - 1; break;
+    if (a.ring) {
+        // workgroups that have had a tile more, or one at all, come last
+        const int n_ring = a.n_valid ? min((int)*a.n_valid, a.N) : a.N, place = deal ? wg * a.n_chunks + chunk_begin : wg;
+        fold_ring<CIN>(a, n_ring, (long)((int)gridDim.x - 1 - place) + (long)wave * gridDim.x, 8l * gridDim.x);
     }
-    const uint4* wp = a.wp + (size_t)(cls * a.n_chunks + chunk) * (25 * KS * 64);
-    const float* bias = a.bias + (cls * a.n_chunks + chunk) * 32;
-    f32x16 acc;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = bias[(e >> 2) * 8 + hi * 4 + (e & 3)];
-    const __bf16* img = a.in + (size_t)n * a.H * a.W * CIN;
-    // one tap row (5 taps x KS k-steps) of operands is requested while the previous one is multiplied:
-    // a wave that waited for every tap's loads in turn spent 100 load latencies per pixel group
-    uint4 A[2][5][KS], B[2][5][KS];
-    auto load_row = [&](int ky, uint4 (&Ar)[5][KS], uint4 (&Br)[5][KS]) __attribute__((always_inline)) {
-        const int yy = y + ky - 2;
-        const bool row_ok = valid && yy >= 0 && yy < a.H;
-#pragma unroll
-        for (int kx = 0; kx < 5; ++kx) {
-            const int xx = x + kx - 2;
-            const bool ok = row_ok && xx >= 0 && xx < a.W;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                Ar[kx][ks] = wp[((ky * 5 + kx) * KS + ks) * 64 + lane];
-                Br[kx][ks] = ok ? *(const uint4*)(img + ((size_t)yy * a.W + xx) * CIN + ks * 16 + hi * 8) : make_uint4(0, 0, 0, 0);
-            }
-        }
-    };
-    load_row(0, A[0], B[0]);
-#pragma unroll
-    for (int ky = 0; ky < 5; ++ky) {
-        if (ky + 1 < 5) load_row(ky + 1, A[(ky + 1) & 1], B[(ky + 1) & 1]);
-#pragma unroll
-        for (int kx = 0; kx < 5; ++kx)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)&A[ky & 1][kx][ks], *(const bf16x8*)&B[ky & 1][kx][ks], acc, 0, 0, 0);
-    }
-    if (valid) fold_store(a, acc, n, y, x, chunk, hi);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -529,22 +530,16 @@ static hipError_t launch_fold(rh_ctx* ctx, const fold_args& a)
         if (e != hipSuccess) return e;
         attr_done[ctx->device] = true;
     }
-    fold_args m = a;                                       // main kernel: the middle class (number 4)
-    m.wp = a.wp + (size_t)4 * a.n_chunks * (25 * (CIN / 16) * 64);
-    m.bias = a.bias + 4 * a.n_chunks * 32;
+    // Needed-region mode: a pasted macroblock lies at least `halo` pixels inside its box, hence inside
+    // the bin, so with a halo no pasted pixel is on the outermost ring.
+    fold_args m = a;
+    m.ring = !(a.tile_list && ctx->cfg.halo >= 1);
     if (a.tile_list) hipLaunchKernelGGL((k_conv_fold<CIN, true>), dim3(ctx->n_cu), dim3(512), lds, ctx->stream, m);
     else hipLaunchKernelGGL((k_conv_fold<CIN, false>), dim3(ctx->n_cu), dim3(512), lds, ctx->stream, m);
-    // Needed-region mode: a pasted macroblock lies at least `halo` pixels inside its box, hence inside
-    // the bin, so with a halo no pasted pixel is on the outermost ring and the ring pass has nothing to add.
-    if (a.tile_list && ctx->cfg.halo >= 1) return hipGetLastError();
-    const long longest = (long)a.N * (a.W > a.H ? a.W : a.H);
-    const long groups = (longest + 31) / 32;
-    if (groups > 0x7FFFFFFFL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_fold_ring<CIN>, dim3((unsigned)groups, 8, a.n_chunks), dim3(64), 0, ctx->stream, a);
     return hipGetLastError();
 }
 
-// t: the body's output [N][H][W][C] bf16 -> raw network output fp32 [N][sH][sW][3]; two launches (one: see launch_fold).
+// t: the body's output [N][H][W][C] bf16 -> raw network output fp32 [N][sH][sW][3]; one launch.
 rh_status rh_launch_fold(rh_ctx* ctx, const __bf16* t, float* out, int N, int H, int W, const uint32_t* n_valid, int rev,
                          const uint32_t* tile_list, const uint32_t* n_list)
 {

@@ -586,7 +586,7 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
             }
             if (fold) {
                 rh_prof_end(ctx, n_conv);
-                rh_prof_scope ps_(ctx, RH_PROF_CONV_LAST, ctx->nd_places && ctx->cfg.halo >= 1 ? 1 : 2);      // rh_launch_fold
+                rh_prof_scope ps_(ctx, RH_PROF_CONV_LAST);
                 // needed-region mode: the composed tail's output is needed on the pasted macroblocks only (radius 0)
                 st = rh_launch_fold(ctx, t, out, N, H, W, n_valid, ctx->conv_parity ^= 1,
                                     ctx->nd_places ? ctx->need_lists : nullptr, ctx->nd_places ? ctx->need_cnt : nullptr);
