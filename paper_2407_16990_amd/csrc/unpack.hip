@@ -16,7 +16,7 @@ __global__ __launch_bounds__(256) void k_identity_places(rh_mbplace* __restrict_
 }
 
 // Bilinear base + paste for integer scale S, one launch.  A workgroup writes a strip of NMBX
-// macroblocks (one macroblock row tall): the 64 lanes of a wave lie side by side along x, 4 output
+// macroblocks (one macroblock row tall; a quarter of it where there are few): the 64 lanes of a wave lie side by side along x, 4 output
 // pixels (12 bytes) each, so a wave instruction writes up to 768 contiguous bytes; the 4 waves
 // split the 16 input rows.
 // Input tile (18 rows, clamped at the frame edge): fetched as aligned 4-byte words, every thread
@@ -34,9 +34,11 @@ __global__ __launch_bounds__(256) void k_identity_places(rh_mbplace* __restrict_
 // pitch that is not a multiple of 4 bytes; those blocks go pixel by pixel.  A place is honoured
 // when the in-frame part of its block lies inside the enhanced image (for whole macroblocks:
 // px + 16 <= iw and py + 16 <= ih), otherwise the macroblock stays bilinear.
+// RPW: input rows per wave.  With 4 a workgroup does a whole strip; a batch of few strips is a chain of a wave's rows, each
+// with the latency of its enhanced values, so there a wave has one row and a strip four workgroups.
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
-template <int S, bool EDGE>
+template <int S, bool EDGE, int RPW>
 __global__ __launch_bounds__(256) void k_unpack(const uint8_t* __restrict__ lr, int H, int W, int mbw,
                                                 const float* __restrict__ enh, int n_img, int ih, int iw,
                                                 const rh_mbplace* __restrict__ places,
@@ -46,11 +48,12 @@ __global__ __launch_bounds__(256) void k_unpack(const uint8_t* __restrict__ lr, 
     constexpr int B = RH_MB * S, D = 2 * S, GPM = B / 4, NMBX = 64 / GPM, LANES = NMBX * GPM;
     constexpr int TWID = RH_MB * NMBX + 2;                   // tile width in pixels
     constexpr int TPD = (TWID * 3 + 3 + 3) / 4 + 1;          // 4-byte words per tile row, any byte shift
-    constexpr int NLD = (18 * TPD + 255) / 256;              // words per thread
-    __shared__ uint32_t tile[18][TPD];
+    constexpr int PARTS = 4 / RPW, TROWS = 4 * RPW + 2;      // workgroups a strip, rows of the tile
+    constexpr int NLD = (TROWS * TPD + 255) / 256;           // words per thread
+    __shared__ uint32_t tile[TROWS][TPD];
     __shared__ float q255[256];
-    const int strip = blockIdx.x, my = blockIdx.y, f = blockIdx.z, tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6, mbh = gridDim.y;
+    const int strip = blockIdx.x, my = blockIdx.y / PARTS, part = blockIdx.y % PARTS, f = blockIdx.z, tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6, mbh = gridDim.y / PARTS, row0 = RH_MB * my + part * (4 * RPW);      // row0: the workgroup's first input row
     const int lx0 = RH_MB * NMBX * strip - 1;                // frame column of tile pixel 0 (may be -1)
     const int xs = max(lx0, 0), xe = min(lx0 + TWID, W);     // columns [xs, xe) are fetched
     // ---- issue the tile's loads ----
@@ -59,8 +62,8 @@ __global__ __launch_bounds__(256) void k_unpack(const uint8_t* __restrict__ lr, 
     for (int j = 0; j < NLD; ++j) {
         const int idx = j * 256 + tid, row = idx / TPD, d = idx - row * TPD;
         tw[j] = 0;
-        if (row < 18) {
-            const int y = min(max(RH_MB * my - 1 + row, 0), H - 1);
+        if (row < TROWS) {
+            const int y = min(max(row0 - 1 + row, 0), H - 1);
             const uintptr_t beg = (uintptr_t)lr + (((size_t)f * H + y) * W + xs) * 3, end = beg + (size_t)(xe - xs) * 3;
             const uintptr_t wa = (beg & ~(uintptr_t)3) + 4u * (uintptr_t)d;      // holds at least one byte of the row
             if (wa < end) tw[j] = *(const uint32_t*)wa;
@@ -95,7 +98,7 @@ __global__ __launch_bounds__(256) void k_unpack(const uint8_t* __restrict__ lr, 
 #pragma unroll
     for (int j = 0; j < NLD; ++j) {
         const int idx = j * 256 + tid;
-        if (idx < 18 * TPD) (&tile[0][0])[idx] = tw[j];
+        if (idx < TROWS * TPD) (&tile[0][0])[idx] = tw[j];
     }
     q255[tid] = __fdiv_rn((float)tid, 255.0f);
     __syncthreads();
@@ -128,7 +131,7 @@ __global__ __launch_bounds__(256) void k_unpack(const uint8_t* __restrict__ lr, 
     }
     // horizontal sums of one tile row for the 4 pixels x 3 channels, as 6 packed pairs (k, k+6)
     auto hsum = [&](int row, u16x2 (&h)[6]) __attribute__((always_inline)) {
-        const int y = min(max(RH_MB * my - 1 + row, 0), H - 1);
+        const int y = min(max(row0 - 1 + row, 0), H - 1);
         const uint8_t* t = (const uint8_t*)&tile[row][0] + ((row_sh0 + y * pitch_sh) & 3);
         unsigned short v[12];
 #pragma unroll
@@ -142,12 +145,12 @@ __global__ __launch_bounds__(256) void k_unpack(const uint8_t* __restrict__ lr, 
     const bool edge = EDGE && (fh < B || fw < B || ((HW * 3) & 3));
     uint8_t* dst = hr + (((size_t)f * H * S + (size_t)my * B) * HW + (size_t)mx * B + gx) * 3;
     u16x2 h0[6], h1[6], h2[6];                             // input rows r-1, r, r+1 (tile rows r, r+1, r+2)
-    const int r0 = wave * 4;
-    hsum(r0, h0); hsum(r0 + 1, h1);
+    const int t0 = wave * RPW;                             // the wave's first tile row
+    hsum(t0, h0); hsum(t0 + 1, h1);
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-        const int r = r0 + rr;
-        hsum(r + 2, h2);
+    for (int rr = 0; rr < RPW; ++rr) {
+        const int r = part * (4 * RPW) + t0 + rr;          // input row of the macroblock
+        hsum(t0 + rr + 2, h2);
 #pragma unroll
         for (int j = 0; j < S; ++j) {
             const int ny = 2 * j + 1 - S;                  // relative to input row r, in units of 1/D
@@ -253,10 +256,17 @@ rh_status rh_launch_unpack(rh_ctx* ctx, const float* enh, int n_img, int ih, int
     rh_prof_scope ps(ctx, RH_PROF_UNPACK, 1);
     const int S = ctx->cfg.net.scale;
     const bool cut = ctx->cfg.frame_w % RH_MB || ctx->cfg.frame_h % RH_MB || ((ctx->cfg.frame_w * S * 3) & 3);
+    const int strips = (ctx->mbw + 64 / (4 * S) - 1) / (64 / (4 * S));
+    // A strip's work grows with the scale's square, and with it the number of strips that fill the chip either way.  Four rows / one
+    // row a wave, us: x4 of 480 x 272 (136 strips a frame), 1 frame 11.6 / 6.9, 4: 17.6 / 14.2, 16: 41.5 / 39.6, 32: 87.3 / 91.8; x3 of 640 x 360
+    // (184), 1 frame 17.1 / 9.0, 5: 23.4 / 20.1; x2 of 640 x 368 (115), 1 frame 8.5 / 6.6, 5: 12.7 / 11.9, 8: 15.4 / 16.7.  The
+    // line is at 640 strips for x2, 1 440 for x3 and 2 560 for x4.
+    const bool few = 8l * strips * ctx->mbh * F <= 5l * S * S * ctx->n_cu;
 #define LAUNCH_UNPACK(SC)                                                                                       \
-    do { if (cut) LAUNCH_UNPACK_E(SC, true); else LAUNCH_UNPACK_E(SC, false); } while (0)
-#define LAUNCH_UNPACK_E(SC, E)                                                                                  \
-    hipLaunchKernelGGL((k_unpack<SC, E>), dim3((ctx->mbw + (64 / (4 * SC)) - 1) / (64 / (4 * SC)), ctx->mbh, F), dim3(256), 0, \
+    do { if (cut && few) LAUNCH_UNPACK_E(SC, true, 1); else if (cut) LAUNCH_UNPACK_E(SC, true, 4);              \
+         else if (few) LAUNCH_UNPACK_E(SC, false, 1); else LAUNCH_UNPACK_E(SC, false, 4); } while (0)
+#define LAUNCH_UNPACK_E(SC, E, RPW)                                                                             \
+    hipLaunchKernelGGL((k_unpack<SC, E, RPW>), dim3(strips, ctx->mbh * (4 / (RPW)), F), dim3(256), 0,           \
                        ctx->stream, lr, ctx->cfg.frame_h, ctx->cfg.frame_w, ctx->mbw, enh, n_img, ih, iw, places,  \
                        n_places, total, hr, sel)
     if (S == 1) LAUNCH_UNPACK(1); else if (S == 2) LAUNCH_UNPACK(2); else if (S == 3) LAUNCH_UNPACK(3); else LAUNCH_UNPACK(4);

@@ -130,6 +130,31 @@ def test_plan_full_bins(F, S, T, max_bins, rotate):
     rh.close()
 
 
+# Paste with one and with four input rows a wave, both sides of the line between them (5/8 scale^2 strips a compute unit),
+# frames with cut macroblocks and row pitches of every alignment, turned boxes, floats of the pasted macroblocks
+@pytest.mark.parametrize("scale,w,h", [(1, 160, 48), (2, 160, 112), (3, 160, 112), (4, 192, 112), (1, 157, 45), (2, 150, 101), (3, 147, 107), (4, 185, 99)])
+@pytest.mark.parametrize("side", [0, 1])
+def test_unpack_rows_per_wave(scale, w, h, side):
+    mbw, mbh, nmb = -(-w // 16), -(-h // 16), 64 // (4 * scale)
+    strips = -(-mbw // nmb) * mbh
+    F = 5 * scale * scale * torch.cuda.get_device_properties(0).multi_processor_count // (8 * strips) + side
+    cfg = wl.replace(wl.config(3), n_frames=F, width=w, height=h, importance="uniform", frac=0.08, halo=3, bin_size=96)
+    r = np.random.default_rng(F)
+    frames = r.integers(0, 256, (F, h, w, 3), dtype=np.uint8)
+    net = wl.Net("plain", 16, 2, scale)
+    most = F * mbw * mbh // 20 + 8
+    rh = make_rh(wl.replace(cfg, net=net), wl.make_weights(net, 0, "fp32"), max_bins=most, precision="fp32", rotate=True)
+    imp = r.random((F, mbh, mbw), dtype=np.float32)
+    plan, po, (d_frames, _, _) = check_select_and_plan(rh, cfg, frames, imp, np.array([[0, F, F * mbw * mbh // 12]], dtype=np.uint32), max_bins=most, rotate=True)
+    out = (0.2 * r.standard_normal((plan.n_bins, 96 * scale, 96 * scale, 3))).astype(np.float32)
+    hr, sel = rh.unpack(torch.from_numpy(out).cuda(), po.places, po.counts[3:4], d_frames, want_sel=True)
+    o_hr, o_sel = oracle.unpack(frames, scale, out, plan.places, place_rot=plan.place_rot)
+    assert np.array_equal(hr.cpu().numpy(), o_hr)
+    # in [0, 1]: one division and one addition in fp32 on both sides, a few units of 2^-24 at most
+    assert np.abs(sel.cpu().numpy()[: len(plan.places)] - o_sel).max() <= 1e-6
+    rh.close()
+
+
 # Exact-border mode's pixel mask: sides that are not multiples of 32 (words and tiles cut), of 8, fewer than 32 pixels,
 # both resolutions (the second upsampling conv of x4 runs on twice the mask's grid), turned boxes, every topology
 @pytest.mark.parametrize("net,halo,S,rotate", [
