@@ -29,6 +29,7 @@
 
 #include "conv_mfma_common.h"
 
+#define FEW_UNITS 4
 #define PW 34
 #define LD_PAST 16                       // loads: sc1
 #define BODY_CLOSED 0x80000000u
@@ -184,8 +185,11 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
     // A unit's two phases: computes `cur`, then - while the other team computes - stores it, and fetches the next one's
     // patch where that is ready.  True: the last.
     int turn = 0;                                            // units of this team so far
-    auto unit = [&](auto skip_c) __attribute__((always_inline)) -> bool {
-        constexpr bool SKIP = decltype(skip_c)::value;
+    // FEW: no look from the compute phase and no early patch.  With up to FEW_UNITS units a workgroup and layer neither is in time,
+    // and the 11 loads of no bytes stood in the way of the words that others wait for: EDSR x4 on 128 x 128 bins, us, always with them / with
+    // this up to 4 units, 1 bin 276 / 254, 3: 296 / 268, 8: 409 / 394, 10: 498 / 460, 16: 666 / 654; with six units (24 bins) 930 / 964.
+    auto unit = [&](auto skip_c, auto few_c) __attribute__((always_inline)) -> bool {
+        constexpr bool SKIP = decltype(skip_c)::value, FEW = decltype(few_c)::value;
         f32x16 acc[RW][MT];
         uint4 sk[SKIP ? NOUT : 1];
         uint32_t kw[KEEP ? RW : 1];
@@ -277,11 +281,11 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
                     asm volatile("s_waitcnt vmcnt(%0)" :: "n"((SKIP ? 6 : 0) + (KEEP ? RW : 0)) : "memory");
                     mark_done(prev);
                 }
-                if (wave == 0) words = load_words(nu);
+                if (!FEW && wave == 0) words = load_words(nu);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (st == NSTEP - 2) {
-                if (wave == 0) {
+                if (!FEW && wave == 0) {
                     const bool ready = __builtin_amdgcn_ballot_w64(words >= (uint32_t)nu.layer) == ~0ull;
                     if (lane == 0) s_ready[team][(turn & 1) ^ 1] = ready;
                 }
@@ -298,7 +302,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
         __builtin_amdgcn_s_setprio(0);
         }
         // ---------------- the other team computes ----------------
-        const uint32_t ready0 = s_ready[team ^ 1][(turn + team) & 1], ready1 = s_ready[team][(turn & 1) ^ 1];
+        const uint32_t ready0 = FEW ? 0u : s_ready[team ^ 1][(turn + team) & 1], ready1 = FEW ? 0u : s_ready[team][(turn & 1) ^ 1];
         uint32_t again = 0;
         const bool at_end = front_layer >= a.layers;
         const bool none = nu.layer >= a.layers, early = !none && __builtin_amdgcn_readfirstlane(ready1);
@@ -322,7 +326,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
                 for (int r = 0; r < RW; ++r) {
                     const int u = (m * 4 + q) * RW + r;
 #pragma unroll
-                    for (int i = u * NPRE / NUNIT; i < (u + 1) * NPRE / NUNIT; ++i) load_piece(i, tt, rin, nu.y0, nu.x0);
+                    for (int i = u * NPRE / NUNIT; i < (u + 1) * NPRE / NUNIT && !FEW; ++i) load_piece(i, tt, rin, nu.y0, nu.x0);
                     uint2 pk;
                     pk.x = pack_bf16x2(acc[r][m][4 * q], acc[r][m][4 * q + 1]); pk.y = pack_bf16x2(acc[r][m][4 * q + 2], acc[r][m][4 * q + 3]);
                     if constexpr (!SKIP) { pk.x = relu_bf16x2(pk.x); pk.y = relu_bf16x2(pk.y); }
@@ -397,6 +401,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
     };
 
     if (team == 1) { body_barrier(); resident = 0; body_barrier(); }      // the first unit is the other team's
+    auto run = [&](auto few_c) __attribute__((always_inline)) {
     for (;;) {
         if (word_due && (cur.layer >= a.layers || !loaded)) {        // ahead of any wait
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -426,8 +431,11 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
             team_sync();
         }
         resident = cur.layer;
-        if (layer_skips(cur.layer) ? unit(std::integral_constant<bool, true>{}) : unit(std::integral_constant<bool, false>{})) break;
+        if (layer_skips(cur.layer) ? unit(std::integral_constant<bool, true>{}, few_c) : unit(std::integral_constant<bool, false>{}, few_c)) break;
     }
+    };
+    if (layer_units <= FEW_UNITS * (int)gridDim.x) run(std::integral_constant<bool, true>{});
+    else run(std::integral_constant<bool, false>{});
 }
 
 hipError_t rh_launch_conv_body(hipStream_t stream, int device, int n_cu, body_args a)
