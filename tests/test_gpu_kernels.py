@@ -130,6 +130,24 @@ def test_plan_full_bins(F, S, T, max_bins, rotate):
     rh.close()
 
 
+# The upsampler and last conv as one 5 x 5 conv: tiles of 4 x 32, rows and columns left over, images of hardly more than the ring,
+# two and four waves that share a sum
+@pytest.mark.parametrize("scale", [2, 3, 4])
+@pytest.mark.parametrize("channels", [32, 64])
+@pytest.mark.parametrize("shape", [(1, 5, 5), (2, 7, 31), (3, 8, 33), (1, 9, 64), (2, 13, 70)])
+def test_fold_tiles(scale, channels, shape):
+    N, H, W = shape
+    net = wl.Net("edsr", channels, 1, scale, 0.02)
+    blob = wl.make_weights(net, 12, "bf16")
+    rh = RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=32, max_bins=4, net=net, weights=blob, precision="bf16")
+    x = np.random.default_rng(N * H * W).integers(0, 256, (N, H, W, 3), dtype=np.uint8)
+    out = torch.full((N, H * scale, W * scale, 3), float("nan"), device="cuda")
+    rh.enhance(dev(x), out=out)
+    # the bar of the bf16 path; a tap, row or wave's share left out is several per cent
+    check_net(out.cpu().numpy(), oracle.sr_forward(net, blob, x), "bf16", f"{net} {shape}")
+    rh.close()
+
+
 # Paste with one and with four input rows a wave, both sides of the line between them (5/8 scale^2 strips a compute unit),
 # frames with cut macroblocks and row pitches of every alignment, turned boxes, floats of the pasted macroblocks
 @pytest.mark.parametrize("scale,w,h", [(1, 160, 48), (2, 160, 112), (3, 160, 112), (4, 192, 112), (1, 157, 45), (2, 150, 101), (3, 147, 107), (4, 185, 99)])
