@@ -21,8 +21,8 @@
 // that LDS has room for, and an activation fragment feeds the up to 3 rows it belongs to: 6 reads per
 // 12 MFMAs.  x's values for the residual add and the next tile's patch are requested before these MFMAs.
 // Measured, residual net of 8 blocks on 121 bins of 96 x 96: 52-55 us per block against 35.3 + 43.3 us for the two
-// launches (0.84-0.89 PFLOP/s executed, 11 % of it the halo of m); 64 tiles: 10.6 us.  Counters, 113 bins: clock 1.78 GHz, matrix
-// pipe busy 45 % and LDS 50 % of the CU's cycles, 3.4 TB/s; a row-wise conv1 that reads 22 % less LDS changed nothing.  None of
+// launches, 64 tiles: 10.6 us.  113 bins with stores through the L2: 47-50 us (0.87-0.92 PFLOP/s executed, 11 % of it the halo of m), clock
+// 1.88 GHz, matrix pipe busy 46 % and LDS 52 % of the CU's cycles, 2.9 TB/s; a row-wise conv1 that reads 22 % less LDS changed nothing.  None of
 // them is the limit by itself; what is left is the chain of short phases between barriers (not tested on its own).
 #include "conv_mfma_common.h"
 

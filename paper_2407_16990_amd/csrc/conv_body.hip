@@ -22,8 +22,8 @@
 // waves look at the start of the unit's own compute phase until it is.  The first is what happens with six units or more a
 // layer and workgroup, the last with one or two.
 //
-// What bounds it: with few units a chain per layer of look, patch, 2 us of MFMAs, rounding, stores and words, 7.4 us on
-// 3 bins of 128 x 128 (192 units) where a launch per layer takes 8.5 to 10; with many the matrix pipe at the chip's power
+// What bounds it: with few units a chain per layer of look, patch, 2 us of MFMAs, rounding, stores and words, 7.9 us on
+// 3 bins of 128 x 128 (192 units) where a launch per layer takes 8.5 to 11; with many the matrix pipe at the chip's power
 // limit, as in k_conv_mfma_duo.  A layer's weights (72 KB) go to LDS while the other team stores.
 #include <type_traits>
 

@@ -511,8 +511,8 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // so their ceil(S / 32) words per row are at most S / 16.
     const size_t mask_words = C == 64 && !fold ? ((size_t)N * H * W + 15) / 16 : 0;
     // The body of a 64-channel net in one launch (conv_body.hip) where a launch per layer would be short: us for EDSR x4 on
-    // 128 x 128 bins, per layer / in one, 3 bins 343 / 310, 8: 509 / 420, 16: 750 / 684, 24: 995 / 937, 32: 1320 / 1287, 40: 1544 / 1515,
-    // 48: 1811 / 1825, 76: 3039 / 3172.  Large batches run at the chip's power limit and lose what is read past the L2.
+    // 128 x 128 bins, per layer / in one, 1 bin 310 / 254, 3: 394 / 279, 8: 501 / 407, 16: 752 / 669, 24: 1010 / 965, 32: 1286 / 1249,
+    // 40: 1582 / 1565, 48: 1885 / 1905, 76: 3039 / 3172.  Large batches run at the chip's power limit and lose what is read past the L2.
     // The line is at 48 bins' units, or 12 a workgroup; how many of the N images are valid the host does not know.
     const std::vector<rh_layer>& L = ctx->layers;
     const int body_layers = d.topology == RH_NET_PLAIN ? d.n_blocks - 2 : 2 * d.n_blocks + (d.topology == RH_NET_EDSR);

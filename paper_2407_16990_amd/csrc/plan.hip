@@ -193,8 +193,8 @@ __global__ __launch_bounds__(256) void k_plan_rank(const rh_rawbox* __restrict__
 //     reached the last lane.  Entries move (a whole-wave DPP shift) only where a used one leaves two in front of others;
 //   - a box that fills a bin (three in four of large batches) takes no step.
 // Measured, before (every box a step of 170 instructions on the vector unit, entries moved after most of them) / now: the launch of the first fit
-// of 745 boxes of 128 frames of 480 x 272 243 / 169 us, the one-launch plan of 139 boxes of 8 frames of 640 x 368 71 / 53 us, of 551
-// isolated macroblocks 249-415 / 229-415 us.
+// of 745 boxes of 128 frames of 480 x 272 243 / 161 us, the one-launch plan of 139 boxes of 8 frames of 640 x 368 71 / 50 us, of 551
+// isolated macroblocks 249-415 / 218-372 us (the one-launch plans with the ranks by waves, below).
 // A list that outgrows the registers is written to LDS and stays there: the 64 lanes then test 64
 // rectangles at a time; the hardware executes the LDS traffic of a single wave in program order, and
 // wave_sync() after every step in which lanes write what other lanes read next keeps the compiler
@@ -603,11 +603,10 @@ __global__ __launch_bounds__(256) void k_plan_emit(const rh_rawbox* __restrict__
 #define PF_THREADS 1024
 #define PF_WAVES (PF_THREADS / 64)
 #define PF_KEYS 2048
-// More frames: phases in launches of their own.  Up to 16 the labelling is one round of waves here.  Plan + gather in us,
-// one launch / several: 480 x 272, 17 frames 58.1 / 56.4, 24: 79.5 / 69.3, 32: 104 / 84; scattered, 17: 267 / 242; 640 x 368,
-// 17: 86.8 / 78.9; 320 x 192, 17: 69.6 / 68.0.  Below the line several launches lose 5-8 us of 24-116 on up to 6 frames, are within
-// 2 us at 14-16 (16 frames of 480 x 272: 56.4 / 57.0), and gain from 12 on where there are many boxes, a number that the host
-// does not know: 16 frames of 640 x 368 79.9 / 75.1, scattered 245 / 228.
+// More frames: phases in launches of their own.  Up to 16 the labelling is one round of waves here.  Select + plan + gather in us,
+// one launch / several: 480 x 272, 6 frames 36.1 / 44.5, 12: 48.3 / 52.5, 16: 55.1 / 57.5, 17: 57.1 / 57.2, 24: 70.9 / 64.4; 640 x 368,
+// 16: 73.5 / 72.5, 17: 74.0 / 72.0; 320 x 192, 17: 40.0 / 41.1.  Where there are many boxes, a number that the host does not know, several
+// are faster: scattered macroblocks, 16 frames of 480 x 272 (551 boxes) 232 / 210, of 640 x 368 (957) 408 / 346.
 #define PF_FRAMES 16
 #define PF_MAX_PER 2304                   // 16 waves x per x 4 B of importance <= 144 KB
 

@@ -257,10 +257,12 @@ rh_status rh_launch_unpack(rh_ctx* ctx, const float* enh, int n_img, int ih, int
     const int S = ctx->cfg.net.scale;
     const bool cut = ctx->cfg.frame_w % RH_MB || ctx->cfg.frame_h % RH_MB || ((ctx->cfg.frame_w * S * 3) & 3);
     const int strips = (ctx->mbw + 64 / (4 * S) - 1) / (64 / (4 * S));
-    // A strip's work grows with the scale's square, and with it the number of strips that fill the chip either way.  Four rows / one
-    // row a wave, us: x4 of 480 x 272 (136 strips a frame), 1 frame 11.6 / 6.9, 4: 17.6 / 14.2, 16: 41.5 / 39.6, 32: 87.3 / 91.8; x3 of 640 x 360
-    // (184), 1 frame 17.1 / 9.0, 5: 23.4 / 20.1; x2 of 640 x 368 (115), 1 frame 8.5 / 6.6, 5: 12.7 / 11.9, 8: 15.4 / 16.7.  The
-    // line is at 640 strips for x2, 1 440 for x3 and 2 560 for x4.
+    // The number of strips that fill the chip either way grows about with the scale's square (a strip is 256 output pixels wide and
+    // 16 S rows high).  Four rows / one row a wave, us: x1 of 480 x 272 (34 strips a frame), 4 frames 7.0 / 6.0, 8: 7.3 / 6.6, 12: 7.8 / 8.0;
+    // x2 of 640 x 368 (115), 1 frame 8.5 / 6.6, 5: 12.7 / 11.9, 7: 13.6 / 15.1; x3 of 640 x 360 (184), 1 frame 17.1 / 9.0, 5: 23.2 / 19.9,
+    // 8: 32.2 / 30.3; x4 of 480 x 272 (136), 1 frame 11.6 / 6.9, 4: 17.6 / 14.2, 12: 32.7 / 30.5, 16: 42.3 / 40.2, 32: 87.3 / 91.8 (in steps, with
+    // an enhanced batch to read, 4 frames 20.6 / 17.1, 16 frames 57-59 / 59).  The line is at 160 strips for x1, 640 for x2, 1 440 for x3
+    // and 2 560 for x4.
     const bool few = 8l * strips * ctx->mbh * F <= 5l * S * S * ctx->n_cu;
 #define LAUNCH_UNPACK(SC)                                                                                       \
     do { if (cut && few) LAUNCH_UNPACK_E(SC, true, 1); else if (cut) LAUNCH_UNPACK_E(SC, true, 4);              \

@@ -134,7 +134,7 @@ def counted(call):
     assert sum(n) == len(k), (list(n), k)
     convs = [x for x in k if any(s in x for s in ("k_conv_mfma", "k_block32", "k_conv3x3_f32", "k_conv_tail3", "k_conv_fold"))]
     cleared = [x for x in k if "k_zero_outside" in x]
-    if convs:                                                # conv + last conv (k_fold_ring goes with the composed tail)
+    if convs:                                                # conv + last conv
         assert len(convs) <= n[4] + n[5] <= len(convs) + len(cleared) + 1, (list(n), k)
 seg = (C.c_uint32 * 8)(0, 1, 3, 0, 1, 9, 5, 0)
 counted(lambda: L.rh_select_regions(ctx, P(1), 9, seg, 2, 0, P(2), P(3), P(4)))
