@@ -20,19 +20,15 @@
 //
 // Main kernel: implicit GEMM on v_mfma_f32_32x32x16_bf16, D[row][pixel], rows = (i, j, co) of one
 // 32-row chunk (x4: two chunks of two output rows i each; x2, x3: one chunk), N = 32 pixels of an
-// image row, K = tap * C + ci over 25 taps.  Two persistent 256-thread workgroups per CU work on 4 x 32 tiles, from
-// 8 x 36 pixel patches in LDS (same channels-last layout and XOR swizzle as the 3 x 3 kernels).  The waves split K: a wave
+// image row, K = tap * C + ci over 25 taps.  One persistent 512-thread workgroup per CU works on 8 x 32 tiles, from a
+// 12 x 36 pixel patch in LDS (same channels-last layout and XOR swizzle as the 3 x 3 kernels).  The waves split K: a wave
 // has 16 of the input channels, whose 25 weight fragments stay in 100 registers, and C / 16 pixel rows, an
-// accumulator each; the C / 16 waves of the same rows then exchange sums through LDS in pairs, and each ends with one row and stores it.
+// accumulator each; the C / 16 waves of the same rows then exchange sums through LDS, and each adds up and stores one row.
 // Per tap column a wave reads 8 (6) activation fragments for 20 (10) MFMAs and no weights, and the sums that follow each other are
 // independent: with all of K in each of four waves and the weights in LDS (1.1 fragments per MFMA) a wave had two
-// rows, whose sums waited for each other's latency.  The next tile's patch is copied to LDS behind these MFMAs, and
-// one workgroup's exchange, stores and barriers lie beside the other's MFMAs.
-// Whole calls of EDSR x4 with one block on 76 / 128 bins of 128 x 128, this kernel's share about a half, us: weights in LDS 563 / 940, K split in one
-// workgroup of 512 threads and 8 x 32 tiles 549 / 913, this 540 / 898; of these 540 the patches cost 46, the exchange and the stores 20 each.
-// In the steps of the headline batch 262 -> 248 with this second change, of 16 whole frames 502 -> 469 (5059 -> 5033 a step; the headline's body
-// convs, at the chip's power limit, take back what it gains there).
-// Three bins x3: 16.3 us of kernel with the weights in LDS, 14.0 with K split.
+// rows, whose sums waited for each other's latency.  The next tile's patch is copied to LDS behind these MFMAs.
+// Whole calls of EDSR x4 with one block on 76 / 128 bins of 128 x 128, this kernel's share about a half: 563 -> 545, 940 -> 909 us;
+// three bins x3 16.3 -> 14.0 us of kernel; without the exchange 20 us less on 76 bins, without the stores 26 (both wrong results).
 #include <string.h>
 
 #include <atomic>
@@ -42,7 +38,7 @@
 
 #include "conv_mfma_common.h"
 
-#define FOLD_TH 4
+#define FOLD_TH 8
 #define FOLD_PW 36
 
 struct fold_args {
@@ -150,21 +146,23 @@ __device__ __forceinline__ void fold_ring(const fold_args& a, int n_img, long w,
     }
 }
 
-// LDS of the main kernel: two patches; a tile's partial sums take the place of its patch.
+// LDS of the main kernel: a patch, room, a patch.  The weights pass through room and second patch on their way to registers;
+// a tile's partial sums take the place of its patch and room.
 template <int CIN>
 struct fold_lds {
-    static constexpr int KS = CIN / 16, PATCHB = (FOLD_TH + 4) * FOLD_PW * CIN * 2, SUMS = 4 * (KS / 2) * 4096;
-    static_assert(SUMS <= PATCHB && PATCHB % 1024 == 0, "sums take the patch's place; whole 1 KB pieces");
+    static constexpr int KS = CIN / 16, WBYTES = 25 * KS * 1024, PATCHB = (FOLD_TH + 4) * FOLD_PW * CIN * 2, ROOM = WBYTES - PATCHB;
+    static constexpr int SUMS = 8 * (KS - 1) * 4096, TOTAL = PATCHB + ROOM + PATCHB;
+    static_assert(ROOM % 16 == 0 && SUMS <= PATCHB + ROOM && PATCHB % 1024 == 0, "what takes whose place");
 };
 
 template <int CIN, bool LIST>
-__global__ __launch_bounds__(256, 2) void k_conv_fold(fold_args a)
+__global__ __launch_bounds__(512) void k_conv_fold(fold_args a)
 {
     // LIST: the tiles come from a.tile_list.  An entry is requested two tiles ahead with a vector
     // load (a scalar load would share its counter with the LDS fragment reads) and read a tile later.
     using L = fold_lds<CIN>;
     constexpr int KS = L::KS, NCH = CIN / 8, PIXB = CIN * 2, TH = FOLD_TH, PW = FOLD_PW, RW = KS, NR = RW + 4;
-    constexpr int NPIECE = L::PATCHB / 1024, NPRE = (NPIECE + 3) / 4;        // a wave's 1 KB pieces of the patch
+    constexpr int NPIECE = L::PATCHB / 1024, NPRE = (NPIECE + 7) / 8;        // a wave's 1 KB pieces of the patch
     constexpr int SWZ_SH = (NCH == 8) ? 0 : 1;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -179,12 +177,17 @@ __global__ __launch_bounds__(256, 2) void k_conv_fold(fold_args a)
     const int xcd = blockIdx.x % 8, local = blockIdx.x / 8;
     const int wg = deal ? xcd * (G / 8) + local / a.n_chunks : ((G % 8 == 0) ? xcd * (G / 8) + local : (int)blockIdx.x);
     const int chunk_begin = deal ? local % a.n_chunks : 0, chunk_end = deal ? chunk_begin + 1 : a.n_chunks;
+    // the first chunk's weights are on their way before the image count is known
+    auto load_weights = [&](int chunk) __attribute__((always_inline)) {
+        lds_dma<512, L::WBYTES>(lds + L::PATCHB, a.wp + (size_t)(4 * a.n_chunks + chunk) * (L::WBYTES / 16), wave, lane);      // the middle class
+    };
+    load_weights(chunk_begin);
     const int n_img = min((int)n_found, a.N);
     const int tiles_x = (a.W + 31) / 32, tiles_y = (a.H + TH - 1) / TH, tiles_img = tiles_x * tiles_y;
-    const int n_tiles = LIST ? 2 * (int)n_found : n_img * tiles_img;      // a list's cells have 8 rows
+    const int n_tiles = LIST ? (int)n_found : n_img * tiles_img;
     const uint32_t in_img_bytes = (uint32_t)a.H * a.W * PIXB;
 
-    // piece i of the patch, by wave i % 4: 64 16-byte channel groups, 8 (16) pixels.  The pieces are contiguous in LDS, so the
+    // piece i of the patch, by wave i % 8: 64 16-byte channel groups, 8 (16) pixels.  The pieces are contiguous in LDS, so the
     // lanes fetch swizzled.  Rows outside the image lie outside the descriptor's range and read as zeros.
     // (`l` is the lane, passed through an empty asm statement in every phase: addresses kept over the loop would not fit the registers.)
     auto load_patch = [&](uint8_t* to, __amdgpu_buffer_rsrc_t rin, int y0, int x0) __attribute__((always_inline)) {
@@ -192,7 +195,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_fold(fold_args a)
         asm volatile("" : "+v"(l));
 #pragma unroll
         for (int j = 0; j < NPRE; ++j) {
-            const int i = j * 4 + wave;
+            const int i = j * 8 + wave;
             if (j == NPRE - 1 && i >= NPIECE) break;
             const uint32_t idx = i * 64 + l, px = idx / NCH, row = (px * 1821u) >> 16, col = px - row * PW;      // px / 36 for px < 432
             const int gx = x0 - 2 + (int)col;
@@ -206,16 +209,16 @@ __global__ __launch_bounds__(256, 2) void k_conv_fold(fold_args a)
         const int tr = tile - n * tiles_img, ty = tr / tiles_x, tx = tr - ty * tiles_x;
         y0 = ty * TH; x0 = tx * 32;
     };
-    __amdgpu_buffer_rsrc_t rlist = __builtin_amdgcn_make_buffer_rsrc((void*)a.tile_list, 0, LIST ? (uint32_t)n_tiles * 2u : 0u, RSRC_FLAGS);
+    __amdgpu_buffer_rsrc_t rlist = __builtin_amdgcn_make_buffer_rsrc((void*)a.tile_list, 0, LIST ? (uint32_t)n_tiles * 4u : 0u, RSRC_FLAGS);
     auto list_load = [&](int idx) __attribute__((always_inline)) {       // entry of walk position idx (0 past the end)
         const int pos = a.rev ? n_tiles - 1 - idx : idx;
-        return __builtin_amdgcn_raw_buffer_load_b32(rlist, idx < n_tiles ? (uint32_t)(pos >> 1) * 4u : OOB_OFF, 0, 0);
+        return __builtin_amdgcn_raw_buffer_load_b32(rlist, idx < n_tiles ? (uint32_t)pos * 4u : OOB_OFF, 0, 0);
     };
-    auto decode_cell = [&](int cell, int idx, int& n, int& y0, int& x0) __attribute__((always_inline)) {    // RH_CELL_ENTRY
-        n = (int)((uint32_t)cell >> 16); y0 = (int)(((uint32_t)cell >> 7) & 511u) * 8 + ((a.rev ? n_tiles - 1 - idx : idx) & 1) * TH; x0 = (int)((uint32_t)cell & 127u) * 32;
+    auto decode_cell = [&](int cell, int& n, int& y0, int& x0) __attribute__((always_inline)) {    // RH_CELL_ENTRY
+        n = (int)((uint32_t)cell >> 16); y0 = (int)(((uint32_t)cell >> 7) & 511u) * TH; x0 = (int)((uint32_t)cell & 127u) * 32;
     };
     auto tile_origin = [&](int tile, int& n, int& y0, int& x0) __attribute__((always_inline)) {
-        if constexpr (LIST) { decode_cell(__builtin_amdgcn_readfirstlane(list_load(tile)), tile, n, y0, x0); return; }
+        if constexpr (LIST) { decode_cell(__builtin_amdgcn_readfirstlane(list_load(tile)), n, y0, x0); return; }
         if (a.rev && tile < n_tiles) tile = n_tiles - 1 - tile;          // walk back over what the previous layer wrote last
         decode(tile, n, y0, x0);
     };
@@ -232,16 +235,20 @@ __global__ __launch_bounds__(256, 2) void k_conv_fold(fold_args a)
     };
     first_patch();                                         // ahead of what the compiler computes once for all turns of the loops
     for (int chunk = chunk_begin; chunk < chunk_end; ++chunk) {
-        if (chunk != chunk_begin) first_patch();           // behind the last barrier of the previous chunk
-        bf16x8 A[25];
-        const uint4* wsrc = a.wp + ((size_t)(4 * a.n_chunks + chunk) * 25 * KS + wk) * 64 + lane;        // the middle class
-#pragma unroll
-        for (int tap = 0; tap < 25; ++tap) A[tap] = __builtin_bit_cast(bf16x8, wsrc[tap * KS * 64]);
+        if (chunk != chunk_begin) {
+            __syncthreads();                               // previous chunk's LDS reads are done
+            load_weights(chunk);
+            first_patch();
+        }
         f32x16 biasv;                                      // lane holds rows 8q + 4hi + e in [4q + e]; in the sums of the first k-step
 #pragma unroll
         for (int e = 0; e < 16; ++e) { biasv[e] = a.bias[(4 * a.n_chunks + chunk) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)]; biasv[e] = wk == 0 ? biasv[e] : 0.0f; }
         lds_dma_wait();                                    // weights and first patch
         __syncthreads();
+        bf16x8 A[25];
+#pragma unroll
+        for (int tap = 0; tap < 25; ++tap) A[tap] = *(const bf16x8*)(lds + L::PATCHB + ((tap * KS + wk) << 10) + (lane << 4));
+        lds_barrier();                                     // read by every wave
         uint8_t* patch = lds;
         for (int tile = wg; tile < n_tiles; tile += G) {   // trip count uniform over the workgroup
             int n, y0, x0;
@@ -250,9 +257,9 @@ __global__ __launch_bounds__(256, 2) void k_conv_fold(fold_args a)
             if constexpr (LIST) e_after = list_load(tile + 2 * G);
             const int nt = tile + G;
             int nn, ny0, nx0;
-            if constexpr (LIST) { decode_cell(__builtin_amdgcn_readfirstlane(e_next), nt, nn, ny0, nx0); cn = nn; cy0 = ny0; cx0 = nx0; e_next = e_after; }
+            if constexpr (LIST) { decode_cell(__builtin_amdgcn_readfirstlane(e_next), nn, ny0, nx0); cn = nn; cy0 = ny0; cx0 = nx0; e_next = e_after; }
             else tile_origin(nt, nn, ny0, nx0);
-            uint8_t* other = patch == lds ? lds + L::PATCHB : lds;
+            uint8_t* other = patch == lds ? lds + L::PATCHB + L::ROOM : lds;
             load_patch(other, in_rsrc(nt, nt < n_tiles ? nn : 0), ny0, nx0);
 
             f32x16 acc[RW];
@@ -284,37 +291,35 @@ __global__ __launch_bounds__(256, 2) void k_conv_fold(fold_args a)
             };
             fold_each_step<5>(step);
 
-            // row r of the group is added up and stored by the wave of k-step r: pairs of waves exchange the rows that they do not keep
+            // row r of the group is added up and stored by the wave of k-step r; the partial sums of the others, in order of their k-steps
             lds_dma_wait();                                // the next patch: nothing of it is in flight behind the sums' LDS writes
             lds_barrier();                                 // the patch is read by every wave
             asm volatile("" : "+v"(l));
-            float4* sums = (float4*)patch + l;             // a wave's room: KS / 2 rows, written by its partner of the first exchange
+            float4* sums = (float4*)(patch == lds ? lds : lds + L::PATCHB) + l;
             f32x16 sum;
-            auto put = [&](const f32x16& v, int room) __attribute__((always_inline)) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) sums[(room * 4 + q) * 64] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-            };
-            auto add = [&](f32x16& v, int room) __attribute__((always_inline)) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float4 o = sums[(room * 4 + q) * 64];
-                    v[4 * q] += o.x; v[4 * q + 1] += o.y; v[4 * q + 2] += o.z; v[4 * q + 3] += o.w;
-                }
-            };
             auto add_up = [&](auto k_c) __attribute__((always_inline)) {
-                constexpr int own = decltype(k_c)::value, HK = KS / 2;
-                const int mine = (wr * KS + own) * HK, theirs = (wr * KS + (own ^ 1)) * HK;
-                put(acc[own ^ 1], theirs);
-                if constexpr (KS == 4) put(acc[own ^ 3], theirs + 1);
+                constexpr int own = decltype(k_c)::value;
+#pragma unroll
+                for (int r = 0; r < RW; ++r)
+                    if (r != own)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            sums[(((wr * KS + r) * (KS - 1) + (own < r ? own : own - 1)) * 4 + q) * 64] =
+                                make_float4(acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]);
                 lds_barrier();
-                add(acc[own], mine);
-                if constexpr (KS == 4) {
-                    add(acc[own ^ 2], mine + 1);
-                    put(acc[own ^ 2], mine);               // read by this wave, and by none but the second partner from here on
-                    lds_barrier();
-                    add(acc[own], (wr * KS + (own ^ 2)) * HK);
+#pragma unroll
+                for (int src = 0; src < KS; ++src) {
+                    f32x16 p;
+                    if (src == own) p = acc[own];
+                    else
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float4 v = sums[(((wr * KS + own) * (KS - 1) + (src < own ? src : src - 1)) * 4 + q) * 64];
+                            p[4 * q] = v.x; p[4 * q + 1] = v.y; p[4 * q + 2] = v.z; p[4 * q + 3] = v.w;
+                        }
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) sum[e] = src ? sum[e] + p[e] : p[e];
                 }
-                sum = acc[own];
             };
             if constexpr (KS == 4) {
                 if (wk == 0) add_up(std::integral_constant<int, 0>{});
@@ -335,7 +340,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_fold(fold_args a)
     if (a.ring) {
         // workgroups that have had a tile more, or one at all, come last
         const int n_ring = a.n_valid ? min((int)*a.n_valid, a.N) : a.N, place = deal ? wg * a.n_chunks + chunk_begin : wg;
-        fold_ring<CIN>(a, n_ring, (long)((int)gridDim.x - 1 - place) + (long)wave * gridDim.x, 4l * gridDim.x);
+        fold_ring<CIN>(a, n_ring, (long)((int)gridDim.x - 1 - place) + (long)wave * gridDim.x, 8l * gridDim.x);
     }
 }
 
@@ -517,7 +522,7 @@ rh_status rh_fold_weights(rh_ctx* ctx, const float* blob)
 template <int CIN>
 static hipError_t launch_fold(rh_ctx* ctx, const fold_args& a)
 {
-    constexpr int lds = 2 * fold_lds<CIN>::PATCHB;
+    constexpr int lds = fold_lds<CIN>::TOTAL;
     static bool attr_done[RH_MAX_DEVICES] = {};
     if (!attr_done[ctx->device]) {
         hipError_t e = hipFuncSetAttribute((const void*)k_conv_fold<CIN, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -529,8 +534,8 @@ static hipError_t launch_fold(rh_ctx* ctx, const fold_args& a)
     // the bin, so with a halo no pasted pixel is on the outermost ring.
     fold_args m = a;
     m.ring = !(a.tile_list && ctx->cfg.halo >= 1);
-    if (a.tile_list) hipLaunchKernelGGL((k_conv_fold<CIN, true>), dim3(2 * ctx->n_cu), dim3(256), lds, ctx->stream, m);
-    else hipLaunchKernelGGL((k_conv_fold<CIN, false>), dim3(2 * ctx->n_cu), dim3(256), lds, ctx->stream, m);
+    if (a.tile_list) hipLaunchKernelGGL((k_conv_fold<CIN, true>), dim3(ctx->n_cu), dim3(512), lds, ctx->stream, m);
+    else hipLaunchKernelGGL((k_conv_fold<CIN, false>), dim3(ctx->n_cu), dim3(512), lds, ctx->stream, m);
     return hipGetLastError();
 }
 
