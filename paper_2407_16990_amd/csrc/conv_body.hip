@@ -12,7 +12,7 @@
 //   - Workgroups sit on eight XCDs with an L2 each: activations and words are stored through (sc1) and loaded past (sc1)
 //     the L2, and a wave's stores are acknowledged (vmcnt 0) before its word is written.
 //   - Only workgroups that run take part: each signs the roll when it starts, and the roll closes when all have, or
-//     BODY_ROLL_POLLS later, where other kernels hold compute units; who comes after that leaves at once.
+//     BODY_ROLL_POLLS later, where other kernels hold compute units; who comes after that leaves at once (conv_body_roll.h).
 // So every wait ends, whatever else the GPU runs: a unit waits for units with smaller numbers only, all in the hands of
 // workgroups that run, and the smallest one not done does not wait.  Its team stores it and writes its words ahead of the
 // phase's first barrier where the team beside it may be waiting inside that phase, and is the next to compute otherwise.
@@ -27,12 +27,12 @@
 // limit, as in k_conv_mfma_duo.  A layer's weights (72 KB) go to LDS while the other team stores.
 #include <type_traits>
 
+#include "conv_body_roll.h"
 #include "conv_mfma_common.h"
 
 #define FEW_UNITS 4
 #define PW 34
 #define LD_PAST 16                       // loads: sc1
-#define BODY_CLOSED 0x80000000u
 #define BODY_ROLL_POLLS 64               // of about a us each
 #define BODY_POLLS (1 << 21)             // a second or more: never reached while the workgroups on the roll run
 
@@ -61,12 +61,12 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
     uint8_t* lds_w = lds;
     uint8_t* lds_p = lds + WBYTES + team * PATCHB;
     __shared__ uint32_t s_ready[2][2];                        // [team][its units in turn]: what it reads was there
-    __shared__ uint32_t s_again[2], s_sync[2], s_lost, s_wg[2];
+    __shared__ uint32_t s_again[2], s_sync[2], s_lost, s_wg[3];
     __shared__ __attribute__((aligned(16))) float s_bias[2][64];
 
     const int n_img = a.n_valid ? min((int)*a.n_valid, a.N) : a.N;
     const int cells_x = (a.W + 31) / 32, cells_y = (a.H + TH - 1) / TH, cells_img = cells_x * cells_y;
-    const int layer_units = n_img * cells_img;
+    const int layer_units = max(n_img, 0) * cells_img;
     const uint32_t img_bytes = (uint32_t)a.H * a.W * PIXB;
     const int row_pitch = a.W * PIXB;
     const size_t img_elems = (size_t)a.H * a.W * CIN;
@@ -150,27 +150,21 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
     // ---- start: who takes part ----
     if (tid == 0) {
         s_lost = 0; s_again[0] = 0; s_again[1] = 0; s_sync[0] = 0; s_sync[1] = 0; s_ready[0][0] = 0; s_ready[1][0] = 0;
-        uint32_t wg = __hip_atomic_fetch_add(a.roll, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), G = 0;
-        if (!(wg & BODY_CLOSED)) {
-            for (int polls = 0;;) {
-                uint32_t r = __hip_atomic_load(a.roll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (r & BODY_CLOSED) { G = r >> 16 & 0x7FFFu; break; }
-                if (r == gridDim.x) { G = r; wg = blockIdx.x; break; }
-                if (++polls > BODY_ROLL_POLLS) __hip_atomic_compare_exchange_strong(a.roll, &r, BODY_CLOSED | r << 16, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            // Workgroups go to the 8 XCDs round-robin.  With many units in a layer an XCD takes a run of neighbouring ones; with few,
-            // pairs: in runs the XCDs work, in step, at addresses a power of two apart, on the same memory channels (EDSR x4 on
-            // 128 x 128 bins, us, runs / pairs: 4 bins 477 / 327, 8: 485 / 420; level on 16; on 15 bins of 160 x 160 958 / 967).
-            if (G == gridDim.x && G % 16 == 0) {
-                const uint32_t run = layer_units >= 4 * (int)G ? G / 8 : 2, local = wg / 8;
-                wg = local / run * (8 * run) + wg % 8 * run + local % run;
-            }
+        const uint32_t sign = __hip_atomic_fetch_add(a.roll, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        body_place p;
+        for (int polls = 0;;) {
+            uint32_t r = __hip_atomic_load(a.roll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (body_roll_place(sign, r, gridDim.x, blockIdx.x, &p)) break;
+            if (++polls > BODY_ROLL_POLLS)
+                __hip_atomic_compare_exchange_strong(a.roll, &r, body_roll_closed(r), __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        s_wg[0] = wg; s_wg[1] = G;
+        body_roll_spread(&p, gridDim.x, (uint32_t)layer_units);
+        s_wg[2] = body_roll_leaves(&p, (uint32_t)layer_units);
+        s_wg[0] = p.wg; s_wg[1] = p.G;
     }
     __syncthreads();
-    const int G = min((int)__builtin_amdgcn_readfirstlane(s_wg[1]), layer_units), wg = (int)__builtin_amdgcn_readfirstlane(s_wg[0]);
-    if (wg >= G) return;                                     // not needed, or too late
+    if (__builtin_amdgcn_readfirstlane(s_wg[2])) return;     // not needed, or too late
+    const int G = (int)__builtin_amdgcn_readfirstlane(s_wg[1]), wg = (int)__builtin_amdgcn_readfirstlane(s_wg[0]);
     body_unit cur = unit_at(0, wg, team * G);                // the unit to compute next
     body_unit prev = cur;                                    // the one in the accumulators
     bool loaded = false, word_due = false;
