@@ -175,6 +175,10 @@ rh_status rh_pack(rh_ctx* ctx, const uint8_t* frames, int32_t F, const float* im
  * synchronises the stream and reallocates it (sized by N, not by *n_valid); later calls of the
  * same or a smaller size allocate nothing.  RH_BF16: one image's activations at the network's
  * highest internal resolution must stay below 2 GiB (RH_E_SHAPE otherwise).
+ * RH_BF16 with 64 channels: on small batches one launch runs several layers, and its workgroups wait for each
+ * other's results.  These waits are bounded (seconds, where an ordinary one takes microseconds).  Should one run out, that
+ * call's output is undefined, and the context's next rh_enhance (any variant; nothing is launched) or rh_read_counts - which
+ * synchronises, and so knows of every call before it - returns RH_E_DEVICE, once.
  */
 rh_status rh_enhance(rh_ctx* ctx, const uint8_t* in, int32_t N, int32_t H, int32_t W,
                      float* out, const uint32_t* n_valid);

@@ -483,6 +483,8 @@ static rh_status conv(rh_ctx* ctx, const rh_layer& L, const __bf16* in, void* ou
 rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, int W, float* out,
                                  const uint32_t* n_valid)
 {
+    rh_status st = rh_check_lost(ctx);
+    if (st != RH_OK) return st;
     const rh_net_desc& d = ctx->cfg.net;
     const int C = d.channels, s = d.scale;
     const size_t lr = (size_t)N * H * W * C;
@@ -521,7 +523,7 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // its counters, in room that is sized like the mask's: bins have at most one half tile per 128 pixels
     const size_t sync_words = C == 64 ? BODY_ROLL_WORDS + 4 * std::max(cells, ((size_t)N * H * W + 127) / 128) : 0;
     need = (need + 63) & ~(size_t)63;
-    rh_status st = rh_ensure_workspace(ctx, need * 2 + (sync_words + mask_words) * 4);
+    st = rh_ensure_workspace(ctx, need * 2 + (sync_words + mask_words) * 4);
     if (st != RH_OK) return st;
     uint32_t* sync = (uint32_t*)((uint8_t*)ctx->act + need * 2);
     uint32_t* keep = masked ? sync + sync_words : nullptr;
@@ -558,7 +560,7 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
         body_args b;
         b.h = h; b.a = a; b.t = t; b.wp = (const uint4*)((const uint8_t*)ctx->wpack + L[li].wp_off); b.bias = ctx->bpack + L[li].bp_off;
         b.n_valid = n_valid; b.keep = keep; b.N = N; b.H = H; b.W = W; b.layers = body_layers; b.topology = d.topology;
-        b.roll = sync; b.done = sync + BODY_ROLL_WORDS;
+        b.roll = sync; b.done = sync + BODY_ROLL_WORDS; b.lost = (uint32_t*)ctx->lost;
         RH_HIP(ctx, rh_launch_conv_body(ctx->stream, ctx->device, ctx->n_cu, b));
         ++n_conv; li += body_layers;
         body_out = d.topology == RH_NET_EDSR ? t : d.topology == RH_NET_RES ? a : (body_layers & 1) ? a : t;

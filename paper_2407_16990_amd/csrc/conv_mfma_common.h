@@ -94,6 +94,7 @@ struct body_args {
     int N, H, W, layers, topology;
     uint32_t* roll;          // workgroups that take part; zero at the launch, as
     uint32_t* done;          // [half tiles of 8 x 32][4]: layers that each wave of its team has stored
+    uint32_t* lost;          // host memory: set to 1 where a wait was given up
     uint32_t img_magic, row_magic;       // division by the half tiles of an image and of its rows (set by the launcher)
 };
 // words for `roll` and `done` together; `done` begins BODY_ROLL_WORDS behind `roll`

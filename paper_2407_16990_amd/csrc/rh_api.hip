@@ -61,6 +61,7 @@ extern "C" void rh_destroy(rh_ctx* ctx)
                     ctx->pcount, ctx->tr_off, ctx->tr_A, ctx->tr_T, ctx->act,
                     ctx->cell_mark, ctx->cell_live, ctx->cell_dead, ctx->cell_cnt, ctx->need_dmin, ctx->need_lists, ctx->need_cnt};
     for (void* p : ptrs) if (p) (void)hipFree(p);
+    if (ctx->lost) (void)hipHostFree((void*)ctx->lost);
     delete ctx;
 }
 
@@ -109,6 +110,10 @@ static rh_status create(const rh_config* cfg, const float* weights, size_t n_flo
     A(dalloc(&ctx->w_f32, n_floats + packed.size()));
     A(hipMemcpy(ctx->w_f32, weights, n_floats * sizeof(float), hipMemcpyHostToDevice));
     if (!packed.empty()) A(hipMemcpy(ctx->w_f32 + n_floats, packed.data(), packed.size() * sizeof(float), hipMemcpyHostToDevice));
+    if (cfg->precision == RH_BF16 && cfg->net.channels == 64) {
+        A(hipHostMalloc((void**)&ctx->lost, sizeof(uint32_t), hipHostMallocDefault));
+        if (ctx->lost) *ctx->lost = 0;
+    }
     A(dalloc(&ctx->frame_seg, cfg->max_frames)); A(dalloc(&ctx->seg_par, 4 * (size_t)cfg->max_frames));
     A(dalloc(&ctx->seg_T, cfg->max_frames)); A(dalloc(&ctx->seg_budget, cfg->max_frames));
     A(dalloc(&ctx->frame_nsel, cfg->max_frames)); A(dalloc(&ctx->frame_ties, cfg->max_frames));
@@ -201,6 +206,13 @@ rh_status rh_ensure_workspace(rh_ctx* ctx, size_t bytes)
     if (e != hipSuccess) RH_FAIL(ctx, RH_E_NOMEM, "workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
     ctx->act_bytes = bytes;
     return RH_OK;
+}
+
+rh_status rh_check_lost(rh_ctx* ctx)
+{
+    if (!ctx->lost || !*ctx->lost) return RH_OK;
+    *ctx->lost = 0;
+    RH_FAIL(ctx, RH_E_DEVICE, "an earlier rh_enhance gave up a wait on the device: its output is undefined");
 }
 
 extern "C" rh_status rh_select_regions(rh_ctx* ctx, const float* importance, int32_t F, const rh_segment* segs,
@@ -355,5 +367,5 @@ extern "C" rh_status rh_read_counts(rh_ctx* ctx, const uint32_t* counts, uint32_
     RH_HIP(ctx, hipMemcpyAsync(out, counts, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream));
     RH_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (out[2]) RH_FAIL(ctx, RH_E_CAPACITY, "packing needs more than max_bins=%d bins", ctx->cfg.max_bins);
-    return RH_OK;
+    return rh_check_lost(ctx);
 }

@@ -107,6 +107,7 @@ struct rh_ctx {
     uint32_t* need_cnt;     // [RH_NEED_RMAX + 1] their numbers
     size_t need_cap;
     int conv_parity;        // direction of the next bf16 conv's tile walk (alternates)
+    volatile uint32_t* lost;   // host, written by the device: a wait of k_conv_mfma_body was given up (64-channel bf16 nets only)
     // enhance workspace (grow-only)
     void* act;
     size_t act_bytes;
@@ -171,6 +172,8 @@ rh_status rh_zero_outside(rh_ctx*, void* act, int px_bytes, int res, int N, cons
 rh_status rh_outside_mask(rh_ctx*, uint32_t* keep, int N, const uint32_t* n_valid);
 void rh_fill_i32(rh_ctx*, int32_t* p, int32_t v, size_t n);
 rh_status rh_ensure_workspace(rh_ctx*, size_t bytes);
+// RH_E_DEVICE, once, where an earlier call's one-launch body has given up a wait
+rh_status rh_check_lost(rh_ctx*);
 
 // Event bracket around the launches of one kernel class (no-ops unless profiling is on).
 void rh_prof_begin(rh_ctx*, int cls);

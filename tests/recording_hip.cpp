@@ -20,6 +20,7 @@ static int g_launches, g_mallocs, g_syncs, g_fail_launch = -1;
 static err_t g_last;
 static uint64_t g_next = 1ull << 40;
 static int g_live;                                       // device allocations not yet freed
+static void* g_pinned;
 static std::atomic<long> g_fail_new{-1};
 static struct { dim3 grid, block; size_t lds; void* stream; } g_cfg;
 
@@ -39,6 +40,7 @@ void rec_fail_new(long k) { g_fail_new = k; }             // likewise the k-th o
 long rec_new_left() { return g_fail_new; }
 int rec_mallocs() { return g_mallocs; }
 int rec_live() { return g_live; }
+void* rec_pinned() { return g_pinned; }                  // the host memory of the context created last
 int rec_syncs() { return g_syncs; }
 const char* rec_log() { return g_log.c_str(); }          // names of the launched kernels, one a line
 
@@ -62,6 +64,8 @@ err_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, void*)
 err_t hipGetLastError() { const err_t e = g_last; g_last = OK; return e; }
 err_t hipMalloc(void** p, size_t n) { *p = (void*)g_next; g_next += (n + 4095) & ~(size_t)4095; ++g_mallocs; ++g_live; return OK; }
 err_t hipFree(void* p) { if (p) --g_live; return OK; }
+err_t hipHostMalloc(void** p, size_t n, unsigned) { *p = g_pinned = calloc(1, n); ++g_live; return *p ? OK : 2; }
+err_t hipHostFree(void* p) { if (p) --g_live; if (p == g_pinned) g_pinned = nullptr; free(p); return OK; }
 err_t hipMemcpy(void*, const void*, size_t, int) { return OK; }
 err_t hipMemcpyAsync(void*, const void*, size_t, int, void*) { return OK; }
 err_t hipMemset(void*, int, size_t) { return OK; }

@@ -180,3 +180,27 @@ for ns in (1, 511, 512, 1024):
     counted(lambda: L.rh_temporal_select(ctx, P(1), off, ns, ns, P(2), P(3), P(4), P(5)))
 counted(lambda: L.rh_temporal_spread(ctx, P(1), 30, P(2), P(3)))
 ''')
+
+
+def test_a_wait_given_up_on_the_device_fails_the_next_call_once(run_child):
+    run_child('''
+rec.rec_pinned.restype = C.c_void_p
+st, ctx = create(EDSR, 64, 1, 2, 1)
+assert st == 0
+lost = C.cast(rec.rec_pinned(), C.POINTER(C.c_uint32))
+out = (C.c_uint32 * 4)()
+calls = [lambda: L.rh_enhance(ctx, P(1), 5, 64, 64, P(2), None), lambda: L.rh_enhance_exact(ctx, P(1), 5, P(3), P(4), P(2), None),
+         lambda: L.rh_enhance_masked(ctx, P(1), 5, P(3), P(4), P(2), None), lambda: L.rh_enhance_needed(ctx, P(1), 5, P(3), P(4), P(2), None),
+         lambda: L.rh_read_counts(ctx, P(1), out)]
+for call in calls:
+    assert lost[0] == 0 and call() == 0
+    lost[0] = 1
+    rec.rec_reset()
+    assert call() == 4 and not names() and b"undefined" in L.rh_last_error(ctx)     # RH_E_DEVICE, nothing launched
+    assert call() == 0
+L.rh_destroy(ctx)
+assert rec.rec_live() == 0
+for net in ((EDSR, 32, 1, 2, 1), (RES, 64, 1, 2, 0)):                        # no such launch: no such word
+    st, ctx = create(*net)
+    assert st == 0 and not rec.rec_pinned()
+''')
