@@ -78,10 +78,10 @@ static_assert(18 * 18 * (LDS_CIN + 4) * sizeof(float) <= 160 * 1024, "the patch 
 //
 // CIN: the number of input channels where it is known (the first conv's 3, nets of 16 and 32 channels), or 0.  On a
 // small batch a conv is a chain of latencies - the image count, the patch, a scalar load for every four channels and
-// tap - around a microsecond of products: with CIN the patch is requested ahead of the image count, and a tap's
-// weights (of 16 channels at a time) in one go.  Nine bins of 64 x 64, four convs of 16 channels: 41.5 -> 28.7 us of kernels, the
-// whole step 73.3 -> 65.4.
-template <bool U8, int CIN>
+// tap - around a microsecond of products: with CIN all of a thread's pieces of the patch are in flight together, and a tap's
+// weights (of 16 channels at a time) are fetched in one go.  Four convs of 16 channels on nine bins of 64 x 64: 37.6 -> 27.4 us a call.
+// AHEAD: the patch is requested before the image count is known (conv() below says when).
+template <bool U8, int CIN, bool AHEAD>
 __global__ __launch_bounds__(256) void k_conv3x3_f32_lds(const void* __restrict__ in_, const float* __restrict__ w4,
                                                          const float* __restrict__ bias, float* out, const float* skip,
                                                          int H, int W, int Cin_, int Cout, int relu, int ps,
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void k_conv3x3_f32_lds(const void* __restrict_
 {
     extern __shared__ __attribute__((aligned(16))) float patch[];       // [18 * 18][pitch]
     const int n = blockIdx.z, Cin = CIN ? CIN : Cin_;
-    if (!CIN && n_valid && (uint32_t)n >= *n_valid) return;
+    if (!AHEAD && n_valid && (uint32_t)n >= *n_valid) return;
     const int tid = threadIdx.x, tyb = blockIdx.x / tiles_x, txb = blockIdx.x - tyb * tiles_x;
     const int x0 = txb * 16, y0 = tyb * 16, pitch = (Cin + 7) & ~3;     // >= Cin + 4: neighbouring pixels start in other banks
     const int co0 = blockIdx.y * CO_L;
@@ -97,28 +97,25 @@ __global__ __launch_bounds__(256) void k_conv3x3_f32_lds(const void* __restrict_
 #pragma unroll
     for (int j = 0; j < CO_L; ++j) acc[j] = bias[min(co0 + j, Cout - 1)];
     if constexpr (CIN != 0) {
-        // all of a thread's pieces (float4, or bytes) in flight together, 24 at most at a time
-        constexpr int PC = U8 ? CIN : CIN / 4, TOTAL = 18 * 18 * PC, NP = (TOTAL + 255) / 256, AT = NP < 24 ? NP : 24;
+        // all of a thread's pieces (float4, or bytes) in flight together
+        constexpr int PC = U8 ? CIN : CIN / 4, TOTAL = 18 * 18 * PC, NP = (TOTAL + 255) / 256;
+        static_assert(NP <= 11, "pieces in registers");
         using piece = std::conditional_t<U8, uint8_t, float4>;
         const piece* src = (const piece*)in_ + (size_t)n * H * W * PC;
-        bool counted = false;
-        for (int j0 = 0; j0 < NP; j0 += AT) {
-            piece v[AT];
+        piece v[NP];
 #pragma unroll
-            for (int j = 0; j < AT; ++j) {
-                const int i = (j0 + j) * 256 + tid, px = i / PC, row = px / 18, gy = y0 - 1 + row, gx = x0 - 1 + px - row * 18;
-                v[j] = piece{};
-                if (i < TOTAL && gy >= 0 && gy < H && gx >= 0 && gx < W) v[j] = src[((size_t)gy * W + gx) * PC + (i - px * PC)];
-            }
-            if (!counted && n_valid && (uint32_t)n >= *n_valid) return;
-            counted = true;
+        for (int j = 0; j < NP; ++j) {
+            const int i = j * 256 + tid, px = i / PC, row = px / 18, gy = y0 - 1 + row, gx = x0 - 1 + px - row * 18;
+            v[j] = piece{};
+            if (i < TOTAL && gy >= 0 && gy < H && gx >= 0 && gx < W) v[j] = src[((size_t)gy * W + gx) * PC + (i - px * PC)];
+        }
+        if (AHEAD && n_valid && (uint32_t)n >= *n_valid) return;
 #pragma unroll
-            for (int j = 0; j < AT; ++j) {
-                const int i = (j0 + j) * 256 + tid, px = i / PC;
-                if (i < TOTAL) {
-                    if constexpr (U8) patch[px * pitch + (i - px * PC)] = __fdiv_rn((float)v[j], 255.0f);
-                    else *(float4*)(patch + px * pitch + (i - px * PC) * 4) = v[j];
-                }
+        for (int j = 0; j < NP; ++j) {
+            const int i = j * 256 + tid, px = i / PC;
+            if (i < TOTAL) {
+                if constexpr (U8) patch[px * pitch + (i - px * PC)] = __fdiv_rn((float)v[j], 255.0f);
+                else *(float4*)(patch + px * pitch + (i - px * PC) * 4) = v[j];
             }
         }
     } else if (!U8 && (Cin & 3) == 0) {
@@ -238,13 +235,20 @@ static void conv(rh_ctx* ctx, const rh_layer& L, const void* in, int in_u8, floa
     if (L.cin <= LDS_CIN) {
         static bool attr_done[RH_MAX_DEVICES] = {};          // the attribute is per device
         if (!attr_done[ctx->device])
-            attr_done[ctx->device] = hipFuncSetAttribute((const void*)k_conv3x3_f32_lds<false, 0>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            attr_done[ctx->device] = hipFuncSetAttribute((const void*)k_conv3x3_f32_lds<false, 0, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                          18 * 18 * (LDS_CIN + 4) * sizeof(float)) == hipSuccess;
         const dim3 grid(tiles_x * tiles_y, (L.cout + CO_L - 1) / CO_L, N);
         const size_t lds = (size_t)18 * 18 * ((L.cin + 7) & ~3) * sizeof(float);
         const float* w4 = ctx->w_f32 + L.wp_off;
-        auto kern = in_u8 ? (L.cin == 3 ? k_conv3x3_f32_lds<true, 3> : k_conv3x3_f32_lds<true, 0>)
-                          : (L.cin == 16 ? k_conv3x3_f32_lds<false, 16> : L.cin == 32 ? k_conv3x3_f32_lds<false, 32> : k_conv3x3_f32_lds<false, 0>);
+        // Ahead of the count where the grid is small enough to run at once: then images that are not valid cost no time.  In a larger one their
+        // patches do.  us a call, ahead / behind the count, 4 convs of 16 channels on 9 valid of N bins of 64 x 64 (64 workgroups each): N = 9
+        // 27.3 / 28.1, 32: 26.6 / 27.8, 64: 31.2 / 27.7, 400: 101 / 31; residual net of 32 channels on 4 valid of N of 96 x 96 (288 each): 4
+        // 117.4 / 119.2, 16: 122.3 / 119.4, 64: 254 / 122; all 64 bins of 64 x 64 valid 87.1 / 88.5.  The line is at 8 workgroups a CU.
+        const bool ahead = (long long)grid.x * grid.y * grid.z <= 8ll * ctx->n_cu;
+#define KERN(U8, CIN) (ahead ? k_conv3x3_f32_lds<U8, CIN, true> : k_conv3x3_f32_lds<U8, CIN, false>)
+        auto kern = in_u8 ? (L.cin == 3 ? KERN(true, 3) : k_conv3x3_f32_lds<true, 0, false>)
+                          : (L.cin == 16 ? KERN(false, 16) : L.cin == 32 ? KERN(false, 32) : k_conv3x3_f32_lds<false, 0, false>);
+#undef KERN
         hipLaunchKernelGGL(kern, grid, dim3(256), lds, ctx->stream, in, w4, ctx->w_f32 + L.b_off, out, skip, H, W, L.cin, L.cout, relu, ps, n_valid, tiles_x);
         return;
     }

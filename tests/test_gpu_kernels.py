@@ -414,3 +414,18 @@ def test_one_launch_body_beside_a_launch_per_layer(n):
     for k in range(2):
         assert all(torch.equal(o, wants[k]) for o in outs[k])
         rhs[k].close()
+
+
+# fp32 convs with a device-side count, the patch requested ahead of it (up to 8 workgroups a compute unit) and behind it:
+# the valid images as without a count, the others untouched, ragged tiles
+@pytest.mark.parametrize("net", [wl.Net("plain", 16, 3, 2), wl.Net("res", 32, 1, 3), wl.Net("edsr", 16, 1, 2, 0.05), wl.Net("res", 24, 1, 2)])
+@pytest.mark.parametrize("N,valid", [(1, 0), (3, 2), (5, 5), (400, 0), (400, 7), (400, 400)])
+def test_fp32_images_behind_the_count(net, N, valid):
+    rh = RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=32, max_bins=4, net=net, weights=wl.make_weights(net, 5, "fp32"), precision="fp32")
+    x = torch.randint(0, 256, (N, 37, 50, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(N + valid))
+    want = torch.cat([rh.enhance(x[i:i + 1]) for i in range(min(N, 8))])
+    out = torch.full((N, 37 * net.scale, 50 * net.scale, 3), 3.0, device="cuda")
+    rh.enhance(x, out=out, n_valid=torch.tensor([valid], dtype=torch.int32, device="cuda"))
+    k = min(valid, 8)
+    assert torch.equal(out[:k], want[:k]) and bool((out[valid:] == 3.0).all()) and not bool((out[:valid] == 3.0).flatten(1).all(1).any())
+    rh.close()

@@ -164,6 +164,23 @@ assert all(("k_conv3x3_f32_lds" in x) == {patch} for x in n[1:]), n
 ''')
 
 
+def test_fp32_convs_look_at_the_image_count_first_on_large_grids(run_child):
+    """Images behind the count cost nothing but their empty workgroups: only a grid of at most 8 workgroups a compute
+    unit requests its patches ahead of the count."""
+    run_child('''
+import re
+for net, per in ((PLAIN, 16, 4, 2, 0), 16 * 4), ((RES, 32, 1, 2, 0), 16 * 8), ((RES, 24, 1, 2, 0), 16 * 6):      # per: workgroups an image
+    st, ctx = create(*net)
+    assert st == 0
+    for n in (1, 8 * 256 // per, 8 * 256 // per + 1, 200):
+        rec.rec_reset()
+        assert L.rh_enhance(ctx, P(1), n, 64, 64, P(2), P(3)) == 0
+        k = [re.search(r"k_conv3x3_f32_ldsILb[01]ELi([0-9]+)ELb([01])E", x).groups() for x in names()]
+        assert k and all((ahead == "1") == (cin != "0" and per * n <= 8 * 256) for cin, ahead in k[:-1]), (net, n, k)
+        if n == 200: assert all(ahead == "0" for _, ahead in k), k
+''')
+
+
 def test_profile_counts_every_launch_of_the_temporal_reuse(run_child):
     run_child('''
 st, ctx = create(PLAIN, 4, 2, 2, 0, w=32, h=32, F=1030)
