@@ -14,7 +14,6 @@
 // Activations are bf16 channels-last [N][H][W][C]; the network's last conv writes fp32.
 // Pixel shuffle is folded into the output-channel order of the upsampling convs: chunk q of
 // the permuted weights produces all C channels of sub-pixel q, i.e. one whole output pixel.
-#include <algorithm>
 #include <stdlib.h>
 #include <string.h>
 
@@ -518,10 +517,10 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // The line is at 48 bins' units, or 12 a workgroup; how many of the N images are valid the host does not know.
     const std::vector<rh_layer>& L = ctx->layers;
     const int body_layers = d.topology == RH_NET_PLAIN ? d.n_blocks - 2 : 2 * d.n_blocks + (d.topology == RH_NET_EDSR);
-    const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32);
-    const bool one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && !ctx->nd_places && cells <= 12 * (size_t)ctx->n_cu;
-    // its counters, in room that is sized like the mask's: bins have at most one half tile per 128 pixels
-    const size_t sync_words = C == 64 ? BODY_ROLL_WORDS + 4 * std::max(cells, ((size_t)N * H * W + 127) / 128) : 0;
+    const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32), most_cells = 12 * (size_t)ctx->n_cu;
+    const bool one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && !ctx->nd_places && cells <= most_cells;
+    // its counters: room for the most that the line allows in every call, so that what a call needs follows from its pixels alone
+    const size_t sync_words = C == 64 ? BODY_ROLL_WORDS + 4 * most_cells : 0;
     need = (need + 63) & ~(size_t)63;
     st = rh_ensure_workspace(ctx, need * 2 + (sync_words + mask_words) * 4);
     if (st != RH_OK) return st;

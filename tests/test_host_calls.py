@@ -88,6 +88,21 @@ for S, shapes in ((36, [(6, 36, 36), (1, 36, 216), (81, 4, 24)]), (64, [(6, 64, 
 ''')
 
 
+def test_a_call_of_as_many_pixels_fits_whatever_its_shape(run_child):
+    """The workspace follows from a call's pixels: images of another shape, however ragged, neither allocate nor
+    synchronise behind a call of as many or more pixels."""
+    run_child('''
+for net in ((EDSR, 64, 1, 4, 1), (PLAIN, 64, 5, 2, 1), (RES, 32, 1, 2, 1), (RES, 16, 1, 2, 0)):
+    for px, shapes in ((64 * 64, [(455, 3, 3), (1, 4, 1024), (13, 9, 33), (1, 1024, 4)]), (40 * 128 * 128, [(40 * 64, 16, 16), (2206, 9, 33), (60000, 3, 3)])):
+        st, ctx = create(*net)
+        assert st == 0 and L.rh_enhance(ctx, P(1), 1, 128, px // 128, P(2), None) == 0
+        for n, h, w in shapes:
+            rec.rec_reset()
+            assert n * h * w <= px and L.rh_enhance(ctx, P(1), n, h, w, P(2), None) == 0
+            assert (rec.rec_mallocs(), rec.rec_syncs()) == (0, 0), (net, n, h, w)
+''')
+
+
 @pytest.mark.parametrize("net", ["PLAIN, 16, 3, 2, 0", "RES, 64, 1, 2, 1", "EDSR, 32, 1, 2, 1"])
 def test_create_reports_any_failed_host_allocation(run_child, net):
     """Nothing throws across the C ABI: whichever host allocation fails, rh_create returns RH_E_NOMEM, with no context
