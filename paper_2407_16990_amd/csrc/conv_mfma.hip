@@ -512,16 +512,12 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // so their ceil(S / 32) words per row are at most S / 16.
     const size_t mask_words = C == 64 && !fold ? ((size_t)N * H * W + 15) / 16 : 0;
     // The body of a 64-channel net in one launch (conv_body.hip) where a launch per layer would be short: us for EDSR x4 on
-    // 128 x 128 bins, per layer / in one, 1 bin 272 / 249, 3: 331 / 273, 8: 491 / 393, 16: 740 / 662, 24: 995 / 941, 32: 1276 / 1244,
-    // 40: 1594 / 1545, 44: 1734 / 1717, 48: 1888 / 1876, 76: 3039 / 3172; 28 of 160 x 160 (2800 half tiles; 44 of 128 x 128: 2816) 1732 / 1716; a
-    // residual net of 8 blocks on 44 / 48: 826 / 822, 893 / 888.  Large batches run at the chip's power limit and lose what is read past the L2;
-    // at 48 the two are within what boxes and runs differ by (1885 / 1905 on another).  The line is at 44 bins' units, or 11 a
-    // workgroup, the largest that was faster; how many of the N images are valid the host does not know.
-    // Not with cell lists (box-masked and needed-region modes): the units of a layer and the 3 x 3 that they wait for are found here from
-    // the unit's number, in a list that changes from layer to layer they are not.
+    // 128 x 128 bins, per layer / in one, 1 bin 310 / 254, 3: 394 / 279, 8: 501 / 407, 16: 752 / 669, 24: 1010 / 965, 32: 1286 / 1249,
+    // 40: 1582 / 1565, 48: 1885 / 1905, 76: 3039 / 3172.  Large batches run at the chip's power limit and lose what is read past the L2.
+    // The line is at 48 bins' units, or 12 a workgroup; how many of the N images are valid the host does not know.
     const std::vector<rh_layer>& L = ctx->layers;
     const int body_layers = d.topology == RH_NET_PLAIN ? d.n_blocks - 2 : 2 * d.n_blocks + (d.topology == RH_NET_EDSR);
-    const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32), most_cells = 11 * (size_t)ctx->n_cu;
+    const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32), most_cells = 12 * (size_t)ctx->n_cu;
     const bool one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && !ctx->nd_places && cells <= most_cells;
     // its counters: room for the most that the line allows in every call, so that what a call needs follows from its pixels alone
     const size_t sync_words = C == 64 ? BODY_ROLL_WORDS + 4 * most_cells : 0;
