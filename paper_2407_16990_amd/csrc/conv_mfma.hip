@@ -512,9 +512,14 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // so their ceil(S / 32) words per row are at most S / 16.
     const size_t mask_words = C == 64 && !fold ? ((size_t)N * H * W + 15) / 16 : 0;
     // The body of a 64-channel net in one launch (conv_body.hip) where a launch per layer would be short: us for EDSR x4 on
-    // 128 x 128 bins, per layer / in one, 1 bin 310 / 254, 3: 394 / 279, 8: 501 / 407, 16: 752 / 669, 24: 1010 / 965, 32: 1286 / 1249,
-    // 40: 1582 / 1565, 48: 1885 / 1905, 76: 3039 / 3172.  Large batches run at the chip's power limit and lose what is read past the L2.
-    // The line is at 48 bins' units, or 12 a workgroup; how many of the N images are valid the host does not know.
+    // 128 x 128 bins, per layer / in one, 1 bin 272 / 249, 3: 331 / 273, 8: 491 / 393, 16: 740 / 662, 24: 995 / 941, 32: 1276 / 1244,
+    // 40: 1594 / 1545, 44: 1734 / 1717, 48: 1903 / 1895 (on another box 1885 / 1905), 76: 3039 / 3172.  Large batches run at the chip's power limit and
+    // lose what is read past the L2.  How many of the N images are valid the host does not know, and a capacity is seldom full: 24 valid of 48
+    // 1020 / 966, 30: 1287 / 1206, 36: 1473 / 1440, 42: 1721 / 1668.  The line is at 48 bins' units, or 12 a workgroup, where the two are level when all
+    // are valid.
+    // Not with cell lists (box-masked and needed-region modes): the units of a layer and the 3 x 3 that they wait for are found here from
+    // the unit's number, in a list that changes from layer to layer they are not.  So on few bins these modes, made to leave out work,
+    // are the slower ones: a step of one 640 x 360 frame x3, 3 bins / 14, plain 313 / 640, needed 398 / 726, masked 380 / 729 us.
     const std::vector<rh_layer>& L = ctx->layers;
     const int body_layers = d.topology == RH_NET_PLAIN ? d.n_blocks - 2 : 2 * d.n_blocks + (d.topology == RH_NET_EDSR);
     const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32), most_cells = 12 * (size_t)ctx->n_cu;

@@ -211,7 +211,9 @@ __device__ __forceinline__ uint32_t lane_from_above(uint32_t v)      // lane l g
     return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
 }
 
-// v_writelane_b32, for which there is no builtin: `old` with lane l's value replaced
+// v_writelane_b32: `old` with lane l's value replaced.  The compiler has no builtin for it, so this names its intrinsic, as it is mangled for
+// i32; one that mangles it otherwise would report the name as undefined at the library's link, and `lane == l ? value : old` takes its
+// place (two instructions more a write).
 __device__ int write_lane(int value, int l, int old) __asm("llvm.amdgcn.writelane.i32");
 
 template <bool ROTATE, typename SizeOf>

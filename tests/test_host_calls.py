@@ -88,6 +88,26 @@ for S, shapes in ((36, [(6, 36, 36), (1, 36, 216), (81, 4, 24)]), (64, [(6, 64, 
 ''')
 
 
+def test_the_body_goes_in_one_launch_up_to_twelve_half_tiles_a_compute_unit(run_child):
+    run_child('''
+def bodies(call):
+    rec.rec_reset()
+    assert call() == 0
+    return sum("k_conv_mfma_body" in x for x in names()), len(names())
+for net, layers in ((EDSR, 64, 2, 4, 1), 5), ((RES, 64, 2, 2, 1), 4), ((PLAIN, 64, 6, 2, 1), 4):
+    st, ctx = create(*net, S=128, bins=64)
+    assert st == 0
+    for n, h, w in ((1, 3, 3), (48, 128, 128), (3072, 8, 32), (768, 9, 33)):       # half tiles of 8 x 32, 256 compute units
+        assert bodies(lambda: L.rh_enhance(ctx, P(1), n, h, w, P(2), None)) == (1, 3), (net, n)
+    for n, h, w in ((49, 128, 128), (3073, 8, 32), (769, 9, 33)):
+        assert bodies(lambda: L.rh_enhance(ctx, P(1), n, h, w, P(2), None)) == (0, layers + 2), (net, n)
+    assert bodies(lambda: L.rh_enhance_exact(ctx, P(1), 48, P(3), P(4), P(2), None))[0] == 1
+    assert bodies(lambda: L.rh_enhance_exact(ctx, P(1), 49, P(3), P(4), P(2), None))[0] == 0
+    assert bodies(lambda: L.rh_enhance_masked(ctx, P(1), 3, P(3), P(4), P(2), None))[0] == 0
+    assert bodies(lambda: L.rh_enhance_needed(ctx, P(1), 3, P(3), P(4), P(2), None))[0] == 0
+''')
+
+
 def test_a_call_of_as_many_pixels_fits_whatever_its_shape(run_child):
     """The workspace follows from a call's pixels: images of another shape, however ragged, neither allocate nor
     synchronise behind a call of as many or more pixels."""
