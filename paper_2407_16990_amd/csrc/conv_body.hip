@@ -27,22 +27,13 @@
 // What bounds it: with few units a chain per layer of look, patch, 2 us of MFMAs, rounding, stores and words, 7.9 us on
 // 3 bins of 128 x 128 (192 units) where a launch per layer takes 8.5 to 11; with many the matrix pipe at the chip's power
 // limit, as in k_conv_mfma_duo.  A layer's weights (72 KB) go to LDS while the other team stores.
-#include <type_traits>
-
 #include "conv_body_roll.h"
-#include "conv_mfma_common.h"
+#include "conv_mfma64.h"
 
 #define FEW_UNITS 4
-#define PW 34
 #define LD_PAST 16                       // loads: sc1
 #define BODY_ROLL_POLLS 64               // of about a us each
 #define BODY_POLLS (1 << 21)             // a second or more: never reached while the workgroups on the roll run
-
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void body_each_step(F& f)
-{
-    if constexpr (I < N) { f(std::integral_constant<int, I>{}); body_each_step<N, I + 1>(f); }
-}
 
 __device__ __forceinline__ void body_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -51,8 +42,8 @@ struct body_unit { int layer, idx, n, y0, x0; };            // idx: its number i
 template <bool KEEP>
 __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
 {
-    constexpr int CIN = 64, MT = 2, KS = 4, NCH = 8, PIXB = 128, TH = 8, PH = TH + 2, RW = 2, NR = RW + 2;
-    constexpr int WBYTES = 9 * KS * MT * 1024, PATCHB = PH * PW * PIXB, NSTEP = 3 * KS, MID = 10;
+    constexpr int CIN = 64, NCH = 8, PIXB = 128, TH = 8, PH = TH + 2, RW = 2;
+    constexpr int WBYTES = 9 * CIN * CIN * 2, PATCHB = PH * PW * PIXB, NSTEP = C64_SUBSTEPS, MID = 15;
     constexpr int NMAIN = PH, NHP = PH * 2 * NCH, NPRE = NMAIN + 1;
     constexpr int NOUT = 8, PPJ = 8, JPR = 4;
     static_assert(NHP <= 256, "halo pieces must fit one per thread");
@@ -193,7 +184,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
     // this up to 4 units, 1 bin 276 / 254, 3: 296 / 268, 8: 409 / 394, 10: 498 / 460, 16: 666 / 654; with six units (24 bins) 930 / 964.
     auto unit = [&](auto skip_c, auto few_c) __attribute__((always_inline)) -> bool {
         constexpr bool SKIP = decltype(skip_c)::value, FEW = decltype(few_c)::value;
-        f32x16 acc[RW][MT];
+        conv64_acc acc;
         uint4 sk[SKIP ? NOUT : 1];
         uint32_t kw[KEEP ? RW : 1];
         body_unit nu;
@@ -202,7 +193,6 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
         const int y0 = cur.y0, x0 = cur.x0;
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        const int lx = ln & 31, hi = ln >> 5;
         __amdgpu_buffer_rsrc_t rsk = rsrc_of(layer_skip(cur.layer), cur.n, SKIP);
         if constexpr (KEEP) {
             const int wpr = (a.W + 31) >> 5;
@@ -210,76 +200,24 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
 #pragma unroll
             for (int r = 0; r < RW; ++r) kw[r] = __builtin_amdgcn_raw_buffer_load_b32(rk, (uint32_t)(((y0 + wave * RW + r) * wpr + (x0 >> 5)) * 4), 0, 0);
         }
-        const uint8_t* wlane = lds_w + (ln << 4);
-        const uint8_t* prow = lds_p + (wave * RW) * (PW * PIXB);
-        bf16x8 A0[3][MT], A1[3][MT], B0[NR], B1[NR];
-        // the sums start from the bias, as the first products' C operand: channels m*32 + 8*q + 4*hi + {0..3} in [m][4q..4q+3]
-        f32x16 bias_c[MT];
-#pragma unroll
-        for (int m = 0; m < MT; ++m)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 bv = *(const float4*)(&s_bias[team][m * 32 + q * 8 + hi * 4]);
-                bias_c[m][4 * q] = bv.x; bias_c[m][4 * q + 1] = bv.y; bias_c[m][4 * q + 2] = bv.z; bias_c[m][4 * q + 3] = bv.w;
-            }
+        f32x4 bias_c[4];
+        conv64_bias(bias_c, s_bias[team], ln);
         uint32_t words = 0;
-        {   // fragments of step 0
-            const uint8_t* b0 = prow + lx * PIXB + ((hi ^ (lx & 7)) << 4);
-#pragma unroll
-            for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-                for (int m = 0; m < MT; ++m) A0[ky][m] = *(const bf16x8*)(wlane + ((((ky * 3) * KS) * MT + m) << 10));
-#pragma unroll
-            for (int py = 0; py < NR; ++py) B0[py] = *(const bf16x8*)(b0 + py * (PW * PIXB));
-        }
-        auto step = [&](auto st_c) __attribute__((always_inline)) {
+        auto hook = [&](auto st_c) __attribute__((always_inline)) {
             constexpr int st = decltype(st_c)::value;
-            constexpr int NMF = 3 * RW * MT, NFR = 3 * MT + NR, NSLOT = 6;
-            constexpr int MPS = NMF / NSLOT, FPS = (NFR + NSLOT - 1) / NSLOT;
-            bf16x8 (&Ac)[3][MT] = (st & 1) ? A1 : A0;
-            bf16x8 (&Bc)[NR] = (st & 1) ? B1 : B0;
-            bf16x8 (&An)[3][MT] = (st & 1) ? A0 : A1;
-            bf16x8 (&Bn)[NR] = (st & 1) ? B0 : B1;
-            constexpr int kxn = (st + 1) / KS, ksn = (st + 1) - kxn * KS;
-            const int pxn = lx + kxn;
-            const uint8_t* b0n = prow + pxn * PIXB + (((2 * ksn + hi) ^ (pxn & 7)) << 4);
-#pragma unroll
-            for (int sl = 0; sl < NSLOT; ++sl) {
-                if (st + 1 < NSTEP) {
-#pragma unroll
-                    for (int f = sl * FPS; f < (sl + 1) * FPS && f < NFR; ++f) {
-                        constexpr int GRP = 1 + MT;            // fragments in the order of their first use, as in k_conv_mfma_duo
-                        const int g = f / GRP, w = f % GRP;
-                        if (g < 3 && w > 0) An[g][w - 1] = *(const bf16x8*)(wlane + ((((g * 3 + kxn) * KS + ksn) * MT + (w - 1)) << 10));
-                        else Bn[g < 3 ? g : 3 + (f - 3 * GRP)] = *(const bf16x8*)(b0n + (g < 3 ? g : 3 + (f - 3 * GRP)) * (PW * PIXB));
-                    }
-                }
-#pragma unroll
-                for (int k = sl * MPS; k < (sl + 1) * MPS; ++k) {
-                    const int m = k % MT, pair = k / MT;
-                    int py = 0, ky = 0, cnt = 0;
-#pragma unroll
-                    for (int p = 0; p < NR; ++p)
-#pragma unroll
-                        for (int q = 0; q < 3; ++q)
-                            if (p - q >= 0 && p - q < RW) { if (cnt == pair) { py = p; ky = q; } ++cnt; }
-                    const int r = py - ky;
-                    acc[r][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Ac[ky][m], Bc[py], st == 0 && ky == 0 ? bias_c[m] : acc[r][m], 0, 0, 0);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if constexpr (SKIP && st < NOUT) {
-                const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsk, out_off(st, ln, y0, x0), 0, LD_PAST);
-                sk[st] = make_uint4(v[0], v[1], v[2], v[3]);
+            if constexpr (SKIP && st % 3 != 0 && st * 2 / 3 < NOUT) {
+                constexpr int j = st * 2 / 3;
+                const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsk, out_off(j, ln, y0, x0), 0, LD_PAST);
+                sk[j] = make_uint4(v[0], v[1], v[2], v[3]);
                 __builtin_amdgcn_sched_barrier(0);
             }
             // is what the team's next unit reads there?  Both teams know after the phase's end
-            if constexpr (st == 2) {
+            if constexpr (st == 3) {
                 nu = unit_at(cur.layer, cur.idx, 2 * G);
                 front_layer = cur.layer + (cur.idx + G >= layer_units ? 1 : 0);        // G <= layer_units
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if constexpr (st == 5) {
+            if constexpr (st == 8) {
                 if (word_due) {                              // the last unit's stores were made a phase ago: all but the loads since then are done
                     asm volatile("s_waitcnt vmcnt(%0)" :: "n"((SKIP ? 6 : 0) + (KEEP ? RW : 0)) : "memory");
                     mark_done(prev);
@@ -301,7 +239,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
             }
         };
         __builtin_amdgcn_s_setprio(2);
-        body_each_step<NSTEP>(step);
+        conv64_products(acc, bias_c, lds_w + (ln << 4), lds_p + wave * RW * (PW * PIXB), ln, hook);
         __builtin_amdgcn_s_setprio(0);
         }
         // ---------------- the other team computes ----------------
@@ -315,27 +253,21 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
         const int y0 = cur.y0, x0 = cur.x0;
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        const int lx = ln & 31, hi = ln >> 5, lcol = ln >> 3, lc = ln & 7, tt = wave * 64 + ln;
+        const int lcol = ln >> 3, lc = ln & 7, tt = wave * 64 + ln;
         __amdgpu_buffer_rsrc_t rin = rsrc_of(layer_in(nu.layer), early ? nu.n : 0, early);      // a range of 0 reads nothing: no branches, which would have the compiler wait for all loads
         __amdgpu_buffer_rsrc_t rout = rsrc_of(layer_out(cur.layer), cur.n, true);
-        constexpr int NUNIT = MT * 4 * RW;
+        constexpr int NUNIT = 16;
         uint8_t* stg = lds_p + wave * (RW * 32 * PIXB);
-        const int okey = lx & 7;
 #pragma unroll
-        for (int m = 0; m < MT; ++m)
+        for (int u = 0; u < NUNIT; ++u) {
+            const int m = u >> 2, n = u >> 1 & 1, r = u & 1;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int r = 0; r < RW; ++r) {
-                    const int u = (m * 4 + q) * RW + r;
-#pragma unroll
-                    for (int i = u * NPRE / NUNIT; i < (u + 1) * NPRE / NUNIT && !FEW; ++i) load_piece(i, tt, rin, nu.y0, nu.x0);
-                    uint2 pk;
-                    pk.x = pack_bf16x2(acc[r][m][4 * q], acc[r][m][4 * q + 1]); pk.y = pack_bf16x2(acc[r][m][4 * q + 2], acc[r][m][4 * q + 3]);
-                    if constexpr (!SKIP) { pk.x = relu_bf16x2(pk.x); pk.y = relu_bf16x2(pk.y); }
-                    *(uint2*)(stg + (r * 32 + lx) * PIXB + (((m * 4 + q) ^ okey) << 4) + hi * 8) = pk;
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+            for (int i = u * NPRE / NUNIT; i < (u + 1) * NPRE / NUNIT && !FEW; ++i) load_piece(i, tt, rin, nu.y0, nu.x0);
+            uint2 pk = conv64_round(acc.v[r][n][m]);
+            if constexpr (!SKIP) { pk.x = relu_bf16x2(pk.x); pk.y = relu_bf16x2(pk.y); }
+            *(uint2*)(stg + conv64_slot(r, n, m, ln)) = pk;
+            __builtin_amdgcn_sched_barrier(0);
+        }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the slice is private to the wave: no barrier
         uint4 ov[NOUT];
 #pragma unroll
@@ -449,7 +381,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
 
 hipError_t rh_launch_conv_body(hipStream_t stream, int device, int n_cu, body_args a)
 {
-    constexpr int lds = 9 * 4 * 2 * 1024 + 2 * 10 * PW * 128;
+    constexpr int lds = 9 * 64 * 64 * 2 + 2 * 10 * PW * 128;
     static bool attr_done[RH_MAX_DEVICES] = {};            // the attribute is per device
     if (!attr_done[device]) {
         hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_body<false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);

@@ -353,8 +353,8 @@ static uint16_t f32_to_bf16_rne(float f)
 }
 
 // Repack every layer with cin = C into fragment order:
-//   [chunk][tap][ks][m][lane][8]  with  cout' = chunk*CQ + m*32 + lane%32,
-//   ci = ks*16 + 8*(lane/32) + e,   cout' -> original cout through the pixel-shuffle fold.
+//   [chunk][tap][ks][m][lane][8]  with  cout' = chunk*CQ + m*FM + lane%FM,
+//   ci = ks*FK + 8*(lane/FM) + e,   cout' -> original cout through the pixel-shuffle fold.
 rh_status rh_pack_weights_bf16(rh_ctx* ctx, const float* blob)
 {
     const int C = ctx->cfg.net.channels, s = ctx->cfg.net.scale;
@@ -400,17 +400,19 @@ rh_status rh_pack_weights_bf16(rh_ctx* ctx, const float* blob)
         L.ps = ps;
         const int CQ = last ? ((L.cout + 31) / 32) * 32 : C;     // channels per chunk
         if (CQ > 64) RH_FAIL(ctx, RH_E_UNIMPLEMENTED, "last conv with %d outputs (scale %d) exceeds 64", L.cout, s);
-        const int n_chunks = last ? 1 : ps * ps, MT = CQ / 32, KS = L.cin / 16;
+        const int n_chunks = last ? 1 : ps * ps;
         L.cout_pad = CQ * n_chunks;
+        // k_conv_mfma: fragments of 32 channels x 16 of K; the two-team kernels (64 channels, not the last conv): of 16 x 32
+        const int FM = C == 64 && !last ? 16 : 32, FK = 512 / FM;
         for (int q = 0; q < n_chunks; ++q)
             for (int tap = 0; tap < 9; ++tap)
-                for (int ks = 0; ks < KS; ++ks)
-                    for (int m = 0; m < MT; ++m)
+                for (int ks = 0; ks < L.cin / FK; ++ks)
+                    for (int m = 0; m < CQ / FM; ++m)
                         for (int lane = 0; lane < 64; ++lane)
                             for (int e = 0; e < 8; ++e) {
-                                const int cp = m * 32 + (lane & 31);             // channel within the chunk
+                                const int cp = m * FM + lane % FM;               // channel within the chunk
                                 const int co = last ? cp : (ps == 1 ? cp : cp * ps * ps + q);
-                                const int ci = ks * 16 + 8 * (lane >> 5) + e;
+                                const int ci = ks * FK + 8 * (lane / FM) + e;
                                 float v = (co < L.cout) ? w[((size_t)co * 9 + tap) * L.cin + ci] : 0.0f;
                                 wp.push_back(f32_to_bf16_rne(v));
                             }

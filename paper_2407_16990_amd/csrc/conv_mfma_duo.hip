@@ -10,7 +10,7 @@
 //
 // The hardware barrier counts all 8 waves, so both teams execute the same barrier sequence:
 // time is cut into phases of exactly two barriers.
-//   compute phase : MFMA steps 0..MID-1 | barrier | steps MID..11 | barrier
+//   compute phase : sub-steps 0..MID-1 of conv64_products | barrier | sub-steps MID..17 | barrier
 //                   (LDS fragment reads and MFMAs only: a wave that issues a wide global memory
 //                   instruction cannot issue MFMAs for some 60-90 cycles, so the MFMA loop
 //                   carries none)
@@ -29,16 +29,7 @@
 // early: every barrier is reached by all 8 waves.
 #include <stdlib.h>
 
-#include <type_traits>
-
-#include "conv_mfma_common.h"
-
-#define PW 34
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void for_each_step2(F& f)
-{
-    if constexpr (I < N) { f(std::integral_constant<int, I>{}); for_each_step2<N, I + 1>(f); }
-}
+#include "conv_mfma64.h"
 
 __device__ __forceinline__ void phase_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ void idle_phase() { phase_barrier(); phase_barrier(); }
@@ -52,13 +43,12 @@ __device__ __forceinline__ void idle_phase() { phase_barrier(); phase_barrier();
 template <bool SKIP, bool RELU, int MID, bool LIST, bool KEEP>
 __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
 {
-    constexpr int CIN = 64, MT = 2, KS = 4, NCH = 8, PIXB = 128, TH = 8, PH = TH + 2, RW = 2, NR = RW + 2;
-    constexpr int WBYTES = 9 * KS * MT * 1024, PATCHB = PH * PW * PIXB, NSTEP = 3 * KS, CQ = 64;
+    constexpr int CIN = 64, NCH = 8, PIXB = 128, TH = 8, PH = TH + 2, RW = 2;
+    constexpr int WBYTES = 9 * CIN * CIN * 2, PATCHB = PH * PW * PIXB, NSTEP = C64_SUBSTEPS, CQ = 64;
     constexpr int NMAIN = PH, NHP = PH * 2 * NCH, NHALO = 1, NPRE = NMAIN + NHALO;      // 16-byte patch pieces per thread
     static_assert(NHP <= 256, "halo pieces must fit one per thread");
-    constexpr bool SKIP_IN_COMPUTE = true;
     static_assert(MID >= 1 && MID <= NSTEP - 1, "the compute phase must hold exactly two barriers");
-    // MID: the compute phase's first barrier comes after MID of the 12 steps; it pairs with the end
+    // MID: the compute phase's first barrier comes after MID of the 18 sub-steps; it pairs with the end
     // of the other team's loads + rounding + skip add + stores
     constexpr int NCHO = 8, OPIXB = 128, NOUT = RW * 32 * NCHO / 64, PPJ = 8, JPR = 4;   // output pieces per lane
 
@@ -67,7 +57,6 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
     // everything derived from them (tile rows, row validity, descriptors) in scalar registers
     const int tid = threadIdx.x, ttid = tid & 255, lane = tid & 63;
     const int team = __builtin_amdgcn_readfirstlane(tid >> 8), wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);
-    const int lx = lane & 31, hi = lane >> 5;
     uint8_t* lds_w = lds;
     uint8_t* lds_p = lds + WBYTES + team * PATCHB;
     float* lds_b = (float*)(lds + WBYTES + 2 * PATCHB);       // the chunk's 64 biases
@@ -199,14 +188,9 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
         // Accumulators start from the bias: lane holds channels m*32 + 8*q + 4*hi + {0..3} in [m][4q..4q+3].  It stays in
         // 32 registers and is the first product's C operand; written into the accumulators anew for every unit (8 LDS
         // reads, 64 moves) it took both phases' time: 16 whole frames 5193 us a step, now 5147, the headline batch 2781, now 2760.
-        f32x16 acc[RW][MT], bias_c[MT];
-#pragma unroll
-        for (int m = 0; m < MT; ++m)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 bv = *(const float4*)(lds_b + m * 32 + q * 8 + hi * 4);
-                bias_c[m][4 * q] = bv.x; bias_c[m][4 * q + 1] = bv.y; bias_c[m][4 * q + 2] = bv.z; bias_c[m][4 * q + 3] = bv.w;
-            }
+        conv64_acc acc;
+        f32x4 bias_c[4];
+        conv64_bias(bias_c, lds_b, lane);
         if (team == 1) idle_phase();
         for (int it = 0; it < iters; ++it) {
             const int unit = u_first + it * 2 * G, nunit = unit + 2 * G;
@@ -225,59 +209,12 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
                     kw[r] = __builtin_amdgcn_raw_buffer_load_b32(rk, (uint32_t)((((y0 + wave * RW + r) >> a.keep_sh) * wpr + (x0 >> (5 + a.keep_sh))) * 4), 0, 0);
             }
             // ---------------- compute phase ----------------
-            const uint8_t* wlane = lds_w + (lane << 4);
-            const uint8_t* prow = lds_p + (wave * RW) * (PW * PIXB);
-            bf16x8 A0[3][MT], A1[3][MT], B0[NR], B1[NR];
-            {   // fragments of step 0
-                const uint8_t* b0 = prow + lx * PIXB + ((hi ^ (lx & 7)) << 4);
-#pragma unroll
-                for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-                    for (int m = 0; m < MT; ++m) A0[ky][m] = *(const bf16x8*)(wlane + ((((ky * 3) * KS) * MT + m) << 10));
-#pragma unroll
-                for (int py = 0; py < NR; ++py) B0[py] = *(const bf16x8*)(b0 + py * (PW * PIXB));
-            }
-            auto step = [&](auto st_c) __attribute__((always_inline)) {
+            auto hook = [&](auto st_c) __attribute__((always_inline)) {
                 constexpr int st = decltype(st_c)::value;
-                constexpr int NMF = 3 * RW * MT, NFR = 3 * MT + NR, NSLOT = 6;
-                constexpr int MPS = NMF / NSLOT, FPS = (NFR + NSLOT - 1) / NSLOT;
-                bf16x8 (&Ac)[3][MT] = (st & 1) ? A1 : A0;
-                bf16x8 (&Bc)[NR] = (st & 1) ? B1 : B0;
-                bf16x8 (&An)[3][MT] = (st & 1) ? A0 : A1;
-                bf16x8 (&Bn)[NR] = (st & 1) ? B0 : B1;
-                constexpr int kxn = (st + 1) / KS, ksn = (st + 1) - kxn * KS;
-                const int pxn = lx + kxn;
-                const uint8_t* b0n = prow + pxn * PIXB + (((2 * ksn + hi) ^ (pxn & 7)) << 4);
-#pragma unroll
-                for (int sl = 0; sl < NSLOT; ++sl) {
-                    if (st + 1 < NSTEP) {
-#pragma unroll
-                        for (int f = sl * FPS; f < (sl + 1) * FPS && f < NFR; ++f) {
-                            // fragments in the order of their first use in the next step:
-                            // B0, A0*, B1, A1*, B2, A2*, B3  (A ky-th pair follows B ky)
-                            constexpr int GRP = 1 + MT;
-                            const int g = f / GRP, w = f % GRP;
-                            if (g < 3 && w > 0) An[g][w - 1] = *(const bf16x8*)(wlane + ((((g * 3 + kxn) * KS + ksn) * MT + (w - 1)) << 10));
-                            else Bn[g < 3 ? g : 3 + (f - 3 * GRP)] = *(const bf16x8*)(b0n + (g < 3 ? g : 3 + (f - 3 * GRP)) * (PW * PIXB));
-                        }
-                    }
-#pragma unroll
-                    for (int k = sl * MPS; k < (sl + 1) * MPS; ++k) {
-                        const int m = k % MT, pair = k / MT;
-                        int py = 0, ky = 0, cnt = 0;
-#pragma unroll
-                        for (int p = 0; p < NR; ++p)
-#pragma unroll
-                            for (int q = 0; q < 3; ++q)
-                                if (p - q >= 0 && p - q < RW) { if (cnt == pair) { py = p; ky = q; } ++cnt; }
-                        const int r = py - ky;
-                        acc[r][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Ac[ky][m], Bc[py], st == 0 && ky == 0 ? bias_c[m] : acc[r][m], 0, 0, 0);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if constexpr (SKIP && SKIP_IN_COMPUTE && st < NOUT) {
-                    const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsk, out_off(st, y0, x0, 0, 0), 0, 0);
-                    sk[st] = make_uint4(v[0], v[1], v[2], v[3]);
+                if constexpr (SKIP && st % 3 != 0 && st * 2 / 3 < NOUT) {
+                    constexpr int j = st * 2 / 3;
+                    const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsk, out_off(j, y0, x0, 0, 0), 0, 0);
+                    sk[j] = make_uint4(v[0], v[1], v[2], v[3]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if constexpr (LIST && st == MID - 1) {              // the next unit's list entry has long arrived: decode it here,
@@ -290,7 +227,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
                 }
             };
             __builtin_amdgcn_s_setprio(2);             // the wave feeding the matrix pipe goes first
-            for_each_step2<NSTEP>(step);
+            conv64_products(acc, bias_c, lds_w + (lane << 4), lds_p + wave * RW * (PW * PIXB), lane, hook);
             __builtin_amdgcn_s_setprio(0);
 
             // ---------------- drain phase ----------------
@@ -310,34 +247,18 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
             // arrive together, so a wave that issues its loads back to back is held for 60-90
             // cycles by each of them: the loads are dealt out one or two at a time between the
             // 16 units of rounding work instead.
-            constexpr bool SKIP_HERE = SKIP && !SKIP_IN_COMPUTE;
-            constexpr int NLD = NPRE + (SKIP_HERE ? NOUT : 0), NUNIT = MT * 4 * RW;
-            auto issue_load = [&](int i) __attribute__((always_inline)) {
-                if (SKIP_HERE && i < NOUT) {
-                    const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsk, out_off(i, y0, x0, 0, 0), 0, 0);
-                    sk[i] = make_uint4(v[0], v[1], v[2], v[3]);
-                } else {
-                    load_piece(i - (SKIP_HERE ? NOUT : 0), rin, ny0, nx0);
-                }
-            };
+            constexpr int NUNIT = 16;
             uint8_t* stg = lds_p + wave * (RW * 32 * OPIXB);
-            const int okey = lx & 7;
 #pragma unroll
-            for (int m = 0; m < MT; ++m)
+            for (int u = 0; u < NUNIT; ++u) {
+                const int m = u >> 2, n = u >> 1 & 1, r = u & 1;
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-#pragma unroll
-                    for (int r = 0; r < RW; ++r) {
-                        const int u = (m * 4 + q) * RW + r;
-#pragma unroll
-                        for (int i = u * NLD / NUNIT; i < (u + 1) * NLD / NUNIT; ++i) issue_load(i);
-                        float v0 = acc[r][m][4 * q + 0], v1 = acc[r][m][4 * q + 1], v2 = acc[r][m][4 * q + 2], v3 = acc[r][m][4 * q + 3];
-                        uint2 pk;
-                        pk.x = pack_bf16x2(v0, v1); pk.y = pack_bf16x2(v2, v3);
-                        if constexpr (RELU) { pk.x = relu_bf16x2(pk.x); pk.y = relu_bf16x2(pk.y); }   // rounding keeps the sign
-                        *(uint2*)(stg + (r * 32 + lx) * OPIXB + (((m * 4 + q) ^ okey) << 4) + hi * 8) = pk;
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
+                for (int i = u * NPRE / NUNIT; i < (u + 1) * NPRE / NUNIT; ++i) load_piece(i, rin, ny0, nx0);
+                uint2 pk = conv64_round(acc.v[r][n][m]);
+                if constexpr (RELU) { pk.x = relu_bf16x2(pk.x); pk.y = relu_bf16x2(pk.y); }   // rounding keeps the sign
+                *(uint2*)(stg + conv64_slot(r, n, m, lane)) = pk;
+                __builtin_amdgcn_sched_barrier(0);
+            }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the slice is private to the wave: no barrier
             uint4 ov[NOUT];
 #pragma unroll
@@ -376,7 +297,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_duo(conv_args a)
 template <bool SKIP, bool RELU, int MID, bool LIST, bool KEEP = false>
 static hipError_t launch_duo(hipStream_t stream, int device, const conv_args& a, int grid)
 {
-    constexpr int lds = 9 * 4 * 2 * 1024 + 2 * 10 * PW * 128 + 256;
+    constexpr int lds = 9 * 64 * 64 * 2 + 2 * 10 * PW * 128 + 256;
     static bool attr_done[RH_MAX_DEVICES] = {};            // the attribute is per device
     if (!attr_done[device]) {
         hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_duo<SKIP, RELU, MID, LIST, KEEP>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -389,8 +310,8 @@ static hipError_t launch_duo(hipStream_t stream, int device, const conv_args& a,
 
 hipError_t rh_launch_conv_duo(hipStream_t stream, int device, const conv_args& a, int grid, bool skip, bool relu)
 {
-    // first barrier of the compute phase after 10 of the 12 steps (A/B on one box: 0.7 % better than 11, 9 is worse)
-    constexpr int MID = 10;
+    // first barrier of the compute phase after 15 of the 18 sub-steps (headline batch, us, 14 / 15 / 16: 2788 / 2784 / 2797)
+    constexpr int MID = 15;
     if (a.tile_list) {
         if (a.n_chunks != 1) return hipErrorInvalidValue;      // a tile list goes with single-chunk layers only
         if (skip) return launch_duo<true, false, MID, true>(stream, device, a, grid);
