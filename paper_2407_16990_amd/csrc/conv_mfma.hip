@@ -513,19 +513,21 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // needs more than a plain one of as many pixels.  A word per 16 pixels holds it: bins are at least 16 wide,
     // so their ceil(S / 32) words per row are at most S / 16.
     const size_t mask_words = C == 64 && !fold ? ((size_t)N * H * W + 15) / 16 : 0;
-    // The body of a 64-channel net in one launch (conv_body.hip) where a launch per layer would be short: us for EDSR x4 on
-    // 128 x 128 bins, per layer / in one, 1 bin 272 / 249, 3: 331 / 273, 8: 491 / 393, 16: 740 / 662, 24: 995 / 941, 32: 1276 / 1244,
-    // 40: 1594 / 1545, 44: 1734 / 1717, 48: 1903 / 1895 (on another box 1885 / 1905), 76: 3039 / 3172.  Large batches run at the chip's power limit and
-    // lose what is read past the L2.  How many of the N images are valid the host does not know, and a capacity is seldom full: 24 valid of 48
-    // 1020 / 966, 30: 1287 / 1206, 36: 1473 / 1440, 42: 1721 / 1668.  The line is at 48 bins' units, or 12 a workgroup, where the two are level when all
-    // are valid.
+    // The body of a 64-channel net in one launch (conv_body.hip) where the batch has room for at most 8 half tiles a compute unit, else two convs a launch
+    // (conv_block64.hip).  us for EDSR x2 of 8 blocks, in one launch / two convs a launch (a launch per conv in brackets): 8 bins of 128 x 128 239 / 257,
+    // 16: 360 / 377, 24: 486 / 502, 32: 633 / 612, 40: 791 / 765, 48: 941 / 897, 56: 1095 / 1021 (a launch per conv); 40 of 100 x 100, 8.1 half tiles, 611 / 545; 60 of
+    // 96 x 96, 8.4, 676 / 642; 20 of 160 x 160, 7.8, 629 / 639; frames of 480 x 272, 3: 489 / 519, 6: 954 / 933; two of 640 x 360, 7: 574 / 577.
+    // How many of the N images are valid the host does not know; a capacity is seldom full, which speaks for neither.  Where two convs a launch are not to be
+    // had (exact-border mode, widths up to 48) the other side is a launch per conv, and the line is at 12 (48 of 128 x 128 1903 / 1895).
     // Not with cell lists (box-masked and needed-region modes): the units of a layer and the 3 x 3 that they wait for are found here from
     // the unit's number, in a list that changes from layer to layer they are not.  So on few bins these modes, made to leave out work,
     // are the slower ones: a step of one 640 x 360 frame x3, 3 bins / 14, plain 313 / 640, needed 398 / 726, masked 380 / 729 us.
     const std::vector<rh_layer>& L = ctx->layers;
     const int body_layers = d.topology == RH_NET_PLAIN ? d.n_blocks - 2 : 2 * d.n_blocks + (d.topology == RH_NET_EDSR);
     const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32), most_cells = 12 * (size_t)ctx->n_cu;
-    const bool one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && !ctx->nd_places && cells <= most_cells;
+    int cut[4];
+    const bool streams = C == 64 && !ctx->bz_boxes && !ctx->mk_boxes && rh_block64_strips(W, cut, cut + 1, cut + 2, cut + 3);
+    const bool one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && !ctx->nd_places && cells <= (streams ? 8 * (size_t)ctx->n_cu : most_cells);
     // its counters: room for the most that the line allows in every call, so that what a call needs follows from its pixels alone
     const size_t sync_words = C == 64 ? BODY_ROLL_WORDS + 4 * most_cells : 0;
     need = (need + 63) & ~(size_t)63;
@@ -556,11 +558,11 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     uint32_t n_conv = 0;
     rh_prof_begin(ctx, RH_PROF_CONV);
 #define CONV(...) do { st = conv(ctx, __VA_ARGS__, n_valid, keep); if (st != RH_OK) return st; ++n_conv; } while (0)
-#define BLOCK32(...) do { RH_HIP(ctx, rh_launch_block32(ctx, __VA_ARGS__)); ++n_conv; } while (0)
+#define PAIR(...) do { RH_HIP(ctx, C == 32 ? rh_launch_block32(ctx, __VA_ARGS__) : rh_launch_block64(ctx, __VA_ARGS__)); ++n_conv; ctx->nd_conv += 2; } while (0)
 #define LAST_CONV(...) do { rh_prof_end(ctx, n_conv); rh_prof_scope ps_(ctx, RH_PROF_CONV_LAST); st = conv(ctx, __VA_ARGS__); if (st != RH_OK) return st; } while (0)
-    // 32 channels: two convs per launch (they are bound by memory, and the tensor between them stays on
-    // the chip); exact-border mode clears part of that tensor and runs them one by one
-    const bool pairs = C == 32 && !ctx->bz_boxes;
+    // Two convs per launch, the tensor between them stays on the chip.  Exact-border mode clears part of that tensor and runs them one by
+    // one; box-masked mode leaves out cells of every layer.
+    const bool pairs = C == 32 ? !ctx->bz_boxes : streams && !one_launch;
     const __bf16* body_out = nullptr;
     if (one_launch) {
         body_args b;
@@ -574,13 +576,13 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     if (d.topology == RH_NET_PLAIN) {
         const __bf16* x = one_launch ? body_out : h;
         int l = one_launch ? body_layers : 0;
-        for (; pairs && l + 1 < d.n_blocks - 2; l += 2, li += 2) { __bf16* o = (x == a) ? t : a; BLOCK32(L[li], L[li + 1], x, o, N, H, W, false, n_valid); x = o; }
+        for (; pairs && l + 1 < d.n_blocks - 2; l += 2, li += 2) { __bf16* o = (x == a) ? t : a; PAIR(L[li], L[li + 1], x, o, N, H, W, false, n_valid); x = o; }
         for (; l < d.n_blocks - 2; ++l) { __bf16* o = (x == a) ? t : a; CONV(L[li++], x, o, nullptr, N, H, W, 1, false, 1); ZERO(o, 1); x = o; }
         LAST_CONV(L[li++], x, out, nullptr, N, H, W, 0, true, s, n_valid);
     } else {
         const __bf16* x = one_launch ? body_out : h;
         for (int b = 0; b < d.n_blocks && !one_launch; ++b) {
-            if (pairs) { __bf16* o = (x == a) ? t : a; BLOCK32(L[li], L[li + 1], x, o, N, H, W, true, n_valid); li += 2; x = o; continue; }
+            if (pairs) { __bf16* o = (x == a) ? t : a; PAIR(L[li], L[li + 1], x, o, N, H, W, true, n_valid); li += 2; x = o; continue; }
             CONV(L[li++], x, t, nullptr, N, H, W, 1, false, 1); ZERO(t, 1);
             CONV(L[li++], t, a, x, N, H, W, 0, false, 1); ZERO(a, 1);      // x + conv(t)
             x = a;
@@ -609,7 +611,7 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
         }
     }
 #undef CONV
-#undef BLOCK32
+#undef PAIR
 #undef LAST_CONV
 #undef ZERO
     RH_HIP(ctx, hipGetLastError());

@@ -105,6 +105,10 @@ hipError_t rh_launch_conv_duo(hipStream_t stream, int device, const conv_args& a
 // two 3x3 convs of a 32-channel net in one launch (conv_block32.hip); res: a residual block, else two ReLU layers.  in != out
 hipError_t rh_launch_block32(rh_ctx* ctx, const rh_layer& L1, const rh_layer& L2, const __bf16* in, __bf16* out, int N, int H, int W,
                              bool res, const uint32_t* n_valid);
+// the same for 64 channels (conv_block64.hip); rh_block64_strips: how it cuts a width, false for those that it is not made for
+bool rh_block64_strips(int W, int* strips, int* wo, int* tiles, int* tiles2);
+hipError_t rh_launch_block64(rh_ctx* ctx, const rh_layer& L1, const rh_layer& L2, const __bf16* in, __bf16* out, int N, int H, int W,
+                             bool res, const uint32_t* n_valid);
 // last conv with 3 output channels and no pixel shuffle (conv_tail.hip)
 hipError_t rh_launch_conv_tail3(hipStream_t stream, int device, const conv_args& a, int cin);
 // first conv 3 -> C on the matrix cores (conv_head.hip)

@@ -416,6 +416,27 @@ def test_one_launch_body_beside_a_launch_per_layer(n):
         rhs[k].close()
 
 
+# Two 64-channel convs a launch as streams of rows: strips of every number of 16-pixel tiles, one to many of them, images of one row and more rows than a
+# workgroup's run.  Every image of a large batch as the same image in a small one, whose body is one launch of another kernel.
+@pytest.mark.parametrize("net", [wl.Net("res", 64, 2, 2, 0.02), wl.Net("edsr", 64, 1, 3, 0.02), wl.Net("plain", 64, 5, 2, 0.1)])
+@pytest.mark.parametrize("H,W", [(3, 49), (4, 64), (9, 56), (5, 80), (40, 96), (3, 112), (24, 128), (7, 129), (16, 160), (33, 192), (13, 333), (60, 480)])
+def test_row_streams_are_the_one_launch_body_bit_for_bit(net, H, W):
+    rh = RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=32, max_bins=4, net=net, weights=wl.make_weights(net, 23, "bf16"),
+            precision="bf16")
+    cells = -(-H // 8) * -(-W // 32)
+    big = 13 * torch.cuda.get_device_properties(0).multi_processor_count // cells + 1
+    x = torch.randint(0, 256, (5, H, W, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(W))
+    want = torch.cat([rh.enhance(x[i:i + 1].clone()) for i in range(5)])
+    xb = x[torch.arange(big, device="cuda") % 5].contiguous()
+    got = rh.enhance(xb)
+    for i in range(5):
+        assert bool((got[i::5] == want[i]).all()), i
+    some = torch.tensor([max(1, big // 3)], dtype=torch.int32, device="cuda")
+    part = rh.enhance(xb, n_valid=some, out=torch.full_like(got, 3.0))
+    assert torch.equal(part[:int(some)], got[:int(some)]) and bool((part[int(some):] == 3.0).all())
+    rh.close()
+
+
 # fp32 convs with a device-side count, the patch requested ahead of it (up to 8 workgroups a compute unit) and behind it:
 # the valid images as without a count, the others untouched, ragged tiles
 @pytest.mark.parametrize("net", [wl.Net("plain", 16, 3, 2), wl.Net("res", 32, 1, 3), wl.Net("edsr", 16, 1, 2, 0.05), wl.Net("res", 24, 1, 2)])
