@@ -18,17 +18,16 @@
 // / middle / right column); the interior is computed with the middle class, the ring pixel by pixel with the
 // weights of its class.
 //
-// Main kernel: implicit GEMM on v_mfma_f32_32x32x16_bf16, D[row][pixel], rows = (i, j, co) of one
-// 32-row chunk (x4: two chunks of two output rows i each; x2, x3: one chunk), N = 32 pixels of an
-// image row, K = tap * C + ci over 25 taps.  One persistent 512-thread workgroup per CU works on 8 x 32 tiles, from a
-// 12 x 36 pixel patch in LDS (same channels-last layout and XOR swizzle as the 3 x 3 kernels).  The waves split K: a wave
-// has 16 of the input channels, whose 25 weight fragments stay in 100 registers, and C / 16 pixel rows, an
-// accumulator each; the C / 16 waves of the same rows then exchange sums through LDS, and each adds up and stores one row.
-// Per tap column a wave reads 8 (6) activation fragments for 20 (10) MFMAs and no weights, and the sums that follow each other are
-// independent: with all of K in each of four waves and the weights in LDS (1.1 fragments per MFMA) a wave had two
-// rows, whose sums waited for each other's latency.  The next tile's patch is copied to LDS behind these MFMAs.
-// Whole calls of EDSR x4 with one block on 76 / 128 bins of 128 x 128, this kernel's share about a half: 563 -> 545, 940 -> 909 us;
-// three bins x3 16.3 -> 14.0 us of kernel; without the exchange 20 us less on 76 bins, without the stores 26 (both wrong results).
+// Main kernel: implicit GEMM on v_mfma_f32_16x16x32_bf16, D[row][pixel], rows = (i, j, co) in tiles of 16 (x4: 48 rows in three, x3: 27 in two, x2: 12 in
+// one), N = 16 pixels of an image row, K = tap * C + ci over 25 taps.  One persistent workgroup per CU works on 8 x 32 pixels, from a
+// 12 x 36 pixel patch in LDS (same channels-last layout and XOR swizzle as the 3 x 3 kernels), the next one's copied meanwhile.  A wave has one tile of
+// rows, 32 of C and a part of the pixels: its 25 weight fragments stay in registers, and an activation fragment, read once, feeds the up to five
+// image rows that it belongs to.  64 channels: the two waves that share rows and pixels exchange half of their sums each.  The sums go through LDS
+// in the order of the output, so that stores are whole lines: 16 bytes a lane, 4 where an image row's start or the ring cuts a group of four.
+// What bounds it: instruction issue (x4, an 8 x 32 tile: 9 600 cycles of products, 17 000 in all; a product of 16 cycles hides two other instructions).
+// With 32-row tiles (two at x4, three quarters full; one at x2, 3/8 full), a quarter of C a wave, all partial sums exchanged, and stores straight from
+// the sums, 4 bytes a lane at x3, then / now: the kernel on 76 bins of 128 x 128 x4 280 / 182 us, 264 bins x3 880 / 655; whole steps, the headline batch
+// 2 540 / 2 470, 16 whole frames 4 490 / 4 390, 32 frames 640 x 368 x3 9 900 / 9 790.
 #include <string.h>
 
 #include <atomic>
@@ -43,12 +42,12 @@
 
 struct fold_args {
     const __bf16* in;        // t: [N][H][W][CIN]
-    const uint4* wp;         // [class][chunk][tap][ks][lane]
-    const float* bias;       // [class][chunk][32]
+    const uint4* wp;         // [class][chunk][tap][ks][lane]; middle class: [tap][32 of C][16 rows][lane]
+    const float* bias;       // [class][chunk][32]; middle class: by row
     float* out;              // [N][s*H][s*W][3]
     const uint32_t* n_valid;
     int N, H, W;
-    int s, n_chunks, rows, ipc;   // scale, chunks, valid rows per chunk, output rows i per chunk
+    int n_chunks;            // of the ring's weights: 32 rows each
     int rev;
     int ring;                // 1: the outermost ring with its classes' weights; 0: it is not needed (no pixel of it is pasted)
     const uint32_t* tile_list;   // the tiles to compute (needed-region mode), or null: all tiles
@@ -58,9 +57,10 @@ struct fold_args {
 // Stores the 16 accumulator values of one lane: rows 8q + 4hi + e of chunk `chunk` for
 // low-resolution pixel (y, x) of image n.  Row rho of a chunk is (il, j, co) = (rho / 3s, rho / 3 % s,
 // rho % 3) with output row i = chunk * ipc + il.
+template <int s>
 __device__ __forceinline__ void fold_store(const fold_args& a, const f32x16& acc, int n, int y, int x, int chunk, int hi)
 {
-    const int s = a.s, OW = a.W * s;
+    const int OW = a.W * s;
     float* base = a.out + (((size_t)n * a.H * s + (size_t)y * s) * OW + (size_t)x * s) * 3;
     if (s == 4) {                      // 12 values per output row i: three aligned groups of four
 #pragma unroll
@@ -75,9 +75,9 @@ __device__ __forceinline__ void fold_store(const fold_args& a, const f32x16& acc
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int rho = 8 * q + 4 * hi + e;
-            if (rho >= a.rows) continue;
+            if (rho >= 3 * s * s) continue;
             const int il = rho / (3 * s), rem = rho - il * 3 * s;
-            base[(size_t)(chunk * a.ipc + il) * OW * 3 + rem] = acc[4 * q + e];
+            base[(size_t)(chunk * s + il) * OW * 3 + rem] = acc[4 * q + e];
         }
 }
 
@@ -94,7 +94,7 @@ __device__ __forceinline__ void fold_each_step(F& f)
 // A launch of its own behind the main kernel took 45 us on 76 bins of 128 x 128 and 9 on three; as the work that the main
 // kernel's waves do when they are out of tiles (idle workgroups at once): whole calls of EDSR x3 with one block on three bins 59.6 -> 51.6 us,
 // x4 on 76 566 -> 563, on 128 943 -> 938, on 16 of 64 x 64 60.0 -> 60.6.
-template <int CIN>
+template <int CIN, int S>
 __device__ __forceinline__ void fold_ring(const fold_args& a, int n_img, long w, long waves)
 {
     constexpr int KS = CIN / 16;
@@ -142,72 +142,89 @@ __device__ __forceinline__ void fold_ring(const fold_args& a, int n_img, long w,
                 load_tap(min(t0 + t + 3, taps - 1), A[t], B[t]);
             }
         }
-        if (valid) fold_store(a, acc, n, y, x, chunk, hi);
+        if (valid) fold_store<S>(a, acc, n, y, x, chunk, hi);
     }
 }
 
-// LDS of the main kernel: a patch, room, a patch.  The weights pass through room and second patch on their way to registers;
-// a tile's partial sums take the place of its patch and room.
-template <int CIN>
-struct fold_lds {
-    static constexpr int KS = CIN / 16, WBYTES = 25 * KS * 1024, PATCHB = (FOLD_TH + 4) * FOLD_PW * CIN * 2, ROOM = WBYTES - PATCHB;
-    static constexpr int SUMS = 8 * (KS - 1) * 4096, TOTAL = PATCHB + ROOM + PATCHB;
-    static_assert(ROOM % 16 == 0 && SUMS <= PATCHB + ROOM && PATCHB % 1024 == 0, "what takes whose place");
+// What a wave of the main kernel has: one of MT tiles of 16 rows, one of KH halves of C, one of PG parts of the 8 x 32 pixels - R image rows, 16 columns.
+template <int CIN, int S>
+struct fold_shape {
+    static constexpr int MT = (3 * S * S + 15) / 16, KH = CIN / 32, PG = MT * KH >= 4 ? 2 : MT * KH >= 2 ? 4 : 8, WAVES = MT * KH * PG, R = 16 / PG;
+    static constexpr int PASSES = KH == 2 && WAVES > 8 ? 2 : 1;      // three waves a SIMD: registers for half of the rows' sums
+    static constexpr int PATCHB = (FOLD_TH + 4) * FOLD_PW * CIN * 2, OUT = FOLD_TH * S * 96 * S * 4, LDS = 2 * PATCHB + OUT;
+    static_assert(PATCHB % 1024 == 0 && LDS <= 160 * 1024, "a patch is whole pieces; all of it fits");
 };
 
-template <int CIN, bool LIST>
-__global__ __launch_bounds__(512) void k_conv_fold(fold_args a)
+// C of a lane's four sums, from the e-th on, to and from LDS; `at` is aligned to C floats
+template <int C, int e>
+__device__ __forceinline__ void fold_put(float* at, const f32x4& v)
+{
+    if constexpr (C == 4) *(float4*)at = make_float4(v[0], v[1], v[2], v[3]);
+    else if constexpr (C == 2) *(float2*)at = make_float2(v[e], v[e + 1]);
+    else *at = v[e];
+}
+template <int C, int e>
+__device__ __forceinline__ void fold_get(f32x4& v, const float* at)
+{
+    if constexpr (C == 4) { const float4 f = *(const float4*)at; v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w; }
+    else if constexpr (C == 2) { const float2 f = *(const float2*)at; v[e] = f.x; v[e + 1] = f.y; }
+    else v[e] = *at;
+}
+
+template <int CIN, int S, bool LIST>
+__global__ __launch_bounds__((fold_shape<CIN, S>::WAVES * 64)) void k_conv_fold(fold_args a)
 {
     // LIST: the tiles come from a.tile_list.  An entry is requested two tiles ahead with a vector
     // load (a scalar load would share its counter with the LDS fragment reads) and read a tile later.
-    using L = fold_lds<CIN>;
-    constexpr int KS = L::KS, NCH = CIN / 8, PIXB = CIN * 2, TH = FOLD_TH, PW = FOLD_PW, RW = KS, NR = RW + 4;
-    constexpr int NPIECE = L::PATCHB / 1024, NPRE = (NPIECE + 7) / 8;        // a wave's 1 KB pieces of the patch
-    constexpr int SWZ_SH = (NCH == 8) ? 0 : 1;
+    using L = fold_shape<CIN, S>;
+    constexpr int NCH = CIN / 8, PIXB = CIN * 2, TH = FOLD_TH, PW = FOLD_PW, R = L::R, MT = L::MT, KH = L::KH, W_ = L::WAVES;
+    constexpr int RP = L::PASSES == 2 ? R / 2 : R, NFRAG = 5 * (RP + 4);             // image rows of a pass, and its fragments
+    constexpr int NPIECE = L::PATCHB / 1024, NPRE = (NPIECE + W_ - 1) / W_;          // a wave's 1 KB pieces of the patch
+    constexpr int SWZ_SH = (NCH == 8) ? 0 : 1, PXF = 3 * S, LINE = 32 * PXF;         // output floats of a pixel's and of the tile's image row
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    float* lds_o = (float*)(lds + 2 * L::PATCHB);                                    // [8 S lines][LINE]
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wk = wave % KS, wr = wave / KS;      // k-step and row group
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = wave % MT, kh = wave / MT % KH, pg = wave / (MT * KH);
+    const int col0 = (pg & 1) * 16, row0 = (pg >> 1) * R;                            // of the wave's pixels
 
     const uint32_t* counter = LIST ? a.n_list : a.n_valid;
     const uint32_t n_found = counter ? *counter : (uint32_t)a.N;
-    // tile lanes and chunks: as in the 3 x 3 kernel, the chunks of a layer are dealt to the workgroups
-    // of one XCD that share a tile lane (the input then comes from HBM once), XCD-contiguous tile runs
-    const bool deal = a.n_chunks > 1 && gridDim.x % (8 * a.n_chunks) == 0;
-    const int G = deal ? gridDim.x / a.n_chunks : gridDim.x;
-    const int xcd = blockIdx.x % 8, local = blockIdx.x / 8;
-    const int wg = deal ? xcd * (G / 8) + local / a.n_chunks : ((G % 8 == 0) ? xcd * (G / 8) + local : (int)blockIdx.x);
-    const int chunk_begin = deal ? local % a.n_chunks : 0, chunk_end = deal ? chunk_begin + 1 : a.n_chunks;
-    // the first chunk's weights are on their way before the image count is known
-    auto load_weights = [&](int chunk) __attribute__((always_inline)) {
-        lds_dma<512, L::WBYTES>(lds + L::PATCHB, a.wp + (size_t)(4 * a.n_chunks + chunk) * (L::WBYTES / 16), wave, lane);      // the middle class
-    };
-    load_weights(chunk_begin);
+    // the weights and the bias are on their way before the image count is known
+    const uint4* wp = a.wp + (size_t)4 * a.n_chunks * 25 * (CIN / 16) * 64 + (kh * MT + m) * 64 + lane;      // the middle class
+    bf16x8 A[25];
+#pragma unroll
+    for (int t = 0; t < 25; ++t) A[t] = *(const bf16x8*)(wp + t * (KH * MT * 64));
+    f32x4 bias_c = {0, 0, 0, 0};                           // of rows 16 m + 4 (lane / 16) + {0..3}; in the sums of the first half of C
+    if (kh == 0) {
+        const float4 v = *(const float4*)(a.bias + 4 * a.n_chunks * 32 + m * 16 + (lane >> 4) * 4);
+        bias_c[0] = v.x; bias_c[1] = v.y; bias_c[2] = v.z; bias_c[3] = v.w;
+    }
+    // XCD-contiguous tile runs, as in the 3 x 3 kernels
+    const int G = gridDim.x;
+    const int wg = (G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : (int)blockIdx.x;
     const int n_img = min((int)n_found, a.N);
     const int tiles_x = (a.W + 31) / 32, tiles_y = (a.H + TH - 1) / TH, tiles_img = tiles_x * tiles_y;
     const int n_tiles = LIST ? (int)n_found : n_img * tiles_img;
     const uint32_t in_img_bytes = (uint32_t)a.H * a.W * PIXB;
 
-    // piece i of the patch, by wave i % 8: 64 16-byte channel groups, 8 (16) pixels.  The pieces are contiguous in LDS, so the
-    // lanes fetch swizzled.  Rows outside the image lie outside the descriptor's range and read as zeros.
+    // piece i of the patch, by wave i % WAVES: 64 16-byte channel groups, 8 (16) pixels.  The pieces are contiguous in LDS, so the
+    // lanes fetch swizzled.  Rows outside the image lie outside the descriptor's range and read as zeros.  (Inline asm, with no register written: behind
+    // the builtin the compiler has LDS accesses wait for the copy.)
     // (`l` is the lane, passed through an empty asm statement in every phase: addresses kept over the loop would not fit the registers.)
+    auto lane_now = [&]() __attribute__((always_inline)) { int l = lane; asm volatile("" : "+v"(l)); return l; };
     auto load_patch = [&](uint8_t* to, __amdgpu_buffer_rsrc_t rin, int y0, int x0) __attribute__((always_inline)) {
-        int l = lane;
-        asm volatile("" : "+v"(l));
+        const int l = lane_now();
 #pragma unroll
         for (int j = 0; j < NPRE; ++j) {
-            const int i = j * 8 + wave;
+            const int i = j * W_ + wave;
             if (j == NPRE - 1 && i >= NPIECE) break;
             const uint32_t idx = i * 64 + l, px = idx / NCH, row = (px * 1821u) >> 16, col = px - row * PW;      // px / 36 for px < 432
             const int gx = x0 - 2 + (int)col;
             const uint32_t off = (uint32_t)((y0 - 2 + (int)row) * a.W + gx) * PIXB + (((idx ^ (col >> SWZ_SH)) & (NCH - 1)) << 4);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rin, (__attribute__((address_space(3))) void*)(to + i * 1024), 16,
-                                                     (uint32_t)gx < (uint32_t)a.W ? off : OOB_OFF, 0, 0, 0);
+            const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)(to + i * 1024));
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                         :: "s"(at), "v"((uint32_t)gx < (uint32_t)a.W ? off : OOB_OFF), "s"(rin) : "memory");
         }
-    };
-    auto decode = [&](int tile, int& n, int& y0, int& x0) __attribute__((always_inline)) {
-        n = tile / tiles_img;
-        const int tr = tile - n * tiles_img, ty = tr / tiles_x, tx = tr - ty * tiles_x;
-        y0 = ty * TH; x0 = tx * 32;
     };
     __amdgpu_buffer_rsrc_t rlist = __builtin_amdgcn_make_buffer_rsrc((void*)a.tile_list, 0, LIST ? (uint32_t)n_tiles * 4u : 0u, RSRC_FLAGS);
     auto list_load = [&](int idx) __attribute__((always_inline)) {       // entry of walk position idx (0 past the end)
@@ -220,127 +237,173 @@ __global__ __launch_bounds__(512) void k_conv_fold(fold_args a)
     auto tile_origin = [&](int tile, int& n, int& y0, int& x0) __attribute__((always_inline)) {
         if constexpr (LIST) { decode_cell(__builtin_amdgcn_readfirstlane(list_load(tile)), n, y0, x0); return; }
         if (a.rev && tile < n_tiles) tile = n_tiles - 1 - tile;          // walk back over what the previous layer wrote last
-        decode(tile, n, y0, x0);
+        n = tile / tiles_img;
+        const int tr = tile - n * tiles_img, ty = tr / tiles_x;
+        y0 = ty * TH; x0 = (tr - ty * tiles_x) * 32;
     };
     auto in_rsrc = [&](int tile, int n) __attribute__((always_inline)) {
         return __builtin_amdgcn_make_buffer_rsrc((void*)(a.in + (size_t)n * a.H * a.W * CIN), 0,
                                                  tile < n_tiles ? in_img_bytes : 0u, RSRC_FLAGS);
     };
-
-    int cn = 0, cy0 = 0, cx0 = 0, e_next = 0;             // LIST: origin of the current tile, entry of the next one
-    auto first_patch = [&]() __attribute__((always_inline)) {
-        tile_origin(wg, cn, cy0, cx0);
-        if constexpr (LIST) e_next = list_load(wg + G);
-        load_patch(lds, in_rsrc(wg, wg < n_tiles ? cn : 0), cy0, cx0);
+    // four rows of sums of a pixel, and their places in the tile's output: LINE floats a line, of which the pixel has 3 S in each of S lines
+    auto places = [&](auto&& put) __attribute__((always_inline)) {       // put(first of the rows, how many, where)
+        const int l = lane_now(), rho = m * 16 + (l >> 4) * 4, px = (l & 15) + col0;
+        constexpr int STEP = S == 4 ? 4 : S == 2 ? 2 : 1;
+        auto part = [&](auto k_c) __attribute__((always_inline)) {
+            constexpr int e = decltype(k_c)::value * STEP;
+            const int i = (rho + e) / PXF;
+            if (S == 4 || rho + e < S * PXF) put(std::integral_constant<int, STEP>{}, std::integral_constant<int, e>{}, lds_o + row0 * S * LINE + i * LINE + px * PXF + (rho + e - i * PXF));
+        };
+        fold_each_step<4 / STEP>(part);
     };
-    first_patch();                                         // ahead of what the compiler computes once for all turns of the loops
-    for (int chunk = chunk_begin; chunk < chunk_end; ++chunk) {
-        if (chunk != chunk_begin) {
-            __syncthreads();                               // previous chunk's LDS reads are done
-            load_weights(chunk);
-            first_patch();
-        }
-        f32x16 biasv;                                      // lane holds rows 8q + 4hi + e in [4q + e]; in the sums of the first k-step
-#pragma unroll
-        for (int e = 0; e < 16; ++e) { biasv[e] = a.bias[(4 * a.n_chunks + chunk) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)]; biasv[e] = wk == 0 ? biasv[e] : 0.0f; }
-        lds_dma_wait();                                    // weights and first patch
-        __syncthreads();
-        bf16x8 A[25];
-#pragma unroll
-        for (int tap = 0; tap < 25; ++tap) A[tap] = *(const bf16x8*)(lds + L::PATCHB + ((tap * KS + wk) << 10) + (lane << 4));
-        lds_barrier();                                     // read by every wave
-        uint8_t* patch = lds;
-        for (int tile = wg; tile < n_tiles; tile += G) {   // trip count uniform over the workgroup
-            int n, y0, x0;
-            if constexpr (LIST) { n = cn; y0 = cy0; x0 = cx0; } else tile_origin(tile, n, y0, x0);
-            int e_after = 0;
-            if constexpr (LIST) e_after = list_load(tile + 2 * G);
-            const int nt = tile + G;
-            int nn, ny0, nx0;
-            if constexpr (LIST) { decode_cell(__builtin_amdgcn_readfirstlane(e_next), nn, ny0, nx0); cn = nn; cy0 = ny0; cx0 = nx0; e_next = e_after; }
-            else tile_origin(nt, nn, ny0, nx0);
-            uint8_t* other = patch == lds ? lds + L::PATCHB + L::ROOM : lds;
-            load_patch(other, in_rsrc(nt, nt < n_tiles ? nn : 0), ny0, nx0);
 
-            f32x16 acc[RW];
-            const uint8_t* prow = patch + (wr * RW) * (PW * PIXB);
-            int l = lane;
-            asm volatile("" : "+v"(l));
-            auto bptr = [&](int kx) __attribute__((always_inline)) {
-                const int px = (l & 31) + kx;
-                return prow + px * PIXB + (((2 * wk + (l >> 5)) ^ ((px >> SWZ_SH) & (NCH - 1))) << 4);
-            };
-            bf16x8 B[NR];
-            {
-                const uint8_t* b0 = bptr(0);
+    // the tile's output, whole in LDS, to memory; n < 0: there is none
+    auto store = [&](int n, int y0, int x0) __attribute__((always_inline)) {
+        if (n < 0) return;
+        const int off = a.ring;                            // the ring's pixels are another wave's
+        const int lo = off && x0 == 0 ? PXF : 0, hi = min(32, a.W - off - x0) * PXF, pitch = a.W * PXF;
+        float* base = a.out + (((size_t)n * a.H + y0) * S) * pitch + x0 * PXF;
+        const int lines0 = off && y0 == 0 ? S : 0, lines1 = min(TH, a.H - off - y0) * S;
+        const int t = wave * 64 + lane_now();
+        if (S == 4 || (pitch & 3) == 0) {
 #pragma unroll
-                for (int py = 0; py < NR; ++py) B[py] = *(const bf16x8*)(b0 + py * (PW * PIXB));
+            for (int u0 = 0; u0 < TH * S * LINE / 4; u0 += W_ * 64) {
+                const int u = u0 + t, line = u / (LINE / 4), col = (u - line * (LINE / 4)) * 4;
+                if (u0 + W_ * 64 > TH * S * LINE / 4 && u >= TH * S * LINE / 4) break;
+                const float4 v = *(const float4*)(lds_o + u * 4);
+                float* to = base + (size_t)line * pitch + col;
+                if (line < lines0 || line >= lines1) continue;
+                if (S == 4 ? col >= lo && col < hi : col >= lo && col + 4 <= hi) { *(float4*)to = v; continue; }
+                if constexpr (S != 4) {                    // the ring or the image's end cuts the four
+                    if (col >= lo && col < hi) to[0] = v.x;
+                    if (col + 1 >= lo && col + 1 < hi) to[1] = v.y;
+                    if (col + 2 >= lo && col + 2 < hi) to[2] = v.z;
+                    if (col + 3 >= lo && col + 3 < hi) to[3] = v.w;
+                }
             }
+        } else {
+#pragma unroll 4
+            for (int u = t; u < TH * S * LINE; u += W_ * 64) {
+                const int line = u / LINE, col = u - line * LINE;
+                const float v = lds_o[u];
+                if (line >= lines0 && line < lines1 && col >= lo && col < hi) base[(size_t)line * pitch + col] = v;
+            }
+        }
+    };
+    int n, y0, x0, e_next = 0;
+    tile_origin(wg, n, y0, x0);
+    if constexpr (LIST) e_next = list_load(wg + G);
+    load_patch(lds, in_rsrc(wg, wg < n_tiles ? n : 0), y0, x0);
+    lds_dma_wait();                                        // and the weights
+    lds_barrier();
+    uint8_t* patch = lds;
+    int nn = n, ny0 = y0, nx0 = x0, pn = -1, py0 = 0, px0 = 0;       // origins of the next and of the last tile
+    for (int tile = wg; tile < n_tiles; tile += G) {       // trip count uniform over the workgroup
+        uint8_t* other = patch == lds ? lds + L::PATCHB : lds;
+        // what is to be done beside the products
+        auto aside = [&]() __attribute__((always_inline)) {
+            store(pn, py0, px0);
+            const int nt = tile + G;
+            if constexpr (LIST) { const int e_after = list_load(tile + 2 * G); decode_cell(__builtin_amdgcn_readfirstlane(e_next), nn, ny0, nx0); e_next = e_after; }
+            else tile_origin(nt, nn, ny0, nx0);
+            load_patch(other, in_rsrc(nt, nt < n_tiles ? nn : 0), ny0, nx0);
+        };
+
+        // RP rows of pixels from patch row `prow` on.  Fragment i: tap column i / (RP + 4), image row i % (RP + 4); two at a time, read a pair ahead.  Two
+        // sums a row, of the taps of a chessboard's colours (three waves a SIMD, where that does not fit the registers: of even and of odd tap columns): with
+        // the halves of C four chains of products.  In one chain a half of C the error against 64 bits was a third larger; so it is what it was with a
+        // quarter of C in each of four waves (64 channels, rms at x2, x3, x4: 4.5, 4.0, 6.6e-9 of 0.055; 4.8, 4.3, 6.7 then).
+        f32x4 acc[2][RP];
+        bf16x8 B[4];
+        auto pass = [&](const uint8_t* prow, auto between) __attribute__((always_inline)) {
+            const int l = lane_now();
+            auto load = [&](int i) __attribute__((always_inline)) {
+                const int px = col0 + (l & 15) + i / (RP + 4);
+                B[i % 4] = *(const bf16x8*)(prow + px * PIXB + (((4 * kh + (l >> 4)) ^ ((px >> SWZ_SH) & (NCH - 1))) << 4) + i % (RP + 4) * (PW * PIXB));
+            };
+            load(0); load(1);
             __builtin_amdgcn_sched_barrier(0);
-            auto step = [&](auto kx_c) __attribute__((always_inline)) {
-                constexpr int kx = decltype(kx_c)::value;
-                const uint8_t* bn = bptr(kx + 1);
+            auto frag = [&](auto i_c) __attribute__((always_inline)) {
+                constexpr int i = decltype(i_c)::value, kx = i / (RP + 4), py = i % (RP + 4), k0 = py < RP ? 0 : py - RP + 1, k1 = py < 4 ? py : 4;
+                if constexpr (i % 2 == 0) asm volatile("" :: "v"(B[i % 4]), "v"(B[(i + 1) % 4]));
 #pragma unroll
-                for (int k = 0; k < 5 * RW; ++k) {         // the rows in turn, so that a sum's products are RW products apart
-                    const int ky = k / RW, r = k % RW;
-                    acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[ky * 5 + kx], B[r + ky], kx == 0 && ky == 0 ? biasv : acc[r], 0, 0, 0);
-                    // a fragment's last product is behind it: the next tap column's takes its place
-                    if (kx < 4 && (r == 0 || ky == 4)) B[r + ky] = *(const bf16x8*)(bn + (r + ky) * (PW * PIXB));
+                for (int k = 0; k <= k1 - k0; ++k) {       // there and back over the rows: from one product to the next only one operand changes
+                    const int ky = i % 2 ? k1 - k : k0 + k;
+                    const int set = (W_ > 8 ? kx : kx + ky) & 1, first = W_ > 8 ? ky == 0 && kx < 2 : kx == 0 && ky < 2;
+                    f32x4& d = acc[set][py - ky];
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[ky * 5 + kx], B[i % 4], !first ? d : set ? f32x4{0, 0, 0, 0} : bias_c, 0, 0, 0);
+                    if (k == 0 && i + 2 < NFRAG) load(i + 2);
                     __builtin_amdgcn_sched_barrier(0);
                 }
+                between(i_c);
             };
-            fold_each_step<5>(step);
-
-            // row r of the group is added up and stored by the wave of k-step r; the partial sums of the others, in order of their k-steps
-            lds_dma_wait();                                // the next patch: nothing of it is in flight behind the sums' LDS writes
-            lds_barrier();                                 // the patch is read by every wave
-            asm volatile("" : "+v"(l));
-            float4* sums = (float4*)(patch == lds ? lds : lds + L::PATCHB) + l;
-            f32x16 sum;
-            auto add_up = [&](auto k_c) __attribute__((always_inline)) {
-                constexpr int own = decltype(k_c)::value;
+            fold_each_step<NFRAG>(frag);
 #pragma unroll
-                for (int r = 0; r < RW; ++r)
-                    if (r != own)
+            for (int r = 0; r < RP; ++r)
 #pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            sums[(((wr * KS + r) * (KS - 1) + (own < r ? own : own - 1)) * 4 + q) * 64] =
-                                make_float4(acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]);
-                lds_barrier();
+                for (int z = 0; z < 4; ++z) acc[0][r][z] += acc[1][r][z];
+        };
+        auto nothing = [](auto) {};
+        auto with_aside = [&](auto i_c) __attribute__((always_inline)) {
+            // in the waves of a SIMD one after the other, so that the others keep the matrix pipe busy
+            constexpr int i = decltype(i_c)::value, D = NFRAG / (L::PASSES == 2 ? 4 : 6);
+            if constexpr (i >= 2 && (i - 2) % D == 0 && (i - 2) / D < W_ / 4) if (wave / 4 == (i - 2) / D) aside();
+            if constexpr (L::PASSES == 1 && i == NFRAG / 2) asm volatile("s_barrier" ::: "memory");       // every wave has read the last tile's output from LDS
+        };
+        // 64 channels: of half of its rows a wave hands its sums over, of the others it adds up both halves of C
+        auto put = [&](int row, auto first_c, auto rows_c) __attribute__((always_inline)) {
+            places([&](auto c, auto e_c, float* to) __attribute__((always_inline)) {
 #pragma unroll
-                for (int src = 0; src < KS; ++src) {
-                    f32x16 p;
-                    if (src == own) p = acc[own];
-                    else
+                for (int r = 0; r < decltype(rows_c)::value; ++r) fold_put<decltype(c)::value, decltype(e_c)::value>(to + (row + r) * S * LINE, acc[0][decltype(first_c)::value + r]);
+            });
+        };
+        auto add = [&](int row, auto first_c, auto rows_c) __attribute__((always_inline)) {
+            places([&](auto c, auto e_c, float* to) __attribute__((always_inline)) {
+                constexpr int C = decltype(c)::value, e = decltype(e_c)::value, N = decltype(rows_c)::value;
+                f32x4 v[N];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const float4 v = sums[(((wr * KS + own) * (KS - 1) + (src < own ? src : src - 1)) * 4 + q) * 64];
-                            p[4 * q] = v.x; p[4 * q + 1] = v.y; p[4 * q + 2] = v.z; p[4 * q + 3] = v.w;
-                        }
+                for (int r = 0; r < N; ++r) fold_get<C, e>(v[r], to + (row + r) * S * LINE);
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) sum[e] = src ? sum[e] + p[e] : p[e];
+                for (int r = 0; r < N; ++r) {
+#pragma unroll
+                    for (int z = e; z < e + C; ++z) v[r][z] += acc[0][decltype(first_c)::value + r][z];
+                    fold_put<C, e>(to + (row + r) * S * LINE, v[r]);
                 }
-            };
-            if constexpr (KS == 4) {
-                if (wk == 0) add_up(std::integral_constant<int, 0>{});
-                else if (wk == 1) add_up(std::integral_constant<int, 1>{});
-                else if (wk == 2) add_up(std::integral_constant<int, 2>{});
-                else add_up(std::integral_constant<int, 3>{});
-            } else {
-                if (wk == 0) add_up(std::integral_constant<int, 0>{});
-                else add_up(std::integral_constant<int, 1>{});
+            });
+        };
+        constexpr std::integral_constant<int, 0> ZERO{};
+        constexpr std::integral_constant<int, KH == 2 ? R / 2 : R> HALF{};
+        const uint8_t* rows = patch + row0 * (PW * PIXB);
+        const int own = kh * HALF;
+        if constexpr (L::PASSES == 2) {
+            pass(rows + (HALF - own) * (PW * PIXB), with_aside);
+            asm volatile("s_barrier" ::: "memory");        // every wave has read the last tile's output from LDS
+            put(HALF - own, ZERO, HALF);
+            pass(rows + own * (PW * PIXB), nothing);
+            lds_barrier();
+            lds_dma_wait();                                // the next patch
+            add(own, ZERO, HALF);
+        } else {
+            pass(rows, with_aside);
+            if constexpr (KH == 2) {
+                if (kh) put(0, ZERO, HALF); else put(HALF, HALF, HALF);
+                lds_barrier();
             }
-            const int x = x0 + (l & 31), y = y0 + wr * RW + wk;
-            const int off = a.ring;                        // the ring's pixels are another wave's
-            if (y >= off && y < a.H - off && x >= off && x < a.W - off) fold_store(a, sum, n, y, x, chunk, l >> 5);
-            lds_barrier();                                 // sums read, next patch visible
-            patch = other;
+            lds_dma_wait();
+            if constexpr (KH == 1) put(0, ZERO, HALF);
+            else if (kh) add(HALF, HALF, HALF);
+            else add(0, ZERO, HALF);
         }
+        lds_barrier();                                     // the tile's output and the next patch are there
+        pn = n; py0 = y0; px0 = x0;
+        n = nn; y0 = ny0; x0 = nx0;
+        patch = other;
     }
+    store(pn, py0, px0);
     if (a.ring) {
         // workgroups that have had a tile more, or one at all, come last
-        const int n_ring = a.n_valid ? min((int)*a.n_valid, a.N) : a.N, place = deal ? wg * a.n_chunks + chunk_begin : wg;
-        fold_ring<CIN>(a, n_ring, (long)((int)gridDim.x - 1 - place) + (long)wave * gridDim.x, 8l * gridDim.x);
+        const int n_ring = a.n_valid ? min((int)*a.n_valid, a.N) : a.N;
+        fold_ring<CIN, S>(a, n_ring, (long)((int)gridDim.x - 1 - wg) + (long)wave * gridDim.x, (long)W_ * gridDim.x);
     }
 }
 
@@ -435,7 +498,8 @@ uint16_t fold_bf16(double v)
 
 // Builds ctx->fold_w / fold_b for an EDSR-shaped net; a no-op for the other topologies.
 // Layout: fold_w [class 9][chunk][tap 25][ks][lane 64][8] bf16 with row = lane % 32 of the chunk and
-// ci = 16 ks + 8 (lane / 32) + e; fold_b [class][chunk][32] fp32.
+// ci = 16 ks + 8 (lane / 32) + e; fold_b [class][chunk][32] fp32.  In the place of the middle class, the main kernel's:
+// [tap 25][kh][m][lane 64][8] with row = 16 m + lane % 16 and ci = 32 kh + 8 (lane / 16) + e; its biases by row.
 rh_status rh_fold_weights(rh_ctx* ctx, const float* blob)
 {
     const rh_net_desc& d = ctx->cfg.net;
@@ -494,6 +558,10 @@ rh_status rh_fold_weights(rh_ctx* ctx, const float* blob)
     for (int cls = 0; cls < 9; ++cls)
         for (int m = 0; m < n_chunks; ++m) {
             const int py = 2 * (cls / 3), px = 2 * (cls % 3);
+            if (cls == 4) {                                // the main kernel's, below
+                wi += (size_t)25 * KS * 64 * 8;
+                continue;
+            }
             for (int tap = 0; tap < 25; ++tap)
                 for (int ks = 0; ks < KS; ++ks)
                     for (int lane = 0; lane < 64; ++lane)
@@ -511,32 +579,49 @@ rh_status rh_fold_weights(rh_ctx* ctx, const float* blob)
                 bp[((size_t)cls * n_chunks + m) * 32 + rho] = (float)bias_all[((size_t)(py * s + i) * gl + (px * s + j)) * 3 + co];
             }
         }
+    const int MT = (R + 15) / 16;
+    wi = (size_t)4 * n_chunks * 25 * KS * 64 * 8;
+    for (int tap = 0; tap < 25; ++tap)
+        for (int kh = 0; kh < C / 32; ++kh)
+            for (int m = 0; m < MT; ++m)
+                for (int lane = 0; lane < 64; ++lane)
+                    for (int e = 0; e < 8; ++e) {
+                        const int o = 16 * m + (lane & 15), ci = kh * 32 + 8 * (lane >> 4) + e;
+                        wp[wi++] = fold_bf16(o < R ? Wc[(((size_t)4 * R + o) * 25 + tap) * C + ci] : 0.0);
+                    }
+    for (int o = 0; o < R; ++o) {
+        const int i = o / (3 * s), j = o / 3 % s, co = o % 3;
+        bp[(size_t)4 * n_chunks * 32 + o] = (float)bias_all[((size_t)(2 * s + i) * gl + (2 * s + j)) * 3 + co];
+    }
     RH_HIP(ctx, hipMalloc(&ctx->fold_w, wp.size() * 2));
     RH_HIP(ctx, hipMalloc((void**)&ctx->fold_b, bp.size() * 4));
     RH_HIP(ctx, hipMemcpy(ctx->fold_w, wp.data(), wp.size() * 2, hipMemcpyHostToDevice));
     RH_HIP(ctx, hipMemcpy(ctx->fold_b, bp.data(), bp.size() * 4, hipMemcpyHostToDevice));
-    ctx->fold_chunks = n_chunks; ctx->fold_rows = rows; ctx->fold_ipc = ipc;
+    ctx->fold_chunks = n_chunks;
     return RH_OK;
+}
+
+template <int CIN, int S, bool LIST>
+static hipError_t launch_fold(rh_ctx* ctx, const fold_args& a)
+{
+    using L = fold_shape<CIN, S>;
+    static bool attr_done[RH_MAX_DEVICES] = {};
+    if (!attr_done[ctx->device]) {
+        hipError_t e = hipFuncSetAttribute((const void*)k_conv_fold<CIN, S, LIST>, hipFuncAttributeMaxDynamicSharedMemorySize, L::LDS);
+        if (e != hipSuccess) return e;
+        attr_done[ctx->device] = true;
+    }
+    hipLaunchKernelGGL((k_conv_fold<CIN, S, LIST>), dim3(ctx->n_cu), dim3(L::WAVES * 64), L::LDS, ctx->stream, a);
+    return hipGetLastError();
 }
 
 template <int CIN>
 static hipError_t launch_fold(rh_ctx* ctx, const fold_args& a)
 {
-    constexpr int lds = fold_lds<CIN>::TOTAL;
-    static bool attr_done[RH_MAX_DEVICES] = {};
-    if (!attr_done[ctx->device]) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_conv_fold<CIN, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_conv_fold<CIN, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-        attr_done[ctx->device] = true;
-    }
-    // Needed-region mode: a pasted macroblock lies at least `halo` pixels inside its box, hence inside
-    // the bin, so with a halo no pasted pixel is on the outermost ring.
-    fold_args m = a;
-    m.ring = !(a.tile_list && ctx->cfg.halo >= 1);
-    if (a.tile_list) hipLaunchKernelGGL((k_conv_fold<CIN, true>), dim3(ctx->n_cu), dim3(512), lds, ctx->stream, m);
-    else hipLaunchKernelGGL((k_conv_fold<CIN, false>), dim3(ctx->n_cu), dim3(512), lds, ctx->stream, m);
-    return hipGetLastError();
+    const int s = ctx->cfg.net.scale;
+    if (s == 4) return a.tile_list ? launch_fold<CIN, 4, true>(ctx, a) : launch_fold<CIN, 4, false>(ctx, a);
+    if (s == 3) return a.tile_list ? launch_fold<CIN, 3, true>(ctx, a) : launch_fold<CIN, 3, false>(ctx, a);
+    return a.tile_list ? launch_fold<CIN, 2, true>(ctx, a) : launch_fold<CIN, 2, false>(ctx, a);
 }
 
 // t: the body's output [N][H][W][C] bf16 -> raw network output fp32 [N][sH][sW][3]; one launch.
@@ -546,8 +631,10 @@ rh_status rh_launch_fold(rh_ctx* ctx, const __bf16* t, float* out, int N, int H,
     fold_args a;
     a.tile_list = tile_list; a.n_list = n_list;
     a.in = t; a.wp = (const uint4*)ctx->fold_w; a.bias = ctx->fold_b; a.out = out; a.n_valid = n_valid;
-    a.N = N; a.H = H; a.W = W; a.s = ctx->cfg.net.scale; a.n_chunks = ctx->fold_chunks; a.rows = ctx->fold_rows;
-    a.ipc = ctx->fold_ipc; a.rev = rev;
+    a.N = N; a.H = H; a.W = W; a.n_chunks = ctx->fold_chunks; a.rev = rev;
+    // Needed-region mode: a pasted macroblock lies at least `halo` pixels inside its box, hence inside
+    // the bin, so with a halo no pasted pixel is on the outermost ring.
+    a.ring = !(tile_list && ctx->cfg.halo >= 1);
     const int C = ctx->cfg.net.channels;
     RH_HIP(ctx, C == 64 ? launch_fold<64>(ctx, a) : launch_fold<32>(ctx, a));
     return RH_OK;

@@ -63,8 +63,7 @@ struct rh_ctx {
     // EDSR-shaped nets, bf16: the upsampler and the last conv composed into one 5 x 5 conv (conv_fold.hip)
     void* fold_w;           // dev: bf16 weights [class 9][chunk][tap 25][k-step][lane][8]
     float* fold_b;          // dev: [class][chunk][32]
-    int fold_chunks;        // 32-row chunks of the composed conv's 3*s*s outputs (0: no composed conv)
-    int fold_rows, fold_ipc;   // valid rows per chunk, output rows i per chunk
+    int fold_chunks;        // 32-row chunks of the composed conv's 3*s*s outputs on the outermost ring (0: no composed conv)
 
     // select scratch (dev)
     int32_t* frame_seg;     // [max_frames] segment of each frame or -1
