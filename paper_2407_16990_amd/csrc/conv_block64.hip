@@ -73,7 +73,7 @@ struct block64_args {
 struct block64_row { int n, strip, y0, y1, r; };
 
 template <int NT, int NT2, bool RES>
-__global__ __launch_bounds__(512) void k_block64(block64_args a)
+__global__ __launch_bounds__(512) void k_conv_mfma_block64(block64_args a)
 {
     constexpr int PIXB = 128, ROWPX = 16 * NT + 8, ROWB = ROWPX * PIXB;
     constexpr int X = B64_X, Y = X + 4 * NT, Z = Y + 4 * NT, BIAS = Z + 4 * NT;
@@ -311,11 +311,11 @@ static hipError_t launch_block64(hipStream_t stream, int device, int grid, const
     constexpr int lds = (B64_RING + 2) * (16 * NT + 8) * 128;
     static bool attr_done[RH_MAX_DEVICES] = {};            // the attribute is per device
     if (!attr_done[device]) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_block64<NT, NT2, RES>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_block64<NT, NT2, RES>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         attr_done[device] = true;
     }
-    hipLaunchKernelGGL((k_block64<NT, NT2, RES>), dim3(grid), dim3(512), lds, stream, a);
+    hipLaunchKernelGGL((k_conv_mfma_block64<NT, NT2, RES>), dim3(grid), dim3(512), lds, stream, a);
     return hipGetLastError();
 }
 

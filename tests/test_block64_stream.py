@@ -1,4 +1,4 @@
-"""The row streams of k_block64 (conv_block64.hip) on the CPU: which input row lies in which place, which row of the tensor between a product reads,
+"""The row streams of k_conv_mfma_block64 (conv_block64.hip) on the CPU: which input row lies in which place, which row of the tensor between a product reads,
 when an output row is finished, rounded and stored, and what columns beside a strip or an image hold - with one channel and whole
 numbers, so that every output must be exact.  And of the compiled kernel: that the compiler keeps nothing in the registers that the kernel
 names itself."""
@@ -167,7 +167,7 @@ def test_the_compiler_keeps_out_of_the_named_registers(tmp_path):
     inside, kernels, written = False, 0, []                  # registers that the last vector instructions wrote
     span = lambda t: set(range(int(t[0]), int(t[-1]) + 1))
     for line in out.read_text().splitlines():
-        kernels += line.startswith("_Z9k_block64") and line.rstrip().endswith(":") or ".amdhsa_kernel" in line
+        kernels += line.startswith("_Z9k_conv_mfma_block64") and line.rstrip().endswith(":") or ".amdhsa_kernel" in line
         if "#ASMSTART" in line or "#ASMEND" in line:
             inside = "#ASMSTART" in line
         code = line.split(";")[0].strip()

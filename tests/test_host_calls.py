@@ -97,10 +97,13 @@ def bodies(call):
 for net, layers in ((EDSR, 64, 2, 4, 1), 5), ((RES, 64, 2, 2, 1), 4), ((PLAIN, 64, 6, 2, 1), 4):
     st, ctx = create(*net, S=128, bins=64)
     assert st == 0
-    for n, h, w in ((1, 3, 3), (48, 128, 128), (3072, 8, 32), (768, 9, 33)):       # half tiles of 8 x 32, 256 compute units
+    # half tiles of 8 x 32, 256 compute units; up to eight a unit where the other side is two convs a launch (widths above 48)
+    for n, h, w in ((1, 3, 3), (32, 128, 128), (3072, 8, 32), (768, 9, 33)):
         assert bodies(lambda: L.rh_enhance(ctx, P(1), n, h, w, P(2), None)) == (1, 3), (net, n)
-    for n, h, w in ((49, 128, 128), (3073, 8, 32), (769, 9, 33)):
+    for n, h, w in ((3073, 8, 32), (769, 9, 33)):
         assert bodies(lambda: L.rh_enhance(ctx, P(1), n, h, w, P(2), None)) == (0, layers + 2), (net, n)
+    for n, h, w in ((33, 128, 128), (48, 128, 128), (49, 128, 128)):
+        assert bodies(lambda: L.rh_enhance(ctx, P(1), n, h, w, P(2), None)) == (0, (layers + 1) // 2 + 2), (net, n)
     assert bodies(lambda: L.rh_enhance_exact(ctx, P(1), 48, P(3), P(4), P(2), None))[0] == 1
     assert bodies(lambda: L.rh_enhance_exact(ctx, P(1), 49, P(3), P(4), P(2), None))[0] == 0
     assert bodies(lambda: L.rh_enhance_masked(ctx, P(1), 3, P(3), P(4), P(2), None))[0] == 0
