@@ -1,5 +1,7 @@
 // The body of a 64-channel bf16 net - every 3x3 conv between the first one and the tail - in ONE launch.
 //
+// A few images go two layers at a time (conv_body_pairs.h), more of them a layer at a time, as follows.
+//
 // A unit of work is one half tile (8 x 32 pixels, all 64 output channels) of one layer; it is computed as in
 // k_conv_mfma_duo: two teams of four waves, one in its MFMA loop while the other rounds, stores and loads, in phases of
 // two barriers.  What differs is where units come from and what they wait for:
@@ -24,16 +26,15 @@
 // waves look at the start of the unit's own compute phase until it is.  The first is what happens with six units or more a
 // layer and workgroup, the last with one or two.
 //
-// What bounds it: with few units a chain per layer of look, patch, 2 us of MFMAs, rounding, stores and words, 7.9 us on
-// 3 bins of 128 x 128 (192 units) where a launch per layer takes 8.5 to 11; with many the matrix pipe at the chip's power
+// What bounds it: with two or three units a workgroup and layer still the chain per layer of look, patch, 2 us of MFMAs, rounding, stores and words; with many the matrix pipe at the chip's power
 // limit, as in k_conv_mfma_duo.  A layer's weights (72 KB) go to LDS while the other team stores.
-#include "conv_body_roll.h"
-#include "conv_mfma64.h"
-
-#define FEW_UNITS 4
 #define LD_PAST 16                       // loads: sc1
 #define BODY_ROLL_POLLS 64               // of about a us each
 #define BODY_POLLS (1 << 21)             // a second or more: never reached while the workgroups on the roll run
+#include "conv_body_pairs.h"
+#include "conv_body_roll.h"
+
+#define FEW_UNITS 4
 
 __device__ __forceinline__ void body_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -54,7 +55,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
     uint8_t* lds_w = lds;
     uint8_t* lds_p = lds + WBYTES + team * PATCHB;
     __shared__ uint32_t s_ready[2][2];                        // [team][its units in turn]: what it reads was there
-    __shared__ uint32_t s_again[2], s_sync[2], s_lost, s_wg[3];
+    __shared__ uint32_t s_again[2], s_sync[2], s_lost, s_wg[3], s_stored;
     __shared__ __attribute__((aligned(16))) float s_bias[2][64];
 
     const int n_img = a.n_valid ? min((int)*a.n_valid, a.N) : a.N;
@@ -63,6 +64,8 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
     const uint32_t img_bytes = (uint32_t)a.H * a.W * PIXB;
     const int row_pitch = a.W * PIXB;
     const size_t img_elems = (size_t)a.H * a.W * CIN;
+    const int pair_rows = body_pair_rows(max(n_img, 0), a.H, a.W, gridDim.x);
+    const uint32_t units = pair_rows ? body_pair_units(max(n_img, 0), a.H, a.W, pair_rows) : layer_units;
 
     // what layer l reads and writes (the order of the buffers is the caller's of one launch per layer)
     const bool plain = a.topology == RH_NET_PLAIN;
@@ -149,7 +152,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
 
     // ---- start: who takes part ----
     if (tid == 0) {
-        s_lost = 0; s_again[0] = 0; s_again[1] = 0; s_sync[0] = 0; s_sync[1] = 0; s_ready[0][0] = 0; s_ready[1][0] = 0;
+        s_lost = 0; s_stored = 0; s_again[0] = 0; s_again[1] = 0; s_sync[0] = 0; s_sync[1] = 0; s_ready[0][0] = 0; s_ready[1][0] = 0;
         const uint32_t sign = __hip_atomic_fetch_add(a.roll, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         body_place p;
         for (int polls = 0;;) {
@@ -158,13 +161,18 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
             if (++polls > BODY_ROLL_POLLS)
                 __hip_atomic_compare_exchange_strong(a.roll, &r, body_roll_closed(r), __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        body_roll_spread(&p, gridDim.x, (uint32_t)layer_units);
-        s_wg[2] = body_roll_leaves(&p, (uint32_t)layer_units);
+        body_roll_spread(&p, gridDim.x, units);
+        s_wg[2] = body_roll_leaves(&p, units);
         s_wg[0] = p.wg; s_wg[1] = p.G;
     }
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(s_wg[2])) return;     // not needed, or too late
     const int G = (int)__builtin_amdgcn_readfirstlane(s_wg[1]), wg = (int)__builtin_amdgcn_readfirstlane(s_wg[0]);
+    switch (pair_rows) {
+#define PAIRS(TH) case TH: body_pairs<TH, KEEP>(lds, &s_stored, &s_lost, n_img, wg, G); return
+    PAIRS(4); PAIRS(6); PAIRS(8); PAIRS(10); PAIRS(12); PAIRS(14); PAIRS(16); PAIRS(18); PAIRS(20); PAIRS(22);
+#undef PAIRS
+    }
     body_unit cur = unit_at(0, wg, team * G);                // the unit to compute next
     body_unit prev = cur;                                    // the one in the accumulators
     bool loaded = false, word_due = false;
@@ -181,7 +189,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
     int turn = 0;                                            // units of this team so far
     // FEW: no look from the compute phase and no early patch.  With up to FEW_UNITS units a workgroup and layer neither is in time,
     // and the 11 loads of no bytes stood in the way of the words that others wait for: EDSR x4 on 128 x 128 bins, us, always with them / with
-    // this up to 4 units, 1 bin 276 / 254, 3: 296 / 268, 8: 409 / 394, 10: 498 / 460, 16: 666 / 654; with six units (24 bins) 930 / 964.
+    // this up to 4 units, 10 bins 498 / 460, 16: 666 / 654; with six units (24 bins) 930 / 964.
     auto unit = [&](auto skip_c, auto few_c) __attribute__((always_inline)) -> bool {
         constexpr bool SKIP = decltype(skip_c)::value, FEW = decltype(few_c)::value;
         conv64_acc acc;
@@ -359,8 +367,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
                         break;
                     }
                 }
-                // Marks the result where no ReLU drops it.  (Without this look between words and patch a call takes 262 instead of 253 us
-                // on one bin of 128 x 128 and 285 instead of 276 on three; why is not known.)
+                // Marks the result where no ReLU drops it.
                 if (lost()) bias = __builtin_nanf("");
                 __amdgpu_buffer_rsrc_t rin = rsrc_of(layer_in(cur.layer), cur.n, true);
 #pragma unroll
@@ -381,7 +388,8 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
 
 hipError_t rh_launch_conv_body(hipStream_t stream, int device, int n_cu, body_args a)
 {
-    constexpr int lds = 9 * 64 * 64 * 2 + 2 * 10 * PW * 128;
+    constexpr int lds = BODY_PAIR_LDS(22);
+    static_assert(lds >= BODY_PAIR_LDS(16) && lds >= 9 * 64 * 64 * 2 + 2 * 10 * PW * 128, "the largest of them");
     static bool attr_done[RH_MAX_DEVICES] = {};            // the attribute is per device
     if (!attr_done[device]) {
         hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_body<false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -393,7 +401,8 @@ hipError_t rh_launch_conv_body(hipStream_t stream, int device, int n_cu, body_ar
     if (units * cells_img >= 1ll << 32) return hipErrorInvalidValue;
     a.img_magic = (uint32_t)(0xFFFFFFFFu / cells_img + 1);   // x / d = high word of x * magic for x * d < 2^32; 0: d = 1
     a.row_magic = (uint32_t)(0xFFFFFFFFu / cells_x + 1);
-    const int grid = (int)(units < n_cu ? units : n_cu);
+    const long long most = (long long)a.N * ((a.H + 3) / 4) * ((a.W + BODY_PAIR_COLS - 1) / BODY_PAIR_COLS);      // at least as many as half tiles
+    const int grid = (int)(most < n_cu ? most : n_cu);
     if (a.keep) hipLaunchKernelGGL(k_conv_mfma_body<true>, dim3(grid), dim3(512), lds, stream, a);
     else hipLaunchKernelGGL(k_conv_mfma_body<false>, dim3(grid), dim3(512), lds, stream, a);
     return hipGetLastError();

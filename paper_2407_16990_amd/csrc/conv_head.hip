@@ -30,7 +30,7 @@ __global__ __launch_bounds__(256) void k_head_mfma(const uint8_t* __restrict__ i
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);          // uniform over the wave: keeps row indices scalar
 
     // words that the launch behind this one wants to find at zero (at most 256 per tile)
-    if (blockIdx.x * 256u + tid < n_clear) clear[blockIdx.x * 256u + tid] = 0;
+    for (uint32_t i = blockIdx.x * 256u + tid; i < n_clear; i += gridDim.x * 256u) clear[i] = 0;
     const int n_img = n_valid ? min((int)*n_valid, N) : N;
     const int tiles_x = (W + 31) / 32, tiles_y = (H + HEAD_TH - 1) / HEAD_TH, tiles_img = tiles_x * tiles_y;
     const int n_tiles = n_img * tiles_img;
@@ -127,7 +127,7 @@ static hipError_t launch_head(hipStream_t stream, const uint8_t* in, const uint4
 {
     const long long tiles = (long long)N * ((H + HEAD_TH - 1) / HEAD_TH) * ((W + 31) / 32);
     const long long grid = (tiles + 8 * HEAD_RUN - 1) / (8 * HEAD_RUN) * (8 * HEAD_RUN);
-    if (grid > 0x7FFFFFFFLL || n_clear > 256 * tiles) return hipErrorInvalidValue;
+    if (grid > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_head_mfma<C>, dim3((unsigned)grid), dim3(256), 0, stream, in, wp, bias, out, N, H, W, relu, n_valid, clear, n_clear);
     return hipGetLastError();
 }

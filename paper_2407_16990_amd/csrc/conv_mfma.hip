@@ -545,7 +545,7 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
         rh_prof_scope ps(ctx, RH_PROF_HEAD, 1u + (masked ? 2u : 0u) + (ctx->bz_boxes ? 1u : 0u) + (ctx->mk_boxes ? 3u : 0u) + (ctx->nd_places ? 2u : 0u));
         if (masked) { st = rh_outside_mask(ctx, keep, N, n_valid); if (st != RH_OK) return st; }
         RH_HIP(ctx, rh_launch_head_mfma(ctx->stream, C, in, (const uint4*)((const uint8_t*)ctx->wpack + l0.wp_off),
-                                        ctx->bpack + l0.bp_off, h, N, H, W, head_relu, n_valid, sync, one_launch ? (uint32_t)(BODY_ROLL_WORDS + 4 * cells) : 0u));
+                                        ctx->bpack + l0.bp_off, h, N, H, W, head_relu, n_valid, sync, one_launch ? (uint32_t)(BODY_ROLL_WORDS + std::max(4 * cells, (size_t)BODY_PAIR_WORDS * ctx->n_cu)) : 0u));
         // box-masked mode: from here to the end of the body the three tensors are zero outside the live cells
         if (ctx->mk_boxes) { st = rh_launch_cell_lists(ctx, N, n_valid, h, a, t); if (st != RH_OK) return st; }
         if (ctx->nd_places) { ctx->nd_conv = 0; st = rh_launch_need_lists(ctx, N, n_valid); if (st != RH_OK) return st; }

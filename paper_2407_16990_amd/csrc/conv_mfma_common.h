@@ -99,6 +99,7 @@ struct body_args {
 };
 // words for `roll` and `done` together; `done` begins BODY_ROLL_WORDS behind `roll`
 #define BODY_ROLL_WORDS 32
+#define BODY_PAIR_WORDS 32               // of `done`, one unit of two layers (at most one a compute unit): a line each
 hipError_t rh_launch_conv_body(hipStream_t stream, int device, int n_cu, body_args a);
 // two-team kernel for the 64-channel bf16-output convs (conv_mfma_duo.hip)
 hipError_t rh_launch_conv_duo(hipStream_t stream, int device, const conv_args& a, int grid, bool skip, bool relu);

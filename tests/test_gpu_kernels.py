@@ -437,6 +437,56 @@ def test_row_streams_are_the_one_launch_body_bit_for_bit(net, H, W):
     rh.close()
 
 
+# A few images, two layers a unit of 4, 6, .. 22 rows of 30 pixels: the images end with a unit, a row or a pixel before or behind its end, and within it;
+# an odd layer at the end; rows = 0: a unit too many.  Against the same images in a batch that goes two convs or one a launch.
+def pair_shapes(rows, cu):
+    def chosen(n, H, W):
+        return next((r for r in range(4, 23, 2) if n * -(-H // r) * -(-W // 30) <= cu), 0)
+    r = rows or 22
+    for H, W in ((128, 128), (3 * r + 1, 91), (2 * r, 60), (4 * r - 1, 32), (r, 269), (r + 2, 31)):
+        n = next((n for n in range(1, 2 * cu) if chosen(n, H, W) == rows), 0)
+        if n:
+            yield n, H, W
+
+
+@pytest.mark.parametrize("net", [wl.Net("edsr", 64, 2, 2, 0.02), wl.Net("res", 64, 1, 2, 0.02), wl.Net("plain", 64, 4, 2, 0.1), wl.Net("plain", 64, 7, 2, 0.1)])
+@pytest.mark.parametrize("rows", [4, 6, 8, 10, 12, 14, 16, 18, 20, 22, 0])
+def test_two_layers_a_unit_are_the_larger_batch_bit_for_bit(net, rows):
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    shapes = list(pair_shapes(rows, cu))
+    assert len(shapes) >= 2
+    for n, H, W in shapes:
+        rh = RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=32, max_bins=4, net=net, weights=wl.make_weights(net, 29, "bf16"), precision="bf16")
+        big = 12 * cu // (-(-H // 8) * -(-W // 32)) + 1
+        x = torch.randint(0, 256, (n, H, W, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(n + H))
+        xb = x[torch.arange(big, device="cuda") % n].contiguous()
+        want = rh.enhance(xb)[:n].clone()
+        for _ in range(3):                                   # again with the counters and buffers of the call before
+            assert torch.equal(rh.enhance(x), want), (n, H, W)
+        rh.close()
+
+
+# The same in exact-border mode, whose convs clear what lies outside the frame, on 1 to 9 bins of a plan whose boxes leave the frame
+@pytest.mark.parametrize("net", [wl.Net("edsr", 64, 1, 2, 0.02), wl.Net("plain", 64, 5, 2, 0.1)])
+def test_two_layers_a_unit_at_frame_borders(net):
+    cfg = wl.replace(wl.config(3), n_frames=16, width=240, height=139, halo=9, bin_size=128, net=net)
+    imp = wl.make_importance(cfg)
+    imp[:, 0, :] += 5.0; imp[:, :, 0] += 5.0; imp[:, -1, -3:] += 5.0
+    most = 12 * torch.cuda.get_device_properties(0).multi_processor_count // 64 + 1
+    rh = make_rh(cfg, wl.make_weights(net, 31, "bf16"), max_bins=most)
+    segs = [tuple(r) for r in wl.make_segments(cfg).tolist()]
+    d_imp = dev(imp)
+    po = rh.pack(dev(wl.make_frames(cfg)), d_imp, *rh.select_regions(d_imp, segs))
+    assert 9 <= int(po.counts[1]) <= most
+    count = lambda k: torch.tensor([k], dtype=torch.int32, device="cuda")
+    want = rh.enhance_exact(po.bins, po.boxes, po.counts, n=most, n_valid=count(9))[:9].clone()
+    assert not torch.equal(want, rh.enhance(po.bins, n=9))
+    for k in range(1, 10):
+        got = rh.enhance_exact(po.bins, po.boxes, po.counts, n=9, n_valid=count(k))
+        assert torch.equal(got[:k], want[:k]), k
+    rh.close()
+
+
 # fp32 convs with a device-side count, the patch requested ahead of it (up to 8 workgroups a compute unit) and behind it:
 # the valid images as without a count, the others untouched, ragged tiles
 @pytest.mark.parametrize("net", [wl.Net("plain", 16, 3, 2), wl.Net("res", 32, 1, 3), wl.Net("edsr", 16, 1, 2, 0.05), wl.Net("res", 24, 1, 2)])
