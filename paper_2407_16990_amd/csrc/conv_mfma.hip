@@ -519,15 +519,16 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // 96 x 96, 8.4, 676 / 642; 20 of 160 x 160, 7.8, 629 / 639; frames of 480 x 272, 3: 489 / 519, 6: 954 / 933; two of 640 x 360, 7: 574 / 577.
     // How many of the N images are valid the host does not know; a capacity is seldom full, which speaks for neither.  Where two convs a launch are not to be
     // had (exact-border mode, widths up to 48) the other side is a launch per conv, and the line is at 12 (48 of 128 x 128 1903 / 1895).
-    // Not with cell lists (box-masked and needed-region modes): the units of a layer and the 3 x 3 that they wait for are found here from
-    // the unit's number, in a list that changes from layer to layer they are not.  So on few bins these modes, made to leave out work,
-    // are the slower ones: a step of one 640 x 360 frame x3, 3 bins / 14, plain 313 / 640, needed 398 / 726, masked 380 / 729 us.
+    // Not with cell lists: the units of a layer and the 3 x 3 that they wait for are found here from the unit's number, in a list that changes from layer
+    // to layer they are not.  So the box-masked mode goes a launch per layer, and on few bins is the slower one: a step of one 640 x 360 frame x3, 3 bins, plain 223,
+    // masked 380 us.  The needed-region mode has lists for its body where the other side is a launch per conv; else its body is the plain mode's
+    // (every value that it needs is the same), which also in one launch is the faster one: 4 frames of 228 x 384 x3, 5 bins, two convs a launch 454, in one 375 us.
     const std::vector<rh_layer>& L = ctx->layers;
     const int body_layers = d.topology == RH_NET_PLAIN ? d.n_blocks - 2 : 2 * d.n_blocks + (d.topology == RH_NET_EDSR);
     const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32), most_cells = 12 * (size_t)ctx->n_cu;
     int cut[4];
     const bool streams = C == 64 && !ctx->bz_boxes && !ctx->mk_boxes && rh_block64_strips(W, cut, cut + 1, cut + 2, cut + 3);
-    const bool one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && !ctx->nd_places && cells <= (streams ? 8 * (size_t)ctx->n_cu : most_cells);
+    const bool one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && (streams || !ctx->nd_places) && cells <= (streams ? 8 * (size_t)ctx->n_cu : most_cells);
     // its counters: room for the most that the line allows in every call, so that what a call needs follows from its pixels alone
     const size_t sync_words = C == 64 ? BODY_ROLL_WORDS + 4 * most_cells : 0;
     need = (need + 63) & ~(size_t)63;
@@ -570,7 +571,7 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
         b.n_valid = n_valid; b.keep = keep; b.N = N; b.H = H; b.W = W; b.layers = body_layers; b.topology = d.topology;
         b.roll = sync; b.done = sync + BODY_ROLL_WORDS; b.lost = (uint32_t*)ctx->lost;
         RH_HIP(ctx, rh_launch_conv_body(ctx->stream, ctx->device, ctx->n_cu, b));
-        ++n_conv; li += body_layers;
+        ++n_conv; li += body_layers; ctx->nd_conv += body_layers;
         body_out = d.topology == RH_NET_EDSR ? t : d.topology == RH_NET_RES ? a : (body_layers & 1) ? a : t;
     }
     if (d.topology == RH_NET_PLAIN) {
