@@ -65,7 +65,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
     const int row_pitch = a.W * PIXB;
     const size_t img_elems = (size_t)a.H * a.W * CIN;
     const int pair_rows = body_pair_rows(max(n_img, 0), a.H, a.W, gridDim.x);
-    const uint32_t units = pair_rows ? body_pair_units(max(n_img, 0), a.H, a.W, pair_rows) : layer_units;
+    const uint32_t units = pair_rows ? (uint32_t)body_pair_units(max(n_img, 0), a.H, a.W, pair_rows) : layer_units;
 
     // what layer l reads and writes (the order of the buffers is the caller's of one launch per layer)
     const bool plain = a.topology == RH_NET_PLAIN;
@@ -386,9 +386,11 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
     else run(std::integral_constant<bool, false>{});
 }
 
+bool rh_conv_body_pairs(int n_cu, int N, int H, int W) { return body_pair_rows(N, H, W, n_cu) > 0; }
+
 hipError_t rh_launch_conv_body(hipStream_t stream, int device, int n_cu, body_args a)
 {
-    constexpr int lds = BODY_PAIR_LDS(22);
+    constexpr int lds = BODY_PAIR_LDS(BODY_PAIR_MOST);
     static_assert(lds >= BODY_PAIR_LDS(16) && lds >= 9 * 64 * 64 * 2 + 2 * 10 * PW * 128, "the largest of them");
     static bool attr_done[RH_MAX_DEVICES] = {};            // the attribute is per device
     if (!attr_done[device]) {
@@ -401,7 +403,7 @@ hipError_t rh_launch_conv_body(hipStream_t stream, int device, int n_cu, body_ar
     if (units * cells_img >= 1ll << 32) return hipErrorInvalidValue;
     a.img_magic = (uint32_t)(0xFFFFFFFFu / cells_img + 1);   // x / d = high word of x * magic for x * d < 2^32; 0: d = 1
     a.row_magic = (uint32_t)(0xFFFFFFFFu / cells_x + 1);
-    const long long most = (long long)a.N * ((a.H + 3) / 4) * ((a.W + BODY_PAIR_COLS - 1) / BODY_PAIR_COLS);      // at least as many as half tiles
+    const long long most = body_pair_units(a.N, a.H, a.W, 4);      // at least as many as half tiles
     const int grid = (int)(most < n_cu ? most : n_cu);
     if (a.keep) hipLaunchKernelGGL(k_conv_mfma_body<true>, dim3(grid), dim3(512), lds, stream, a);
     else hipLaunchKernelGGL(k_conv_mfma_body<false>, dim3(grid), dim3(512), lds, stream, a);

@@ -21,16 +21,17 @@
 #pragma once
 #include "conv_mfma64.h"
 
+#define BODY_PAIR_MOST 22
 #define BODY_PAIR_COLS 30                // output columns of a unit: the 32 of the tensor between, less one at each side
 
 // Rows of a unit, 0: a layer at a time.  Units never outnumber the 4 words a half tile of 8 x 32 that `done` has.
-__host__ __device__ __forceinline__ int body_pair_units(int images, int H, int W, int rows)
+__host__ __device__ __forceinline__ long long body_pair_units(int images, int H, int W, int rows)
 {
-    return images * ((H + rows - 1) / rows) * ((W + BODY_PAIR_COLS - 1) / BODY_PAIR_COLS);
+    return (long long)images * ((H + rows - 1) / rows) * ((W + BODY_PAIR_COLS - 1) / BODY_PAIR_COLS);
 }
-__device__ __forceinline__ int body_pair_rows(int images, int H, int W, int grid)
+__host__ __device__ __forceinline__ int body_pair_rows(int images, int H, int W, int grid)
 {
-    for (int rows = 4; rows <= 22; rows += 2)
+    for (int rows = 4; rows <= BODY_PAIR_MOST; rows += 2)
         if (body_pair_units(images, H, W, rows) <= grid) return rows;
     return 0;
 }

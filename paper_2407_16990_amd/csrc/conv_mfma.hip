@@ -521,14 +521,15 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // had (exact-border mode, widths up to 48) the other side is a launch per conv, and the line is at 12 (48 of 128 x 128 1903 / 1895).
     // Not with cell lists: the units of a layer and the 3 x 3 that they wait for are found here from the unit's number, in a list that changes from layer
     // to layer they are not.  So the box-masked mode goes a launch per layer, and on few bins is the slower one: a step of one 640 x 360 frame x3, 3 bins, plain 223,
-    // masked 380 us.  The needed-region mode has lists for its body where the other side is a launch per conv; else its body is the plain mode's
-    // (every value that it needs is the same), which also in one launch is the faster one: 4 frames of 228 x 384 x3, 5 bins, two convs a launch 454, in one 375 us.
+    // masked 380 us.  The needed-region mode does too, unless all N images are so few that they go two layers a unit (conv_body_pairs.h; every value that it needs is
+    // the same there).  EDSR x4, all N valid, a launch per layer over lists / in one launch, 16 blocks: 9 bins 476 / 451, 17: 658 / 661, 28: 960 / 1034, 4 blocks: 9 bins
+    // 157 / 173, 28: 286 / 339; large batches over lists / two convs a launch: 182 bins of isolated macroblocks 5510 / 5760, 4 blocks on 87 bins 1013 / 1115.
     const std::vector<rh_layer>& L = ctx->layers;
     const int body_layers = d.topology == RH_NET_PLAIN ? d.n_blocks - 2 : 2 * d.n_blocks + (d.topology == RH_NET_EDSR);
     const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32), most_cells = 12 * (size_t)ctx->n_cu;
     int cut[4];
     const bool streams = C == 64 && !ctx->bz_boxes && !ctx->mk_boxes && rh_block64_strips(W, cut, cut + 1, cut + 2, cut + 3);
-    const bool one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && (streams || !ctx->nd_places) && cells <= (streams ? 8 * (size_t)ctx->n_cu : most_cells);
+    const bool one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && (!ctx->nd_places || rh_conv_body_pairs(ctx->n_cu, N, H, W)) && cells <= (streams ? 8 * (size_t)ctx->n_cu : most_cells);
     // its counters: room for the most that the line allows in every call, so that what a call needs follows from its pixels alone
     const size_t sync_words = C == 64 ? BODY_ROLL_WORDS + 4 * most_cells : 0;
     need = (need + 63) & ~(size_t)63;
@@ -563,7 +564,7 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
 #define LAST_CONV(...) do { rh_prof_end(ctx, n_conv); rh_prof_scope ps_(ctx, RH_PROF_CONV_LAST); st = conv(ctx, __VA_ARGS__); if (st != RH_OK) return st; } while (0)
     // Two convs per launch, the tensor between them stays on the chip.  Exact-border mode clears part of that tensor and runs them one by
     // one; box-masked mode leaves out cells of every layer.
-    const bool pairs = C == 32 ? !ctx->bz_boxes : streams && !one_launch;
+    const bool pairs = C == 32 ? !ctx->bz_boxes : streams && !one_launch && !ctx->nd_places;
     const __bf16* body_out = nullptr;
     if (one_launch) {
         body_args b;

@@ -101,6 +101,7 @@ struct body_args {
 #define BODY_ROLL_WORDS 32
 #define BODY_PAIR_WORDS 32               // of `done`, one unit of two layers (at most one a compute unit): a line each
 hipError_t rh_launch_conv_body(hipStream_t stream, int device, int n_cu, body_args a);
+bool rh_conv_body_pairs(int n_cu, int N, int H, int W);        // all N images go two layers a unit (conv_body_pairs.h)
 // two-team kernel for the 64-channel bf16-output convs (conv_mfma_duo.hip)
 hipError_t rh_launch_conv_duo(hipStream_t stream, int device, const conv_args& a, int grid, bool skip, bool relu);
 // two 3x3 convs of a 32-channel net in one launch (conv_block32.hip); res: a residual block, else two ReLU layers.  in != out

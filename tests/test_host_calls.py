@@ -107,8 +107,8 @@ for net, layers in ((EDSR, 64, 2, 4, 1), 5), ((RES, 64, 2, 2, 1), 4), ((PLAIN, 6
     assert bodies(lambda: L.rh_enhance_exact(ctx, P(1), 48, P(3), P(4), P(2), None))[0] == 1
     assert bodies(lambda: L.rh_enhance_exact(ctx, P(1), 49, P(3), P(4), P(2), None))[0] == 0
     assert bodies(lambda: L.rh_enhance_masked(ctx, P(1), 3, P(3), P(4), P(2), None))[0] == 0
-    if net[0] == EDSR:                                       # this mode's body is the plain one where that goes two convs a launch or all in one
-        for n, one in ((3, 1), (32, 1), (33, 0)):
+    if net[0] == EDSR:                                       # this mode goes in one launch where all images go two layers a unit of up to 22 x 30 pixels
+        for n, one in ((3, 1), (8, 1), (9, 0), (33, 0)):
             assert bodies(lambda: L.rh_enhance_needed(ctx, P(1), n, P(3), P(4), P(2), None))[0] == one, n
 ''')
 
