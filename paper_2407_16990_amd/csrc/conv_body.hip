@@ -41,31 +41,57 @@ __device__ __forceinline__ void body_barrier() { asm volatile("s_waitcnt lgkmcnt
 struct body_unit { int layer, idx, n, y0, x0; };            // idx: its number in the layer
 
 template <bool KEEP>
-__global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
+__global__ __launch_bounds__(512) void k_conv_mfma_body(body_args args)
 {
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    __shared__ uint32_t s_ready[2][2];                        // [team][its units in turn]: what it reads was there
+    __shared__ uint32_t s_again[2], s_sync[2], s_lost, s_wg[3], s_stored;
+    const int tid = threadIdx.x;
+    int n_img = max(args.n_valid ? min((int)*args.n_valid, args.N) : args.N, 0);
+    const int pair_rows = body_pair_rows(n_img, args.H, args.W, gridDim.x);
+
+    // ---- start: who takes part ----
+    if (tid == 0) {
+        const uint32_t units = pair_rows ? (uint32_t)body_pair_units(n_img, args.H, args.W, pair_rows) : (uint32_t)(n_img * ((args.W + 31) / 32) * ((args.H + 7) / 8));
+        s_lost = 0; s_stored = 0; s_again[0] = 0; s_again[1] = 0; s_sync[0] = 0; s_sync[1] = 0; s_ready[0][0] = 0; s_ready[1][0] = 0;
+        const uint32_t sign = __hip_atomic_fetch_add(args.roll, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        body_place p;
+        for (int polls = 0;;) {
+            uint32_t r = __hip_atomic_load(args.roll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (body_roll_place(sign, r, gridDim.x, blockIdx.x, &p)) break;
+            if (++polls > BODY_ROLL_POLLS)
+                __hip_atomic_compare_exchange_strong(args.roll, &r, body_roll_closed(r), __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        body_roll_spread(&p, gridDim.x, units);
+        s_wg[2] = body_roll_leaves(&p, units);
+        s_wg[0] = p.wg; s_wg[1] = p.G;
+    }
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(s_wg[2])) return;     // not needed, or too late
+    int G = (int)__builtin_amdgcn_readfirstlane(s_wg[1]), wg = (int)__builtin_amdgcn_readfirstlane(s_wg[0]);
+    switch (pair_rows) {
+#define PAIRS(TH) case TH: body_pairs<TH, KEEP>(lds, &s_stored, &s_lost, n_img, wg, G); return
+    PAIRS(4); PAIRS(6); PAIRS(8); PAIRS(10); PAIRS(12); PAIRS(14); PAIRS(16); PAIRS(18); PAIRS(20); PAIRS(22);
+#undef PAIRS
+    }
+    const body_args a = body_args_anew(n_img, wg, G);
     constexpr int CIN = 64, NCH = 8, PIXB = 128, TH = 8, PH = TH + 2, RW = 2;
     constexpr int WBYTES = 9 * CIN * CIN * 2, PATCHB = PH * PW * PIXB, NSTEP = C64_SUBSTEPS, MID = 15;
     constexpr int NMAIN = PH, NHP = PH * 2 * NCH, NPRE = NMAIN + 1;
     constexpr int NOUT = 8, PPJ = 8, JPR = 4;
     static_assert(NHP <= 256, "halo pieces must fit one per thread");
 
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    const int tid = threadIdx.x, ttid = tid & 255, lane = tid & 63;
+    const int ttid = tid & 255, lane = tid & 63;
     const int team = __builtin_amdgcn_readfirstlane(tid >> 8), wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);
     uint8_t* lds_w = lds;
     uint8_t* lds_p = lds + WBYTES + team * PATCHB;
-    __shared__ uint32_t s_ready[2][2];                        // [team][its units in turn]: what it reads was there
-    __shared__ uint32_t s_again[2], s_sync[2], s_lost, s_wg[3], s_stored;
     __shared__ __attribute__((aligned(16))) float s_bias[2][64];
 
-    const int n_img = a.n_valid ? min((int)*a.n_valid, a.N) : a.N;
     const int cells_x = (a.W + 31) / 32, cells_y = (a.H + TH - 1) / TH, cells_img = cells_x * cells_y;
-    const int layer_units = max(n_img, 0) * cells_img;
+    const int layer_units = n_img * cells_img;
     const uint32_t img_bytes = (uint32_t)a.H * a.W * PIXB;
     const int row_pitch = a.W * PIXB;
     const size_t img_elems = (size_t)a.H * a.W * CIN;
-    const int pair_rows = body_pair_rows(max(n_img, 0), a.H, a.W, gridDim.x);
-    const uint32_t units = pair_rows ? (uint32_t)body_pair_units(max(n_img, 0), a.H, a.W, pair_rows) : layer_units;
 
     // what layer l reads and writes (the order of the buffers is the caller's of one launch per layer)
     const bool plain = a.topology == RH_NET_PLAIN;
@@ -150,29 +176,6 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args a)
         asm volatile("global_store_dword %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" :: "v"(a.lost), "v"(1u) : "memory");
     };
 
-    // ---- start: who takes part ----
-    if (tid == 0) {
-        s_lost = 0; s_stored = 0; s_again[0] = 0; s_again[1] = 0; s_sync[0] = 0; s_sync[1] = 0; s_ready[0][0] = 0; s_ready[1][0] = 0;
-        const uint32_t sign = __hip_atomic_fetch_add(a.roll, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        body_place p;
-        for (int polls = 0;;) {
-            uint32_t r = __hip_atomic_load(a.roll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (body_roll_place(sign, r, gridDim.x, blockIdx.x, &p)) break;
-            if (++polls > BODY_ROLL_POLLS)
-                __hip_atomic_compare_exchange_strong(a.roll, &r, body_roll_closed(r), __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        body_roll_spread(&p, gridDim.x, units);
-        s_wg[2] = body_roll_leaves(&p, units);
-        s_wg[0] = p.wg; s_wg[1] = p.G;
-    }
-    __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(s_wg[2])) return;     // not needed, or too late
-    const int G = (int)__builtin_amdgcn_readfirstlane(s_wg[1]), wg = (int)__builtin_amdgcn_readfirstlane(s_wg[0]);
-    switch (pair_rows) {
-#define PAIRS(TH) case TH: body_pairs<TH, KEEP>(lds, &s_stored, &s_lost, n_img, wg, G); return
-    PAIRS(4); PAIRS(6); PAIRS(8); PAIRS(10); PAIRS(12); PAIRS(14); PAIRS(16); PAIRS(18); PAIRS(20); PAIRS(22);
-#undef PAIRS
-    }
     body_unit cur = unit_at(0, wg, team * G);                // the unit to compute next
     body_unit prev = cur;                                    // the one in the accumulators
     bool loaded = false, word_due = false;

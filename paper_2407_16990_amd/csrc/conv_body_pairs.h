@@ -81,14 +81,19 @@ __device__ __forceinline__ void body_pair_products(f32x4 (&acc)[N][2], const f32
     conv64_each<C64_SUBSTEPS>(sub);
 }
 
+// k_conv_mfma_body's arguments, read anew for each of its ways: what is worked out of them for one is not kept in registers for another
+__device__ __forceinline__ body_args body_args_anew(int& n_img, int& wg, int& G)
+{
+    auto args = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args), "+s"(n_img), "+s"(wg), "+s"(G));
+    return *(const body_args*)args;
+}
+
 // lds: BODY_PAIR_LDS(TH) bytes; stored: a zeroed word of LDS, as is lost (1: a wave has given up a wait).  All waves of workgroup wg of the G.
 template <int TH, bool KEEP>
 __device__ __forceinline__ void body_pairs(uint8_t* lds, uint32_t* stored, uint32_t* s_lost, int n_img, int wg, int G)
 {
-    // the kernel's arguments anew: what is worked out of them here is not kept for the rest of the kernel
-    auto args = __builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(args), "+s"(n_img), "+s"(wg), "+s"(G));
-    const body_args a = *(const body_args*)args;
+    const body_args a = body_args_anew(n_img, wg, G);
     constexpr int PIXB = 128, THIRD = BODY_PAIR_THIRD, WBYTES = 3 * THIRD, SLOTS = BODY_PAIR_SLOTS(TH), N1 = (TH + 2) / 2, N2 = TH / 2;
     constexpr int NP = ((TH + 4) * PW * 8 + 63) / 64, NPW = (NP + 7) / 8;   // loads of 64 x 16 bytes of a patch, of a wave
     constexpr int NH = (4 * PW + 4 * TH) * 8, NHW = (NH + 511) / 512;       // 16-byte pieces around a unit, of a thread
