@@ -514,8 +514,8 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // so their ceil(S / 32) words per row are at most S / 16.
     const size_t mask_words = C == 64 && !fold ? ((size_t)N * H * W + 15) / 16 : 0;
     // The body of a 64-channel net in one launch (conv_body.hip) where the batch has room for at most 8 half tiles a compute unit, else two convs a launch
-    // (conv_block64.hip).  us for EDSR x2 of 8 blocks, in one launch / two convs a launch (a launch per conv in brackets): 8 bins of 128 x 128 239 / 257,
-    // 16: 360 / 377, 24: 486 / 502, 32: 633 / 612, 40: 791 / 765, 48: 941 / 897, 56: 1095 / 1021 (a launch per conv); 40 of 100 x 100, 8.1 half tiles, 611 / 545; 60 of
+    // (conv_block64.hip).  us for EDSR x2 of 8 blocks, in one launch / two convs a launch (a launch per conv in brackets): 16 bins of 128 x 128
+    // 360 / 377, 24: 486 / 502, 32: 633 / 612, 40: 791 / 765, 48: 941 / 897, 56: 1095 / 1021 (a launch per conv); 40 of 100 x 100, 8.1 half tiles, 611 / 545; 60 of
     // 96 x 96, 8.4, 676 / 642; 20 of 160 x 160, 7.8, 629 / 639; frames of 480 x 272, 3: 489 / 519, 6: 954 / 933; two of 640 x 360, 7: 574 / 577.
     // How many of the N images are valid the host does not know; a capacity is seldom full, which speaks for neither.  Where two convs a launch are not to be
     // had (exact-border mode, widths up to 48) the other side is a launch per conv, and the line is at 12 (48 of 128 x 128 1903 / 1895).

@@ -1,7 +1,7 @@
 // 64 -> 64-channel-chunk bf16 conv3x3 on the matrix cores, two-team variant.
 //
-// Same implicit GEMM, LDS layouts, fragment order and buffer addressing as k_conv_mfma
-// (conv_mfma.hip), but the workgroup has 8 waves = two teams of 4.  The teams share the
+// Same implicit GEMM, patch layout and buffer addressing as k_conv_mfma (conv_mfma.hip), products and weight layout of
+// conv_mfma64.h; the workgroup has 8 waves = two teams of 4.  The teams share the
 // LDS-resident weights and own one 10 x 34 pixel patch each: a team computes one half (8 x 32
 // pixels) of a 16 x 32 tile at a time.  The teams run one half apart: while one team is in its
 // MFMA loop, the other rounds its finished accumulators to bf16, adds the skip tensor, writes
