@@ -102,7 +102,9 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args args)
     auto layer_skip = [&](int l) __attribute__((always_inline)) { return (l & 1) && l != 1 ? a.a : a.h; };       // l = 1 and the body's end: h
 
     // Where a lane reads and writes is worked out anew in every phase (`lane` and `ttid` pass through an empty asm
-    // statement there): kept over the loop these addresses would not fit the registers.
+    // statement there): kept over the loop these addresses would not fit the registers.  With some of them kept, 11 registers (exact-border
+    // mode: 24) lay in scratch memory, from where every unit loaded them again, and 275 (506) scalars in lanes of others: EDSR x2 of 8 blocks
+    // on 128 x 128 bins, us, so / now, 9 bins 242 / 228, 12: 277 / 267, 16: 354 / 338, 20: 397 / 394.
     uint4 pre[NPRE];
     auto load_piece = [&](int j, int tt, __amdgpu_buffer_rsrc_t rin, int y0, int x0) __attribute__((always_inline)) {
         const int m_col = tt >> 3, m_goff = m_col * PIXB + (tt & 7) * 16;
@@ -137,6 +139,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args args)
     auto rsrc_of = [&](const __bf16* base, int n, bool on) __attribute__((always_inline)) {
         return __builtin_amdgcn_make_buffer_rsrc((void*)(base + (size_t)n * img_elems), 0, on ? img_bytes : 0u, RSRC_FLAGS);
     };
+    auto lane_now = [&]() __attribute__((always_inline)) { int l = lane; asm volatile("" : "+v"(l)); return l; };
     // unit number `u` places behind; layer = a.layers: there is none
     auto unit_at = [&](int layer, int idx, int ahead) __attribute__((always_inline)) {
         body_unit u;
@@ -150,9 +153,9 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args args)
     };
     // the words around a unit: lane j < 36 has word j % 4 of half tile j / 4 of the 3 x 3 around it
     auto load_words = [&](const body_unit& u) __attribute__((always_inline)) {
-        const int j = lane >> 2, cy = u.y0 / TH + j / 3 - 1, cx = u.x0 / 32 + j % 3 - 1;
-        const bool in = lane < 36 && cy >= 0 && cy < cells_y && cx >= 0 && cx < cells_x && u.layer > 0 && u.layer < a.layers;
-        return in ? __hip_atomic_load(a.done + ((size_t)u.n * cells_img + cy * cells_x + cx) * 4 + (lane & 3), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+        const int l = lane_now(), j = l >> 2, cy = u.y0 / TH + j / 3 - 1, cx = u.x0 / 32 + j % 3 - 1;
+        const bool in = l < 36 && cy >= 0 && cy < cells_y && cx >= 0 && cx < cells_x && u.layer > 0 && u.layer < a.layers;
+        return in ? __hip_atomic_load(a.done + ((size_t)u.n * cells_img + cy * cells_x + cx) * 4 + (l & 3), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                   : 0x7FFFFFFFu;
     };
     // all four waves of a team have come here (their LDS writes are done)
@@ -166,8 +169,8 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args args)
         asm volatile("" ::: "memory");
     };
     int bias_layer = -1;                                     // layer whose biases lie in s_bias[team]
-    auto load_bias = [&](int l) __attribute__((always_inline)) { return ttid < 64 ? a.bias[l * 64 + ttid] : 0.0f; };
-    auto store_bias = [&](float v) __attribute__((always_inline)) { if (ttid < 64) s_bias[team][ttid] = v; };
+    auto load_bias = [&](int l) __attribute__((always_inline)) { return wave == 0 ? a.bias[l * 64 + lane_now()] : 0.0f; };
+    auto store_bias = [&](float v) __attribute__((always_inline)) { if (wave == 0) s_bias[team][lane_now()] = v; };
 
     // A wave of the workgroup has given up a wait.
     auto lost = [&]() __attribute__((always_inline)) { return __hip_atomic_load(&s_lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
@@ -356,8 +359,11 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args args)
         }
         if (cur.layer >= a.layers) break;
         if (!loaded || cur.layer != resident) {
-            if (cur.layer != resident)
-                lds_dma<256, WBYTES>(lds_w, a.wp + (size_t)cur.layer * (WBYTES / 16), wave, lane);
+            if (cur.layer != resident) {
+                int w = wave;
+                asm volatile("" : "+s"(w));                  // as `lane`: its 18 offsets are not kept
+                lds_dma<256, WBYTES>(lds_w, a.wp + (size_t)cur.layer * (WBYTES / 16), w, lane_now());
+            }
             float bias = load_bias(cur.layer);
             if (!loaded) {
                 int tt = ttid;

@@ -103,7 +103,7 @@ __device__ __forceinline__ void body_pairs(uint8_t* lds, uint32_t* stored, uint3
     const uint8_t* rows = lds_p + rp * (PW * PIXB) + hf * (16 * PIXB);
     // What is worked out of the lane is worked out anew in every phase (it passes through an empty asm statement): kept over the loop it would not
     // fit the registers.  Pixel and 16-byte group of a lane's 8 channels (body_pair_lanes):
-    auto lane_now = [&]() __attribute__((always_inline)) { int l = lane; if (TH > 16) asm volatile("" : "+v"(l)); return l; };
+    auto lane_now = [&]() __attribute__((always_inline)) { int l = lane; if (TH > 14) asm volatile("" : "+v"(l)); return l; };
     auto col_of = [&](int l) __attribute__((always_inline)) { return hf * 16 + (l & 15); };
     auto grp_of = [&](int l) __attribute__((always_inline)) { return mh * 4 + (l >> 4 & 1) * 2 + (l >> 5); };
 
@@ -148,9 +148,10 @@ __device__ __forceinline__ void body_pairs(uint8_t* lds, uint32_t* stored, uint3
         for (int k = 0; k < 3; ++k) wt[k] = lds + slot_of(k) * THIRD + (mh << 11) + (l << 4);
     };
     auto bias_of = [&](f32x4 (&b)[2], int layer) __attribute__((always_inline)) {
+        const int l = lane_now();
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
-            const float4 v = *(const float4*)(a.bias + min(layer, a.layers - 1) * 64 + (mh * 2 + m) * 16 + (lane >> 4) * 4);
+            const float4 v = *(const float4*)(a.bias + min(layer, a.layers - 1) * 64 + (mh * 2 + m) * 16 + (l >> 4) * 4);
             b[m][0] = v.x; b[m][1] = v.y; b[m][2] = v.z; b[m][3] = v.w;
         }
     };
@@ -196,21 +197,25 @@ __device__ __forceinline__ void body_pairs(uint8_t* lds, uint32_t* stored, uint3
         {
             const int wpr = (a.W + 31) >> 5, x1 = x0 - 1 + col_of(l0), x2 = x0 + col_of(l0);
             __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)(a.keep + (KEEP ? (size_t)n * a.H * wpr : 0)), 0, KEEP ? (uint32_t)(a.H * wpr) * 4u : 0u, RSRC_FLAGS);
-            auto kept = [&](int y, int x, bool in) __attribute__((always_inline)) {
-                if constexpr (KEEP) return in && (__builtin_amdgcn_raw_buffer_load_b32(rk, in ? (uint32_t)(y * wpr + (x >> 5)) * 4u : OOB_OFF, 0, 0) >> (x & 31) & 1u);
-                else return in;
+            // words outside the image lie outside the descriptor's range, by their column or by their row, and read as zeros
+            auto kept = [&](int y, int x, uint32_t at) __attribute__((always_inline)) {
+                return __builtin_amdgcn_raw_buffer_load_b32(rk, at + ((uint32_t)y < (uint32_t)a.H ? (uint32_t)(y * wpr) * 4u : OOB_OFF), 0, 0) >> (x & 31) & 1u;
             };
+            const uint32_t at1 = (uint32_t)x1 < (uint32_t)a.W ? (uint32_t)(x1 >> 5) * 4u : OOB_OFF >> 1, at2 = x2 < a.W ? (uint32_t)(x2 >> 5) * 4u : OOB_OFF >> 1;
             kept1 = 0; kept2 = 0;
 #pragma unroll
-            for (int i = 0; i < N1; ++i) { const int y = y0 - 1 + 2 * i + rp; kept1 |= (uint32_t)kept(y, x1, ((uint32_t)y < (uint32_t)a.H) & ((uint32_t)x1 < (uint32_t)a.W)) << i; }
+            for (int i = 0; i < N1; ++i) {
+                const int y = y0 - 1 + 2 * i + rp;
+                kept1 |= (KEEP ? kept(y, x1, at1) : (uint32_t)(((uint32_t)y < (uint32_t)a.H) & ((uint32_t)x1 < (uint32_t)a.W))) << i;
+            }
             if constexpr (KEEP)
 #pragma unroll
-                for (int i = 0; i < N2; ++i) { const int y = y0 + 2 * i + rp; kept2 |= (uint32_t)kept(y, x2, (y < a.H) & (x2 < a.W)) << i; }
+                for (int i = 0; i < N2; ++i) kept2 |= kept(y0 + 2 * i + rp, x2, at2) << i;
         }
         // ---- every wave for itself: the 3 x 3 units around have done the step before ----
         if (s) {
-            const int yy = cy + lane / 3 - 1, xx = cx + lane % 3 - 1;
-            const bool look = lane < 9 && yy >= 0 && yy < cells_y && xx >= 0 && xx < cells_x;
+            const int l = lane_now(), yy = cy + l / 3 - 1, xx = cx + l % 3 - 1;
+            const bool look = l < 9 && yy >= 0 && yy < cells_y && xx >= 0 && xx < cells_x;
             const uint32_t* word = a.done + (size_t)(n * cells_img + (look ? yy * cells_x + xx : 0)) * BODY_PAIR_WORDS;
             int polls = 0;
             while (__builtin_amdgcn_ballot_w64(look && __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)s) != 0) {
@@ -232,7 +237,7 @@ __device__ __forceinline__ void body_pairs(uint8_t* lds, uint32_t* stored, uint3
             } else
 #pragma unroll
             for (int i = 0; i < NPW; ++i) {
-                if (i * 8 + wave >= NP) break;
+                if (i == NPW - 1 && i * 8 + wave >= NP) break;
                 asm volatile("s_add_u32 m0, %0, %c1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen sc1 lds"
                              :: "s"(base), "n"(SLOTS * THIRD + i * 8192), "v"(poff[i]), "s"(rin) : "memory", "scc");
             }
