@@ -48,6 +48,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args args)
     __shared__ uint32_t s_again[2], s_sync[2], s_lost, s_wg[3], s_stored;
     const int tid = threadIdx.x;
     int n_img = max(args.n_valid ? min((int)*args.n_valid, args.N) : args.N, 0);
+    if (n_img == 0) return;                                  // nothing to do, or another way's to do
     const int pair_rows = body_pair_rows(n_img, args.H, args.W, gridDim.x);
 
     // ---- start: who takes part ----

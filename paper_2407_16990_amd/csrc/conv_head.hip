@@ -18,7 +18,7 @@ template <int C>
 __global__ __launch_bounds__(256) void k_head_mfma(const uint8_t* __restrict__ in, const uint4* __restrict__ wp /*[3][MT][64]*/,
                                                    const float* __restrict__ bias, __bf16* __restrict__ out, int N, int H,
                                                    int W, int relu, const uint32_t* __restrict__ n_valid,
-                                                   uint32_t* __restrict__ clear, uint32_t n_clear)
+                                                   uint32_t* __restrict__ clear, uint32_t n_clear, int few)
 {
     constexpr int MT = C / 32, PH = HEAD_TH + 2, PWB = 34 * 3, OPIXB = C * 2, NCHO = OPIXB / 16;
     constexpr int PPJ = 64 / NCHO, NOUT = 32 / PPJ;                      // pixels per store instruction, stores per row
@@ -29,9 +29,10 @@ __global__ __launch_bounds__(256) void k_head_mfma(const uint8_t* __restrict__ i
     const int tid = threadIdx.x, lane = tid & 63, lx = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);          // uniform over the wave: keeps row indices scalar
 
-    // words that the launch behind this one wants to find at zero (at most 256 per tile)
-    for (uint32_t i = blockIdx.x * 256u + tid; i < n_clear; i += gridDim.x * 256u) clear[i] = 0;
     const int n_img = n_valid ? min((int)*n_valid, N) : N;
+    // words that the launch behind this one wants to find at zero, and the counts of images between them
+    for (uint32_t i = blockIdx.x * 256u + tid; i < n_clear; i += gridDim.x * 256u)
+        clear[i] = i == (n_img <= few ? BODY_FEW_WORD : BODY_MANY_WORD) ? (uint32_t)max(n_img, 0) : 0u;
     const int tiles_x = (W + 31) / 32, tiles_y = (H + HEAD_TH - 1) / HEAD_TH, tiles_img = tiles_x * tiles_y;
     const int n_tiles = n_img * tiles_img;
     // XCD-aware order: each XCD takes runs of HEAD_RUN consecutive tiles, all XCDs stay close together
@@ -123,20 +124,20 @@ __global__ __launch_bounds__(256) void k_head_mfma(const uint8_t* __restrict__ i
 
 template <int C>
 static hipError_t launch_head(hipStream_t stream, const uint8_t* in, const uint4* wp, const float* bias, __bf16* out, int N,
-                              int H, int W, int relu, const uint32_t* n_valid, uint32_t* clear, uint32_t n_clear)
+                              int H, int W, int relu, const uint32_t* n_valid, uint32_t* clear, uint32_t n_clear, int few)
 {
     const long long tiles = (long long)N * ((H + HEAD_TH - 1) / HEAD_TH) * ((W + 31) / 32);
     const long long grid = (tiles + 8 * HEAD_RUN - 1) / (8 * HEAD_RUN) * (8 * HEAD_RUN);
     if (grid > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_head_mfma<C>, dim3((unsigned)grid), dim3(256), 0, stream, in, wp, bias, out, N, H, W, relu, n_valid, clear, n_clear);
+    hipLaunchKernelGGL(k_head_mfma<C>, dim3((unsigned)grid), dim3(256), 0, stream, in, wp, bias, out, N, H, W, relu, n_valid, clear, n_clear, few);
     return hipGetLastError();
 }
 
 // wp: [ky 3][m C/32][64 lanes][8] bf16 with cout = m*32 + lane%32 and k = 8*(lane/32) + e = kx*3 + c (k >= 9: zero)
 hipError_t rh_launch_head_mfma(hipStream_t stream, int C, const uint8_t* in, const uint4* wp, const float* bias, __bf16* out,
-                               int N, int H, int W, int relu, const uint32_t* n_valid, uint32_t* clear, uint32_t n_clear)
+                               int N, int H, int W, int relu, const uint32_t* n_valid, uint32_t* clear, uint32_t n_clear, int few)
 {
-    if (C == 64) return launch_head<64>(stream, in, wp, bias, out, N, H, W, relu, n_valid, clear, n_clear);
-    if (C == 32) return launch_head<32>(stream, in, wp, bias, out, N, H, W, relu, n_valid, clear, n_clear);
+    if (C == 64) return launch_head<64>(stream, in, wp, bias, out, N, H, W, relu, n_valid, clear, n_clear, few);
+    if (C == 32) return launch_head<32>(stream, in, wp, bias, out, N, H, W, relu, n_valid, clear, n_clear, few);
     return hipErrorInvalidValue;
 }

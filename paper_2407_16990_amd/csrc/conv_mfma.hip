@@ -514,11 +514,16 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // so their ceil(S / 32) words per row are at most S / 16.
     const size_t mask_words = C == 64 && !fold ? ((size_t)N * H * W + 15) / 16 : 0;
     // The body of a 64-channel net in one launch (conv_body.hip) where the batch has room for at most 8 half tiles a compute unit, else two convs a launch
-    // (conv_block64.hip).  us for EDSR x2 of 8 blocks, in one launch / two convs a launch (a launch per conv in brackets): 16 bins of 128 x 128
-    // 360 / 377, 24: 486 / 502, 32: 633 / 612, 40: 791 / 765, 48: 941 / 897, 56: 1095 / 1021 (a launch per conv); 40 of 100 x 100, 8.1 half tiles, 611 / 545; 60 of
-    // 96 x 96, 8.4, 676 / 642; 20 of 160 x 160, 7.8, 629 / 639; frames of 480 x 272, 3: 489 / 519, 6: 954 / 933; two of 640 x 360, 7: 574 / 577.
-    // How many of the N images are valid the host does not know; a capacity is seldom full, which speaks for neither.  Where two convs a launch are not to be
-    // had (exact-border mode, widths up to 48) the other side is a launch per conv, and the line is at 12 (48 of 128 x 128 1903 / 1895).
+    // (conv_block64.hip).  us for EDSR x2 of 8 blocks, all N valid, in one launch / two convs a launch: 16 bins of 128 x 128 351 / 370, 24: 490 / 505, 28: 570 / 569,
+    // 32: 641 / 602, 40: 796 / 754, 48: 949 / 881; 50 of 96 x 96, 7.0 half tiles, 570 / 566, 60, 8.4: 680 / 650; 20 of 160 x 160, 7.8, 628 / 642, 24, 9.4: 752 / 749;
+    // 14 of 192 x 192, 7.9, 633 / 641; frames of 480 x 272, 3: 492 / 533, 4: 638 / 627; two of 640 x 360, 7: 572 / 583; 30 of 100 x 100, 6.1, 471 / 445.
+    // How many of the N images are valid only the device knows, and a caller who sizes buffers once has seldom more than two thirds of them valid.  So between 8
+    // and 12 half tiles both are launched, and the one leaves at once that is not for this count (2 us each): in one launch go up to 5 valid half tiles a compute unit.  Room
+    // for 44 bins of 128 x 128, us, two convs a launch / both launched and all in the one: 4 valid 200 / 154, 8: 257 / 236, 12: 333 / 299, 16: 371 / 364, 20: 445 / 430, 24:
+    // 503 / 502; 16 blocks, 8: 465 / 413, 16: 686 / 653, 24: 938 / 916; 4 blocks, 8: 151 / 148, 16: 216 / 220; for 76 of 96 x 96, 7: 185 / 154, 15: 255 / 249, 35, 4.9: 432 / 427;
+    // for 28 of 160 x 160, 5: 267 / 224, 14, 5.5: 497 / 467.
+    // Where two convs a launch are not to be had (exact-border mode, widths up to 48) the other side is a launch per conv, and the line is at 12 (48 of
+    // 128 x 128 1903 / 1895).
     // Not with cell lists: the units of a layer and the 3 x 3 that they wait for are found here from the unit's number, in a list that changes from layer
     // to layer they are not.  So the box-masked mode goes a launch per layer, and on few bins is the slower one: a step of one 640 x 360 frame x3, 3 bins, plain 223,
     // masked 380 us.  The needed-region mode does too, unless all N images are so few that they go two layers a unit (conv_body_pairs.h; every value that it needs is
@@ -529,7 +534,13 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32), most_cells = 12 * (size_t)ctx->n_cu;
     int cut[4];
     const bool streams = C == 64 && !ctx->bz_boxes && !ctx->mk_boxes && rh_block64_strips(W, cut, cut + 1, cut + 2, cut + 3);
-    const bool one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && (!ctx->nd_places || rh_conv_body_pairs(ctx->n_cu, N, H, W)) && cells <= (streams ? 8 * (size_t)ctx->n_cu : most_cells);
+    const bool may_one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && (!ctx->nd_places || rh_conv_body_pairs(ctx->n_cu, N, H, W)) && cells <= most_cells;
+    const bool one_launch = may_one_launch && (!streams || cells <= 8 * (size_t)ctx->n_cu);
+    // Two convs per launch, the tensor between them stays on the chip.  Exact-border mode clears part of that tensor and runs them one by
+    // one; box-masked mode leaves out cells of every layer.
+    const bool pairs = C == 32 ? !ctx->bz_boxes : streams && !one_launch && !ctx->nd_places;
+    const int few = may_one_launch && pairs && n_valid ? (int)(5 * (size_t)ctx->n_cu * N / cells) : 0;
+    const bool by_count = few > 0;
     // its counters: room for the most that the line allows in every call, so that what a call needs follows from its pixels alone
     const size_t sync_words = C == 64 ? BODY_ROLL_WORDS + 4 * most_cells : 0;
     need = (need + 63) & ~(size_t)63;
@@ -547,7 +558,8 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
         rh_prof_scope ps(ctx, RH_PROF_HEAD, 1u + (masked ? 2u : 0u) + (ctx->bz_boxes ? 1u : 0u) + (ctx->mk_boxes ? 3u : 0u) + (ctx->nd_places ? 2u : 0u));
         if (masked) { st = rh_outside_mask(ctx, keep, N, n_valid); if (st != RH_OK) return st; }
         RH_HIP(ctx, rh_launch_head_mfma(ctx->stream, C, in, (const uint4*)((const uint8_t*)ctx->wpack + l0.wp_off),
-                                        ctx->bpack + l0.bp_off, h, N, H, W, head_relu, n_valid, sync, one_launch ? (uint32_t)(BODY_ROLL_WORDS + std::max(4 * cells, (size_t)BODY_PAIR_WORDS * ctx->n_cu)) : 0u));
+                                        ctx->bpack + l0.bp_off, h, N, H, W, head_relu, n_valid, sync,
+                                        one_launch || by_count ? (uint32_t)(BODY_ROLL_WORDS + std::max(4 * cells, (size_t)BODY_PAIR_WORDS * ctx->n_cu)) : 0u, few));
         // box-masked mode: from here to the end of the body the three tensors are zero outside the live cells
         if (ctx->mk_boxes) { st = rh_launch_cell_lists(ctx, N, n_valid, h, a, t); if (st != RH_OK) return st; }
         if (ctx->nd_places) { ctx->nd_conv = 0; st = rh_launch_need_lists(ctx, N, n_valid); if (st != RH_OK) return st; }
@@ -559,32 +571,36 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // one around the last conv: per-launch events would put a bubble between the launches
     uint32_t n_conv = 0;
     rh_prof_begin(ctx, RH_PROF_CONV);
-#define CONV(...) do { st = conv(ctx, __VA_ARGS__, n_valid, keep); if (st != RH_OK) return st; ++n_conv; } while (0)
+#define CONV(...) do { st = conv(ctx, __VA_ARGS__, n_many, keep); if (st != RH_OK) return st; ++n_conv; } while (0)
 #define PAIR(...) do { RH_HIP(ctx, C == 32 ? rh_launch_block32(ctx, __VA_ARGS__) : rh_launch_block64(ctx, __VA_ARGS__)); ++n_conv; ctx->nd_conv += 2; } while (0)
 #define LAST_CONV(...) do { rh_prof_end(ctx, n_conv); rh_prof_scope ps_(ctx, RH_PROF_CONV_LAST); st = conv(ctx, __VA_ARGS__); if (st != RH_OK) return st; } while (0)
-    // Two convs per launch, the tensor between them stays on the chip.  Exact-border mode clears part of that tensor and runs them one by
-    // one; box-masked mode leaves out cells of every layer.
-    const bool pairs = C == 32 ? !ctx->bz_boxes : streams && !one_launch && !ctx->nd_places;
     const __bf16* body_out = nullptr;
-    if (one_launch) {
+    const uint32_t* n_many = by_count ? sync + BODY_MANY_WORD : n_valid;     // for the body where it does not go in one launch
+    if (one_launch || by_count) {
         body_args b;
         b.h = h; b.a = a; b.t = t; b.wp = (const uint4*)((const uint8_t*)ctx->wpack + L[li].wp_off); b.bias = ctx->bpack + L[li].bp_off;
-        b.n_valid = n_valid; b.keep = keep; b.N = N; b.H = H; b.W = W; b.layers = body_layers; b.topology = d.topology;
+        b.n_valid = by_count ? sync + BODY_FEW_WORD : n_valid; b.keep = keep; b.N = N; b.H = H; b.W = W; b.layers = body_layers; b.topology = d.topology;
         b.roll = sync; b.done = sync + BODY_ROLL_WORDS; b.lost = (uint32_t*)ctx->lost;
         RH_HIP(ctx, rh_launch_conv_body(ctx->stream, ctx->device, ctx->n_cu, b));
-        ++n_conv; li += body_layers; ctx->nd_conv += body_layers;
-        body_out = d.topology == RH_NET_EDSR ? t : d.topology == RH_NET_RES ? a : (body_layers & 1) ? a : t;
+        ++n_conv;
+        if (one_launch) {
+            li += body_layers; ctx->nd_conv += body_layers;
+            body_out = d.topology == RH_NET_EDSR ? t : d.topology == RH_NET_RES ? a : (body_layers & 1) ? a : t;
+        } else {                                             // the launches behind it end in the same tensor: they begin with a and take a and t in turn
+            const bool plain = d.topology == RH_NET_PLAIN;
+            if (plain ? ((body_layers + 1) / 2 ^ body_layers) & 1 : !(d.n_blocks & 1)) std::swap(a, t);
+        }
     }
     if (d.topology == RH_NET_PLAIN) {
         const __bf16* x = one_launch ? body_out : h;
         int l = one_launch ? body_layers : 0;
-        for (; pairs && l + 1 < d.n_blocks - 2; l += 2, li += 2) { __bf16* o = (x == a) ? t : a; PAIR(L[li], L[li + 1], x, o, N, H, W, false, n_valid); x = o; }
+        for (; pairs && l + 1 < d.n_blocks - 2; l += 2, li += 2) { __bf16* o = (x == a) ? t : a; PAIR(L[li], L[li + 1], x, o, N, H, W, false, n_many); x = o; }
         for (; l < d.n_blocks - 2; ++l) { __bf16* o = (x == a) ? t : a; CONV(L[li++], x, o, nullptr, N, H, W, 1, false, 1); ZERO(o, 1); x = o; }
         LAST_CONV(L[li++], x, out, nullptr, N, H, W, 0, true, s, n_valid);
     } else {
         const __bf16* x = one_launch ? body_out : h;
         for (int b = 0; b < d.n_blocks && !one_launch; ++b) {
-            if (pairs) { __bf16* o = (x == a) ? t : a; PAIR(L[li], L[li + 1], x, o, N, H, W, true, n_valid); li += 2; x = o; continue; }
+            if (pairs) { __bf16* o = (x == a) ? t : a; PAIR(L[li], L[li + 1], x, o, N, H, W, true, n_many); li += 2; x = o; continue; }
             CONV(L[li++], x, t, nullptr, N, H, W, 1, false, 1); ZERO(t, 1);
             CONV(L[li++], t, a, x, N, H, W, 0, false, 1); ZERO(a, 1);      // x + conv(t)
             x = a;

@@ -97,8 +97,11 @@ struct body_args {
     uint32_t* lost;          // host memory: set to 1 where a wait was given up
     uint32_t img_magic, row_magic;       // division by the half tiles of an image and of its rows (set by the launcher)
 };
-// words for `roll` and `done` together; `done` begins BODY_ROLL_WORDS behind `roll`
+// words for `roll` and `done` together; `done` begins BODY_ROLL_WORDS behind `roll`.  Two of those between are counts of images, written by the first
+// conv's launch: the valid ones where they are so few that they go in one launch, else 0, and the valid ones where they are more, else 0.
 #define BODY_ROLL_WORDS 32
+#define BODY_FEW_WORD 8
+#define BODY_MANY_WORD 9
 #define BODY_PAIR_WORDS 32               // of `done`, one unit of two layers (at most one a compute unit): a line each
 hipError_t rh_launch_conv_body(hipStream_t stream, int device, int n_cu, body_args a);
 bool rh_conv_body_pairs(int n_cu, int N, int H, int W);        // all N images go two layers a unit (conv_body_pairs.h)
@@ -115,7 +118,7 @@ hipError_t rh_launch_block64(rh_ctx* ctx, const rh_layer& L1, const rh_layer& L2
 hipError_t rh_launch_conv_tail3(hipStream_t stream, int device, const conv_args& a, int cin);
 // first conv 3 -> C on the matrix cores (conv_head.hip)
 hipError_t rh_launch_head_mfma(hipStream_t stream, int C, const uint8_t* in, const uint4* wp, const float* bias, __bf16* out,
-                               int N, int H, int W, int relu, const uint32_t* n_valid, uint32_t* clear, uint32_t n_clear);
+                               int N, int H, int W, int relu, const uint32_t* n_valid, uint32_t* clear, uint32_t n_clear, int few);
 // upsampler + last conv of an EDSR-shaped net as one composed 5 x 5 conv (conv_fold.hip): t -> raw network output
 // tile_list / n_list (dev, or null for all tiles): the 8 x 32 tiles to compute, as RH_CELL_ENTRY(n, ty, tx)
 rh_status rh_launch_fold(rh_ctx* ctx, const __bf16* t, float* out, int N, int H, int W, const uint32_t* n_valid, int rev,

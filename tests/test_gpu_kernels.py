@@ -437,6 +437,24 @@ def test_row_streams_are_the_one_launch_body_bit_for_bit(net, H, W):
     rh.close()
 
 
+# Room for 8 to 12 half tiles of 8 x 32 a compute unit: one launch for up to 5 valid ones, two convs a launch for more, whichever tensor either ends in.
+# Nothing behind the count is written; after a call of the one, the other finds nothing of it.
+@pytest.mark.parametrize("net", [wl.Net("edsr", 64, 2, 2, 0.02), wl.Net("edsr", 64, 3, 2, 0.02), wl.Net("res", 64, 1, 2, 0.02), wl.Net("res", 64, 4, 3, 0.02)]
+                         + [wl.Net("plain", 64, k, 2, 0.1) for k in (4, 5, 6, 7, 8)])
+@pytest.mark.parametrize("H,W", [(128, 128), (57, 97), (200, 500)])
+def test_the_count_decides_between_one_launch_and_row_streams(net, H, W):
+    cu, cells = torch.cuda.get_device_properties(0).multi_processor_count, -(-H // 8) * -(-W // 32)
+    N, few = 10 * cu // cells, 5 * cu // cells
+    assert 8 * cu < N * cells <= 12 * cu and few >= 1
+    rh = RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=32, max_bins=4, net=net, weights=wl.make_weights(net, 37, "bf16"), precision="bf16")
+    x = torch.randint(0, 256, (N, H, W, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(H))
+    want = rh.enhance(x)                                     # no count: row streams
+    for k in (few, few + 1, 0, 1, N, few, N - 1):
+        got = rh.enhance(x, n_valid=torch.tensor([k], dtype=torch.int32, device="cuda"), out=torch.full_like(want, 3.0))
+        assert torch.equal(got[:k], want[:k]) and bool((got[k:] == 3.0).all()), k
+    rh.close()
+
+
 # A few images, two layers a unit of 4, 6, .. 22 rows of 30 pixels: the images end with a unit, a row or a pixel before or behind its end, and within it;
 # an odd layer at the end; rows = 0: a unit too many.  Against the same images in a batch that goes two convs or one a launch.
 def pair_shapes(rows, cu):

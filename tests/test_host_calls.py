@@ -104,6 +104,10 @@ for net, layers in ((EDSR, 64, 2, 4, 1), 5), ((RES, 64, 2, 2, 1), 4), ((PLAIN, 6
         assert bodies(lambda: L.rh_enhance(ctx, P(1), n, h, w, P(2), None)) == (0, layers + 2), (net, n)
     for n, h, w in ((33, 128, 128), (48, 128, 128), (49, 128, 128)):
         assert bodies(lambda: L.rh_enhance(ctx, P(1), n, h, w, P(2), None)) == (0, (layers + 1) // 2 + 2), (net, n)
+    # between eight and twelve a device-side count decides: both are launched
+    one, two = (1, 3), (0, (layers + 1) // 2 + 2)
+    for n, h, w, want in ((32, 128, 128, one), (33, 128, 128, (1, two[1] + 1)), (48, 128, 128, (1, two[1] + 1)), (49, 128, 128, two), (2, 384, 768, (1, two[1] + 1)), (1, 520, 1024, two)):
+        assert bodies(lambda: L.rh_enhance(ctx, P(1), n, h, w, P(2), P(7))) == want, (net, n)
     assert bodies(lambda: L.rh_enhance_exact(ctx, P(1), 48, P(3), P(4), P(2), None))[0] == 1
     assert bodies(lambda: L.rh_enhance_exact(ctx, P(1), 49, P(3), P(4), P(2), None))[0] == 0
     assert bodies(lambda: L.rh_enhance_masked(ctx, P(1), 3, P(3), P(4), P(2), None))[0] == 0
