@@ -152,7 +152,7 @@ struct fold_shape {
     static constexpr int MT = (3 * S * S + 15) / 16, KH = CIN / 32, PG = MT * KH >= 4 ? 2 : MT * KH >= 2 ? 4 : 8, WAVES = MT * KH * PG, R = 16 / PG;
     static constexpr int PASSES = KH == 2 && WAVES > 8 ? 2 : 1;      // three waves a SIMD: registers for half of the rows' sums
     static constexpr int PATCHB = (FOLD_TH + 4) * FOLD_PW * CIN * 2, OUT = FOLD_TH * S * 96 * S * 4, LDS = 2 * PATCHB + OUT;
-    static_assert(PATCHB % 1024 == 0 && LDS <= 160 * 1024, "a patch is whole pieces; all of it fits");
+    static_assert(PATCHB % 1024 == 0 && LDS + KH * MT * 64 <= 160 * 1024, "a patch is whole pieces; all of it fits");
 };
 
 // C of a lane's four sums, from the e-th on, to and from LDS; `at` is aligned to C floats
@@ -194,11 +194,10 @@ __global__ __launch_bounds__((fold_shape<CIN, S>::WAVES * 64)) void k_conv_fold(
     bf16x8 A[25];
 #pragma unroll
     for (int t = 0; t < 25; ++t) A[t] = *(const bf16x8*)(wp + t * (KH * MT * 64));
-    f32x4 bias_c = {0, 0, 0, 0};                           // of rows 16 m + 4 (lane / 16) + {0..3}; in the sums of the first half of C
-    if (kh == 0) {
-        const float4 v = *(const float4*)(a.bias + 4 * a.n_chunks * 32 + m * 16 + (lane >> 4) * 4);
-        bias_c[0] = v.x; bias_c[1] = v.y; bias_c[2] = v.z; bias_c[3] = v.w;
-    }
+    // The bias, in the sums of the first half of C, is read from LDS for every tile: kept over the loop it was loaded again from scratch memory for every
+    // tile of a list at x4, 32 channels.  Whole calls with one block on 16 of 64 x 64, 32 channels, us, so / now, x2 38.9 / 36.0, x4 42.5 / 40.3; others level.
+    __shared__ __attribute__((aligned(16))) float s_bias[KH][16 * MT];
+    if (tid < KH * 16 * MT) s_bias[0][tid] = tid < 16 * MT ? a.bias[4 * a.n_chunks * 32 + tid] : 0.0f;
     // XCD-contiguous tile runs, as in the 3 x 3 kernels
     const int G = gridDim.x;
     const int wg = (G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : (int)blockIdx.x;
@@ -321,6 +320,7 @@ __global__ __launch_bounds__((fold_shape<CIN, S>::WAVES * 64)) void k_conv_fold(
                 const int px = col0 + (l & 15) + i / (RP + 4);
                 B[i % 4] = *(const bf16x8*)(prow + px * PIXB + (((4 * kh + (l >> 4)) ^ ((px >> SWZ_SH) & (NCH - 1))) << 4) + i % (RP + 4) * (PW * PIXB));
             };
+            const f32x4 bias_c = *(const f32x4*)(s_bias[kh] + m * 16 + (l >> 4) * 4);      // of rows 16 m + 4 (lane / 16) + {0..3}
             load(0); load(1);
             __builtin_amdgcn_sched_barrier(0);
             auto frag = [&](auto i_c) __attribute__((always_inline)) {
