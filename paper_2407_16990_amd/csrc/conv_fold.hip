@@ -194,8 +194,8 @@ __global__ __launch_bounds__((fold_shape<CIN, S>::WAVES * 64)) void k_conv_fold(
     bf16x8 A[25];
 #pragma unroll
     for (int t = 0; t < 25; ++t) A[t] = *(const bf16x8*)(wp + t * (KH * MT * 64));
-    // The bias, in the sums of the first half of C, is read from LDS for every tile: kept over the loop it was loaded again from scratch memory for every
-    // tile of a list at x4, 32 channels.  Whole calls with one block on 16 of 64 x 64, 32 channels, us, so / now, x2 38.9 / 36.0, x4 42.5 / 40.3; others level.
+    // The bias, in the sums of the first half of C, is read from LDS for every tile: three waves a SIMD have few registers to spare.  With the bias kept over
+    // the loop / with this, whole calls with one block on 16 of 64 x 64, 32 channels, us, x2 38.9 / 36.0, x4 42.5 / 40.3; others level.
     __shared__ __attribute__((aligned(16))) float s_bias[KH][16 * MT];
     if (tid < KH * 16 * MT) s_bias[0][tid] = tid < 16 * MT ? a.bias[4 * a.n_chunks * 32 + tid] : 0.0f;
     // XCD-contiguous tile runs, as in the 3 x 3 kernels
@@ -615,13 +615,11 @@ static hipError_t launch_fold(rh_ctx* ctx, const fold_args& a)
     return hipGetLastError();
 }
 
-template <int CIN>
+template <int CIN, bool LIST>
 static hipError_t launch_fold(rh_ctx* ctx, const fold_args& a)
 {
     const int s = ctx->cfg.net.scale;
-    if (s == 4) return a.tile_list ? launch_fold<CIN, 4, true>(ctx, a) : launch_fold<CIN, 4, false>(ctx, a);
-    if (s == 3) return a.tile_list ? launch_fold<CIN, 3, true>(ctx, a) : launch_fold<CIN, 3, false>(ctx, a);
-    return a.tile_list ? launch_fold<CIN, 2, true>(ctx, a) : launch_fold<CIN, 2, false>(ctx, a);
+    return s == 4 ? launch_fold<CIN, 4, LIST>(ctx, a) : s == 3 ? launch_fold<CIN, 3, LIST>(ctx, a) : launch_fold<CIN, 2, LIST>(ctx, a);
 }
 
 // t: the body's output [N][H][W][C] bf16 -> raw network output fp32 [N][sH][sW][3]; one launch.
@@ -635,7 +633,9 @@ rh_status rh_launch_fold(rh_ctx* ctx, const __bf16* t, float* out, int N, int H,
     // Needed-region mode: a pasted macroblock lies at least `halo` pixels inside its box, hence inside
     // the bin, so with a halo no pasted pixel is on the outermost ring.
     a.ring = !(tile_list && ctx->cfg.halo >= 1);
-    const int C = ctx->cfg.net.channels;
-    RH_HIP(ctx, C == 64 ? launch_fold<64>(ctx, a) : launch_fold<32>(ctx, a));
+    // lists of tiles come from the needed-region mode, which takes nets of 64 channels only (rh_enhance_needed)
+    if (ctx->cfg.net.channels == 64) RH_HIP(ctx, (tile_list ? launch_fold<64, true>(ctx, a) : launch_fold<64, false>(ctx, a)));
+    else if (tile_list) RH_FAIL(ctx, RH_E_UNIMPLEMENTED, "a list of tiles with %d channels", ctx->cfg.net.channels);
+    else RH_HIP(ctx, (launch_fold<32, false>(ctx, a)));
     return RH_OK;
 }

@@ -20,7 +20,7 @@ def resources(source, out):
     return found
 
 
-@pytest.mark.parametrize("source,kernel,how_many", [("conv_body.hip", "k_conv_mfma_body", 2), ("conv_fold.hip", "k_conv_fold", 12)])
+@pytest.mark.parametrize("source,kernel,how_many", [("conv_body.hip", "k_conv_mfma_body", 2), ("conv_fold.hip", "k_conv_fold", 9)])
 def test_no_scratch_memory(source, kernel, how_many, tmp_path):
     found = {n: r for n, r in resources(source, tmp_path / "k.s").items() if kernel in n}
     assert len(found) == how_many
