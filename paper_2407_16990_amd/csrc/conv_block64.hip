@@ -187,7 +187,7 @@ __global__ __launch_bounds__(512) void k_conv_mfma_block64(block64_args a)
             // inline asm, with no register written: behind the builtin the compiler has every LDS read wait for the copy
             const uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)(lds + slot * ROWB + (i * 4 + m) * 1024));
             const uint32_t o = (uint32_t)(gx + i * 32) < (uint32_t)a.W ? off + i * (32 * PIXB) : OOB_OFF;
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(to), "v"(o), "s"(rin) : "memory");
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(to), "v"(o), "s"(rin) : "memory", "m0");
         }
     };
 

@@ -126,7 +126,7 @@ __device__ __forceinline__ void body_pairs(uint8_t* lds, uint32_t* stored, uint3
 #pragma unroll
         for (int i = 0; i < THIRD / 8192; ++i)
             asm volatile("s_add_u32 m0, %0, %c1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds"
-                         :: "s"(base + slot * THIRD), "n"(i * 8192), "v"(wlane_off), "s"(rw), "s"(from + i * 8192) : "memory", "scc");
+                         :: "s"(base + slot * THIRD), "n"(i * 8192), "v"(wlane_off), "s"(rw), "s"(from + i * 8192) : "memory", "scc", "m0");
     };
     int par = 0;                                             // two slots: that of the layer's first third
     auto slot_of = [&](int k) __attribute__((always_inline)) { return SLOTS == 3 ? k : (k + par) & 1; };
@@ -239,7 +239,7 @@ __device__ __forceinline__ void body_pairs(uint8_t* lds, uint32_t* stored, uint3
             for (int i = 0; i < NPW; ++i) {
                 if (i == NPW - 1 && i * 8 + wave >= NP) break;
                 asm volatile("s_add_u32 m0, %0, %c1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen sc1 lds"
-                             :: "s"(base), "n"(SLOTS * THIRD + i * 8192), "v"(poff[i]), "s"(rin) : "memory", "scc");
+                             :: "s"(base), "n"(SLOTS * THIRD + i * 8192), "v"(poff[i]), "s"(rin) : "memory", "scc", "m0");
             }
         }
         // the skip of the odd layer

@@ -222,7 +222,7 @@ __global__ __launch_bounds__((fold_shape<CIN, S>::WAVES * 64)) void k_conv_fold(
             const uint32_t off = (uint32_t)((y0 - 2 + (int)row) * a.W + gx) * PIXB + (((idx ^ (col >> SWZ_SH)) & (NCH - 1)) << 4);
             const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)(to + i * 1024));
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                         :: "s"(at), "v"((uint32_t)gx < (uint32_t)a.W ? off : OOB_OFF), "s"(rin) : "memory");
+                         :: "s"(at), "v"((uint32_t)gx < (uint32_t)a.W ? off : OOB_OFF), "s"(rin) : "memory", "m0");
         }
     };
     __amdgpu_buffer_rsrc_t rlist = __builtin_amdgcn_make_buffer_rsrc((void*)a.tile_list, 0, LIST ? (uint32_t)n_tiles * 4u : 0u, RSRC_FLAGS);

@@ -59,6 +59,10 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
 
+// Copies to LDS in inline asm set m0 and say so, for the compiler sets it too (lds_dma), and would otherwise take it for what it was before.  The compiler
+// warns of a register that it does not keep for others; nothing is kept there.
+#pragma clang diagnostic ignored "-Winline-asm"
+
 // `bytes` from `src` to LDS, 16 bytes per thread and turn, with no registers between: every piece of a layer's
 // weights is in flight at once.  `wave` (scalar) is the thread's wave of the THREADS / 64; the data is there
 // after lds_dma_wait() of all waves and a barrier.

@@ -25,3 +25,14 @@ def test_no_scratch_memory(source, kernel, how_many, tmp_path):
     found = {n: r for n, r in resources(source, tmp_path / "k.s").items() if kernel in n}
     assert len(found) == how_many
     assert not {n: r for n, r in found.items() if any(r.values())}
+
+
+def test_asm_that_sets_m0_says_so():
+    found = 0
+    for name in sorted(os.listdir(build.CSRC)):
+        text = open(os.path.join(build.CSRC, name)).read()
+        for m in re.finditer(r"\basm\s*(?:volatile)?\s*\((.*?)\);", text, re.S):
+            if re.search(r'"\s*s_\w+ m0,', m[1]):
+                found += 1
+                assert re.search(r'"m0"[^:]*$', m[1]), (name, m[1])
+    assert found >= 4
