@@ -29,8 +29,9 @@
 
 // The sums live in registers that this file names itself: left to the compiler, which would give a row's sums other registers where they
 // are finished, they are copied in every turn of the loop and do not fit.  From B64_X on: the row that is finished next, then the one after it, then
-// the newest, 4 NT each, then the bias.  Every statement that names one lists all of them as overwritten, so that the compiler keeps nothing of its
-// own there.
+// the newest, 4 NT each, then the bias.  Every statement that names one lists all of them as overwritten, so that nothing of the compiler's that lives
+// across such a statement lies there.  What lives between two of them only, it could still put there: the build reads the code that the compiler made
+// of this file and fails where it has (build.py, named_registers).
 #define B64_X 156
 #define B64_REGS "v156", "v157", "v158", "v159", "v160", "v161", "v162", "v163", "v164", "v165", "v166", "v167", "v168", "v169", "v170", "v171", "v172", "v173", \
     "v174", "v175", "v176", "v177", "v178", "v179", "v180", "v181", "v182", "v183", "v184", "v185", "v186", "v187", "v188", "v189", "v190", "v191", \
@@ -275,7 +276,8 @@ __global__ __launch_bounds__(512) void k_conv_mfma_block64(block64_args a)
         block64_row ahead = c;
         next(ahead);
         copy_row(ahead, wrap(slot + 1));
-        if (done.n >= 0) {                                   // rounding, + x, rounding, into x's place
+        if (done.n >= 0) {                                   // rounding, + x, rounding, into x's place.  (No b64_settle(), which would cost 0.3 %: the last product lies
+                                                             // a barrier, the fragments' loads and a copy back, 47 wait states at least; the build checks for 20.)
             const int l = lane_now(), ci = (l & 15) + left(done.strip) + 1;
             uint8_t* at = lds + wrap(slot + 3) * ROWB + ci * PIXB + (((m * 2 + (l >> 5)) ^ (ci & 7)) << 4) + (l >> 4 & 1) * 8;       // slot - 4
             uint2 x[RES ? NT2 : 1];

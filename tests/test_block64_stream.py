@@ -1,7 +1,7 @@
 """The row streams of k_conv_mfma_block64 (conv_block64.hip) on the CPU: which input row lies in which place, which row of the tensor between a product reads,
 when an output row is finished, rounded and stored, and what columns beside a strip or an image hold - with one channel and whole
 numbers, so that every output must be exact.  And of the compiled kernel: that the compiler keeps nothing in the registers that the kernel
-names itself."""
+names itself, which build() checks too."""
 import os
 import re
 import subprocess
@@ -158,27 +158,39 @@ def test_strips_cover_every_width():
         assert wo <= 16 * nt2 and nt2 in (nt - 1, nt)
 
 
-def test_the_compiler_keeps_out_of_the_named_registers(tmp_path):
-    out = tmp_path / "b.s"
-    src = os.path.join(build.CSRC, "conv_block64.hip")
-    first = int(re.search(r"#define B64_X (\d+)", open(src).read())[1])
-    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + build.FLAGS + ["-I" + build.INCLUDE, "-I" + build.CSRC, "-S", "--cuda-device-only",
-                    src, "-o", str(out)], check=True, capture_output=True)
-    inside, kernels, written = False, 0, []                  # registers that the last vector instructions wrote
-    span = lambda t: set(range(int(t[0]), int(t[-1]) + 1))
-    for line in out.read_text().splitlines():
-        kernels += line.startswith("_Z9k_conv_mfma_block64") and line.rstrip().endswith(":") or ".amdhsa_kernel" in line
-        if "#ASMSTART" in line or "#ASMEND" in line:
-            inside = "#ASMSTART" in line
-        code = line.split(";")[0].strip()
-        if code.startswith("v_mfma"):                        # a product must not follow at once on a move of what it reads
-            for m in re.findall(r"v\[(\d+):(\d+)\]", code)[1:3]:
-                assert not any(span(m) & w for w in written[-2:]), line
-        if code and not code.endswith(":") and not code.startswith("."):
-            m = re.match(r"v_(?!mfma|cmp)\w+ v\[?(\d+)(?::(\d+))?", code)
-            written.append(span([g for g in m.groups() if g]) if m else set())
-        if not inside and "#ASM" not in line:
-            for m in re.finditer(r"\bv(\d+)\b|\bv\[\d+:(\d+)\]", line.split(";")[0]):
-                assert int(m[1] or m[2]) < first, line
-        assert "scratch_" not in line or line.lstrip().startswith((".", ";")), line
-    assert kernels >= 20
+@pytest.fixture(scope="module")
+def assembly():
+    r = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + build.FLAGS + ["-I" + build.INCLUDE, "-I" + build.CSRC, "-S", "--cuda-device-only",
+                        os.path.join(build.CSRC, "conv_block64.hip"), "-o", "-"], check=True, capture_output=True, text=True)
+    return r.stdout
+
+
+FIRST = int(re.search(r"#define B64_X (\d+)", open(os.path.join(build.CSRC, "conv_block64.hip")).read())[1])
+
+
+def test_the_compiler_keeps_out_of_the_named_registers(assembly):
+    assert build.named_registers(assembly, FIRST) >= 20
+
+
+# Each planted in the compiler's code of one kernel: what build() has to refuse
+def test_the_check_finds_what_it_is_for(assembly):
+    lines = assembly[:assembly.index(".end_amdhsa_kernel")].splitlines()
+    code = lambda i: lines[i].split(";")[0].strip()
+    assert build.named_registers("\n".join(lines), FIRST) == 1
+    cvt = [i for i in range(len(lines)) if code(i).startswith("v_cvt_pk") and int(re.search(r", v(\d+),", code(i))[1]) >= FIRST]
+    mfma = next(i for i in range(len(lines)) if code(i).startswith("v_mfma"))
+    start = next(i for i in range(mfma, 0, -1) if "#ASMSTART" in lines[i])
+    operand = re.findall(r"v\[(\d+):", code(mfma))[1]
+    put = lambda at, *what: lines[:at] + list(what) + lines[at:]
+    bad = {"registers": put(start, f"\tv_mov_b32_e32 v{FIRST + 7}, v1"), "scratch": put(start, "\tscratch_load_dword v1, off, off"),
+           "move": put(start, f"\tv_mov_b32_e32 v{operand}, v1"),
+           "product just before conv1's rounding": put(cvt[0], code(mfma), "\ts_nop 15"), "before conv2's": put(cvt[-1], code(mfma), "\ts_nop 3")}
+    around = list(lines)
+    for at, what in sorted([(cvt[0], ".Lround:"), (mfma + 1, "\ts_cbranch_scc1 .Lround")], reverse=True):
+        around.insert(at, what)
+    bad["a way around the waits"] = around
+    for what, text in bad.items():
+        with pytest.raises(ValueError):
+            build.named_registers("\n".join(text), FIRST)
+            pytest.fail(what)
+    build.named_registers("\n".join(put(cvt[0], code(mfma), "\ts_nop 15", "\ts_nop 3")), FIRST)
