@@ -24,7 +24,7 @@
 #define BODY_PAIR_MOST 22
 #define BODY_PAIR_COLS 30                // output columns of a unit: the 32 of the tensor between, less one at each side
 
-// Rows of a unit, 0: a layer at a time.  Units never outnumber the 4 words a half tile of 8 x 32 that `done` has.
+// Rows of a unit, 0: a layer at a time.  There are at most `grid` units, of which each has BODY_PAIR_WORDS words of `done`.
 __host__ __device__ __forceinline__ long long body_pair_units(int images, int H, int W, int rows)
 {
     return (long long)images * ((H + rows - 1) / rows) * ((W + BODY_PAIR_COLS - 1) / BODY_PAIR_COLS);

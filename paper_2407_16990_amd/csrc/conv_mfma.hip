@@ -531,7 +531,7 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // 157 / 173, 28: 286 / 339; large batches over lists / two convs a launch: 182 bins of isolated macroblocks 5510 / 5760, 4 blocks on 87 bins 1013 / 1115.
     const std::vector<rh_layer>& L = ctx->layers;
     const int body_layers = d.topology == RH_NET_PLAIN ? d.n_blocks - 2 : 2 * d.n_blocks + (d.topology == RH_NET_EDSR);
-    const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32), most_cells = 12 * (size_t)ctx->n_cu;
+    const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32), most_cells = BODY_MOST_CELLS * (size_t)ctx->n_cu;
     int cut[4];
     const bool streams = C == 64 && !ctx->bz_boxes && !ctx->mk_boxes && rh_block64_strips(W, cut, cut + 1, cut + 2, cut + 3);
     const bool may_one_launch = C == 64 && body_layers > 1 && !ctx->mk_boxes && (!ctx->nd_places || rh_conv_body_pairs(ctx->n_cu, N, H, W)) && cells <= most_cells;

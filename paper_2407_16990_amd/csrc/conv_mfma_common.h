@@ -97,7 +97,8 @@ struct body_args {
     const uint32_t* keep;    // as in conv_args, or null
     int N, H, W, layers, topology;
     uint32_t* roll;          // workgroups that take part; zero at the launch, as
-    uint32_t* done;          // [half tiles of 8 x 32][4]: layers that each wave of its team has stored
+    uint32_t* done;          // a layer at a time: [half tiles of 8 x 32][4], layers that each wave of its team has stored; two layers a unit:
+                             // [units][BODY_PAIR_WORDS], of which the first says how many steps of two layers the unit has done
     uint32_t* lost;          // host memory: set to 1 where a wait was given up
     uint32_t img_magic, row_magic;       // division by the half tiles of an image and of its rows (set by the launcher)
 };
@@ -106,7 +107,9 @@ struct body_args {
 #define BODY_ROLL_WORDS 32
 #define BODY_FEW_WORD 8
 #define BODY_MANY_WORD 9
+#define BODY_MOST_CELLS 12               // half tiles of 8 x 32 a compute unit, at most: so much room `done` has
 #define BODY_PAIR_WORDS 32               // of `done`, one unit of two layers (at most one a compute unit): a line each
+static_assert(BODY_PAIR_WORDS <= 4 * BODY_MOST_CELLS, "the words of either way have room");
 hipError_t rh_launch_conv_body(hipStream_t stream, int device, int n_cu, body_args a);
 bool rh_conv_body_pairs(int n_cu, int N, int H, int W);        // all N images go two layers a unit (conv_body_pairs.h)
 // two-team kernel for the 64-channel bf16-output convs (conv_mfma_duo.hip)
