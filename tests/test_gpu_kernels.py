@@ -342,19 +342,32 @@ def test_recorded_step_replays(F, net):
     rh.close()
 
 
-# The body of a 64-channel net in one launch (up to 12 half tiles per compute unit) against the launch per layer that larger
-# batches take: the same images in a batch of that size with a device-side count.  One unit in all, fewer units than
-# workgroups, one and two and some rounds a layer, ragged rows and columns, an odd number of layers, a first layer alone.
+def body_way(n, H, W):
+    """How the body of a 64-channel net goes in the plain mode with no count: two layers a unit of so many rows, a layer at a time, or two convs or one a launch"""
+    cu, cells = torch.cuda.get_device_properties(0).multi_processor_count, n * -(-H // 8) * -(-W // 32)
+    rows = next((r for r in range(4, 23, 2) if n * -(-H // r) * -(-W // 30) <= cu), 0)
+    if cells > (8 if W > 48 else 12) * cu:
+        return "streams" if W > 48 else "launches"
+    return f"{rows} rows" if rows else "few" if cells <= 4 * cu else "many"
+
+
+# The body of a 64-channel net in one launch against the two convs or the conv a launch that larger batches take: the same images in a batch of that
+# size with a device-side count.  Two layers a unit: one unit in all, fewer units than workgroups, ragged rows and columns.  A layer at a time, up
+# to 4 units a workgroup and more: one and two and some rounds a layer, ragged rows and columns.  An odd number of layers, a first layer alone.
 @pytest.mark.parametrize("net", [wl.Net("edsr", 64, 1, 2, 0.02), wl.Net("edsr", 64, 3, 4, 0.02), wl.Net("res", 64, 1, 2, 0.02), wl.Net("res", 64, 4, 3, 0.02),
                                  wl.Net("plain", 64, 4, 2, 0.1), wl.Net("plain", 64, 7, 2, 0.1)])
-@pytest.mark.parametrize("n,H,W", [(1, 3, 5), (1, 8, 32), (2, 9, 33), (3, 50, 100), (7, 64, 128), (31, 57, 33), (40, 60, 140), (3, 200, 1000)])
-def test_one_launch_body_is_a_launch_per_layer_bit_for_bit(net, n, H, W):
+@pytest.mark.parametrize("n,H,W,way,other", [(1, 3, 5, "4 rows", "launches"), (1, 8, 32, "4 rows", "launches"), (2, 9, 33, "4 rows", "launches"), (3, 50, 100, "4 rows", "streams"),
+                                             (7, 64, 128, "10 rows", "streams"), (31, 57, 33, "16 rows", "launches"), (9, 128, 128, "few", "streams"), (270, 8, 30, "few", "launches"),
+                                             (130, 9, 33, "few", "launches"), (25, 57, 100, "few", "streams"), (40, 60, 140, "many", "streams"), (100, 50, 60, "many", "streams"),
+                                             (2, 200, 1000, "many", "streams"), (150, 57, 40, "many", "launches")])
+def test_one_launch_body_is_a_launch_per_layer_bit_for_bit(net, n, H, W, way, other):
     rh = RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=32, max_bins=4, net=net, weights=wl.make_weights(net, 16, "bf16"),
             precision="bf16")
     lim = 12 * torch.cuda.get_device_properties(0).multi_processor_count
     cells = -(-H // 8) * -(-W // 32)
     assert n * cells <= lim
     big = lim // cells + 1
+    assert (body_way(n, H, W), body_way(big, H, W)) == (way, other)
     x = torch.randint(0, 256, (n, H, W, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(n))
     xb = torch.zeros((big, H, W, 3), dtype=torch.uint8, device="cuda")
     xb[:n] = x
@@ -369,14 +382,15 @@ def test_one_launch_body_is_a_launch_per_layer_bit_for_bit(net, n, H, W):
     rh.close()
 
 
-def test_one_launch_bodies_share_the_gpu():
-    # two contexts on two streams, each with units for every compute unit: whichever workgroups start, all units are done
+# Two contexts on two streams, each with units for every compute unit, a layer at a time or two layers a unit: whichever workgroups start, all units are done
+@pytest.mark.parametrize("counts", [(40, 60), (28, 27), (28, 60)])
+def test_one_launch_bodies_share_the_gpu(counts):
     net = wl.Net("edsr", 64, 4, 2, 0.02)
     rhs, xs, wants, streams = [], [], [], [torch.cuda.Stream(), torch.cuda.Stream()]
     for k in range(2):
         rhs.append(RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=64, max_bins=64, net=net, weights=wl.make_weights(net, 17 + k, "bf16"),
                       precision="bf16", stream=streams[k]))
-        xs.append(torch.randint(0, 256, (40 + 20 * k, 64, 64, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(k)))
+        xs.append(torch.randint(0, 256, (counts[k], 64, 64, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(k)))
     outs = [[torch.zeros((len(x), 128, 128, 3), device="cuda") for _ in range(12)] for x in xs]
     torch.cuda.synchronize()
     for k in range(2):                                       # one alone
@@ -393,16 +407,18 @@ def test_one_launch_bodies_share_the_gpu():
         rhs[k].close()
 
 
-# A small batch's body while another context's launches, one a layer, hold the compute units: workgroups of the body that find
+# A small batch's body while another context's launches, two convs or one each, hold the compute units: workgroups of the body that find
 # room only after its roll has closed leave, and the others do their share
+@pytest.mark.parametrize("S,other", [(64, "streams"), (48, "launches")])
 @pytest.mark.parametrize("n", [1, 12, 100])
-def test_one_launch_body_beside_a_launch_per_layer(n):
+def test_one_launch_body_beside_a_launch_per_layer(n, S, other):
     net = wl.Net("edsr", 64, 4, 2, 0.02)
-    streams, counts = [torch.cuda.Stream(), torch.cuda.Stream()], [12 * torch.cuda.get_device_properties(0).multi_processor_count // 16 + 1, n]
+    streams, counts = [torch.cuda.Stream(), torch.cuda.Stream()], [12 * torch.cuda.get_device_properties(0).multi_processor_count // (-(-S // 8) * -(-S // 32)) + 1, n]
+    assert body_way(counts[0], S, S) == other and (body_way(n, S, S) == "many" if n == 100 else "rows" in body_way(n, S, S))
     rhs = [RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=64, max_bins=64, net=net, weights=wl.make_weights(net, 19, "bf16"),
               precision="bf16", stream=s) for s in streams]
-    xs = [torch.randint(0, 256, (c, 64, 64, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(c)) for c in counts]
-    wants, outs = [torch.zeros((c, 128, 128, 3), device="cuda") for c in counts], [torch.zeros((6, c, 128, 128, 3), device="cuda") for c in counts]
+    xs = [torch.randint(0, 256, (c, S, S, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(c)) for c in counts]
+    wants, outs = [torch.zeros((c, 2 * S, 2 * S, 3), device="cuda") for c in counts], [torch.zeros((6, c, 2 * S, 2 * S, 3), device="cuda") for c in counts]
     for k in range(2):                                       # one alone
         torch.cuda.synchronize()
         rhs[k].enhance(xs[k], out=wants[k])
@@ -419,12 +435,13 @@ def test_one_launch_body_beside_a_launch_per_layer(n):
 # Two 64-channel convs a launch as streams of rows: strips of every number of 16-pixel tiles, one to many of them, images of one row and more rows than a
 # workgroup's run.  Every image of a large batch as the same image in a small one, whose body is one launch of another kernel.
 @pytest.mark.parametrize("net", [wl.Net("res", 64, 2, 2, 0.02), wl.Net("edsr", 64, 1, 3, 0.02), wl.Net("plain", 64, 5, 2, 0.1)])
-@pytest.mark.parametrize("H,W", [(3, 49), (4, 64), (9, 56), (5, 80), (40, 96), (3, 112), (24, 128), (7, 129), (16, 160), (33, 192), (13, 333), (60, 480)])
+@pytest.mark.parametrize("H,W", [(1, 64), (2, 100), (3, 49), (4, 64), (9, 56), (5, 80), (40, 96), (3, 112), (24, 128), (7, 129), (16, 160), (33, 192), (13, 333), (60, 480)])
 def test_row_streams_are_the_one_launch_body_bit_for_bit(net, H, W):
     rh = RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=32, max_bins=4, net=net, weights=wl.make_weights(net, 23, "bf16"),
             precision="bf16")
     cells = -(-H // 8) * -(-W // 32)
     big = 13 * torch.cuda.get_device_properties(0).multi_processor_count // cells + 1
+    assert body_way(big, H, W) == "streams" and body_way(1, H, W) not in ("streams", "launches")
     x = torch.randint(0, 256, (5, H, W, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(W))
     want = torch.cat([rh.enhance(x[i:i + 1].clone()) for i in range(5)])
     xb = x[torch.arange(big, device="cuda") % 5].contiguous()
