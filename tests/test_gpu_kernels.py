@@ -432,10 +432,10 @@ def test_one_launch_body_beside_a_launch_per_layer(n, S, other):
         rhs[k].close()
 
 
-# Two 64-channel convs a launch as streams of rows: strips of every number of 16-pixel tiles, one to many of them, images of one row and more rows than a
-# workgroup's run.  Every image of a large batch as the same image in a small one, whose body is one launch of another kernel.
+# Two 64-channel convs a launch as streams of rows: strips of every number of 16-pixel tiles, one to many of them, images of three rows (the fewest that the
+# library takes) and more rows than a workgroup's run.  Every image of a large batch as the same image in a small one, whose body is one launch of another kernel.
 @pytest.mark.parametrize("net", [wl.Net("res", 64, 2, 2, 0.02), wl.Net("edsr", 64, 1, 3, 0.02), wl.Net("plain", 64, 5, 2, 0.1)])
-@pytest.mark.parametrize("H,W", [(1, 64), (2, 100), (3, 49), (4, 64), (9, 56), (5, 80), (40, 96), (3, 112), (24, 128), (7, 129), (16, 160), (33, 192), (13, 333), (60, 480)])
+@pytest.mark.parametrize("H,W", [(3, 49), (4, 64), (9, 56), (5, 80), (40, 96), (3, 112), (24, 128), (7, 129), (16, 160), (33, 192), (13, 333), (60, 480)])
 def test_row_streams_are_the_one_launch_body_bit_for_bit(net, H, W):
     rh = RH(frame_w=64, frame_h=64, max_frames=1, halo=2, bin_size=32, max_bins=4, net=net, weights=wl.make_weights(net, 23, "bf16"),
             precision="bf16")
