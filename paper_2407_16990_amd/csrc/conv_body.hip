@@ -195,8 +195,8 @@ __global__ __launch_bounds__(512) void k_conv_mfma_body(body_args args)
     // patch where that is ready.  True: the last.
     int turn = 0;                                            // units of this team so far
     // FEW: no look from the compute phase and no early patch.  With up to FEW_UNITS units a workgroup and layer neither is in time,
-    // and the 11 loads of no bytes stood in the way of the words that others wait for: EDSR x4 on 128 x 128 bins, us, always with them / with
-    // this up to 4 units, 10 bins 498 / 460, 16: 666 / 654; with six units (24 bins) 930 / 964.
+    // and the 11 loads of no bytes stood in the way of the words that others wait for: EDSR x4 on 128 x 128 bins, us, with them / without,
+    // 9 bins 492 / 444, 10: 486 / 459, 12: 521 / 512, 16: 658 / 643, 18, 4.5 units: 710 / 732, 24: 912 / 948; 30 of 96 x 96, 4.2: 675 / 685.
     auto unit = [&](auto skip_c, auto few_c) __attribute__((always_inline)) -> bool {
         constexpr bool SKIP = decltype(skip_c)::value, FEW = decltype(few_c)::value;
         conv64_acc acc;

@@ -14,7 +14,7 @@
 // 22 200 so; with a word a wave, 8 in a line, 24 000.
 // TH is the least of 4, 6, .. 22 with which there is a workgroup for every unit; where 22 rows are not enough, the batch goes a layer at a time, as it
 // does with 2 units a workgroup of fewer rows.  us, EDSR x4 on 128 x 128 bins, a layer / two layers a unit: 1 bin 248 / 136, 2: 261 / 159, 3: 272 / 189, 4: 286 / 228,
-// 5: 343 / 259, 6: 332 / 290, 7: 368 / 349, 8: 408 / 380 (on another card 365 / 372 and 400 / 409).
+// 6: 328 / 285, 7: 347 / 339, 8: 385 / 364; 12 of 96 x 96 335 / 334; 5 of 160 x 160 383 / 342; a frame of 480 x 272 399 / 324.
 // What bounds it: of a step's 22 200 cycles on 3 bins 10 400 are products, 3 000 the wait for words and what lies around, 2 200 stores until they are
 // acknowledged; from 4 bins on also the instructions of the two roundings, and the slower of the two waves of a SIMD.
 // Sums as in the other kernels of the body (conv_mfma64.h): the same bits.

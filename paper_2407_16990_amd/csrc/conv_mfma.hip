@@ -522,13 +522,13 @@ rh_status rh_launch_enhance_bf16(rh_ctx* ctx, const uint8_t* in, int N, int H, i
     // for 44 bins of 128 x 128, us, two convs a launch / both launched and all in the one: 4 valid 200 / 154, 8: 257 / 236, 12: 333 / 299, 16: 371 / 364, 20: 445 / 430, 24:
     // 503 / 502; 16 blocks, 8: 465 / 413, 16: 686 / 653, 24: 938 / 916; 4 blocks, 8: 151 / 148, 16: 216 / 220; for 76 of 96 x 96, 7: 185 / 154, 15: 255 / 249, 35, 4.9: 432 / 427;
     // for 28 of 160 x 160, 5: 267 / 224, 14, 5.5: 497 / 467.
-    // Where two convs a launch are not to be had (exact-border mode, widths up to 48) the other side is a launch per conv, and the line is at 12 (48 of
-    // 128 x 128 1903 / 1895).
+    // Where two convs a launch are not to be had (exact-border mode, widths up to 48) the other side is a launch per conv, and the line is at 12: residual net of 16 blocks in
+    // exact-border mode, us, in one launch / a launch per conv, 16 of 128 x 128 626 / 711, 32: 1142 / 1176, 40: 1422 / 1434, 44: 1569 / 1564, 48: 1696 / 1686; 4 blocks, 40: 417 / 415, 48: 494 / 486.
     // Not with cell lists: the units of a layer and the 3 x 3 that they wait for are found here from the unit's number, in a list that changes from layer
     // to layer they are not.  So the box-masked mode goes a launch per layer, and on few bins is the slower one: a step of one 640 x 360 frame x3, 3 bins, plain 223,
     // masked 380 us.  The needed-region mode does too, unless all N images are so few that they go two layers a unit (conv_body_pairs.h; every value that it needs is
-    // the same there).  EDSR x4, all N valid, a launch per layer over lists / in one launch, 16 blocks: 9 bins 476 / 451, 17: 658 / 661, 28: 960 / 1034, 4 blocks: 9 bins
-    // 157 / 173, 28: 286 / 339; large batches over lists / two convs a launch: 182 bins of isolated macroblocks 5510 / 5760, 4 blocks on 87 bins 1013 / 1115.
+    // the same there), however few of N are valid.  EDSR x4, all N valid, a launch per layer over lists / in one launch, 16 blocks: 9 bins 504 / 441, 17: 719 / 665, 26: 929 / 970, 4 blocks: 9 bins
+    // 158 / 168, 17: 215 / 244, 26: 277 / 331; large batches over lists / two convs a launch: 182 bins of isolated macroblocks 5510 / 5760, 4 blocks on 87 bins 1013 / 1115.
     const std::vector<rh_layer>& L = ctx->layers;
     const int body_layers = d.topology == RH_NET_PLAIN ? d.n_blocks - 2 : 2 * d.n_blocks + (d.topology == RH_NET_EDSR);
     const size_t cells = (size_t)N * ((H + 7) / 8) * ((W + 31) / 32), most_cells = BODY_MOST_CELLS * (size_t)ctx->n_cu;
